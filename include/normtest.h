@@ -160,8 +160,9 @@ size_t normtest_workspace_bytes_for(nt_dtype gdtype, int64_t J, int64_t d, uint3
  * has synchronised it.  A call enqueues kernel launches only (no memsets, copies or allocations): a long vector
  * is walked by several launches of the same kernel over consecutive runs of tiles (about one per 1.3e8
  * coordinates up to 16 rows, one per 8e6 beyond; the memory system serves blocks that start together faster),
- * followed by one or two small reduction kernels; results do not depend on how many launches there were.  Any pointer alignment is accepted: rows, w, m, v (and gbar_out) that are not
- * all 16-byte aligned take a slower path with bit-identical results.  d == 0 succeeds (sums are 0).
+ * followed by one or two small reduction kernels; results do not depend on how many launches there were.  Any element-aligned pointer and
+ * any row stride is accepted: the kernels access rows, w, m, v and gbar_out with the same vector instructions whatever
+ * the alignment, with bit-identical results.  d == 0 succeeds (sums are 0).
  * AdamW is fused into the same pass: it has been applied even if status reports NONFINITE.
  * Returns NT_OK or a negative code; on any error nothing was enqueued and no buffer was touched,
  * except that a failing launch (HIP code returned) may follow launches that already succeeded.
@@ -175,8 +176,8 @@ int normtest_step(const void* grads, nt_dtype gdtype, int64_t J, int64_t d, int6
 /*
  * The same step for gradient rows that are separate allocations (one buffer per worker or micro-batch,
  * Sec. 3.2): grad_rows_dev is a device-resident array of J device pointers (8-byte aligned), row j
- * holding at least d elements of type gdtype.  The table is read by the kernels, never by the host; rows
- * that are not all 16-byte aligned take the slower path, with bit-identical results.  Everything else
+ * holding at least d elements of type gdtype.  The table is read by the kernels, never by the host, and must
+ * not change until they have run.  Everything else
  * as in normtest_step; for the same rows the two calls return the same bits.
  */
 int normtest_step_rows(const void* const* grad_rows_dev, nt_dtype gdtype, int64_t J, int64_t d,

@@ -12,8 +12,8 @@
 // call and were chosen by measurement; see tile_cfg() and the NT_CHUNK_* constants.  Two things about the memory
 // system shape the host side: blocks that start together stay in step for a while and are served faster than an
 // even mix of loads and stores, so a long vector is walked by several launches; and writes sprinkled among many
-// reads cost several times their volume, so with more than 16 rows (fast_tile_multi), and in long vectors from 28
-// bytes of gradient per coordinate on (fast_tile_defer), a block updates the state of its whole tile only after it
+// reads cost several times their volume, so with more than 16 rows (tile_multi), and in long vectors from 28
+// bytes of gradient per coordinate on (tile_defer), a block updates the state of its whole tile only after it
 // has read all the rows.
 //
 // Numerics.  The centred sum C = sum_j (g_j - gbar)^2 is formed directly from the J values of a
@@ -101,7 +101,6 @@
 #define NT_GROUP_TILES 2048    // ... and tile partials per block
 #define NT_DIRECT_TILES 4096   // up to this many tiles one block reads the tile partials itself
 #define NT_WS_HEADER 32        // doubles in front of the tile partials: a record of the step that wrote them
-#define NT_WS_CONTROL 24       // ... of which this one starts the words the step's kernels hand to each other
 #define NT_WS_MAGIC 0x4e54574f524b5350ll
 #define NT_LAYER_THREADS 1024  // per-layer kernel: one block per layer
 
@@ -118,19 +117,38 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 enum { MODE_FULL = 0, MODE_STATS = 1, MODE_ADAMW = 2 };
 
-template <bool NT, class T>
-__device__ inline T ld_vec(const void* p) {
-  if constexpr (NT)
-    return __builtin_nontemporal_load((const T*)p);
-  else
-    return *(const T*)p;
+// One vector access per lane whatever the alignment: gfx950 serves global loads and stores of 8 and 16 bytes from any
+// element's address, so the types below promise the compiler no more than that (2 bytes for a pair of bfloat16 words,
+// 4 for fp32) and it still emits one dwordx2 / dwordx4.  Rows of an odd-sized matrix without padding (row j starts
+// j*d elements in) therefore run like aligned ones: a wave touches one more line per access.  J = 8 bf16,
+// d = 30,000,001, unpadded: 224 us (5.4 TB/s) against 406 us (3.0) element by element, which is how such calls ran.
+typedef uint32_t u32x2_any __attribute__((ext_vector_type(2), aligned(2)));
+typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+
+// Every array the kernels touch is in global memory; saying so keeps the accesses global (not flat) where the compiler
+// cannot trace a pointer back to a kernel argument.
+#define NT_GLOBAL __attribute__((address_space(1)))
+
+template <class T, class P>
+__device__ inline T ld_nt(P p) {
+  return __builtin_nontemporal_load((const T NT_GLOBAL*)p);
 }
 
 struct F32 {
   static constexpr int VEC = 4;
   static constexpr int ESIZE = 4;
   typedef u32x4 raw_t;
-  __device__ static inline raw_t ldraw(const void* p) { return ld_vec<true, raw_t>(p); }
+  __device__ static inline raw_t ldraw(const char NT_GLOBAL* p) { return ld_nt<u32x4_any>(p); }
+  // the first n < VEC values, zeros behind them
+  __device__ static inline raw_t ldraw_part(const char NT_GLOBAL* p, int n) {
+    const uint32_t NT_GLOBAL* q = (const uint32_t NT_GLOBAL*)p;
+    raw_t r = {0u, 0u, 0u, 0u};
+    if (n > 0) r[0] = q[0];
+    if (n > 1) r[1] = q[1];
+    if (n > 2) r[2] = q[2];
+    return r;
+  }
   __device__ static inline float val(const raw_t& r, int e) { return __builtin_bit_cast(float, (uint32_t)r[e]); }
   __device__ static inline float ld(const void* base, int64_t i) { return ((const float*)base)[i]; }
 };
@@ -139,7 +157,15 @@ struct BF16 {
   static constexpr int VEC = 4;
   static constexpr int ESIZE = 2;
   typedef u32x2 raw_t;
-  __device__ static inline raw_t ldraw(const void* p) { return ld_vec<true, raw_t>(p); }
+  __device__ static inline raw_t ldraw(const char NT_GLOBAL* p) { return ld_nt<u32x2_any>(p); }
+  __device__ static inline raw_t ldraw_part(const char NT_GLOBAL* p, int n) {
+    const uint16_t NT_GLOBAL* q = (const uint16_t NT_GLOBAL*)p;
+    raw_t r = {0u, 0u};
+    if (n > 0) r[0] = q[0];
+    if (n > 1) r[0] |= (uint32_t)q[1] << 16;
+    if (n > 2) r[1] = q[2];
+    return r;
+  }
   // bfloat16 is the high half of a binary32: widening is a shift or a mask
   __device__ static inline float val(const raw_t& r, int e) {
     uint32_t u = r[e >> 1];
@@ -169,22 +195,23 @@ struct StepParams {
   float coord_thr;   // eta^2 b_k (J - ddof) when the coordinate-wise count is wanted, else negative
 };
 
-// Words of the workspace record that kernels of one step hand to each other.
-struct WsControl {
-  unsigned int rows_aligned;  // pointer-table calls: 1 if every row pointer is 16-byte aligned
-};
-
 // Start of gradient row j: base + j*ld elements, or the j-th entry of the caller's pointer table.
 template <class GT, bool TABLE>
 __device__ inline const char* row_base(const StepParams& p, int j) {
-  if constexpr (TABLE)
-    return ((const char* const*)p.grads)[j];
+  if constexpr (TABLE)   // constant address space: nothing writes the table while the step runs, so scalar loads serve
+    return ((const char* const __attribute__((address_space(4)))*)(uintptr_t)p.grads)[j];
   else
     return (const char*)p.grads + (int64_t)j * p.ld * GT::ESIZE;
 }
 
-__device__ inline u32x4 ld16(const void* p) { return ld_vec<true, u32x4>(p); }
-__device__ inline void st16(void* p, f32x4 x) { __builtin_nontemporal_store(x, (f32x4*)p); }
+template <class P>
+__device__ inline u32x4 ld16(P p) {
+  return ld_nt<u32x4_any>(p);
+}
+template <class P>
+__device__ inline void st16(P p, f32x4 x) {
+  __builtin_nontemporal_store(x, (f32x4_any NT_GLOBAL*)p);
+}
 
 // AdamW on one coordinate (Alg. 1): moments, bias corrections folded into step_size and
 // inv_sqrt_bc2, decoupled decay.  sqrt and reciprocal are the 1-ulp hardware forms: the term they
@@ -273,7 +300,7 @@ __device__ inline void coord_test(float thr, float c, float gb, LaneAcc& acc) {
   }
 }
 
-// Per-chunk bookkeeping of the J > 16 walk, shared by the fast and the guarded path so that both
+// Per-chunk bookkeeping of the J > 16 walk, shared by the tiles and the per-coordinate form below so that both
 // perform the same operations.  For one coordinate and a chunk of nb rows with shift K (the running
 // mean before the chunk, or the first row for the first chunk) two sums have been accumulated:
 // sb = sum x in fp64 (exact for all practical purposes, so the mean handed to AdamW is correctly rounded
@@ -313,7 +340,7 @@ __device__ inline void coord_stats_generic(const StepParams& p, int64_t i, doubl
   const int J = p.J;
   a = 0.f;
   if (J <= NT_JCHUNK) {
-    // all rows at once: fp64 row sum, then squares centred on the mean, exactly as in the fast tile
+    // all rows at once: fp64 row sum, then squares centred on the mean, exactly as in the tiles
     double sb = (double)GT::ld(row_base<GT, TABLE>(p, 0), i);
     for (int j = 1; j < J; ++j) sb += (double)GT::ld(row_base<GT, TABLE>(p, j), i);
     const float mb = (float)(sb * p.inv_J);
@@ -371,86 +398,127 @@ __device__ inline void coord_stats(const StepParams& p, int64_t i, double& S, fl
   }
 }
 
-template <class GT, int J_T, int MODE, int BLOCK, bool TABLE, bool GBAR>
-__device__ inline void guarded_tile(const StepParams& p, int64_t tile, int tile_coords, double (*red)[BLOCK / 64][NT_NV],
-                                    int buf) {
-  constexpr int VEC = GT::VEC;
-  const int iters = tile_coords / (BLOCK * VEC);
-  LaneAcc acc;
-  for (int it = 0; it < iters; ++it) {
-    const int64_t i0 = tile * (int64_t)tile_coords + ((int64_t)it * BLOCK + threadIdx.x) * VEC;
-    float a[VEC], b[VEC], c[VEC];
-#pragma unroll
-    for (int e = 0; e < VEC; ++e) {
-      const int64_t i = i0 + e;
-      a[e] = b[e] = c[e] = 0.f;
-      if (i < p.d) {
-        double S;
-        float M2, aa;
-        coord_stats<GT, TABLE, J_T>(p, i, S, M2, aa);
-        const float gb = (float)(S * p.inv_J);
-        const float sf = (float)S;
-        a[e] = aa;
-        b[e] = sf * sf;
-        c[e] = M2;
-        if constexpr (MODE != MODE_ADAMW) coord_test(p.coord_thr, M2, gb, acc);
-        if constexpr (MODE != MODE_STATS) {
-          float w = p.w[i], m = p.m[i], v = p.v[i];
-          adamw_coord(p, gb, w, m, v);
-          p.w[i] = w;
-          p.m[i] = m;
-          p.v[i] = v;
-        }
-        if (GBAR && p.gbar) p.gbar[i] = gb;
-      }
-    }
-    if constexpr (MODE != MODE_ADAMW) {
-      acc.A += (double)lane_tree<VEC>(a);
-      acc.B += (double)lane_tree<VEC>(b);
-      acc.C += (double)lane_tree<VEC>(c);
-    }
-  }
-  if constexpr (MODE != MODE_ADAMW) tile_reduce<BLOCK>(acc, red, buf, p.partials, tile);
+// ---------------------------------------------------------------------------------------------
+// Loads and stores of a lane's VEC coordinates i0 .. i0+3.  PART: the tile may reach past d and only n of the four lie
+// below it; those (one group per call) are moved one by one, and what lies past d is zero rows on zero state, which add
+// exact zeros to every sum.  The arithmetic is the same for whole and part tiles, hence the same bits.  With at most 16
+// rows the part tile is a copy of its own (the branch in the only copy makes a wave wait for all its rows before the
+// first sum, -2 % on the fused step); beyond 16 rows one copy serves both, since two would need more scalar registers
+// for row addresses than there are.  128 rows, d = 1,000,003, unpadded: 73 us against 386 us with the part tile and
+// everything misaligned element by element.
+// ---------------------------------------------------------------------------------------------
+// coordinates i0 .. i0+3 that lie below d: 4 or fewer, 0 or negative where none does
+__device__ inline int below(int64_t d, int64_t i0) { return (int)(d - i0 < 4 ? (d - i0 < 0 ? 0 : d - i0) : 4); }
+// Where a lane's four coordinates start: s0, the sweep's first coordinate (the same for the whole block), plus the lane's
+// own offset.  scalar() pins a block-uniform address to scalar registers: every access is then a scalar base and one
+// shared lane offset, where the compiler would otherwise form a 64-bit vector address per row and array (fused step at 8
+// rows: 79 vector registers instead of 88; 4 rows in tables, d = 304.6M: 1737 -> 1684 us).
+struct Place {
+  int64_t s0;
+  uint32_t u;
+  __device__ inline int64_t i0() const { return s0 + u; }
+};
+template <class T>
+__device__ inline T NT_GLOBAL* scalar(T* p) {
+  const uint64_t a = (uintptr_t)p;
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((int)(uint32_t)a), hi = __builtin_amdgcn_readfirstlane((int)(a >> 32));
+  return (T NT_GLOBAL*)(((uint64_t)hi << 32) | lo);
+}
+template <class T>
+__device__ inline T NT_GLOBAL* at(T* base, const Place& pl) {
+  return scalar(base + pl.s0) + pl.u;
 }
 
-// AdamW on VEC coordinates whose state was loaded as 16-byte vectors, then the 16-byte stores.
-template <int VEC>
-__device__ inline void adamw_store(const StepParams& p, int64_t i0, const float* gb, const u32x4* sw, const u32x4* sm,
-                                   const u32x4* sv) {
-  f32x4 ow[VEC / 4], om[VEC / 4], ov[VEC / 4];
+// Rows j0, j0+1, ... at coordinate s0, one after the other: a matrix is walked by adding its row stride.
+template <class GT, bool TABLE>
+struct RowWalk {
+  const StepParams& p;
+  int j;
+  int64_t off;
+  const char* at;
+  __device__ inline RowWalk(const StepParams& p_, int j0, int64_t s0)
+      : p(p_), j(j0), off(s0 * GT::ESIZE), at(TABLE ? nullptr : row_base<GT, false>(p_, j0) + off) {}
+  __device__ inline const char NT_GLOBAL* next() {
+    if constexpr (TABLE) return scalar(row_base<GT, true>(p, j++) + off);
+    const char NT_GLOBAL* a = scalar(at);
+    at = (const char*)(uintptr_t)a + p.ld * GT::ESIZE;
+    return a;
+  }
+};
+
+// Rows j0 .. j0+N-1 of the lane's coordinates (RT: only the first nb of them), and with STATE w, m, v too, all under one
+// branch so that every load of a sweep is in flight before the first wait.
+template <class GT, bool TABLE, bool PART, int N, bool RT, bool STATE>
+__device__ inline void load_sweep(const StepParams& p, int j0, int nb, const Place& pl, int n, typename GT::raw_t* raw,
+                                  u32x4* state) {
+  const uint32_t lane = pl.u * GT::ESIZE;
+  if (!PART || n >= GT::VEC) {
+    RowWalk<GT, TABLE> row(p, j0, pl.s0);
 #pragma unroll
-  for (int q = 0; q < VEC / 4; ++q) {
+    for (int j = 0; j < N; ++j)
+      if (!RT || j < nb) raw[j] = GT::ldraw(row.next() + lane);
+    if constexpr (STATE) {
+      state[0] = ld16(at(p.w, pl));
+      state[1] = ld16(at(p.m, pl));
+      state[2] = ld16(at(p.v, pl));
+    }
+  } else {
+    RowWalk<GT, TABLE> row(p, j0, pl.s0);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      float w = __builtin_bit_cast(float, (uint32_t)sw[q][e]);
-      float m = __builtin_bit_cast(float, (uint32_t)sm[q][e]);
-      float v = __builtin_bit_cast(float, (uint32_t)sv[q][e]);
-      adamw_coord(p, gb[4 * q + e], w, m, v);
-      ow[q][e] = w;
-      om[q][e] = m;
-      ov[q][e] = v;
+    for (int j = 0; j < N; ++j)
+      if (!RT || j < nb) raw[j] = GT::ldraw_part(row.next() + lane, n);
+    if constexpr (STATE) {
+      state[0] = F32::ldraw_part((const char NT_GLOBAL*)at(p.w, pl), n);
+      state[1] = F32::ldraw_part((const char NT_GLOBAL*)at(p.m, pl), n);
+      state[2] = F32::ldraw_part((const char NT_GLOBAL*)at(p.v, pl), n);
     }
   }
+}
+template <class GT, bool TABLE, bool PART, int N, bool RT = false>
+__device__ inline void load_rows(const StepParams& p, int j0, int nb, const Place& pl, int n, typename GT::raw_t* raw) {
+  load_sweep<GT, TABLE, PART, N, RT, false>(p, j0, nb, pl, n, raw, nullptr);
+}
+
+template <bool PART>
+__device__ inline void store4(float* base, const Place& pl, int n, f32x4 x) {
+  if (!PART || n >= 4) {
+    st16(at(base, pl), x);
+  } else {
+    float NT_GLOBAL* p = at(base, pl);
 #pragma unroll
-  for (int q = 0; q < VEC / 4; ++q) {
-    st16(p.w + i0 + 4 * q, ow[q]);
-    st16(p.m + i0 + 4 * q, om[q]);
-    st16(p.v + i0 + 4 * q, ov[q]);
+    for (int e = 0; e < 3; ++e)
+      if (e < n) p[e] = x[e];
   }
 }
 
-template <int VEC>
-__device__ inline void gbar_store(const StepParams& p, int64_t i0, const float* gb) {
+// AdamW on VEC coordinates whose state was loaded as 16-byte vectors, then the stores.
+template <bool PART>
+__device__ inline void adamw_store(const StepParams& p, const Place& pl, int n, const float* gb,
+                                   const u32x4* state) {
+  f32x4 ow, om, ov;
 #pragma unroll
-  for (int q = 0; q < VEC / 4; ++q) {
-    f32x4 og = {gb[4 * q], gb[4 * q + 1], gb[4 * q + 2], gb[4 * q + 3]};
-    st16(p.gbar + i0 + 4 * q, og);
+  for (int e = 0; e < 4; ++e) {
+    float w = __builtin_bit_cast(float, (uint32_t)state[0][e]);
+    float m = __builtin_bit_cast(float, (uint32_t)state[1][e]);
+    float v = __builtin_bit_cast(float, (uint32_t)state[2][e]);
+    adamw_coord(p, gb[e], w, m, v);
+    ow[e] = w;
+    om[e] = m;
+    ov[e] = v;
+  }
+  if (!PART || n >= 4) {
+    store4<false>(p.w, pl, 4, ow);
+    store4<false>(p.m, pl, 4, om);
+    store4<false>(p.v, pl, 4, ov);
+  } else {
+    store4<true>(p.w, pl, n, ow);
+    store4<true>(p.m, pl, n, om);
+    store4<true>(p.v, pl, n, ov);
   }
 }
 
 // ---------------------------------------------------------------------------------------------
-// Fast tiles, J <= 16 known at compile time: all J rows of a group of VEC coordinates sit in
-// registers; they need 16-byte aligned rows and state and a tile that lies wholly below d.
+// Tiles, J <= 16 known at compile time: all J rows of a group of VEC coordinates sit in registers.
 // The row sum is carried in fp64 so that the mean is correctly rounded even when the rows cancel.
 // ---------------------------------------------------------------------------------------------
 // One sweep's arithmetic: the means of the lane's VEC coordinates into gb, the sweep's sums into acc.
@@ -493,29 +561,24 @@ __device__ inline void sweep_rows(const StepParams& p, const typename GT::raw_t*
 }
 
 // State update interleaved with the rows: each sweep reads its rows and w, m, v, and writes the state back.
-template <class GT, int J, int MODE, int BLOCK, int ITERS, bool TABLE, bool GBAR>
-__device__ inline void fast_tile(const StepParams& p, int64_t tile, double (*red)[BLOCK / 64][NT_NV], int buf) {
+template <class GT, int J, int MODE, int BLOCK, int ITERS, bool TABLE, bool GBAR, bool PART>
+__device__ inline void tile_rows(const StepParams& p, int64_t tile, double (*red)[BLOCK / 64][NT_NV], int buf) {
   constexpr int VEC = GT::VEC;
   constexpr int TILE = BLOCK * VEC * ITERS;
   LaneAcc acc;
   // a statistics-only sweep with few rows has little in flight per lane: overlap sweeps up to about 64 bytes
   constexpr int ROW_BYTES = VEC * GT::ESIZE;
   constexpr int WANT = 64 / (J * ROW_BYTES);
-  constexpr int U = (MODE == MODE_STATS && ITERS > 1) ? (WANT >= 4 ? 4 : (WANT >= 2 ? 2 : 1)) : 1;
+  constexpr int U = (MODE == MODE_STATS && ITERS > 1 && !PART) ? (WANT >= 4 ? 4 : (WANT >= 2 ? 2 : 1)) : 1;
 #pragma unroll U
   for (int it = 0; it < ITERS; ++it) {
-    const int64_t i0 = tile * TILE + ((int64_t)it * BLOCK + threadIdx.x) * VEC;
+    const Place pl = {tile * TILE + (int64_t)it * BLOCK * VEC, threadIdx.x * VEC};
+    if (PART && pl.s0 >= p.d) break;
+    const int n = PART ? below(p.d, pl.i0()) : VEC;
     typename GT::raw_t raw[J];
-    u32x4 sw[VEC / 4], sm[VEC / 4], sv[VEC / 4];
-#pragma unroll
-    for (int j = 0; j < J; ++j) raw[j] = GT::ldraw(row_base<GT, TABLE>(p, j) + i0 * GT::ESIZE);
+    u32x4 state[3];
+    load_sweep<GT, TABLE, PART, J, false, MODE != MODE_STATS>(p, 0, J, pl, n, raw, state);
     if constexpr (MODE != MODE_STATS) {
-#pragma unroll
-      for (int q = 0; q < VEC / 4; ++q) {
-        sw[q] = ld16(p.w + i0 + 4 * q);
-        sm[q] = ld16(p.m + i0 + 4 * q);
-        sv[q] = ld16(p.v + i0 + 4 * q);
-      }
       // Every load of the sweep is issued before any arithmetic: the compiler must neither sink loads below
       // the arithmetic that precedes their use nor hoist arithmetic between them (measured: up to 5 % at 16
       // rows against schedules that issue the state loads after the rows have arrived).  Statistics-only
@@ -524,8 +587,8 @@ __device__ inline void fast_tile(const StepParams& p, int64_t tile, double (*red
     }
     float gb[VEC];
     sweep_rows<GT, J, MODE>(p, raw, gb, acc);
-    if constexpr (MODE != MODE_STATS) adamw_store<VEC>(p, i0, gb, sw, sm, sv);
-    if (GBAR && p.gbar) gbar_store<VEC>(p, i0, gb);
+    if constexpr (MODE != MODE_STATS) adamw_store<PART>(p, pl, n, gb, state);
+    if (GBAR && p.gbar) store4<PART>(p.gbar, pl, n, f32x4{gb[0], gb[1], gb[2], gb[3]});
   }
   if constexpr (MODE != MODE_ADAMW) tile_reduce<BLOCK>(acc, red, buf, p.partials, tile);
   // AdamW-only tiles end with a block barrier like the other modes: the waves of a block then finish together
@@ -537,7 +600,7 @@ __device__ inline void fast_tile(const StepParams& p, int64_t tile, double (*red
 // row has been read, then w, m, v of all sweeps are read and written in one go.  The memory system charges writes
 // sprinkled among reads several times their volume; gathered at the end of a block's life, and with all blocks
 // of a launch living at the same time (one generation per launch), they reach it as a dense burst.
-template <int MODE, int BLOCK, int ITERS, bool GBAR>
+template <int MODE, int BLOCK, int ITERS, bool GBAR, bool PART>
 __device__ inline void deferred_update(const StepParams& p, int64_t tile, double (*red)[BLOCK / 64][NT_NV], int buf,
                                        const LaneAcc& acc, const f32x4* gbs) {
   constexpr int VEC = 4;
@@ -550,24 +613,24 @@ __device__ inline void deferred_update(const StepParams& p, int64_t tile, double
   if (MODE != MODE_STATS || p.gbar) {
 #pragma unroll 2
     for (int it = 0; it < ITERS; ++it) {
-      const int64_t i0 = tile * TILE + ((int64_t)it * BLOCK + threadIdx.x) * VEC;
+      const Place pl = {tile * TILE + (int64_t)it * BLOCK * VEC, threadIdx.x * VEC};
+      if (PART && pl.s0 >= p.d) break;
+      const int n = PART ? below(p.d, pl.i0()) : VEC;
       const f32x4 g4 = gbs[it * BLOCK + threadIdx.x];   // this lane's own values: no barrier needed for them
       const float gb[VEC] = {g4[0], g4[1], g4[2], g4[3]};
       if constexpr (MODE != MODE_STATS) {
-        u32x4 sw[1], sm[1], sv[1];
-        sw[0] = ld16(p.w + i0);
-        sm[0] = ld16(p.m + i0);
-        sv[0] = ld16(p.v + i0);
-        adamw_store<VEC>(p, i0, gb, sw, sm, sv);
+        u32x4 state[3];
+        load_sweep<F32, false, PART, 0, false, true>(p, 0, 0, pl, n, nullptr, state);
+        adamw_store<PART>(p, pl, n, gb, state);
       }
-      if (GBAR && p.gbar) gbar_store<VEC>(p, i0, gb);
+      if (GBAR && p.gbar) store4<PART>(p.gbar, pl, n, g4);
     }
   }
 }
 
 // Deferred state update, rows in registers: the sweeps read rows only.
-template <class GT, int J, int MODE, int BLOCK, int ITERS, bool TABLE, bool GBAR>
-__device__ inline void fast_tile_defer(const StepParams& p, int64_t tile, double (*red)[BLOCK / 64][NT_NV], int buf,
+template <class GT, int J, int MODE, int BLOCK, int ITERS, bool TABLE, bool GBAR, bool PART>
+__device__ inline void tile_defer(const StepParams& p, int64_t tile, double (*red)[BLOCK / 64][NT_NV], int buf,
                                        f32x4* gbs) {
   constexpr int VEC = GT::VEC;
   static_assert(VEC == 4, "one 16-byte LDS slot per lane and sweep");
@@ -575,19 +638,19 @@ __device__ inline void fast_tile_defer(const StepParams& p, int64_t tile, double
   LaneAcc acc;
 #pragma unroll NT_DEFER_UNROLL
   for (int it = 0; it < ITERS; ++it) {
-    const int64_t i0 = tile * TILE + ((int64_t)it * BLOCK + threadIdx.x) * VEC;
+    const Place pl = {tile * TILE + (int64_t)it * BLOCK * VEC, threadIdx.x * VEC};
+    if (PART && pl.s0 >= p.d) break;
     typename GT::raw_t raw[J];
-#pragma unroll
-    for (int j = 0; j < J; ++j) raw[j] = GT::ldraw(row_base<GT, TABLE>(p, j) + i0 * GT::ESIZE);
+    load_rows<GT, TABLE, PART, J>(p, 0, J, pl, PART ? below(p.d, pl.i0()) : VEC, raw);
     float gb[VEC];
     sweep_rows<GT, J, MODE>(p, raw, gb, acc);
     gbs[it * BLOCK + threadIdx.x] = f32x4{gb[0], gb[1], gb[2], gb[3]};
   }
-  deferred_update<MODE, BLOCK, ITERS, GBAR>(p, tile, red, buf, acc, gbs);
+  deferred_update<MODE, BLOCK, ITERS, GBAR, PART>(p, tile, red, buf, acc, gbs);
 }
 
 // ---------------------------------------------------------------------------------------------
-// Fast tile, J > 16: rows are walked NT_MCHUNK at a time.  One pass over a chunk gives its plain sum
+// Tile, J > 16: rows are walked NT_MCHUNK at a time.  One pass over a chunk gives its plain sum
 // (fp64) and the sum of squares of the values shifted by K, the running mean of the rows before it, hence
 // its centred sum of squares without cancellation; see chunk_merge for the bookkeeping.
 // ---------------------------------------------------------------------------------------------
@@ -614,8 +677,8 @@ __device__ inline void chunk_accumulate(const typename GT::raw_t* raw, int nb, c
 
 // The state update (and the gbar store) of a tile is deferred (see deferred_update): with many rows the writes are
 // a few per cent of the traffic.
-template <class GT, int MODE, int BLOCK, int ITERS, bool TABLE, bool GBAR>
-__device__ inline void fast_tile_multi(const StepParams& p, int64_t tile, double (*red)[BLOCK / 64][NT_NV], int buf,
+template <class GT, int MODE, int BLOCK, int ITERS, bool TABLE, bool GBAR, bool PART>
+__device__ inline void tile_multi(const StepParams& p, int64_t tile, double (*red)[BLOCK / 64][NT_NV], int buf,
                                        f32x4* gbs) {
   constexpr int VEC = GT::VEC;
   static_assert(VEC == 4, "one 16-byte LDS slot per lane and sweep");
@@ -625,16 +688,16 @@ __device__ inline void fast_tile_multi(const StepParams& p, int64_t tile, double
   LaneAcc acc;
 #pragma unroll 1
   for (int it = 0; it < ITERS; ++it) {
-    const int64_t i0 = tile * TILE + ((int64_t)it * BLOCK + threadIdx.x) * VEC;
-    const int64_t goff = i0 * GT::ESIZE;
+    const Place pl = {tile * TILE + (int64_t)it * BLOCK * VEC, threadIdx.x * VEC};
+    if (PART && pl.s0 >= p.d) break;
+    const int n = PART ? below(p.d, pl.i0()) : VEC;
     double S[VEC], sb[VEC];
     float M2[VEC], a[VEC], K[VEC], q[VEC];
 #pragma unroll
     for (int e = 0; e < VEC; ++e) a[e] = 0.f;
     typename GT::raw_t raw[NT_MCHUNK];
     // first chunk (J > NT_JCHUNK >= NT_MCHUNK - 1 here, so it is full), shifted by the first row
-#pragma unroll
-    for (int j = 0; j < NT_MCHUNK; ++j) raw[j] = GT::ldraw(row_base<GT, TABLE>(p, j) + goff);
+    load_rows<GT, TABLE, PART, NT_MCHUNK>(p, 0, NT_MCHUNK, pl, n, raw);
 #pragma unroll
     for (int e = 0; e < VEC; ++e) K[e] = GT::val(raw[0], e);
     chunk_accumulate<GT, false>(raw, NT_MCHUNK, K, sb, q);
@@ -643,17 +706,14 @@ __device__ inline void fast_tile_multi(const StepParams& p, int64_t tile, double
     int j0 = NT_MCHUNK;
 #pragma unroll 1
     for (; j0 + NT_MCHUNK <= J; j0 += NT_MCHUNK) {
-#pragma unroll
-      for (int j = 0; j < NT_MCHUNK; ++j) raw[j] = GT::ldraw(row_base<GT, TABLE>(p, j0 + j) + goff);
+      load_rows<GT, TABLE, PART, NT_MCHUNK>(p, j0, NT_MCHUNK, pl, n, raw);
       chunk_accumulate<GT, false>(raw, NT_MCHUNK, K, sb, q);
 #pragma unroll
       for (int e = 0; e < VEC; ++e) K[e] = chunk_merge(false, j0, NT_MCHUNK, K[e], sb[e], q[e], S[e], M2[e], a[e]);
     }
     if (j0 < J) {
       const int nb = J - j0;
-#pragma unroll
-      for (int j = 0; j < NT_MCHUNK; ++j)
-        if (j < nb) raw[j] = GT::ldraw(row_base<GT, TABLE>(p, j0 + j) + goff);
+      load_rows<GT, TABLE, PART, NT_MCHUNK, true>(p, j0, nb, pl, n, raw);
       chunk_accumulate<GT, true>(raw, nb, K, sb, q);
 #pragma unroll
       for (int e = 0; e < VEC; ++e) K[e] = chunk_merge(false, j0, nb, K[e], sb[e], q[e], S[e], M2[e], a[e]);
@@ -677,23 +737,31 @@ __device__ inline void fast_tile_multi(const StepParams& p, int64_t tile, double
     if constexpr (WRITES) gbs[it * BLOCK + threadIdx.x] = f32x4{gb[0], gb[1], gb[2], gb[3]};
   }
   if constexpr (WRITES)
-    deferred_update<MODE, BLOCK, ITERS, GBAR>(p, tile, red, buf, acc, gbs);
+    deferred_update<MODE, BLOCK, ITERS, GBAR, PART>(p, tile, red, buf, acc, gbs);
   else
     tile_reduce<BLOCK>(acc, red, buf, p.partials, tile);
 }
 
 // ---------------------------------------------------------------------------------------------
 // Kernels.  A launch covers the slots slot0 .. slot1-1 of the ntiles tile slots; block b takes slots slot0 + b,
-// slot0 + b + gridDim.x, ...; tiles below nfull are whole and aligned (fast path), the others go through the
-// guarded path.  When the vector ends in a ragged tile, it has slot 0, so that the slow tile overlaps with
-// everything else.
+// slot0 + b + gridDim.x, ...; tiles below nfull are whole, and when the vector ends in a part of a tile (nfull =
+// ntiles - 1), that one has slot 0, so that its few element-sized accesses overlap with everything else.
 // J_T = 0 selects the J > 16 row-walking variant.
 // ---------------------------------------------------------------------------------------------
+template <class GT, int J_T, int MODE, int BLOCK, int ITERS, bool TABLE, bool GBAR, bool DEFER_T, bool PART>
+__device__ inline void run_tile(const StepParams& p, int64_t tile, double (*red)[BLOCK / 64][NT_NV], int buf, f32x4* gbs) {
+  if constexpr (J_T == 0)   // one copy serves both: its chunks of rows need the scalar registers of two
+    tile_multi<GT, MODE, BLOCK, ITERS, TABLE, GBAR, true>(p, tile, red, buf, gbs);
+  else if constexpr (DEFER_T)
+    tile_defer<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, PART>(p, tile, red, buf, gbs);
+  else
+    tile_rows<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, PART>(p, tile, red, buf);
+}
+
 // GBAR = false compiles the gbar store out (statistics-only launch class, so that sweeps can overlap).
 // DEFER_T: up to 16 rows with the state update deferred to the end of the tile (always so beyond 16 rows).
 template <class GT, int J_T, int MODE, int BLOCK, int ITERS, bool TABLE, bool GBAR, bool DEFER_T = false>
-__global__ __launch_bounds__(BLOCK) void k_step(StepParams p, int64_t nfull, int64_t ntiles, int64_t slot0, int64_t slot1,
-                                                 WsControl* ctl) {
+__global__ __launch_bounds__(BLOCK) void k_step(StepParams p, int64_t nfull, int64_t ntiles, int64_t slot0, int64_t slot1) {
   constexpr int TILE = BLOCK * GT::VEC * ITERS;
   static_assert(NT_TILE_MAX % TILE == 0, "tile sizes must divide NT_TILE_MAX");
   __shared__ double red[2][BLOCK / 64][NT_NV];
@@ -702,39 +770,17 @@ __global__ __launch_bounds__(BLOCK) void k_step(StepParams p, int64_t nfull, int
   static_assert(!DEFER_T || DEFER, "a deferred update needs something to write");
   __shared__ f32x4 gbs[DEFER ? ITERS * BLOCK + NT_LDS_PAD_LARGE / 16 : 1];
   int buf = 0;
-  if constexpr (TABLE) {
-    // the host cannot see the row pointers: k_rows_aligned has looked at them and left its verdict here
-    if (!ctl->rows_aligned) nfull = 0;
-  }
-  const int64_t nrest = ntiles - nfull;  // guarded tiles (0 or 1 on the aligned path)
+  const int64_t npart = ntiles - nfull;  // 0 or 1
   for (int64_t t = slot0 + blockIdx.x; t < slot1; t += gridDim.x) {
-    // rotate: the first nrest slots are the guarded tiles nfull.., then the fast tiles 0..nfull-1
-    const int64_t tile = (t < nrest) ? nfull + t : t - nrest;
-    if (tile < nfull) {
-      if constexpr (J_T > 0 && DEFER_T)
-        fast_tile_defer<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR>(p, tile, red, buf, gbs);
-      else if constexpr (J_T > 0)
-        fast_tile<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR>(p, tile, red, buf);
-      else
-        fast_tile_multi<GT, MODE, BLOCK, ITERS, TABLE, GBAR>(p, tile, red, buf, gbs);
-    } else {
-      guarded_tile<GT, J_T, MODE, BLOCK, TABLE, GBAR>(p, tile, TILE, red, buf);
-    }
+    // rotate: the part tile (if any) first, then the whole tiles 0..nfull-1
+    const bool part = t < npart;
+    const int64_t tile = part ? nfull : t - npart;
+    if (J_T > 0 && !part)
+      run_tile<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, DEFER_T, false>(p, tile, red, buf, gbs);
+    else
+      run_tile<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, DEFER_T, true>(p, tile, red, buf, gbs);
     buf ^= 1;
   }
-}
-
-// Pointer-table calls: are all J row pointers 16-byte aligned?  One small block, once per call, so that the
-// blocks of k_step need not walk the table themselves.
-__global__ __launch_bounds__(256) void k_rows_aligned(const void* const* rows, int J, WsControl* ctl) {
-  __shared__ unsigned int bits;
-  if (threadIdx.x == 0) bits = 0u;
-  __syncthreads();
-  unsigned int mine = 0u;
-  for (int j = threadIdx.x; j < J; j += 256) mine |= (unsigned int)((uintptr_t)rows[j] & 15u);
-  if (mine) atomicOr(&bits, mine);
-  __syncthreads();
-  if (threadIdx.x == 0) ctl->rows_aligned = bits ? 0u : 1u;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1108,31 +1154,22 @@ __global__ __launch_bounds__(NT_LAYER_THREADS) void k_layer_stats(StepParams p, 
   out[l] = r;
 }
 
-// Phase 2 of the clipped variant: AdamW on scale * gbar, gbar read from memory.  One sweep per block,
-// 4 coordinates per lane; lanes whose 4 coordinates are not all below d, or unaligned buffers, go
-// element by element.
+// Phase 2 of the clipped variant: AdamW on scale * gbar, gbar read from memory.  One sweep per block, 4 coordinates
+// per lane.
 __global__ __launch_bounds__(NT_AUX_BLOCK) void k_adamw_gbar(StepParams p, const float* gbar, float grad_scale,
-                                                         const nt_result* res, int aligned, int64_t block0) {
+                                                         const nt_result* res, int64_t block0) {
   float scale = grad_scale;
   if (res) scale *= (float)res->clip_coef;
-  const int64_t i0 = ((block0 + blockIdx.x) * NT_AUX_BLOCK + threadIdx.x) * NT_VEC;
-  if (i0 >= p.d) return;
-  if (aligned && i0 + NT_VEC <= p.d) {
-    const u32x4 sg = ld16(gbar + i0);
-    u32x4 sw = ld16(p.w + i0), sm = ld16(p.m + i0), sv = ld16(p.v + i0);
-    float gb[NT_VEC];
+  const Place pl = {(block0 + blockIdx.x) * NT_AUX_BLOCK * NT_VEC, threadIdx.x * NT_VEC};
+  const int n = below(p.d, pl.i0());
+  if (n == 0) return;
+  u32x4 sg, state[3];
+  p.grads = gbar;   // as the only row
+  load_sweep<F32, false, true, 1, false, true>(p, 0, 0, pl, n, &sg, state);
+  float gb[NT_VEC];
 #pragma unroll
-    for (int e = 0; e < NT_VEC; ++e) gb[e] = scale * __builtin_bit_cast(float, (uint32_t)sg[e]);
-    adamw_store<NT_VEC>(p, i0, gb, &sw, &sm, &sv);
-  } else {
-    for (int64_t i = i0; i < i0 + NT_VEC && i < p.d; ++i) {
-      float w = p.w[i], m = p.m[i], v = p.v[i];
-      adamw_coord(p, scale * gbar[i], w, m, v);
-      p.w[i] = w;
-      p.m[i] = m;
-      p.v[i] = v;
-    }
-  }
+  for (int e = 0; e < NT_VEC; ++e) gb[e] = scale * __builtin_bit_cast(float, (uint32_t)sg[e]);
+  adamw_store<true>(p, pl, n, gb, state);
 }
 
 __global__ __launch_bounds__(NT_AUX_BLOCK) void k_copy16(f32x4* dst, const u32x4* src, int64_t n16) {
@@ -1167,7 +1204,7 @@ __global__ __launch_bounds__(NT_AUX_BLOCK) void k_calib_streams(CalibStreams s, 
     u32x4 b[R16 > 0 ? R16 : 1];
     u32x4 c[W > 0 ? W : 1];
 #pragma unroll
-    for (int k = 0; k < R8; ++k) a[k] = ld_vec<true, u32x2>(s.r8[k] + 8 * i);
+    for (int k = 0; k < R8; ++k) a[k] = ld_nt<u32x2>(s.r8[k] + 8 * i);
 #pragma unroll
     for (int k = 0; k < R16; ++k) b[k] = ld16(s.r16[k] + 16 * i);
     if constexpr (RMW) {
@@ -1309,8 +1346,8 @@ int blocks_per_cu() {
 }
 
 template <class GT, int MODE, bool TABLE, int BS, int IS, bool GBAR>
-hipError_t launch_step_shape(const StepParams& p, int cls, int64_t nfull, int64_t ntiles, WsControl* ctl,
-                             int max_grid, hipStream_t st) {
+hipError_t launch_step_shape(const StepParams& p, int cls, int64_t nfull, int64_t ntiles, int max_grid,
+                             hipStream_t st) {
   const bool long_class = cls == CLS_LONG;
   constexpr bool WRITES = (MODE != MODE_STATS) || GBAR;
   const bool gbar = MODE == MODE_STATS && p.gbar != nullptr;
@@ -1347,12 +1384,12 @@ hipError_t launch_step_shape(const StepParams& p, int cls, int64_t nfull, int64_
     if constexpr (WRITES && JJ * GT::ESIZE >= defer_row_bytes(MODE)) {                                          \
       if (long_class) {                                                                                         \
         hipLaunchKernelGGL((k_step<GT, JJ, MODE, NT_BLOCK_DEFER, NT_ITERS_DEFER, TABLE, true, true>), dim3(grid), \
-                           dim3(NT_BLOCK_DEFER), 0, st, p, nfull, ntiles, slot0, slot1, ctl);                   \
+                           dim3(NT_BLOCK_DEFER), 0, st, p, nfull, ntiles, slot0, slot1);                   \
         break;                                                                                                  \
       }                                                                                                         \
     }                                                                                                           \
     hipLaunchKernelGGL((k_step<GT, JJ, MODE, BS, IS, TABLE, GBAR>), dim3(grid), dim3(BS), 0, st, p, nfull,      \
-                       ntiles, slot0, slot1, ctl);                                                              \
+                       ntiles, slot0, slot1);                                                              \
     break;
     switch (p.J) {
       NT_CASE(2) NT_CASE(3) NT_CASE(4) NT_CASE(5) NT_CASE(6) NT_CASE(7) NT_CASE(8) NT_CASE(9)
@@ -1360,16 +1397,16 @@ hipError_t launch_step_shape(const StepParams& p, int cls, int64_t nfull, int64_
       default:
         if (MODE == MODE_STATS && p.gbar == nullptr)
           hipLaunchKernelGGL((k_step<GT, 0, MODE, NT_BLOCK_LARGE_STATS, NT_ITERS_LARGE_STATS, TABLE, false>), dim3(grid),
-                             dim3(NT_BLOCK_LARGE_STATS), 0, st, p, nfull, ntiles, slot0, slot1, ctl);
+                             dim3(NT_BLOCK_LARGE_STATS), 0, st, p, nfull, ntiles, slot0, slot1);
         else if (!long_class)
           hipLaunchKernelGGL((k_step<GT, 0, MODE, NT_BLOCK_MANY_SHORT, NT_ITERS_MANY_SHORT, TABLE, true>), dim3(grid),
-                             dim3(NT_BLOCK_MANY_SHORT), 0, st, p, nfull, ntiles, slot0, slot1, ctl);
+                             dim3(NT_BLOCK_MANY_SHORT), 0, st, p, nfull, ntiles, slot0, slot1);
         else if (p.J <= NT_FEW_ROWS)
           hipLaunchKernelGGL((k_step<GT, 0, MODE, NT_BLOCK_FEW, NT_ITERS_FEW, TABLE, true>), dim3(grid),
-                             dim3(NT_BLOCK_FEW), 0, st, p, nfull, ntiles, slot0, slot1, ctl);
+                             dim3(NT_BLOCK_FEW), 0, st, p, nfull, ntiles, slot0, slot1);
         else
           hipLaunchKernelGGL((k_step<GT, 0, MODE, NT_BLOCK_LARGE, NT_ITERS_LARGE, TABLE, true>), dim3(grid),
-                             dim3(NT_BLOCK_LARGE), 0, st, p, nfull, ntiles, slot0, slot1, ctl);
+                             dim3(NT_BLOCK_LARGE), 0, st, p, nfull, ntiles, slot0, slot1);
     }
 #undef NT_CASE
     const hipError_t e = hipGetLastError();
@@ -1380,30 +1417,29 @@ hipError_t launch_step_shape(const StepParams& p, int cls, int64_t nfull, int64_
 
 // picks the launch class (block size, sweeps per tile) that tile_cfg() describes
 template <class GT, int MODE, bool TABLE>
-hipError_t launch_step(const StepParams& p, int cls, int64_t nfull, int64_t ntiles, WsControl* ctl, int grid,
-                       hipStream_t st) {
+hipError_t launch_step(const StepParams& p, int cls, int64_t nfull, int64_t ntiles, int grid, hipStream_t st) {
   if constexpr (MODE == MODE_STATS) {
     // read-only statistics over a short vector borrow the kernels that can also store gbar (there is none to store)
     if (p.gbar || (cls == CLS_SHORT_STATS && p.J <= NT_JCHUNK))
       return launch_step_shape<GT, MODE, TABLE, NT_BLOCK_STATS_GBAR, NT_ITERS_STATS_GBAR, true>(p, cls, nfull, ntiles,
-                                                                                                 ctl, grid, st);
-    return launch_step_shape<GT, MODE, TABLE, NT_BLOCK_STATS, NT_ITERS_STATS, false>(p, cls, nfull, ntiles, ctl, grid,
+                                                                                                 grid, st);
+    return launch_step_shape<GT, MODE, TABLE, NT_BLOCK_STATS, NT_ITERS_STATS, false>(p, cls, nfull, ntiles, grid,
                                                                                       st);
   } else if constexpr (MODE == MODE_ADAMW) {
-    return launch_step_shape<GT, MODE, TABLE, NT_BLOCK_ADAMW, NT_ITERS_ADAMW, true>(p, cls, nfull, ntiles, ctl, grid,
+    return launch_step_shape<GT, MODE, TABLE, NT_BLOCK_ADAMW, NT_ITERS_ADAMW, true>(p, cls, nfull, ntiles, grid,
                                                                                      st);
   } else {
-    return launch_step_shape<GT, MODE, TABLE, NT_BLOCK, NT_ITERS, true>(p, cls, nfull, ntiles, ctl, grid, st);
+    return launch_step_shape<GT, MODE, TABLE, NT_BLOCK, NT_ITERS, true>(p, cls, nfull, ntiles, grid, st);
   }
 }
 
 template <class GT, bool TABLE>
-hipError_t launch_step_mode(int mode, const StepParams& p, int cls, int64_t nfull, int64_t ntiles, WsControl* ctl,
-                            int grid, hipStream_t st) {
+hipError_t launch_step_mode(int mode, const StepParams& p, int cls, int64_t nfull, int64_t ntiles, int grid,
+                            hipStream_t st) {
   switch (mode) {
-    case MODE_FULL: return launch_step<GT, MODE_FULL, TABLE>(p, cls, nfull, ntiles, ctl, grid, st);
-    case MODE_STATS: return launch_step<GT, MODE_STATS, TABLE>(p, cls, nfull, ntiles, ctl, grid, st);
-    default: return launch_step<GT, MODE_ADAMW, TABLE>(p, cls, nfull, ntiles, ctl, grid, st);
+    case MODE_FULL: return launch_step<GT, MODE_FULL, TABLE>(p, cls, nfull, ntiles, grid, st);
+    case MODE_STATS: return launch_step<GT, MODE_STATS, TABLE>(p, cls, nfull, ntiles, grid, st);
+    default: return launch_step<GT, MODE_ADAMW, TABLE>(p, cls, nfull, ntiles, grid, st);
   }
 }
 
@@ -1514,27 +1550,17 @@ static int enqueue_step(const void* grads, bool table, nt_dtype gdtype, int64_t 
                     ? (float)(hyper->eta * hyper->eta * (double)hyper->b_k * (double)(J - hyper->ddof))
                     : -1.0f;
 
-  WsControl* ctl = (WsControl*)((double*)workspace + NT_WS_CONTROL);
   if (ntiles > 0) {
-    // row alignment: checked here for a strided matrix, by a small kernel for a pointer table
-    if (table) {
-      hipLaunchKernelGGL(k_rows_aligned, dim3(1), dim3(256), 0, st, (const void* const*)grads, (int)J, ctl);
-      const hipError_t e = hipGetLastError();
-      if (e != hipSuccess) return hip_code(e);
-    }
-    bool al = table || (aligned16(grads) && ((ld * esize) % 16 == 0));
-    if (mode != MODE_STATS) al = al && aligned16(w) && aligned16(m) && aligned16(v);
-    if (p.gbar) al = al && aligned16(p.gbar);
-    const int64_t nfull = al ? d / tc : 0;
+    const int64_t nfull = d / tc;
     const int64_t max_grid = (int64_t)cu_count() * NT_BLOCKS_PER_CU;
     const int grid = (int)(ntiles < max_grid ? ntiles : max_grid);
     hipError_t e;
     if (table)
-      e = (gdtype == NT_F32) ? launch_step_mode<F32, true>(mode, p, cls, nfull, ntiles, ctl, grid, st)
-                             : launch_step_mode<BF16, true>(mode, p, cls, nfull, ntiles, ctl, grid, st);
+      e = (gdtype == NT_F32) ? launch_step_mode<F32, true>(mode, p, cls, nfull, ntiles, grid, st)
+                             : launch_step_mode<BF16, true>(mode, p, cls, nfull, ntiles, grid, st);
     else
-      e = (gdtype == NT_F32) ? launch_step_mode<F32, false>(mode, p, cls, nfull, ntiles, ctl, grid, st)
-                             : launch_step_mode<BF16, false>(mode, p, cls, nfull, ntiles, ctl, grid, st);
+      e = (gdtype == NT_F32) ? launch_step_mode<F32, false>(mode, p, cls, nfull, ntiles, grid, st)
+                             : launch_step_mode<BF16, false>(mode, p, cls, nfull, ntiles, grid, st);
     if (e != hipSuccess) return hip_code(e);
   }
 
@@ -1586,7 +1612,6 @@ static int enqueue_adamw_gbar(const float* gbar, int64_t d, float* w, float* m, 
   p.m = m;
   p.v = v;
   fill_adamw_params(p, hyper);
-  const int aligned = aligned16(gbar) && aligned16(w) && aligned16(m) && aligned16(v);
   const int64_t per_block = (int64_t)NT_AUX_BLOCK * NT_VEC;
   const int64_t nblocks = (d + per_block - 1) / per_block;
   // in runs of blocks, like the step kernel (see NT_CHUNK_FULL)
@@ -1594,7 +1619,7 @@ static int enqueue_adamw_gbar(const float* gbar, int64_t d, float* w, float* m, 
   for (int64_t b0 = 0; b0 < nblocks; b0 += per_launch) {
     const int64_t grid = (nblocks - b0 < per_launch) ? nblocks - b0 : per_launch;
     hipLaunchKernelGGL(k_adamw_gbar, dim3((unsigned)grid), dim3(NT_AUX_BLOCK), 0, st, p, gbar, (float)grad_scale,
-                       result_dev, aligned, b0);
+                       result_dev, b0);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_code(e);
   }
