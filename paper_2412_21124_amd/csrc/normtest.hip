@@ -522,7 +522,7 @@ __device__ inline void adamw_store(const StepParams& p, const Place& pl, int n, 
 // The row sum is carried in fp64 so that the mean is correctly rounded even when the rows cancel.
 // ---------------------------------------------------------------------------------------------
 // One sweep's arithmetic: the means of the lane's VEC coordinates into gb, the sweep's sums into acc.
-template <class GT, int J, int MODE>
+template <class GT, int J, int MODE, bool COORD>
 __device__ inline void sweep_rows(const StepParams& p, const typename GT::raw_t* raw, float* gb, LaneAcc& acc) {
   constexpr int VEC = GT::VEC;
   double s[VEC];
@@ -552,7 +552,7 @@ __device__ inline void sweep_rows(const StepParams& p, const typename GT::raw_t*
     for (int e = 0; e < VEC; ++e) {
       const float sf = (float)s[e];
       b[e] = sf * sf;
-      coord_test(p.coord_thr, c[e], gb[e], acc);
+      if constexpr (COORD) coord_test(p.coord_thr, c[e], gb[e], acc);
     }
     acc.A += (double)lane_tree<VEC>(a);
     acc.B += (double)lane_tree<VEC>(b);
@@ -561,14 +561,16 @@ __device__ inline void sweep_rows(const StepParams& p, const typename GT::raw_t*
 }
 
 // State update interleaved with the rows: each sweep reads its rows and w, m, v, and writes the state back.
-template <class GT, int J, int MODE, int BLOCK, int ITERS, bool TABLE, bool GBAR, bool PART>
+template <class GT, int J, int MODE, int BLOCK, int ITERS, bool TABLE, bool GBAR, bool COORD, bool PART>
 __device__ inline void tile_rows(const StepParams& p, int64_t tile, double (*red)[BLOCK / 64][NT_NV], int buf) {
   constexpr int VEC = GT::VEC;
   constexpr int TILE = BLOCK * VEC * ITERS;
   LaneAcc acc;
-  // a statistics-only sweep with few rows has little in flight per lane: overlap sweeps up to about 64 bytes
+  // a statistics-only sweep with few rows has little in flight per lane: overlap sweeps up to about 64 bytes (read-only,
+  // 128 bytes are 35 % slower at 4 bf16 rows), and where gbar is stored two sweeps of 64 bytes (8 bf16 rows, d = 2e8: 656
+  // -> 630 us; 4 fp32 rows 674 -> 650; two sweeps of 40 or 48 bytes are 10 and 4 % slower than one)
   constexpr int ROW_BYTES = VEC * GT::ESIZE;
-  constexpr int WANT = 64 / (J * ROW_BYTES);
+  constexpr int WANT = (GBAR && J * ROW_BYTES >= 64 ? 128 : 64) / (J * ROW_BYTES);
   constexpr int U = (MODE == MODE_STATS && ITERS > 1 && !PART) ? (WANT >= 4 ? 4 : (WANT >= 2 ? 2 : 1)) : 1;
 #pragma unroll U
   for (int it = 0; it < ITERS; ++it) {
@@ -586,7 +588,7 @@ __device__ inline void tile_rows(const StepParams& p, int64_t tile, double (*red
       __builtin_amdgcn_sched_barrier(0);
     }
     float gb[VEC];
-    sweep_rows<GT, J, MODE>(p, raw, gb, acc);
+    sweep_rows<GT, J, MODE, COORD>(p, raw, gb, acc);
     if constexpr (MODE != MODE_STATS) adamw_store<PART>(p, pl, n, gb, state);
     if (GBAR && p.gbar) store4<PART>(p.gbar, pl, n, f32x4{gb[0], gb[1], gb[2], gb[3]});
   }
@@ -643,7 +645,7 @@ __device__ inline void tile_defer(const StepParams& p, int64_t tile, double (*re
     typename GT::raw_t raw[J];
     load_rows<GT, TABLE, PART, J>(p, 0, J, pl, PART ? below(p.d, pl.i0()) : VEC, raw);
     float gb[VEC];
-    sweep_rows<GT, J, MODE>(p, raw, gb, acc);
+    sweep_rows<GT, J, MODE, true>(p, raw, gb, acc);
     gbs[it * BLOCK + threadIdx.x] = f32x4{gb[0], gb[1], gb[2], gb[3]};
   }
   deferred_update<MODE, BLOCK, ITERS, GBAR, PART>(p, tile, red, buf, acc, gbs);
@@ -748,19 +750,20 @@ __device__ inline void tile_multi(const StepParams& p, int64_t tile, double (*re
 // ntiles - 1), that one has slot 0, so that its few element-sized accesses overlap with everything else.
 // J_T = 0 selects the J > 16 row-walking variant.
 // ---------------------------------------------------------------------------------------------
-template <class GT, int J_T, int MODE, int BLOCK, int ITERS, bool TABLE, bool GBAR, bool DEFER_T, bool PART>
+template <class GT, int J_T, int MODE, int BLOCK, int ITERS, bool TABLE, bool GBAR, bool DEFER_T, bool COORD, bool PART>
 __device__ inline void run_tile(const StepParams& p, int64_t tile, double (*red)[BLOCK / 64][NT_NV], int buf, f32x4* gbs) {
   if constexpr (J_T == 0)   // one copy serves both: its chunks of rows need the scalar registers of two
     tile_multi<GT, MODE, BLOCK, ITERS, TABLE, GBAR, true>(p, tile, red, buf, gbs);
   else if constexpr (DEFER_T)
     tile_defer<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, PART>(p, tile, red, buf, gbs);
   else
-    tile_rows<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, PART>(p, tile, red, buf);
+    tile_rows<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, COORD, PART>(p, tile, red, buf);
 }
 
 // GBAR = false compiles the gbar store out (statistics-only launch class, so that sweeps can overlap).
 // DEFER_T: up to 16 rows with the state update deferred to the end of the tile (always so beyond 16 rows).
-template <class GT, int J_T, int MODE, int BLOCK, int ITERS, bool TABLE, bool GBAR, bool DEFER_T = false>
+// COORD = false compiles the coordinate-wise test out (see plain_stats).
+template <class GT, int J_T, int MODE, int BLOCK, int ITERS, bool TABLE, bool GBAR, bool DEFER_T = false, bool COORD = true>
 __global__ __launch_bounds__(BLOCK) void k_step(StepParams p, int64_t nfull, int64_t ntiles, int64_t slot0, int64_t slot1) {
   constexpr int TILE = BLOCK * GT::VEC * ITERS;
   static_assert(NT_TILE_MAX % TILE == 0, "tile sizes must divide NT_TILE_MAX");
@@ -776,9 +779,9 @@ __global__ __launch_bounds__(BLOCK) void k_step(StepParams p, int64_t nfull, int
     const bool part = t < npart;
     const int64_t tile = part ? nfull : t - npart;
     if (J_T > 0 && !part)
-      run_tile<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, DEFER_T, false>(p, tile, red, buf, gbs);
+      run_tile<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, DEFER_T, COORD, false>(p, tile, red, buf, gbs);
     else
-      run_tile<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, DEFER_T, true>(p, tile, red, buf, gbs);
+      run_tile<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, DEFER_T, COORD, true>(p, tile, red, buf, gbs);
     buf ^= 1;
   }
 }
@@ -1251,6 +1254,15 @@ struct TileCfg {
   int block, iters;
   int64_t coords() const { return (int64_t)block * NT_VEC * iters; }
 };
+// Kernels without the coordinate-wise test, for calls that do not ask for it: its branch per coordinate keeps a sweep's
+// instructions from being scheduled together and consecutive sweeps from overlapping, which shows where there is little
+// traffic per coordinate.  Measured without against with it, GB/s at d = 2e8..3e8: read-only statistics of 2 / 4 / 8 bf16
+// rows 6250 / 6810 / 6990 against 3940 / 6040 / 6960; statistics with gbar, 2 / 3 / 4 rows 5900 / 6040 / 6130 against
+// 5350 / 5730 / 5290, 5 and 6 rows -5 and -1 %; fused step, 2 / 3 / 4 bf16 and 2 fp32 rows 5920 / 5870 / 5940 / 5800
+// against 5550 / 5560 / 5790 / 5600, 5 to 8 bf16 rows -1 .. +0.8 %, 3 to 5 fp32 rows -3 .. -5 %.
+constexpr bool plain_stats(int esize, int J, int mode, bool gbar) {
+  return (mode == MODE_STATS && !gbar) || (mode != MODE_ADAMW && J * esize <= 8);
+}
 constexpr int defer_row_bytes(int mode) { return mode == MODE_ADAMW ? NT_DEFER_ROW_BYTES_ADAMW : NT_DEFER_ROW_BYTES; }
 // Which launch class a call takes beside its row count, dtype and mode: CLS_LONG, the classes for long vectors
 // (large tiles, state update deferred, one generation of blocks per launch); CLS_SHORT_STATS, read-only statistics
@@ -1388,8 +1400,15 @@ hipError_t launch_step_shape(const StepParams& p, int cls, int64_t nfull, int64_
         break;                                                                                                  \
       }                                                                                                         \
     }                                                                                                           \
+    if constexpr (plain_stats(GT::ESIZE, JJ, MODE, GBAR)) {                                                     \
+      if (p.coord_thr < 0.f) {                                                                                  \
+        hipLaunchKernelGGL((k_step<GT, JJ, MODE, BS, IS, TABLE, GBAR, false, false>), dim3(grid), dim3(BS), 0,  \
+                           st, p, nfull, ntiles, slot0, slot1);                                                 \
+        break;                                                                                                  \
+      }                                                                                                         \
+    }                                                                                                           \
     hipLaunchKernelGGL((k_step<GT, JJ, MODE, BS, IS, TABLE, GBAR>), dim3(grid), dim3(BS), 0, st, p, nfull,      \
-                       ntiles, slot0, slot1);                                                              \
+                       ntiles, slot0, slot1);                                                                   \
     break;
     switch (p.J) {
       NT_CASE(2) NT_CASE(3) NT_CASE(4) NT_CASE(5) NT_CASE(6) NT_CASE(7) NT_CASE(8) NT_CASE(9)

@@ -1,0 +1,39 @@
+"""Calls without the coordinate-wise test run kernels that have it compiled out (few bytes of rows per coordinate, and
+read-only statistics): they must give the bits of the calls that ask for it, in every output both share."""
+from __future__ import annotations
+
+import pytest
+import torch
+
+import helpers as H
+from paper_2412_21124_amd import binding as B
+from paper_2412_21124_amd import synth
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+STATS, ADAMW, GBAR = B.NT_DO_STATS, B.NT_DO_ADAMW, B.NT_WRITE_GBAR
+
+
+# both sides of the 8 bytes per coordinate, and overlapped sweeps of 64 bytes (8 bf16 / 4 fp32 rows); short and long
+# statistics vectors (2^21), each with a part tile
+@pytest.mark.parametrize("J,gdtype", [(2, torch.bfloat16), (4, torch.bfloat16), (5, torch.bfloat16), (8, torch.bfloat16),
+                                      (2, torch.float32), (3, torch.float32), (4, torch.float32), (16, torch.bfloat16)])
+@pytest.mark.parametrize("flags", [STATS | ADAMW, STATS, STATS | GBAR])
+@pytest.mark.parametrize("d", [4097, 3 * 16384 + 5, (1 << 21) + 4099])
+def test_same_bits_with_and_without_the_coordinate_test(J, gdtype, flags, d):
+    wl = synth.make("t", J, d, gdtype=gdtype, sigma=1e-2, seed=J + d, device=DEV, hyper=synth.Hyper(b_k=64, round_to=J))
+    h = wl.hyper
+    got = []
+    for extra in (0, B.NT_COORD_TEST):
+        hy = B.make_hyper(lr=h.lr, beta1=h.beta1, beta2=h.beta2, eps=h.eps, weight_decay=h.weight_decay, eta=h.eta,
+                          step=h.step, b_k=h.b_k, b_max=h.b_max, round_to=h.round_to, ddof=h.ddof, flags=flags | extra)
+        state = [wl.w.clone(), wl.m.clone(), wl.v.clone(), torch.zeros_like(wl.w)]
+        res = B.read_result(B.normtest_step(wl.grads, *state[:3], hy, gbar_out=state[3])).as_dict()
+        got.append((res, state))
+    (plain, s0), (coord, s1) = got
+    assert plain["coord_fail"] == -1 and coord["coord_fail"] >= 0
+    for k in plain:
+        if k not in ("coord_fail", "coord_max_ratio"):
+            assert plain[k] == coord[k], k
+    assert all(torch.equal(a, b) for a, b in zip(s0, s1))
+    H.assert_stats_close(plain, H.oracle_full(wl.grads, d, J, h))
