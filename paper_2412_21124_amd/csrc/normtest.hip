@@ -446,17 +446,16 @@ struct RowWalk {
   }
 };
 
-// Rows j0 .. j0+N-1 of the lane's coordinates (RT: only the first nb of them), and with STATE w, m, v too, all under one
-// branch so that every load of a sweep is in flight before the first wait.
-template <class GT, bool TABLE, bool PART, int N, bool RT, bool STATE>
-__device__ inline void load_sweep(const StepParams& p, int j0, int nb, const Place& pl, int n, typename GT::raw_t* raw,
+// Rows j0 .. j0+N-1 of the lane's coordinates, and with STATE w, m, v too, all under one branch so that every load of a
+// sweep is in flight before the first wait.
+template <class GT, bool TABLE, bool PART, int N, bool STATE>
+__device__ inline void load_sweep(const StepParams& p, int j0, const Place& pl, int n, typename GT::raw_t* raw,
                                   u32x4* state) {
   const uint32_t lane = pl.u * GT::ESIZE;
   if (!PART || n >= GT::VEC) {
     RowWalk<GT, TABLE> row(p, j0, pl.s0);
 #pragma unroll
-    for (int j = 0; j < N; ++j)
-      if (!RT || j < nb) raw[j] = GT::ldraw(row.next() + lane);
+    for (int j = 0; j < N; ++j) raw[j] = GT::ldraw(row.next() + lane);
     if constexpr (STATE) {
       state[0] = ld16(at(p.w, pl));
       state[1] = ld16(at(p.m, pl));
@@ -465,8 +464,12 @@ __device__ inline void load_sweep(const StepParams& p, int j0, int nb, const Pla
   } else {
     RowWalk<GT, TABLE> row(p, j0, pl.s0);
 #pragma unroll
-    for (int j = 0; j < N; ++j)
-      if (!RT || j < nb) raw[j] = GT::ldraw_part(row.next() + lane, n);
+    for (int j = 0; j < N; ++j) {
+      raw[j] = GT::ldraw_part(row.next() + lane, n);
+      // used at once, so that no load of this branch is pending behind it: the wait before each row's first use below
+      // would have to allow for it and be a wait for all rows (24 rows, d = 3e7: 377 -> 454 us)
+      asm volatile("" : "+v"(raw[j]));
+    }
     if constexpr (STATE) {
       state[0] = F32::ldraw_part((const char NT_GLOBAL*)at(p.w, pl), n);
       state[1] = F32::ldraw_part((const char NT_GLOBAL*)at(p.m, pl), n);
@@ -474,9 +477,9 @@ __device__ inline void load_sweep(const StepParams& p, int j0, int nb, const Pla
     }
   }
 }
-template <class GT, bool TABLE, bool PART, int N, bool RT = false>
-__device__ inline void load_rows(const StepParams& p, int j0, int nb, const Place& pl, int n, typename GT::raw_t* raw) {
-  load_sweep<GT, TABLE, PART, N, RT, false>(p, j0, nb, pl, n, raw, nullptr);
+template <class GT, bool TABLE, bool PART, int N>
+__device__ inline void load_rows(const StepParams& p, int j0, const Place& pl, int n, typename GT::raw_t* raw) {
+  load_sweep<GT, TABLE, PART, N, false>(p, j0, pl, n, raw, nullptr);
 }
 
 template <bool PART>
@@ -579,7 +582,7 @@ __device__ inline void tile_rows(const StepParams& p, int64_t tile, double (*red
     const int n = PART ? below(p.d, pl.i0()) : VEC;
     typename GT::raw_t raw[J];
     u32x4 state[3];
-    load_sweep<GT, TABLE, PART, J, false, MODE != MODE_STATS>(p, 0, J, pl, n, raw, state);
+    load_sweep<GT, TABLE, PART, J, MODE != MODE_STATS>(p, 0, pl, n, raw, state);
     if constexpr (MODE != MODE_STATS) {
       // Every load of the sweep is issued before any arithmetic: the compiler must neither sink loads below
       // the arithmetic that precedes their use nor hoist arithmetic between them (measured: up to 5 % at 16
@@ -598,6 +601,26 @@ __device__ inline void tile_rows(const StepParams& p, int64_t tile, double (*red
   if constexpr (MODE == MODE_ADAMW) __syncthreads();
 }
 
+template <int MODE, int BLOCK, int ITERS, bool GBAR, bool PART>
+__device__ inline void deferred_sweeps(const StepParams& p, int64_t tile, const f32x4* gbs) {
+  constexpr int VEC = 4;
+  constexpr int TILE = BLOCK * VEC * ITERS;
+#pragma unroll 2
+  for (int it = 0; it < ITERS; ++it) {
+    const Place pl = {tile * TILE + (int64_t)it * BLOCK * VEC, threadIdx.x * VEC};
+    if (PART && pl.s0 >= p.d) break;
+    const int n = PART ? below(p.d, pl.i0()) : VEC;
+    const f32x4 g4 = gbs[it * BLOCK + threadIdx.x];   // this lane's own values: no barrier needed for them
+    const float gb[VEC] = {g4[0], g4[1], g4[2], g4[3]};
+    if constexpr (MODE != MODE_STATS) {
+      u32x4 state[3];
+      load_sweep<F32, false, PART, 0, true>(p, 0, pl, n, nullptr, state);
+      adamw_store<PART>(p, pl, n, gb, state);
+    }
+    if (GBAR && p.gbar) store4<PART>(p.gbar, pl, n, g4);
+  }
+}
+
 // The end of a tile whose state update was deferred: the means of all its sweeps wait in LDS (gbs) until every
 // row has been read, then w, m, v of all sweeps are read and written in one go.  The memory system charges writes
 // sprinkled among reads several times their volume; gathered at the end of a block's life, and with all blocks
@@ -613,20 +636,11 @@ __device__ inline void deferred_update(const StepParams& p, int64_t tile, double
   else
     __syncthreads();
   if (MODE != MODE_STATS || p.gbar) {
-#pragma unroll 2
-    for (int it = 0; it < ITERS; ++it) {
-      const Place pl = {tile * TILE + (int64_t)it * BLOCK * VEC, threadIdx.x * VEC};
-      if (PART && pl.s0 >= p.d) break;
-      const int n = PART ? below(p.d, pl.i0()) : VEC;
-      const f32x4 g4 = gbs[it * BLOCK + threadIdx.x];   // this lane's own values: no barrier needed for them
-      const float gb[VEC] = {g4[0], g4[1], g4[2], g4[3]};
-      if constexpr (MODE != MODE_STATS) {
-        u32x4 state[3];
-        load_sweep<F32, false, PART, 0, false, true>(p, 0, 0, pl, n, nullptr, state);
-        adamw_store<PART>(p, pl, n, gb, state);
-      }
-      if (GBAR && p.gbar) store4<PART>(p.gbar, pl, n, g4);
-    }
+    // a copy of the loop for whole tiles: its sweeps overlap
+    if (!PART || tile * TILE + TILE <= p.d)
+      deferred_sweeps<MODE, BLOCK, ITERS, GBAR, false>(p, tile, gbs);
+    else
+      deferred_sweeps<MODE, BLOCK, ITERS, GBAR, true>(p, tile, gbs);
   }
 }
 
@@ -643,7 +657,7 @@ __device__ inline void tile_defer(const StepParams& p, int64_t tile, double (*re
     const Place pl = {tile * TILE + (int64_t)it * BLOCK * VEC, threadIdx.x * VEC};
     if (PART && pl.s0 >= p.d) break;
     typename GT::raw_t raw[J];
-    load_rows<GT, TABLE, PART, J>(p, 0, J, pl, PART ? below(p.d, pl.i0()) : VEC, raw);
+    load_rows<GT, TABLE, PART, J>(p, 0, pl, PART ? below(p.d, pl.i0()) : VEC, raw);
     float gb[VEC];
     sweep_rows<GT, J, MODE, true>(p, raw, gb, acc);
     gbs[it * BLOCK + threadIdx.x] = f32x4{gb[0], gb[1], gb[2], gb[3]};
@@ -656,25 +670,41 @@ __device__ inline void tile_defer(const StepParams& p, int64_t tile, double (*re
 // (fp64) and the sum of squares of the values shifted by K, the running mean of the rows before it, hence
 // its centred sum of squares without cancellation; see chunk_merge for the bookkeeping.
 // ---------------------------------------------------------------------------------------------
-template <class GT, bool RT>
-__device__ inline void chunk_accumulate(const typename GT::raw_t* raw, int nb, const float* K, double* sb, float* q) {
+template <class GT, int N>
+__device__ inline void chunk_accumulate(const typename GT::raw_t* raw, const float* K, double* sb, float* q) {
   constexpr int VEC = GT::VEC;
+#pragma unroll
+  for (int j = 0; j < N; ++j) {
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) {
+      const float x = GT::val(raw[j], e);
+      const float r = x - K[e];
+      sb[e] += (double)x;
+      q[e] = __builtin_fmaf(r, r, q[e]);
+    }
+  }
+}
+template <int VEC>
+__device__ inline void chunk_clear(double* sb, float* q) {
 #pragma unroll
   for (int e = 0; e < VEC; ++e) {
     sb[e] = 0.0;
     q[e] = 0.f;
   }
-#pragma unroll
-  for (int j = 0; j < NT_MCHUNK; ++j)
-    if (!RT || j < nb) {
-#pragma unroll
-      for (int e = 0; e < VEC; ++e) {
-        const float x = GT::val(raw[j], e);
-        const float r = x - K[e];
-        sb[e] += (double)x;
-        q[e] = __builtin_fmaf(r, r, q[e]);
-      }
-    }
+}
+
+// The last nb < 16 rows, in runs of 8, 4, 2 and 1 with a branch each, first all loads and then all sums (a branch per row
+// costs more than it saves).  The rows keep their order.
+static_assert(NT_MCHUNK <= 16, "the last chunk is walked in runs of 8, 4, 2 and 1 rows");
+template <class GT, bool TABLE, bool PART, int RUN>
+__device__ inline void load_last(const StepParams& p, int j0, int nb, const Place& pl, int n, typename GT::raw_t* raw) {
+  if (nb & RUN) load_rows<GT, TABLE, PART, RUN>(p, j0 + (nb & ~(2 * RUN - 1)), pl, n, raw);
+  if constexpr (RUN > 1) load_last<GT, TABLE, PART, RUN / 2>(p, j0, nb, pl, n, raw + RUN);
+}
+template <class GT, int RUN>
+__device__ inline void accumulate_last(int nb, const typename GT::raw_t* raw, const float* K, double* sb, float* q) {
+  if (nb & RUN) chunk_accumulate<GT, RUN>(raw, K, sb, q);
+  if constexpr (RUN > 1) accumulate_last<GT, RUN / 2>(nb, raw + RUN, K, sb, q);
 }
 
 // The state update (and the gbar store) of a tile is deferred (see deferred_update): with many rows the writes are
@@ -699,24 +729,27 @@ __device__ inline void tile_multi(const StepParams& p, int64_t tile, double (*re
     for (int e = 0; e < VEC; ++e) a[e] = 0.f;
     typename GT::raw_t raw[NT_MCHUNK];
     // first chunk (J > NT_JCHUNK >= NT_MCHUNK - 1 here, so it is full), shifted by the first row
-    load_rows<GT, TABLE, PART, NT_MCHUNK>(p, 0, NT_MCHUNK, pl, n, raw);
+    load_rows<GT, TABLE, PART, NT_MCHUNK>(p, 0, pl, n, raw);
 #pragma unroll
     for (int e = 0; e < VEC; ++e) K[e] = GT::val(raw[0], e);
-    chunk_accumulate<GT, false>(raw, NT_MCHUNK, K, sb, q);
+    chunk_clear<VEC>(sb, q);
+    chunk_accumulate<GT, NT_MCHUNK>(raw, K, sb, q);
 #pragma unroll
     for (int e = 0; e < VEC; ++e) K[e] = chunk_merge(true, 0, NT_MCHUNK, K[e], sb[e], q[e], S[e], M2[e], a[e]);
     int j0 = NT_MCHUNK;
 #pragma unroll 1
     for (; j0 + NT_MCHUNK <= J; j0 += NT_MCHUNK) {
-      load_rows<GT, TABLE, PART, NT_MCHUNK>(p, j0, NT_MCHUNK, pl, n, raw);
-      chunk_accumulate<GT, false>(raw, NT_MCHUNK, K, sb, q);
+      load_rows<GT, TABLE, PART, NT_MCHUNK>(p, j0, pl, n, raw);
+      chunk_clear<VEC>(sb, q);
+      chunk_accumulate<GT, NT_MCHUNK>(raw, K, sb, q);
 #pragma unroll
       for (int e = 0; e < VEC; ++e) K[e] = chunk_merge(false, j0, NT_MCHUNK, K[e], sb[e], q[e], S[e], M2[e], a[e]);
     }
     if (j0 < J) {
       const int nb = J - j0;
-      load_rows<GT, TABLE, PART, NT_MCHUNK, true>(p, j0, nb, pl, n, raw);
-      chunk_accumulate<GT, true>(raw, nb, K, sb, q);
+      load_last<GT, TABLE, PART, 8>(p, j0, nb, pl, n, raw);
+      chunk_clear<VEC>(sb, q);
+      accumulate_last<GT, 8>(nb, raw, K, sb, q);
 #pragma unroll
       for (int e = 0; e < VEC; ++e) K[e] = chunk_merge(false, j0, nb, K[e], sb[e], q[e], S[e], M2[e], a[e]);
     }
@@ -1168,7 +1201,7 @@ __global__ __launch_bounds__(NT_AUX_BLOCK) void k_adamw_gbar(StepParams p, const
   if (n == 0) return;
   u32x4 sg, state[3];
   p.grads = gbar;   // as the only row
-  load_sweep<F32, false, true, 1, false, true>(p, 0, 0, pl, n, &sg, state);
+  load_sweep<F32, false, true, 1, true>(p, 0, pl, n, &sg, state);
   float gb[NT_VEC];
 #pragma unroll
   for (int e = 0; e < NT_VEC; ++e) gb[e] = scale * __builtin_bit_cast(float, (uint32_t)sg[e]);
