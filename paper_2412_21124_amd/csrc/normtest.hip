@@ -246,6 +246,244 @@ __device__ inline float wave_max(float x) {
   return x;
 }
 
+// ---------------------------------------------------------------------------------------------
+// Double-double helpers (error-free transformations; the file is compiled with contraction off).
+// ---------------------------------------------------------------------------------------------
+struct dd {
+  double hi, lo;
+};
+__host__ __device__ inline dd dd_add(dd x, dd y) {
+  double s = x.hi + y.hi;
+  double bb = s - x.hi;
+  double e = (x.hi - (s - bb)) + (y.hi - bb);
+  e += x.lo + y.lo;
+  dd r;
+  r.hi = s + e;
+  r.lo = e - (r.hi - s);
+  return r;
+}
+
+struct DecideParams {
+  int64_t J;
+  double eta;
+  double max_norm;  // gradient-norm bound of the clipped variant, <= 0: none
+  int64_t b_k, b_max, round_to;
+  int32_t ddof;
+  uint32_t flags;
+};
+
+// Record of the step whose tile partials sit in a workspace, kept in its first NT_WS_HEADER doubles so that
+// normtest_layer_stats can regroup them per layer and can tell when they belong to another call.
+struct WsHeader {
+  int64_t magic;
+  int64_t tile_coords, ntiles, ngroups;  // ngroups > 0: double-double group partials follow the tile partials
+  int64_t d, J;
+  int32_t gdtype, has_stats;
+  double coord_thr;                      // threshold factor of the coordinate-wise count, negative if off
+  DecideParams q;
+};
+static_assert(sizeof(WsHeader) <= NT_WS_HEADER * sizeof(double) && sizeof(WsHeader) % 8 == 0, "workspace header");
+// The record as words, the form in which kernels take and store it: a struct copied whole goes through scratch memory,
+// which every wave of the launch then pays for (fused step -33 %).
+struct WsRecord {
+  uint64_t word[sizeof(WsHeader) / 8];
+};
+
+// Global-norm clipping factor (training specifications of Sec. 5; usual convention with the 1e-6 guard).
+__host__ __device__ inline double clip_coef(double gbar_sq, double max_norm) {
+  if (!(max_norm > 0.0)) return 1.0;
+  const double c = max_norm / (sqrt(gbar_sq) + 1e-6);
+  return c < 1.0 ? c : 1.0;
+}
+
+// From the sums in r->A, r->B, r->C to ||gbar||^2, ||Var||_1, T, pass and next_b (Alg. 1: test
+// statistic, strict comparison with b_k, ceiling, rounding through micro-batch, minibatch and
+// global batch, which composes to the next multiple of J*M; Sec. 5: cap at the maximum batch size).
+__host__ __device__ inline void decide(const DecideParams& q, nt_result* r) {
+  const double Jd = (double)q.J;
+  const int64_t cap = (q.b_max > q.b_k) ? q.b_max : q.b_k;
+  r->pass = 1;
+  r->next_b = q.b_k;
+  r->gbar_sq = r->B / (Jd * Jd);
+  r->var_l1 = r->C / (double)(q.J - q.ddof);
+  r->clip_coef = clip_coef(r->gbar_sq, q.max_norm);
+  if (!(__builtin_isfinite(r->A) && __builtin_isfinite(r->B) && __builtin_isfinite(r->C))) {
+    r->status |= NT_STATUS_NONFINITE;
+    r->T = __builtin_nan("");
+    return;
+  }
+  if (r->gbar_sq == 0.0) {
+    r->status |= NT_STATUS_ZERO_GRAD_NORM;
+    if (r->C == 0.0) {
+      r->T = __builtin_nan("");
+    } else {
+      r->T = __builtin_inf();
+      r->pass = 0;
+      r->next_b = cap;
+    }
+    return;
+  }
+  const double T = r->var_l1 / (q.eta * q.eta * r->gbar_sq);
+  r->T = T;
+  if (T > (double)q.b_k) {
+    r->pass = 0;
+    if (!(T < 4611686018427387904.0)) {
+      r->status |= NT_STATUS_T_SATURATED;
+      r->next_b = cap;
+      return;
+    }
+    // t < 2^62 and round_to <= 2^31 (validated), so the next multiple fits an int64
+    const int64_t t = (int64_t)ceil(T);
+    int64_t nb = (t / q.round_to + (t % q.round_to != 0)) * q.round_to;
+    if (q.b_max > 0 && nb > q.b_max) {
+      nb = q.b_max;
+      r->status |= NT_STATUS_CLAMPED;
+    }
+    r->next_b = nb < q.b_k ? q.b_k : nb;
+  }
+}
+
+__device__ inline dd dd_wave_sum(dd x) {
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) {
+    dd y;
+    y.hi = __shfl_xor(x.hi, off, 64);
+    y.lo = __shfl_xor(x.lo, off, 64);
+    // both partners must form the same sum: order the operands by lane
+    const bool low = (threadIdx.x & off) == 0;
+    x = low ? dd_add(x, y) : dd_add(y, x);
+  }
+  return x;
+}
+__device__ inline double wave_max(double x) {
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) x = __builtin_fmax(x, __shfl_xor(x, off, 64));
+  return x;
+}
+
+// Running totals of partial records: the NT_NSUM sums in double-double and the largest ratio.
+struct Totals {
+  dd s[NT_NSUM];
+  double mx;
+};
+__device__ inline void totals_clear(Totals& t) {
+#pragma unroll
+  for (int k = 0; k < NT_NSUM; ++k) t.s[k] = {0.0, 0.0};
+  t.mx = 0.0;
+}
+
+// Adds this thread's share (entries threadIdx.x, threadIdx.x + THREADS, ...) of n records into acc.
+// packed = false: tile partials {A, B, C, n_fail, r_max}; packed = true: group partials
+// {A, A_lo, B, B_lo, C, C_lo, n, n_lo, r_max, unused}.
+template <int THREADS>
+__device__ inline void totals_accumulate(const double* in, int64_t n, bool packed, Totals& acc) {
+  for (int64_t t = threadIdx.x; t < n; t += THREADS) {
+    const double* rec = in + (packed ? 2 * NT_NV : NT_NV) * t;
+#pragma unroll
+    for (int k = 0; k < NT_NSUM; ++k) {
+      dd x;
+      if (!packed) {
+        x.hi = rec[k];
+        x.lo = 0.0;
+      } else {
+        x.hi = rec[2 * k];
+        x.lo = rec[2 * k + 1];
+      }
+      acc.s[k] = dd_add(acc.s[k], x);
+    }
+    acc.mx = __builtin_fmax(acc.mx, rec[packed ? 2 * NT_NSUM : NT_NSUM]);
+  }
+}
+
+// Block total of the threads' accumulators; all threads take part, thread 0 returns the totals.
+template <int THREADS>
+__device__ inline void block_totals_finish(Totals& acc, double (*sh)[2 * NT_NV], Totals& tot) {
+#pragma unroll
+  for (int k = 0; k < NT_NSUM; ++k) acc.s[k] = dd_wave_sum(acc.s[k]);
+  acc.mx = wave_max(acc.mx);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  if (lane == 0) {
+#pragma unroll
+    for (int k = 0; k < NT_NSUM; ++k) {
+      sh[wave][2 * k] = acc.s[k].hi;
+      sh[wave][2 * k + 1] = acc.s[k].lo;
+    }
+    sh[wave][2 * NT_NSUM] = acc.mx;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+#pragma unroll
+    for (int k = 0; k < NT_NSUM; ++k) {
+      tot.s[k].hi = sh[0][2 * k];
+      tot.s[k].lo = sh[0][2 * k + 1];
+      for (int wv = 1; wv < THREADS / 64; ++wv) {
+        dd x = {sh[wv][2 * k], sh[wv][2 * k + 1]};
+        tot.s[k] = dd_add(tot.s[k], x);
+      }
+    }
+    tot.mx = sh[0][2 * NT_NSUM];
+    for (int wv = 1; wv < THREADS / 64; ++wv) tot.mx = __builtin_fmax(tot.mx, sh[wv][2 * NT_NSUM]);
+  }
+}
+
+// Sum of n records (layouts as in totals_accumulate); thread 0 returns the totals.
+template <int THREADS>
+__device__ inline void block_totals(const double* in, int64_t n, bool packed, double (*sh)[2 * NT_NV], Totals& tot) {
+  Totals acc;
+  totals_clear(acc);
+  totals_accumulate<THREADS>(in, n, packed, acc);
+  block_totals_finish<THREADS>(acc, sh, tot);
+}
+
+// From the totals of a step to the record of it in the workspace and the caller's result; one thread.
+__device__ inline void write_record(const Totals& tot, const DecideParams& q, nt_result* out, const WsRecord& hdr,
+                                    WsRecord* hdr_out) {
+  const bool stats = (q.flags & NT_DO_STATS) != 0;
+#pragma unroll
+  for (size_t k = 0; k < sizeof(WsHeader) / 8; ++k) hdr_out->word[k] = hdr.word[k];
+  nt_result r;
+  r.status = 0;
+  const bool coord = stats && (q.flags & NT_COORD_TEST);
+  r.coord_fail = coord ? (int64_t)tot.s[3].hi : -1;
+  r.coord_max_ratio = coord ? tot.mx : -1.0;
+  const double nan = __builtin_nan("");
+  if (!stats) {
+    r.A = r.B = r.C = r.A_lo = r.B_lo = r.C_lo = nan;
+    r.gbar_sq = r.var_l1 = r.T = nan;
+    r.clip_coef = 1.0;
+    r.pass = 1;
+    r.next_b = q.b_k;
+    r.status = NT_STATUS_NO_STATS;
+  } else {
+    r.A = tot.s[0].hi; r.A_lo = tot.s[0].lo;
+    r.B = tot.s[1].hi; r.B_lo = tot.s[1].lo;
+    r.C = tot.s[2].hi; r.C_lo = tot.s[2].lo;
+    if (q.flags & NT_PARTIAL) {
+      r.gbar_sq = r.var_l1 = r.T = nan;
+      r.clip_coef = 1.0;
+      r.pass = 1;
+      r.next_b = q.b_k;
+      r.status = NT_STATUS_PARTIAL_ONLY;
+      if (!(__builtin_isfinite(r.A) && __builtin_isfinite(r.B) && __builtin_isfinite(r.C)))
+        r.status |= NT_STATUS_NONFINITE;
+    } else {
+      decide(q, &r);
+    }
+  }
+  *out = r;
+}
+
+// What a step takes along that needs no reduction kernel: AdamW only (no sums), or a vector of a single tile.
+struct Finish {
+  DecideParams q;
+  WsRecord hdr;
+  WsRecord* hdr_out;
+  nt_result* out;   // null: k_finalize follows
+};
+
+// ---------------------------------------------------------------------------------------------
+// The tile loop's parts.
+// ---------------------------------------------------------------------------------------------
 // What a lane gathers over the sweeps of one tile: the three sums in fp64 (each fed with fp32 sums of four
 // coordinates), the number of coordinates failing the coordinate-wise test and their largest ratio.
 struct LaneAcc {
@@ -796,8 +1034,8 @@ __device__ inline void run_tile(const StepParams& p, int64_t tile, double (*red)
 // GBAR = false compiles the gbar store out (statistics-only launch class, so that sweeps can overlap).
 // DEFER_T: up to 16 rows with the state update deferred to the end of the tile (always so beyond 16 rows).
 // COORD = false compiles the coordinate-wise test out (see plain_stats).
-template <class GT, int J_T, int MODE, int BLOCK, int ITERS, bool TABLE, bool GBAR, bool DEFER_T = false, bool COORD = true>
-__global__ __launch_bounds__(BLOCK) void k_step(StepParams p, int64_t nfull, int64_t ntiles, int64_t slot0, int64_t slot1) {
+template <class GT, int J_T, int MODE, int BLOCK, int ITERS, bool TABLE, bool GBAR, bool DEFER_T, bool COORD>
+__device__ inline void walk_tiles(const StepParams& p, int64_t nfull, int64_t ntiles, int64_t slot0, int64_t slot1) {
   constexpr int TILE = BLOCK * GT::VEC * ITERS;
   static_assert(NT_TILE_MAX % TILE == 0, "tile sizes must divide NT_TILE_MAX");
   __shared__ double red[2][BLOCK / 64][NT_NV];
@@ -819,190 +1057,37 @@ __global__ __launch_bounds__(BLOCK) void k_step(StepParams p, int64_t nfull, int
   }
 }
 
+template <class GT, int J_T, int MODE, int BLOCK, int ITERS, bool TABLE, bool GBAR, bool DEFER_T = false, bool COORD = true>
+__global__ __launch_bounds__(BLOCK) void k_step(StepParams p, int64_t nfull, int64_t ntiles, int64_t slot0, int64_t slot1) {
+  walk_tiles<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, DEFER_T, COORD>(p, nfull, ntiles, slot0, slot1);
+}
+
+// A step that writes its result itself: AdamW only, which has no sums, or a single tile, whose partial is the total.  A
+// second kernel costs such a call 3.7 us on the host and some 4 on the GPU (steps back to back: 4 fp32 rows, d = 1000,
+// 9.9 -> 6.1 us; AdamW only, 8 bf16 rows, d = 1e6, 8.5 -> 6.7 us).  It is a kernel of its own because this tail in every
+// kernel slows the long steps by 0.3 to 1 %.  Steps of more tiles keep their reduction kernels: a handshake between blocks
+// needs a device-wide acquire in each, since the XCDs' L2s hand out stale partials otherwise, and that is dearer than a
+// launch (4 fp32 rows, d = 2^20: 17.6 us against 13.2).
+template <class GT, int J_T, int MODE, int BLOCK, int ITERS, bool TABLE, bool GBAR, bool DEFER_T = false>
+__global__ __launch_bounds__(BLOCK) void k_step_end(StepParams p, int64_t nfull, int64_t ntiles, int64_t slot0,
+                                                    int64_t slot1, Finish fin) {
+  walk_tiles<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, DEFER_T, true>(p, nfull, ntiles, slot0, slot1);
+  if (slot0 == 0 && blockIdx.x == 0 && threadIdx.x == 0) {
+    Totals tot;
+    totals_clear(tot);
+    if constexpr (MODE != MODE_ADAMW) {
+      // the only tile's partial, which this thread has stored
+#pragma unroll
+      for (int k = 0; k < NT_NSUM; ++k) tot.s[k].hi = p.partials[k];
+      tot.mx = p.partials[NT_NSUM];
+    }
+    write_record(tot, fin.q, fin.out, fin.hdr, fin.hdr_out);
+  }
+}
+
 // ---------------------------------------------------------------------------------------------
-// Double-double helpers (error-free transformations; the file is compiled with contraction off).
+// Reduction of the tile partials.
 // ---------------------------------------------------------------------------------------------
-struct dd {
-  double hi, lo;
-};
-__host__ __device__ inline dd dd_add(dd x, dd y) {
-  double s = x.hi + y.hi;
-  double bb = s - x.hi;
-  double e = (x.hi - (s - bb)) + (y.hi - bb);
-  e += x.lo + y.lo;
-  dd r;
-  r.hi = s + e;
-  r.lo = e - (r.hi - s);
-  return r;
-}
-
-struct DecideParams {
-  int64_t J;
-  double eta;
-  double max_norm;  // gradient-norm bound of the clipped variant, <= 0: none
-  int64_t b_k, b_max, round_to;
-  int32_t ddof;
-  uint32_t flags;
-};
-
-// Record of the step whose tile partials sit in a workspace, kept in its first NT_WS_HEADER doubles so that
-// normtest_layer_stats can regroup them per layer and can tell when they belong to another call.
-struct WsHeader {
-  int64_t magic;
-  int64_t tile_coords, ntiles, ngroups;  // ngroups > 0: double-double group partials follow the tile partials
-  int64_t d, J;
-  int32_t gdtype, has_stats;
-  double coord_thr;                      // threshold factor of the coordinate-wise count, negative if off
-  DecideParams q;
-};
-static_assert(sizeof(WsHeader) <= NT_WS_HEADER * sizeof(double), "workspace header too small");
-
-// Global-norm clipping factor (training specifications of Sec. 5; usual convention with the 1e-6 guard).
-__host__ __device__ inline double clip_coef(double gbar_sq, double max_norm) {
-  if (!(max_norm > 0.0)) return 1.0;
-  const double c = max_norm / (sqrt(gbar_sq) + 1e-6);
-  return c < 1.0 ? c : 1.0;
-}
-
-// From the sums in r->A, r->B, r->C to ||gbar||^2, ||Var||_1, T, pass and next_b (Alg. 1: test
-// statistic, strict comparison with b_k, ceiling, rounding through micro-batch, minibatch and
-// global batch, which composes to the next multiple of J*M; Sec. 5: cap at the maximum batch size).
-__host__ __device__ inline void decide(const DecideParams& q, nt_result* r) {
-  const double Jd = (double)q.J;
-  const int64_t cap = (q.b_max > q.b_k) ? q.b_max : q.b_k;
-  r->pass = 1;
-  r->next_b = q.b_k;
-  r->gbar_sq = r->B / (Jd * Jd);
-  r->var_l1 = r->C / (double)(q.J - q.ddof);
-  r->clip_coef = clip_coef(r->gbar_sq, q.max_norm);
-  if (!(__builtin_isfinite(r->A) && __builtin_isfinite(r->B) && __builtin_isfinite(r->C))) {
-    r->status |= NT_STATUS_NONFINITE;
-    r->T = __builtin_nan("");
-    return;
-  }
-  if (r->gbar_sq == 0.0) {
-    r->status |= NT_STATUS_ZERO_GRAD_NORM;
-    if (r->C == 0.0) {
-      r->T = __builtin_nan("");
-    } else {
-      r->T = __builtin_inf();
-      r->pass = 0;
-      r->next_b = cap;
-    }
-    return;
-  }
-  const double T = r->var_l1 / (q.eta * q.eta * r->gbar_sq);
-  r->T = T;
-  if (T > (double)q.b_k) {
-    r->pass = 0;
-    if (!(T < 4611686018427387904.0)) {
-      r->status |= NT_STATUS_T_SATURATED;
-      r->next_b = cap;
-      return;
-    }
-    // t < 2^62 and round_to <= 2^31 (validated), so the next multiple fits an int64
-    const int64_t t = (int64_t)ceil(T);
-    int64_t nb = (t / q.round_to + (t % q.round_to != 0)) * q.round_to;
-    if (q.b_max > 0 && nb > q.b_max) {
-      nb = q.b_max;
-      r->status |= NT_STATUS_CLAMPED;
-    }
-    r->next_b = nb < q.b_k ? q.b_k : nb;
-  }
-}
-
-__device__ inline dd dd_wave_sum(dd x) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    dd y;
-    y.hi = __shfl_xor(x.hi, off, 64);
-    y.lo = __shfl_xor(x.lo, off, 64);
-    // both partners must form the same sum: order the operands by lane
-    const bool low = (threadIdx.x & off) == 0;
-    x = low ? dd_add(x, y) : dd_add(y, x);
-  }
-  return x;
-}
-__device__ inline double wave_max(double x) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) x = __builtin_fmax(x, __shfl_xor(x, off, 64));
-  return x;
-}
-
-// Running totals of partial records: the NT_NSUM sums in double-double and the largest ratio.
-struct Totals {
-  dd s[NT_NSUM];
-  double mx;
-};
-__device__ inline void totals_clear(Totals& t) {
-#pragma unroll
-  for (int k = 0; k < NT_NSUM; ++k) t.s[k] = {0.0, 0.0};
-  t.mx = 0.0;
-}
-
-// Adds this thread's share (entries threadIdx.x, threadIdx.x + THREADS, ...) of n records into acc.
-// packed = false: tile partials {A, B, C, n_fail, r_max}; packed = true: group partials
-// {A, A_lo, B, B_lo, C, C_lo, n, n_lo, r_max, unused}.
-template <int THREADS>
-__device__ inline void totals_accumulate(const double* in, int64_t n, bool packed, Totals& acc) {
-  for (int64_t t = threadIdx.x; t < n; t += THREADS) {
-    const double* rec = in + (packed ? 2 * NT_NV : NT_NV) * t;
-#pragma unroll
-    for (int k = 0; k < NT_NSUM; ++k) {
-      dd x;
-      if (!packed) {
-        x.hi = rec[k];
-        x.lo = 0.0;
-      } else {
-        x.hi = rec[2 * k];
-        x.lo = rec[2 * k + 1];
-      }
-      acc.s[k] = dd_add(acc.s[k], x);
-    }
-    acc.mx = __builtin_fmax(acc.mx, rec[packed ? 2 * NT_NSUM : NT_NSUM]);
-  }
-}
-
-// Block total of the threads' accumulators; all threads take part, thread 0 returns the totals.
-template <int THREADS>
-__device__ inline void block_totals_finish(Totals& acc, double (*sh)[2 * NT_NV], Totals& tot) {
-#pragma unroll
-  for (int k = 0; k < NT_NSUM; ++k) acc.s[k] = dd_wave_sum(acc.s[k]);
-  acc.mx = wave_max(acc.mx);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  if (lane == 0) {
-#pragma unroll
-    for (int k = 0; k < NT_NSUM; ++k) {
-      sh[wave][2 * k] = acc.s[k].hi;
-      sh[wave][2 * k + 1] = acc.s[k].lo;
-    }
-    sh[wave][2 * NT_NSUM] = acc.mx;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-#pragma unroll
-    for (int k = 0; k < NT_NSUM; ++k) {
-      tot.s[k].hi = sh[0][2 * k];
-      tot.s[k].lo = sh[0][2 * k + 1];
-      for (int wv = 1; wv < THREADS / 64; ++wv) {
-        dd x = {sh[wv][2 * k], sh[wv][2 * k + 1]};
-        tot.s[k] = dd_add(tot.s[k], x);
-      }
-    }
-    tot.mx = sh[0][2 * NT_NSUM];
-    for (int wv = 1; wv < THREADS / 64; ++wv) tot.mx = __builtin_fmax(tot.mx, sh[wv][2 * NT_NSUM]);
-  }
-}
-
-// Sum of n records (layouts as in totals_accumulate); thread 0 returns the totals.
-template <int THREADS>
-__device__ inline void block_totals(const double* in, int64_t n, bool packed, double (*sh)[2 * NT_NV], Totals& tot) {
-  Totals acc;
-  totals_clear(acc);
-  totals_accumulate<THREADS>(in, n, packed, acc);
-  block_totals_finish<THREADS>(acc, sh, tot);
-}
-
 // First stage for long vectors: block g adds tile partials [g*NT_GROUP_TILES, ...) into one double-double
 // group partial.  The two stages are separate launches on purpose: the eight XCDs of this GPU do not share an
 // L2, so a block that waits for the other blocks' partials inside one kernel (a ticket taken after a device-wide
@@ -1031,44 +1116,14 @@ __global__ __launch_bounds__(NT_GROUP_THREADS) void k_reduce_groups(const double
 // up to NT_FIN_SMALL records (short vectors, where this kernel's latency is a large part of the step).
 template <int THREADS>
 __global__ __launch_bounds__(THREADS) void k_finalize(const double* in, int64_t n, bool packed, DecideParams q,
-                                                      nt_result* out, WsHeader hdr, WsHeader* hdr_out) {
+                                                      nt_result* out, WsRecord hdr, WsRecord* hdr_out) {
   __shared__ double sh[THREADS / 64][2 * NT_NV];
   const bool stats = (q.flags & NT_DO_STATS) != 0;
   Totals tot;
   totals_clear(tot);
   if (stats) block_totals<THREADS>(in, n, packed, sh, tot);
   if (threadIdx.x != 0) return;
-  *hdr_out = hdr;
-  nt_result r;
-  r.status = 0;
-  const bool coord = stats && (q.flags & NT_COORD_TEST);
-  r.coord_fail = coord ? (int64_t)tot.s[3].hi : -1;
-  r.coord_max_ratio = coord ? tot.mx : -1.0;
-  const double nan = __builtin_nan("");
-  if (!stats) {
-    r.A = r.B = r.C = r.A_lo = r.B_lo = r.C_lo = nan;
-    r.gbar_sq = r.var_l1 = r.T = nan;
-    r.clip_coef = 1.0;
-    r.pass = 1;
-    r.next_b = q.b_k;
-    r.status = NT_STATUS_NO_STATS;
-  } else {
-    r.A = tot.s[0].hi; r.A_lo = tot.s[0].lo;
-    r.B = tot.s[1].hi; r.B_lo = tot.s[1].lo;
-    r.C = tot.s[2].hi; r.C_lo = tot.s[2].lo;
-    if (q.flags & NT_PARTIAL) {
-      r.gbar_sq = r.var_l1 = r.T = nan;
-      r.clip_coef = 1.0;
-      r.pass = 1;
-      r.next_b = q.b_k;
-      r.status = NT_STATUS_PARTIAL_ONLY;
-      if (!(__builtin_isfinite(r.A) && __builtin_isfinite(r.B) && __builtin_isfinite(r.C)))
-        r.status |= NT_STATUS_NONFINITE;
-    } else {
-      decide(q, &r);
-    }
-  }
-  *out = r;
+  write_record(tot, q, out, hdr, hdr_out);
 }
 
 // Sums over the coordinates [plo, phi) taken one by one, NT_LAYER_THREADS apart per thread.  J_T > 0: row
@@ -1337,6 +1392,13 @@ inline int64_t launch_tiles(int64_t J, int esize, int mode, bool gbar, int cls, 
   const int64_t n = coords / tile_cfg(J, esize, mode, gbar, 0).coords();
   return (n < 1 || n > ntiles) ? ntiles : n;
 }
+// Whether the step kernel writes the result itself (k_step_end): AdamW only, and vectors of one tile in a matrix, in the
+// classes that short vectors take.
+inline bool writes_own_result(bool table, int64_t J, int mode, bool gbar, int cls, int64_t ntiles) {
+  if (mode == MODE_ADAMW) return ntiles > 0;
+  const bool long_stats = mode == MODE_STATS && !gbar && J <= NT_JCHUNK && cls == CLS_BASE;
+  return ntiles == 1 && !table && cls != CLS_LONG && !long_stats;
+}
 // smallest tile any mode and gradient type uses for this J: sizes the workspace
 inline int64_t min_tile_coords(int64_t J) {
   int64_t best = tile_cfg(J, 2, MODE_FULL, false, 0).coords();
@@ -1390,9 +1452,34 @@ int blocks_per_cu() {
   return n;
 }
 
+// The kernel of a launch class: with AdamW only the one that writes the result.
+template <class GT, int J_T, int MODE, int BLOCK, int ITERS, bool TABLE, bool GBAR, bool DEFER_T = false>
+constexpr auto step_kernel() {
+  if constexpr (MODE == MODE_ADAMW)
+    return k_step_end<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, DEFER_T>;
+  else
+    return k_step<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, DEFER_T>;
+}
+template <class GT, int J_T, int MODE, int BLOCK, int ITERS, bool TABLE, bool GBAR, bool DEFER_T = false, bool COORD = true>
+void launch_tiles_of(const StepParams& p, int64_t nfull, int64_t ntiles, int64_t slot0, int64_t slot1, const Finish& fin,
+                     unsigned grid, hipStream_t st) {
+  // (single tiles of the classes that can have them: see writes_own_result)
+  constexpr bool CAN_END = MODE == MODE_ADAMW || (!TABLE && !DEFER_T && (J_T == 0 ? ITERS == NT_ITERS_MANY_SHORT : GBAR));
+  if constexpr (CAN_END) {
+    if (fin.out) {
+      hipLaunchKernelGGL((k_step_end<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, DEFER_T>), dim3(grid), dim3(BLOCK), 0, st, p,
+                         nfull, ntiles, slot0, slot1, fin);
+      return;
+    }
+  }
+  if constexpr (MODE != MODE_ADAMW)
+    hipLaunchKernelGGL((k_step<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, DEFER_T, COORD>), dim3(grid), dim3(BLOCK), 0, st, p,
+                       nfull, ntiles, slot0, slot1);
+}
+
 template <class GT, int MODE, bool TABLE, int BS, int IS, bool GBAR>
-hipError_t launch_step_shape(const StepParams& p, int cls, int64_t nfull, int64_t ntiles, int max_grid,
-                             hipStream_t st) {
+hipError_t launch_step_shape(const StepParams& p, int cls, int64_t nfull, int64_t ntiles, const Finish& fin,
+                             int max_grid, hipStream_t st) {
   const bool long_class = cls == CLS_LONG;
   constexpr bool WRITES = (MODE != MODE_STATS) || GBAR;
   const bool gbar = MODE == MODE_STATS && p.gbar != nullptr;
@@ -1405,7 +1492,7 @@ hipError_t launch_step_shape(const StepParams& p, int cls, int64_t nfull, int64_
 #define NT_OCC(JJ)                                                                                          \
   case JJ:                                                                                                  \
     if constexpr (JJ * GT::ESIZE >= defer_row_bytes(MODE))                                                  \
-      per_cu = blocks_per_cu<k_step<GT, JJ, MODE, NT_BLOCK_DEFER, NT_ITERS_DEFER, TABLE, true, true>,       \
+      per_cu = blocks_per_cu<step_kernel<GT, JJ, MODE, NT_BLOCK_DEFER, NT_ITERS_DEFER, TABLE, true, true>(),       \
                              NT_BLOCK_DEFER>();                                                             \
     break;
       switch (p.J) {
@@ -1413,8 +1500,8 @@ hipError_t launch_step_shape(const StepParams& p, int cls, int64_t nfull, int64_
         NT_OCC(10) NT_OCC(11) NT_OCC(12) NT_OCC(13) NT_OCC(14) NT_OCC(15) NT_OCC(16)
         default:
           per_cu = (p.J <= NT_FEW_ROWS)
-                       ? blocks_per_cu<k_step<GT, 0, MODE, NT_BLOCK_FEW, NT_ITERS_FEW, TABLE, true>, NT_BLOCK_FEW>()
-                       : blocks_per_cu<k_step<GT, 0, MODE, NT_BLOCK_LARGE, NT_ITERS_LARGE, TABLE, true>, NT_BLOCK_LARGE>();
+                       ? blocks_per_cu<step_kernel<GT, 0, MODE, NT_BLOCK_FEW, NT_ITERS_FEW, TABLE, true>(), NT_BLOCK_FEW>()
+                       : blocks_per_cu<step_kernel<GT, 0, MODE, NT_BLOCK_LARGE, NT_ITERS_LARGE, TABLE, true>(), NT_BLOCK_LARGE>();
       }
 #undef NT_OCC
     }
@@ -1424,42 +1511,39 @@ hipError_t launch_step_shape(const StepParams& p, int cls, int64_t nfull, int64_
   for (int64_t slot0 = 0; slot0 < ntiles; slot0 += per_launch) {
     const int64_t slot1 = (ntiles - slot0 < per_launch) ? ntiles : slot0 + per_launch;
     const unsigned grid = (unsigned)((slot1 - slot0 < max_grid) ? slot1 - slot0 : max_grid);
+#define NT_ARGS p, nfull, ntiles, slot0, slot1, fin, grid, st
 #define NT_CASE(JJ)                                                                                             \
   case JJ:                                                                                                      \
     if constexpr (WRITES && JJ * GT::ESIZE >= defer_row_bytes(MODE)) {                                          \
       if (long_class) {                                                                                         \
-        hipLaunchKernelGGL((k_step<GT, JJ, MODE, NT_BLOCK_DEFER, NT_ITERS_DEFER, TABLE, true, true>), dim3(grid), \
-                           dim3(NT_BLOCK_DEFER), 0, st, p, nfull, ntiles, slot0, slot1);                   \
+        launch_tiles_of<GT, JJ, MODE, NT_BLOCK_DEFER, NT_ITERS_DEFER, TABLE, true, true>(NT_ARGS);              \
         break;                                                                                                  \
       }                                                                                                         \
     }                                                                                                           \
     if constexpr (plain_stats(GT::ESIZE, JJ, MODE, GBAR)) {                                                     \
       if (p.coord_thr < 0.f) {                                                                                  \
-        hipLaunchKernelGGL((k_step<GT, JJ, MODE, BS, IS, TABLE, GBAR, false, false>), dim3(grid), dim3(BS), 0,  \
-                           st, p, nfull, ntiles, slot0, slot1);                                                 \
+        launch_tiles_of<GT, JJ, MODE, BS, IS, TABLE, GBAR, false, false>(NT_ARGS);                              \
         break;                                                                                                  \
       }                                                                                                         \
     }                                                                                                           \
-    hipLaunchKernelGGL((k_step<GT, JJ, MODE, BS, IS, TABLE, GBAR>), dim3(grid), dim3(BS), 0, st, p, nfull,      \
-                       ntiles, slot0, slot1);                                                                   \
+    launch_tiles_of<GT, JJ, MODE, BS, IS, TABLE, GBAR>(NT_ARGS);                                                \
     break;
     switch (p.J) {
       NT_CASE(2) NT_CASE(3) NT_CASE(4) NT_CASE(5) NT_CASE(6) NT_CASE(7) NT_CASE(8) NT_CASE(9)
       NT_CASE(10) NT_CASE(11) NT_CASE(12) NT_CASE(13) NT_CASE(14) NT_CASE(15) NT_CASE(16)
       default:
-        if (MODE == MODE_STATS && p.gbar == nullptr)
-          hipLaunchKernelGGL((k_step<GT, 0, MODE, NT_BLOCK_LARGE_STATS, NT_ITERS_LARGE_STATS, TABLE, false>), dim3(grid),
-                             dim3(NT_BLOCK_LARGE_STATS), 0, st, p, nfull, ntiles, slot0, slot1);
-        else if (!long_class)
-          hipLaunchKernelGGL((k_step<GT, 0, MODE, NT_BLOCK_MANY_SHORT, NT_ITERS_MANY_SHORT, TABLE, true>), dim3(grid),
-                             dim3(NT_BLOCK_MANY_SHORT), 0, st, p, nfull, ntiles, slot0, slot1);
-        else if (p.J <= NT_FEW_ROWS)
-          hipLaunchKernelGGL((k_step<GT, 0, MODE, NT_BLOCK_FEW, NT_ITERS_FEW, TABLE, true>), dim3(grid),
-                             dim3(NT_BLOCK_FEW), 0, st, p, nfull, ntiles, slot0, slot1);
-        else
-          hipLaunchKernelGGL((k_step<GT, 0, MODE, NT_BLOCK_LARGE, NT_ITERS_LARGE, TABLE, true>), dim3(grid),
-                             dim3(NT_BLOCK_LARGE), 0, st, p, nfull, ntiles, slot0, slot1);
+        if constexpr (MODE == MODE_STATS && !GBAR) {
+          launch_tiles_of<GT, 0, MODE, NT_BLOCK_LARGE_STATS, NT_ITERS_LARGE_STATS, TABLE, false>(NT_ARGS);
+        } else {
+          if (!long_class)
+            launch_tiles_of<GT, 0, MODE, NT_BLOCK_MANY_SHORT, NT_ITERS_MANY_SHORT, TABLE, true>(NT_ARGS);
+          else if (p.J <= NT_FEW_ROWS)
+            launch_tiles_of<GT, 0, MODE, NT_BLOCK_FEW, NT_ITERS_FEW, TABLE, true>(NT_ARGS);
+          else
+            launch_tiles_of<GT, 0, MODE, NT_BLOCK_LARGE, NT_ITERS_LARGE, TABLE, true>(NT_ARGS);
+        }
     }
+#undef NT_ARGS
 #undef NT_CASE
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -1469,36 +1553,37 @@ hipError_t launch_step_shape(const StepParams& p, int cls, int64_t nfull, int64_
 
 // picks the launch class (block size, sweeps per tile) that tile_cfg() describes
 template <class GT, int MODE, bool TABLE>
-hipError_t launch_step(const StepParams& p, int cls, int64_t nfull, int64_t ntiles, int grid, hipStream_t st) {
+hipError_t launch_step(const StepParams& p, int cls, int64_t nfull, int64_t ntiles, const Finish& fin, int grid,
+                       hipStream_t st) {
   if constexpr (MODE == MODE_STATS) {
     // read-only statistics over a short vector borrow the kernels that can also store gbar (there is none to store)
     if (p.gbar || (cls == CLS_SHORT_STATS && p.J <= NT_JCHUNK))
       return launch_step_shape<GT, MODE, TABLE, NT_BLOCK_STATS_GBAR, NT_ITERS_STATS_GBAR, true>(p, cls, nfull, ntiles,
-                                                                                                 grid, st);
-    return launch_step_shape<GT, MODE, TABLE, NT_BLOCK_STATS, NT_ITERS_STATS, false>(p, cls, nfull, ntiles, grid,
+                                                                                                 fin, grid, st);
+    return launch_step_shape<GT, MODE, TABLE, NT_BLOCK_STATS, NT_ITERS_STATS, false>(p, cls, nfull, ntiles, fin, grid,
                                                                                       st);
   } else if constexpr (MODE == MODE_ADAMW) {
-    return launch_step_shape<GT, MODE, TABLE, NT_BLOCK_ADAMW, NT_ITERS_ADAMW, true>(p, cls, nfull, ntiles, grid,
+    return launch_step_shape<GT, MODE, TABLE, NT_BLOCK_ADAMW, NT_ITERS_ADAMW, true>(p, cls, nfull, ntiles, fin, grid,
                                                                                      st);
   } else {
-    return launch_step_shape<GT, MODE, TABLE, NT_BLOCK, NT_ITERS, true>(p, cls, nfull, ntiles, grid, st);
+    return launch_step_shape<GT, MODE, TABLE, NT_BLOCK, NT_ITERS, true>(p, cls, nfull, ntiles, fin, grid, st);
   }
 }
 
 template <class GT, bool TABLE>
-hipError_t launch_step_mode(int mode, const StepParams& p, int cls, int64_t nfull, int64_t ntiles, int grid,
-                            hipStream_t st) {
+hipError_t launch_step_mode(int mode, const StepParams& p, int cls, int64_t nfull, int64_t ntiles, const Finish& fin,
+                            int grid, hipStream_t st) {
   switch (mode) {
-    case MODE_FULL: return launch_step<GT, MODE_FULL, TABLE>(p, cls, nfull, ntiles, grid, st);
-    case MODE_STATS: return launch_step<GT, MODE_STATS, TABLE>(p, cls, nfull, ntiles, grid, st);
-    default: return launch_step<GT, MODE_ADAMW, TABLE>(p, cls, nfull, ntiles, grid, st);
+    case MODE_FULL: return launch_step<GT, MODE_FULL, TABLE>(p, cls, nfull, ntiles, fin, grid, st);
+    case MODE_STATS: return launch_step<GT, MODE_STATS, TABLE>(p, cls, nfull, ntiles, fin, grid, st);
+    default: return launch_step<GT, MODE_ADAMW, TABLE>(p, cls, nfull, ntiles, fin, grid, st);
   }
 }
 
 inline bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 
 inline void launch_finalize(const double* in, int64_t n, bool packed, const DecideParams& q, nt_result* out,
-                            const WsHeader& hdr, WsHeader* hdr_out, hipStream_t st) {
+                            const WsRecord& hdr, WsRecord* hdr_out, hipStream_t st) {
   if (n <= NT_FIN_SMALL)
     hipLaunchKernelGGL(k_finalize<256>, dim3(1), dim3(256), 0, st, in, n, packed, q, out, hdr, hdr_out);
   else
@@ -1602,20 +1687,6 @@ static int enqueue_step(const void* grads, bool table, nt_dtype gdtype, int64_t 
                     ? (float)(hyper->eta * hyper->eta * (double)hyper->b_k * (double)(J - hyper->ddof))
                     : -1.0f;
 
-  if (ntiles > 0) {
-    const int64_t nfull = d / tc;
-    const int64_t max_grid = (int64_t)cu_count() * NT_BLOCKS_PER_CU;
-    const int grid = (int)(ntiles < max_grid ? ntiles : max_grid);
-    hipError_t e;
-    if (table)
-      e = (gdtype == NT_F32) ? launch_step_mode<F32, true>(mode, p, cls, nfull, ntiles, grid, st)
-                             : launch_step_mode<BF16, true>(mode, p, cls, nfull, ntiles, grid, st);
-    else
-      e = (gdtype == NT_F32) ? launch_step_mode<F32, false>(mode, p, cls, nfull, ntiles, grid, st)
-                             : launch_step_mode<BF16, false>(mode, p, cls, nfull, ntiles, grid, st);
-    if (e != hipSuccess) return hip_code(e);
-  }
-
   DecideParams q;
   q.J = J;
   q.eta = hyper->eta;
@@ -1625,7 +1696,6 @@ static int enqueue_step(const void* grads, bool table, nt_dtype gdtype, int64_t 
   q.round_to = hyper->round_to;
   q.ddof = hyper->ddof;
   q.flags = flags;
-  const double* partials = (const double*)workspace + NT_WS_HEADER;
   const bool two_level = (flags & NT_DO_STATS) && ntiles > NT_DIRECT_TILES;
   const int64_t ngroups = two_level ? (ntiles + NT_GROUP_TILES - 1) / NT_GROUP_TILES : 0;
   WsHeader hdr;
@@ -1640,15 +1710,43 @@ static int enqueue_step(const void* grads, bool table, nt_dtype gdtype, int64_t 
   hdr.has_stats = (flags & NT_DO_STATS) ? 1 : 0;
   hdr.coord_thr = (double)p.coord_thr;
   hdr.q = q;
-  WsHeader* hdr_out = (WsHeader*)workspace;
+  WsRecord record;
+  std::memcpy(&record, &hdr, sizeof(record));
+  WsRecord* hdr_out = (WsRecord*)workspace;
+  const bool self = writes_own_result(table, J, mode, p.gbar != nullptr, cls, ntiles);
+
+  if (ntiles > 0) {
+    Finish fin;
+    std::memset(&fin, 0, sizeof(fin));
+    if (self) {
+      fin.q = q;
+      fin.hdr = record;
+      fin.hdr_out = hdr_out;
+      fin.out = result_dev;
+    }
+    const int64_t nfull = d / tc;
+    const int64_t max_grid = (int64_t)cu_count() * NT_BLOCKS_PER_CU;
+    const int grid = (int)(ntiles < max_grid ? ntiles : max_grid);
+    hipError_t e;
+    if (table)
+      e = (gdtype == NT_F32) ? launch_step_mode<F32, true>(mode, p, cls, nfull, ntiles, fin, grid, st)
+                             : launch_step_mode<BF16, true>(mode, p, cls, nfull, ntiles, fin, grid, st);
+    else
+      e = (gdtype == NT_F32) ? launch_step_mode<F32, false>(mode, p, cls, nfull, ntiles, fin, grid, st)
+                             : launch_step_mode<BF16, false>(mode, p, cls, nfull, ntiles, fin, grid, st);
+    if (e != hipSuccess) return hip_code(e);
+  }
+  if (self) return NT_OK;
+
+  const double* partials = (const double*)workspace + NT_WS_HEADER;
   if (two_level) {
     double* groups = (double*)workspace + NT_WS_HEADER + NT_NV * ntiles;
     hipLaunchKernelGGL(k_reduce_groups, dim3((unsigned)ngroups), dim3(NT_GROUP_THREADS), 0, st, partials, ntiles, groups);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_code(e);
-    launch_finalize(groups, ngroups, true, q, result_dev, hdr, hdr_out, st);
+    launch_finalize(groups, ngroups, true, q, result_dev, record, hdr_out, st);
   } else {
-    launch_finalize(partials, ntiles, false, q, result_dev, hdr, hdr_out, st);
+    launch_finalize(partials, ntiles, false, q, result_dev, record, hdr_out, st);
   }
   return hip_code(hipGetLastError());
 }
