@@ -3,7 +3,8 @@
 // One streaming kernel (k_step) reads the J gradient rows and w, m, v once, writes w, m, v once and
 // leaves five fp64 values per fixed-size tile of coordinates (the sums A, B, C, the count of coordinates
 // failing the coordinate-wise form of the test, and their largest ratio); k_reduce_groups / k_finalize then add
-// the tile partials in double-double arithmetic and take Alg. 1's decision on the device.  The partials stay in the caller's workspace
+// the tile partials in double-double arithmetic and take Alg. 1's decision on the device (steps of one tile, and AdamW only,
+// need no second kernel: k_step_end).  The partials stay in the caller's workspace
 // behind a small record of the step, from which k_layer_stats can regroup them into a per-layer table.
 // k_adamw_gbar is the second phase of the gradient-clipped variant.  The
 // path is bound by HBM bandwidth (about two lane-operations per byte), so there is no MFMA here: the work is
