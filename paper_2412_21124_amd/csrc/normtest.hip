@@ -1076,12 +1076,10 @@ __global__ __launch_bounds__(BLOCK) void k_step_end(StepParams p, int64_t nfull,
   if (slot0 == 0 && blockIdx.x == 0 && threadIdx.x == 0) {
     Totals tot;
     totals_clear(tot);
-    if constexpr (MODE != MODE_ADAMW) {
-      // the only tile's partial, which this thread has stored
-#pragma unroll
-      for (int k = 0; k < NT_NSUM; ++k) tot.s[k].hi = p.partials[k];
-      tot.mx = p.partials[NT_NSUM];
-    }
+    // the only tile's partial, which this thread has stored, added to zero as in k_finalize: the addition leaves finite sums
+    // as they are and turns an infinite one into NaN, so sums that overflow (and the clipping factor, which is 1 then) read
+    // the same whatever the number of tiles
+    if constexpr (MODE != MODE_ADAMW) totals_accumulate<1>(p.partials, 1, false, tot);
     write_record(tot, fin.q, fin.out, fin.hdr, fin.hdr_out);
   }
 }

@@ -57,3 +57,43 @@ def test_adamw_only_reports_no_statistics(J, gdtype, d):
     assert all(math.isnan(res[k]) for k in ("A", "B", "C", "A_lo", "B_lo", "C_lo", "gbar_sq", "var_l1", "T"))
     layers = B.read_layers(B.normtest_layer_stats(wl.grads, torch.tensor([0, d], dtype=torch.int64, device=DEV), ws))
     assert layers[0].status & B.NT_STATUS_NO_STATS
+
+
+def _same(a, b):
+    assert a.keys() == b.keys()
+    for k in a:
+        assert a[k] == b[k] or (a[k] != a[k] and b[k] != b[k]), (k, a[k], b[k])
+
+
+# a tile, which the step's kernel ends by itself for a matrix and not for a table, and one coordinate more
+@pytest.mark.parametrize("J,gdtype,tile", [(2, torch.float32, 4096), (16, torch.bfloat16, 4096), (33, torch.float32, 2048)])
+@pytest.mark.parametrize("value", [math.inf, 1e20])   # in one row; in all rows, finite, where only the squares overflow
+def test_sums_that_are_not_finite_read_the_same_on_every_way(J, gdtype, tile, value):
+    wl = synth.make("t", J, tile + 1, gdtype=gdtype, sigma=1e-2, seed=J, device=DEV, hyper=synth.Hyper(b_k=64, round_to=J))
+    wl.grads[:1 if math.isinf(value) else J, 7] = value
+    h = wl.hyper
+    hy = B.make_hyper(lr=h.lr, beta1=h.beta1, beta2=h.beta2, eps=h.eps, weight_decay=h.weight_decay, eta=h.eta,
+                      step=h.step, b_k=h.b_k, b_max=h.b_max, round_to=h.round_to, ddof=h.ddof)
+    gbar = torch.empty(tile + 1, dtype=torch.float32, device=DEV)
+    ways = {"matrix": lambda d, s: B.normtest_step(wl.grads, *s, hy, d=d),
+            "table": lambda d, s: B.normtest_step_rows(list(wl.grads), *s, hy, d=d),
+            "static": lambda d, s: B.normtest_step_static(
+                wl.grads, *s, hy, torch.empty(B.RESULT_BYTES, dtype=torch.uint8, device=DEV), d=d),
+            "clipped": lambda d, s: B.normtest_step_clipped(wl.grads, *s, gbar, 1.0, hy, d=d)}
+    got = {}
+    for name, way in ways.items():
+        for d in (tile, tile + 1):
+            state = [t.clone() for t in (wl.w, wl.m, wl.v)]
+            res = B.read_result(way(d, state)).as_dict()
+            assert res["status"] == B.NT_STATUS_NONFINITE and res["pass"] == 1 and res["next_b"] == h.b_k
+            # the double-double sums turn an infinite partial into NaN; a norm that is not a number clips nothing
+            for k in ("A", "B", "gbar_sq", "T"):
+                assert math.isnan(res[k]), (name, d, k, res[k])
+            assert res["clip_coef"] == 1.0
+            got[name, d] = res, state
+    for d in (tile, tile + 1):
+        res, state = got["matrix", d]
+        for name in ways:
+            _same(res, got[name, d][0])
+            for a, b in zip(state, got[name, d][1]):
+                assert torch.allclose(a[:d], b[:d], rtol=0.0, atol=0.0, equal_nan=True), (name, d)
