@@ -1507,7 +1507,12 @@ hipError_t launch_step_shape(const StepParams& p, int cls, int64_t nfull, int64_
     per_launch = (int64_t)cu_count() * per_cu * (p.J <= NT_JCHUNK ? NT_GENS_DEFER : NT_GENS_LARGE);
     if (per_launch > ntiles) per_launch = ntiles;
   }
-  for (int64_t slot0 = 0; slot0 < ntiles; slot0 += per_launch) {
+  // AdamW only runs its launches from the last slots to the first: the launch with slot 0 writes the result (k_step_end), and
+  // no result is to precede an update that has yet to be launched.  (Asking in the kernel for the last slot instead takes
+  // scalar registers that the deferred kernels over pointer tables do not have: they would need scratch memory.)
+  const int64_t runs = (ntiles + per_launch - 1) / per_launch;
+  for (int64_t run = 0; run < runs; ++run) {
+    const int64_t slot0 = (MODE == MODE_ADAMW ? runs - 1 - run : run) * per_launch;
     const int64_t slot1 = (ntiles - slot0 < per_launch) ? ntiles : slot0 + per_launch;
     const unsigned grid = (unsigned)((slot1 - slot0 < max_grid) ? slot1 - slot0 : max_grid);
 #define NT_ARGS p, nfull, ntiles, slot0, slot1, fin, grid, st

@@ -97,3 +97,21 @@ def test_sums_that_are_not_finite_read_the_same_on_every_way(J, gdtype, tile, va
             _same(res, got[name, d][0])
             for a, b in zip(state, got[name, d][1]):
                 assert torch.allclose(a[:d], b[:d], rtol=0.0, atol=0.0, equal_nan=True), (name, d)
+
+
+@pytest.mark.parametrize("J,d", [(2, 3 * (1 << 25) + 5), (10, (1 << 26) + 3), (20, 5 * (1 << 23) + 3)])
+def test_adamw_only_writes_its_result_in_the_last_launch(J, d):
+    """The record goes into memory of row 0 that a launch between the first and the last reads: had it been written before,
+    that launch would average its words.  Every launch class of AdamW only that is walked in several launches."""
+    wl = synth.make("t", J, d, gdtype=torch.bfloat16, sigma=1e-2, seed=5, device=DEV, hyper=synth.Hyper(b_k=96, round_to=J))
+    h = wl.hyper
+    hy = B.make_hyper(lr=h.lr, beta1=h.beta1, beta2=h.beta2, eps=h.eps, weight_decay=h.weight_decay, eta=h.eta,
+                      step=h.step, b_k=h.b_k, b_max=h.b_max, round_to=h.round_to, ddof=h.ddof, flags=ADAMW)
+    want = [t.clone() for t in (wl.w, wl.m, wl.v)]
+    B.normtest_step(wl.grads, *want, hy)
+    at = d // 2 // 64 * 64
+    result = wl.grads[0, at:at + B.RESULT_BYTES // 2].view(torch.uint8)
+    res = B.read_result(B.normtest_step(wl.grads, wl.w, wl.m, wl.v, hy, result=result)).as_dict()
+    assert res["status"] == B.NT_STATUS_NO_STATS and res["pass"] == 1 and res["next_b"] == 96
+    for a, b in zip(want, (wl.w, wl.m, wl.v)):
+        assert torch.equal(a, b)
