@@ -1391,13 +1391,6 @@ inline int64_t launch_tiles(int64_t J, int esize, int mode, bool gbar, int cls, 
   const int64_t n = coords / tile_cfg(J, esize, mode, gbar, 0).coords();
   return (n < 1 || n > ntiles) ? ntiles : n;
 }
-// Whether the step kernel writes the result itself (k_step_end): AdamW only, and vectors of one tile in a matrix, in the
-// classes that short vectors take.
-inline bool writes_own_result(bool table, int64_t J, int mode, bool gbar, int cls, int64_t ntiles) {
-  if (mode == MODE_ADAMW) return ntiles > 0;
-  const bool long_stats = mode == MODE_STATS && !gbar && J <= NT_JCHUNK && cls == CLS_BASE;
-  return ntiles == 1 && !table && cls != CLS_LONG && !long_stats;
-}
 // smallest tile any mode and gradient type uses for this J: sizes the workspace
 inline int64_t min_tile_coords(int64_t J) {
   int64_t best = tile_cfg(J, 2, MODE_FULL, false, 0).coords();
@@ -1459,25 +1452,29 @@ constexpr auto step_kernel() {
   else
     return k_step<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, DEFER_T>;
 }
-template <class GT, int J_T, int MODE, int BLOCK, int ITERS, bool TABLE, bool GBAR, bool DEFER_T = false, bool COORD = true>
-void launch_tiles_of(const StepParams& p, int64_t nfull, int64_t ntiles, int64_t slot0, int64_t slot1, const Finish& fin,
+// ONE_TILE: the class that vectors of a single tile take.  Of those, matrices have a kernel that writes the result; pointer
+// tables of one tile keep the two kernels, as the 31 further kernels per dtype would serve only calls of at most 4096
+// coordinates whose rows are allocations of their own (not built, not measured).  Returns whether the launched kernel writes
+// the result when it is the step's last: the caller's only source for that, so that no step can end without a result.
+template <class GT, int J_T, int MODE, int BLOCK, int ITERS, bool TABLE, bool GBAR, bool ONE_TILE, bool DEFER_T = false,
+          bool COORD = true>
+bool launch_tiles_of(const StepParams& p, int64_t nfull, int64_t ntiles, int64_t slot0, int64_t slot1, const Finish& fin,
                      unsigned grid, hipStream_t st) {
-  // (single tiles of the classes that can have them: see writes_own_result)
-  constexpr bool CAN_END = MODE == MODE_ADAMW || (!TABLE && !DEFER_T && (J_T == 0 ? ITERS == NT_ITERS_MANY_SHORT : GBAR));
-  if constexpr (CAN_END) {
+  if constexpr (MODE == MODE_ADAMW || (ONE_TILE && !TABLE)) {
     if (fin.out) {
       hipLaunchKernelGGL((k_step_end<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, DEFER_T>), dim3(grid), dim3(BLOCK), 0, st, p,
                          nfull, ntiles, slot0, slot1, fin);
-      return;
+      return true;
     }
   }
   if constexpr (MODE != MODE_ADAMW)
     hipLaunchKernelGGL((k_step<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, DEFER_T, COORD>), dim3(grid), dim3(BLOCK), 0, st, p,
                        nfull, ntiles, slot0, slot1);
+  return false;
 }
 
 template <class GT, int MODE, bool TABLE, int BS, int IS, bool GBAR>
-hipError_t launch_step_shape(const StepParams& p, int cls, int64_t nfull, int64_t ntiles, const Finish& fin,
+hipError_t launch_step_shape(const StepParams& p, int cls, int64_t nfull, int64_t ntiles, const Finish& fin, bool& ended,
                              int max_grid, hipStream_t st) {
   const bool long_class = cls == CLS_LONG;
   constexpr bool WRITES = (MODE != MODE_STATS) || GBAR;
@@ -1520,31 +1517,31 @@ hipError_t launch_step_shape(const StepParams& p, int cls, int64_t nfull, int64_
   case JJ:                                                                                                      \
     if constexpr (WRITES && JJ * GT::ESIZE >= defer_row_bytes(MODE)) {                                          \
       if (long_class) {                                                                                         \
-        launch_tiles_of<GT, JJ, MODE, NT_BLOCK_DEFER, NT_ITERS_DEFER, TABLE, true, true>(NT_ARGS);              \
+        ended = launch_tiles_of<GT, JJ, MODE, NT_BLOCK_DEFER, NT_ITERS_DEFER, TABLE, true, false, true>(NT_ARGS); \
         break;                                                                                                  \
       }                                                                                                         \
     }                                                                                                           \
     if constexpr (plain_stats(GT::ESIZE, JJ, MODE, GBAR)) {                                                     \
       if (p.coord_thr < 0.f) {                                                                                  \
-        launch_tiles_of<GT, JJ, MODE, BS, IS, TABLE, GBAR, false, false>(NT_ARGS);                              \
+        ended = launch_tiles_of<GT, JJ, MODE, BS, IS, TABLE, GBAR, GBAR, false, false>(NT_ARGS);                \
         break;                                                                                                  \
       }                                                                                                         \
     }                                                                                                           \
-    launch_tiles_of<GT, JJ, MODE, BS, IS, TABLE, GBAR>(NT_ARGS);                                                \
+    ended = launch_tiles_of<GT, JJ, MODE, BS, IS, TABLE, GBAR, GBAR>(NT_ARGS);                                  \
     break;
     switch (p.J) {
       NT_CASE(2) NT_CASE(3) NT_CASE(4) NT_CASE(5) NT_CASE(6) NT_CASE(7) NT_CASE(8) NT_CASE(9)
       NT_CASE(10) NT_CASE(11) NT_CASE(12) NT_CASE(13) NT_CASE(14) NT_CASE(15) NT_CASE(16)
       default:
         if constexpr (MODE == MODE_STATS && !GBAR) {
-          launch_tiles_of<GT, 0, MODE, NT_BLOCK_LARGE_STATS, NT_ITERS_LARGE_STATS, TABLE, false>(NT_ARGS);
+          ended = launch_tiles_of<GT, 0, MODE, NT_BLOCK_LARGE_STATS, NT_ITERS_LARGE_STATS, TABLE, false, true>(NT_ARGS);
         } else {
           if (!long_class)
-            launch_tiles_of<GT, 0, MODE, NT_BLOCK_MANY_SHORT, NT_ITERS_MANY_SHORT, TABLE, true>(NT_ARGS);
+            ended = launch_tiles_of<GT, 0, MODE, NT_BLOCK_MANY_SHORT, NT_ITERS_MANY_SHORT, TABLE, true, true>(NT_ARGS);
           else if (p.J <= NT_FEW_ROWS)
-            launch_tiles_of<GT, 0, MODE, NT_BLOCK_FEW, NT_ITERS_FEW, TABLE, true>(NT_ARGS);
+            ended = launch_tiles_of<GT, 0, MODE, NT_BLOCK_FEW, NT_ITERS_FEW, TABLE, true, false>(NT_ARGS);
           else
-            launch_tiles_of<GT, 0, MODE, NT_BLOCK_LARGE, NT_ITERS_LARGE, TABLE, true>(NT_ARGS);
+            ended = launch_tiles_of<GT, 0, MODE, NT_BLOCK_LARGE, NT_ITERS_LARGE, TABLE, true, false>(NT_ARGS);
         }
     }
 #undef NT_ARGS
@@ -1557,30 +1554,30 @@ hipError_t launch_step_shape(const StepParams& p, int cls, int64_t nfull, int64_
 
 // picks the launch class (block size, sweeps per tile) that tile_cfg() describes
 template <class GT, int MODE, bool TABLE>
-hipError_t launch_step(const StepParams& p, int cls, int64_t nfull, int64_t ntiles, const Finish& fin, int grid,
-                       hipStream_t st) {
+hipError_t launch_step(const StepParams& p, int cls, int64_t nfull, int64_t ntiles, const Finish& fin, bool& ended,
+                       int grid, hipStream_t st) {
   if constexpr (MODE == MODE_STATS) {
     // read-only statistics over a short vector borrow the kernels that can also store gbar (there is none to store)
     if (p.gbar || (cls == CLS_SHORT_STATS && p.J <= NT_JCHUNK))
       return launch_step_shape<GT, MODE, TABLE, NT_BLOCK_STATS_GBAR, NT_ITERS_STATS_GBAR, true>(p, cls, nfull, ntiles,
-                                                                                                 fin, grid, st);
-    return launch_step_shape<GT, MODE, TABLE, NT_BLOCK_STATS, NT_ITERS_STATS, false>(p, cls, nfull, ntiles, fin, grid,
+                                                                                                 fin, ended, grid, st);
+    return launch_step_shape<GT, MODE, TABLE, NT_BLOCK_STATS, NT_ITERS_STATS, false>(p, cls, nfull, ntiles, fin, ended, grid,
                                                                                       st);
   } else if constexpr (MODE == MODE_ADAMW) {
-    return launch_step_shape<GT, MODE, TABLE, NT_BLOCK_ADAMW, NT_ITERS_ADAMW, true>(p, cls, nfull, ntiles, fin, grid,
+    return launch_step_shape<GT, MODE, TABLE, NT_BLOCK_ADAMW, NT_ITERS_ADAMW, true>(p, cls, nfull, ntiles, fin, ended, grid,
                                                                                      st);
   } else {
-    return launch_step_shape<GT, MODE, TABLE, NT_BLOCK, NT_ITERS, true>(p, cls, nfull, ntiles, fin, grid, st);
+    return launch_step_shape<GT, MODE, TABLE, NT_BLOCK, NT_ITERS, true>(p, cls, nfull, ntiles, fin, ended, grid, st);
   }
 }
 
 template <class GT, bool TABLE>
 hipError_t launch_step_mode(int mode, const StepParams& p, int cls, int64_t nfull, int64_t ntiles, const Finish& fin,
-                            int grid, hipStream_t st) {
+                            bool& ended, int grid, hipStream_t st) {
   switch (mode) {
-    case MODE_FULL: return launch_step<GT, MODE_FULL, TABLE>(p, cls, nfull, ntiles, fin, grid, st);
-    case MODE_STATS: return launch_step<GT, MODE_STATS, TABLE>(p, cls, nfull, ntiles, fin, grid, st);
-    default: return launch_step<GT, MODE_ADAMW, TABLE>(p, cls, nfull, ntiles, fin, grid, st);
+    case MODE_FULL: return launch_step<GT, MODE_FULL, TABLE>(p, cls, nfull, ntiles, fin, ended, grid, st);
+    case MODE_STATS: return launch_step<GT, MODE_STATS, TABLE>(p, cls, nfull, ntiles, fin, ended, grid, st);
+    default: return launch_step<GT, MODE_ADAMW, TABLE>(p, cls, nfull, ntiles, fin, ended, grid, st);
   }
 }
 
@@ -1717,12 +1714,11 @@ static int enqueue_step(const void* grads, bool table, nt_dtype gdtype, int64_t 
   WsRecord record;
   std::memcpy(&record, &hdr, sizeof(record));
   WsRecord* hdr_out = (WsRecord*)workspace;
-  const bool self = writes_own_result(table, J, mode, p.gbar != nullptr, cls, ntiles);
-
+  bool ended = false;   // the result has been left to the step's own kernel
   if (ntiles > 0) {
     Finish fin;
     std::memset(&fin, 0, sizeof(fin));
-    if (self) {
+    if (mode == MODE_ADAMW || ntiles == 1) {   // no sums, or one partial that is the total: launch_tiles_of has the kernels
       fin.q = q;
       fin.hdr = record;
       fin.hdr_out = hdr_out;
@@ -1733,14 +1729,14 @@ static int enqueue_step(const void* grads, bool table, nt_dtype gdtype, int64_t 
     const int grid = (int)(ntiles < max_grid ? ntiles : max_grid);
     hipError_t e;
     if (table)
-      e = (gdtype == NT_F32) ? launch_step_mode<F32, true>(mode, p, cls, nfull, ntiles, fin, grid, st)
-                             : launch_step_mode<BF16, true>(mode, p, cls, nfull, ntiles, fin, grid, st);
+      e = (gdtype == NT_F32) ? launch_step_mode<F32, true>(mode, p, cls, nfull, ntiles, fin, ended, grid, st)
+                             : launch_step_mode<BF16, true>(mode, p, cls, nfull, ntiles, fin, ended, grid, st);
     else
-      e = (gdtype == NT_F32) ? launch_step_mode<F32, false>(mode, p, cls, nfull, ntiles, fin, grid, st)
-                             : launch_step_mode<BF16, false>(mode, p, cls, nfull, ntiles, fin, grid, st);
+      e = (gdtype == NT_F32) ? launch_step_mode<F32, false>(mode, p, cls, nfull, ntiles, fin, ended, grid, st)
+                             : launch_step_mode<BF16, false>(mode, p, cls, nfull, ntiles, fin, ended, grid, st);
     if (e != hipSuccess) return hip_code(e);
   }
-  if (self) return NT_OK;
+  if (ended) return NT_OK;
 
   const double* partials = (const double*)workspace + NT_WS_HEADER;
   if (two_level) {

@@ -115,3 +115,28 @@ def test_adamw_only_writes_its_result_in_the_last_launch(J, d):
     assert res["status"] == B.NT_STATUS_NO_STATS and res["pass"] == 1 and res["next_b"] == 96
     for a, b in zip(want, (wl.w, wl.m, wl.v)):
         assert torch.equal(a, b)
+
+
+# every row count with a kernel of its own, both shapes beyond 16 rows and the one beyond 20; one tile in the classes of short
+# vectors and, for a part of a long one, in those of long vectors
+@pytest.mark.parametrize("whole", [None, 1 << 26])
+@pytest.mark.parametrize("gdtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("flags", [STATS | ADAMW, STATS, STATS | GBAR, STATS | COORD, ADAMW])
+def test_every_class_leaves_a_result(gdtype, flags, whole):
+    """Whether the step's own kernel writes the result or a second one does, it is written, and it is the one that the same
+    rows in a pointer table give, which (AdamW only apart) always take the second kernel."""
+    d = 700
+    for J in [*range(2, 22), 33]:
+        wl = synth.make("t", J, d, gdtype=gdtype, sigma=1e-2, seed=J, device=DEV, hyper=synth.Hyper(b_k=64, round_to=J))
+        kw = {} if whole is None else {"shard": B.nt_shard_info(0, 1, 0, whole)}
+        w, m, v = (t.clone() for t in (wl.w, wl.m, wl.v))
+        res, _ = _run(wl, flags, **kw)
+        h = wl.hyper
+        hy = B.make_hyper(lr=h.lr, beta1=h.beta1, beta2=h.beta2, eps=h.eps, weight_decay=h.weight_decay, eta=h.eta,
+                          step=h.step, b_k=h.b_k, b_max=h.b_max, round_to=h.round_to, ddof=h.ddof, flags=flags)
+        gbar = torch.empty(d, dtype=torch.float32, device=DEV)
+        out = torch.full((B.RESULT_BYTES,), 0xA5, dtype=torch.uint8, device=DEV)
+        _same(res, B.read_result(B.normtest_step_rows(list(wl.grads), w, m, v, hy, gbar_out=gbar, result=out, **kw)).as_dict())
+        assert (res["status"] == B.NT_STATUS_NO_STATS) == (not flags & STATS)
+        for a, b in zip((w, m, v), (wl.w, wl.m, wl.v)):
+            assert torch.equal(a, b)
