@@ -642,9 +642,8 @@ __device__ inline void coord_stats(const StepParams& p, int64_t i, double& S, fl
 // below it; those (one group per call) are moved one by one, and what lies past d is zero rows on zero state, which add
 // exact zeros to every sum.  The arithmetic is the same for whole and part tiles, hence the same bits.  With at most 16
 // rows the part tile is a copy of its own (the branch in the only copy makes a wave wait for all its rows before the
-// first sum, -2 % on the fused step); beyond 16 rows one copy serves both, since two would need more scalar registers
-// for row addresses than there are.  128 rows, d = 1,000,003, unpadded: 73 us against 386 us with the part tile and
-// everything misaligned element by element.
+// first sum, -2 % on the fused step); beyond 16 rows that depends (whole_copy).  128 rows, d = 1,000,003, unpadded: 73 us
+// against 386 us with the part tile and everything misaligned element by element.
 // ---------------------------------------------------------------------------------------------
 // coordinates i0 .. i0+3 that lie below d: 4 or fewer, 0 or negative where none does
 __device__ inline int below(int64_t d, int64_t i0) { return (int)(d - i0 < 4 ? (d - i0 < 0 ? 0 : d - i0) : 4); }
@@ -1024,12 +1023,25 @@ __device__ inline void tile_multi(const StepParams& p, int64_t tile, double (*re
 // ---------------------------------------------------------------------------------------------
 template <class GT, int J_T, int MODE, int BLOCK, int ITERS, bool TABLE, bool GBAR, bool DEFER_T, bool COORD, bool PART>
 __device__ inline void run_tile(const StepParams& p, int64_t tile, double (*red)[BLOCK / 64][NT_NV], int buf, f32x4* gbs) {
-  if constexpr (J_T == 0)   // one copy serves both: its chunks of rows need the scalar registers of two
-    tile_multi<GT, MODE, BLOCK, ITERS, TABLE, GBAR, true>(p, tile, red, buf, gbs);
+  if constexpr (J_T == 0)
+    tile_multi<GT, MODE, BLOCK, ITERS, TABLE, GBAR, PART>(p, tile, red, buf, gbs);
   else if constexpr (DEFER_T)
     tile_defer<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, PART>(p, tile, red, buf, gbs);
   else
     tile_rows<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, COORD, PART>(p, tile, red, buf);
+}
+
+// More than 16 rows: which of a kernel's whole tiles run a copy of the walk without the part branch instead of the copy that
+// the part tile needs anyway.  The branch costs a short walk and a short vector (bf16, with it against without: statistics of
+// 17 / 40 / 128 / 512 rows at d = 2^21 22.3 / 21.7, 40.3 / 38.5, 118.3 / 109.3, 404 / 392 us, 512 rows at 2^22 668 / 680;
+// fused step of 17 / 24 / 32 rows at d = 3e7 302 / 299, 371 / 365, 432 / 429 us, with gbar 17 rows 212 / 206).  It stays in
+// the tiles of the long class from 33 rows on, where it keeps the blocks of a full generation in step (512 rows, d = 2^24:
+// 2571 us with it, 2640 without; 64 rows 408 and 419), with AdamW only (32 rows, d = 3e7: 415 and 418 us) and with fp32 rows
+// (statistics of 17 rows, d = 2^24: 189 and 196 us).
+template <class GT, int MODE, int BLOCK, int ITERS>
+__device__ inline bool whole_copy(int J) {
+  constexpr bool LONG = BLOCK == NT_BLOCK_LARGE && ITERS == NT_ITERS_LARGE;
+  return GT::ESIZE == 2 && MODE != MODE_ADAMW && (!LONG || J <= 32);
 }
 
 // GBAR = false compiles the gbar store out (statistics-only launch class, so that sweeps can overlap).
@@ -1050,7 +1062,7 @@ __device__ inline void walk_tiles(const StepParams& p, int64_t nfull, int64_t nt
     // rotate: the part tile (if any) first, then the whole tiles 0..nfull-1
     const bool part = t < npart;
     const int64_t tile = part ? nfull : t - npart;
-    if (J_T > 0 && !part)
+    if (!part && (J_T > 0 || whole_copy<GT, MODE, BLOCK, ITERS>(p.J)))
       run_tile<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, DEFER_T, COORD, false>(p, tile, red, buf, gbs);
     else
       run_tile<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, DEFER_T, COORD, true>(p, tile, red, buf, gbs);

@@ -63,3 +63,51 @@ def test_ragged_ends_at_every_alignment(J, gdtype, flags):
             assert bool(((gbar.double() - ref_gbar).abs() <= 2.0 ** -23 * ref_gbar.abs() + 1e-45).all())
         for base, s in state:
             assert _guards_untouched(base, s, 5.0), (d, "guard words")
+
+
+# with `whole` the vector is the start of a long one: deferred updates (16 bf16 and 8 fp32 rows), the shapes beyond 16 and 20
+# rows, with (24) and without (40) a copy of their walk for whole tiles, and statistics in 16384-coordinate tiles
+@pytest.mark.parametrize("whole", [None, 1 << 26])
+@pytest.mark.parametrize("flags", [STATS | ADAMW | B.NT_WRITE_GBAR, STATS, STATS | B.NT_WRITE_GBAR, ADAMW])
+@pytest.mark.parametrize("J,gdtype", [(3, torch.bfloat16), (16, torch.bfloat16), (8, torch.float32), (17, torch.bfloat16),
+                                      (20, torch.float32), (24, torch.bfloat16), (40, torch.bfloat16), (40, torch.float32)])
+def test_ragged_ends_of_a_matrix(J, gdtype, flags, whole):
+    """The same of one matrix with an odd row stride and NaN between its rows, around the edges of the 8192- and
+    16384-coordinate tiles too; and the same bits as from a table of the same rows."""
+    kw = {} if whole is None else {"shard": B.nt_shard_info(0, 1, 0, whole)}
+    for d in (1, 2, 3, 4, 1026, 2049, 4099, 8191, 8194, 16387):
+        wl = synth.make("t", J, d, gdtype=gdtype, sigma=1e-2, seed=J + d, device=DEV,
+                        hyper=synth.Hyper(b_k=64, round_to=J, step=3))
+        h = wl.hyper
+        hy = B.make_hyper(lr=h.lr, beta1=h.beta1, beta2=h.beta2, eps=h.eps, weight_decay=h.weight_decay, eta=h.eta,
+                          step=h.step, b_k=h.b_k, b_max=h.b_max, round_to=h.round_to, ddof=h.ddof, flags=flags)
+        big = torch.full((J, d + 5 + d % 2), float("nan"), dtype=gdtype, device=DEV)
+        view = big[:, 3:3 + d]
+        view.copy_(wl.grads[:, :d])
+        got = []
+        for table in (False, True):
+            state = [_padded(d, torch.float32, k + 1, 5.0) for k in range(4)]
+            for (_, s), src in zip(state, (wl.w, wl.m, wl.v)):
+                s.copy_(src)
+            w, m, v, gbar = (s for _, s in state)
+            if table:
+                res = B.normtest_step_rows([view[j] for j in range(J)], w, m, v, hy, gbar_out=gbar, **kw)
+            else:
+                res = B.normtest_step(view, w, m, v, hy, d=d, gbar_out=gbar, **kw)
+            got.append((B.read_result(res).as_dict(), state))
+            for base, s in state:
+                assert _guards_untouched(base, s, 5.0), (d, "guard words")
+        (res, state), (other, other_state) = got
+        if flags & STATS:
+            assert res == other
+            H.assert_stats_close(res, H.oracle_full(wl.grads, d, J, h))
+        for (_, a), (_, b) in zip(state, other_state):
+            assert torch.equal(a, b)
+        if flags & ADAMW and d > 4:
+            # (of one to four coordinates one may be a moment that cancels: its error is then half an ulp of the summands, which
+            # the root mean square of so few does not cover; they have the table's bits)
+            H.oracle_adamw_check(wl.grads, d, wl.w, wl.m, wl.v, *(s for _, s in state[:3]), h)
+        if flags & B.NT_WRITE_GBAR:
+            # as above: half an ulp, and one more for the scaling
+            ref_gbar = wl.grads[:, :d].double().mean(0)
+            assert bool(((state[3][1].double() - ref_gbar).abs() <= 2.0 ** -23 * ref_gbar.abs() + 1e-45).all())
