@@ -136,6 +136,20 @@ __device__ inline T ld_nt(P p) {
   return __builtin_nontemporal_load((const T NT_GLOBAL*)p);
 }
 
+// A group of four bfloat16 coordinates of which only the first n = 0 .. 3 lie below d, without a branch between its loads:
+// which elements exist, as lane masks.  All three are loaded, the first in place of one that does not exist and the sweep's
+// first coordinate in place of a group that lies wholly past d.
+typedef uint32_t Part __attribute__((ext_vector_type(3)));
+struct Exists {
+  uint32_t first, second, third;   // all ones or zero
+  __device__ inline Exists(int n)
+      : first((int)(0u - (uint32_t)n) >> 31), second((int)(1u - (uint32_t)n) >> 31), third((int)(2u - (uint32_t)n) >> 31) {}
+};
+__device__ inline Part ld_part16(const char NT_GLOBAL* sweep, uint32_t lane, const Exists& x) {
+  const uint16_t NT_GLOBAL* q = (const uint16_t NT_GLOBAL*)(sweep + (lane & x.first));
+  return {q[0], q[x.second & 1u], q[x.third & 2u]};
+}
+
 struct F32 {
   static constexpr int VEC = 4;
   static constexpr int ESIZE = 4;
@@ -166,6 +180,9 @@ struct BF16 {
     if (n > 1) r[0] |= (uint32_t)q[1] << 16;
     if (n > 2) r[1] = q[2];
     return r;
+  }
+  __device__ static inline raw_t join(const Part& w, const Exists& x) {
+    return {(w[0] & x.first) | (w[1] << 16 & x.second), w[2] & x.third};
   }
   // bfloat16 is the high half of a binary32: widening is a shift or a mask
   __device__ static inline float val(const raw_t& r, int e) {
@@ -685,7 +702,16 @@ struct RowWalk {
 };
 
 // Rows j0 .. j0+N-1 of the lane's coordinates, and with STATE w, m, v too, all under one branch so that every load of a
-// sweep is in flight before the first wait.
+// sweep is in flight before the first wait.  The sweep's first coordinate lies below d.  In the branch for the part group
+// every row is used at once, so that none of its loads is pending behind it: the wait before each row's first use below would
+// have to allow for it and be a wait for all rows (24 rows, d = 3e7: 377 -> 454 us).  A bf16 matrix without the state has up
+// to eight rows in flight there: one by one they were the longest chain of loads in a short vector (128 unpadded rows of
+// 1,000,003 coordinates 76 us against 58, statistics of 16 rows over 100,003 coordinates 12.5 against 11.4).  Elsewhere they
+// do go one by one.  With the state the elements would wait in vector registers that take the fused kernels of 8 and 12 rows
+// past the next step in how many waves a CU holds (11 rows with 98 instead of 91: +3 %), with a table the pointers in scalar
+// registers that the kernels which also carry the result's record do not have (they would need scratch memory); and beyond 16
+// fp32 rows four blocks instead of three fit a CU then, which is slower by 2 to 4 % from 2^22 coordinates on and gains 0.3 %
+// on ragged vectors.
 template <class GT, bool TABLE, bool PART, int N, bool STATE>
 __device__ inline void load_sweep(const StepParams& p, int j0, const Place& pl, int n, typename GT::raw_t* raw,
                                   u32x4* state) {
@@ -699,19 +725,36 @@ __device__ inline void load_sweep(const StepParams& p, int j0, const Place& pl, 
       state[1] = ld16(at(p.m, pl));
       state[2] = ld16(at(p.v, pl));
     }
-  } else {
+  } else if constexpr (STATE || TABLE || GT::ESIZE == 4) {
     RowWalk<GT, TABLE> row(p, j0, pl.s0);
 #pragma unroll
     for (int j = 0; j < N; ++j) {
       raw[j] = GT::ldraw_part(row.next() + lane, n);
-      // used at once, so that no load of this branch is pending behind it: the wait before each row's first use below
-      // would have to allow for it and be a wait for all rows (24 rows, d = 3e7: 377 -> 454 us)
       asm volatile("" : "+v"(raw[j]));
     }
     if constexpr (STATE) {
       state[0] = F32::ldraw_part((const char NT_GLOBAL*)at(p.w, pl), n);
       state[1] = F32::ldraw_part((const char NT_GLOBAL*)at(p.m, pl), n);
       state[2] = F32::ldraw_part((const char NT_GLOBAL*)at(p.v, pl), n);
+    }
+  } else {
+    int few = n;   // opaque: the masks are not to be kept in registers throughout the loop over tiles
+    asm volatile("" : "+v"(few));
+    const Exists x(few);
+    RowWalk<GT, TABLE> row(p, j0, pl.s0);
+    constexpr int RUN = N < 8 ? N : 8;
+#pragma unroll
+    for (int j = 0; j < N; j += RUN) {
+      Part w[RUN];
+#pragma unroll
+      for (int k = 0; k < RUN; ++k)
+        if (j + k < N) w[k] = ld_part16(row.next(), lane, x);
+#pragma unroll
+      for (int k = 0; k < RUN; ++k)
+        if (j + k < N) {
+          raw[j + k] = GT::join(w[k], x);
+          asm volatile("" : "+v"(raw[j + k]));
+        }
     }
   }
 }
