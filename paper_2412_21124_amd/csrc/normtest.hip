@@ -844,6 +844,13 @@ __device__ inline void sweep_rows(const StepParams& p, const typename GT::raw_t*
   }
 }
 
+// Statistics kernels whose loads have to be kept together: at these row counts the compiler sinks the last two or three loads
+// of a sweep below the first sums, and every sweep then waits for memory three times (read-only statistics, d = 2^21: 15 bf16
+// rows 27.4 -> 21.5 us, 11 / 15 fp32 rows 25.4 -> 23.8 and 35.6 -> 30.3; d = 1e8: 446 -> 434, +-0.3 %).  At the other counts
+// it issues them together by itself, and holding it to that only keeps sums from starting early (14 and 16 bf16 rows,
+// d = 5e6 .. 1e7: +0.9 .. 2.7 % time).
+constexpr bool pin_loads(int esize, int J, bool coord) { return !coord && (J == 15 || (J == 11 && esize == 4)); }
+
 // State update interleaved with the rows: each sweep reads its rows and w, m, v, and writes the state back.
 template <class GT, int J, int MODE, int BLOCK, int ITERS, bool TABLE, bool GBAR, bool COORD, bool PART>
 __device__ inline void tile_rows(const StepParams& p, int64_t tile, double (*red)[BLOCK / 64][NT_NV], int buf) {
@@ -864,6 +871,7 @@ __device__ inline void tile_rows(const StepParams& p, int64_t tile, double (*red
     typename GT::raw_t raw[J];
     u32x4 state[3];
     load_sweep<GT, TABLE, PART, J, MODE != MODE_STATS>(p, 0, pl, n, raw, state);
+    if constexpr (MODE == MODE_STATS && U == 1 && !PART && pin_loads(GT::ESIZE, J, COORD)) __builtin_amdgcn_sched_barrier(0);
     if constexpr (MODE != MODE_STATS) {
       // Every load of the sweep is issued before any arithmetic: the compiler must neither sink loads below
       // the arithmetic that precedes their use nor hoist arithmetic between them (measured: up to 5 % at 16

@@ -37,3 +37,29 @@ def test_same_bits_with_and_without_the_coordinate_test(J, gdtype, flags, d):
             assert plain[k] == coord[k], k
     assert all(torch.equal(a, b) for a, b in zip(s0, s1))
     H.assert_stats_close(plain, H.oracle_full(wl.grads, d, J, h))
+
+
+# statistics with more bytes of rows run without the test up to 2^22 coordinates of the call (16 bytes per coordinate, 8 bf16
+# or 4 fp32 rows: up to 2^25); read-only ones of 15 rows, and of 11 fp32 rows, hold their loads together
+@pytest.mark.parametrize("J,gdtype,edge", [(9, torch.bfloat16, 1 << 22), (13, torch.bfloat16, 1 << 22), (15, torch.bfloat16, 1 << 22),
+                                           (5, torch.float32, 1 << 22), (11, torch.float32, 1 << 22), (15, torch.float32, 1 << 22),
+                                           (8, torch.bfloat16, 1 << 25), (4, torch.float32, 1 << 25)])
+def test_same_bits_on_both_sides_of_a_length(J, gdtype, edge):
+    for d in (5, 8192 + 3, edge, edge + 1):
+        wl = synth.make("t", J, d, gdtype=gdtype, sigma=1e-2, seed=J + d, device=DEV, hyper=synth.Hyper(b_k=64, round_to=J))
+        h = wl.hyper
+        for flags in (STATS, STATS | GBAR):
+            got = []
+            for extra in (0, B.NT_COORD_TEST):
+                hy = B.make_hyper(eta=h.eta, step=h.step, b_k=h.b_k, b_max=h.b_max, round_to=h.round_to, ddof=h.ddof,
+                                  flags=flags | extra)
+                gbar = torch.zeros(d, dtype=torch.float32, device=DEV)
+                got.append((B.read_result(B.normtest_step(wl.grads, None, None, None, hy, d=d, gbar_out=gbar)).as_dict(), gbar))
+            (plain, g0), (coord, g1) = got
+            assert plain["coord_fail"] == -1 and coord["coord_fail"] >= 0
+            for k in plain:
+                if k not in ("coord_fail", "coord_max_ratio"):
+                    assert plain[k] == coord[k], (k, d, flags)
+            assert torch.equal(g0, g1)
+        if J * d <= 1 << 26:
+            H.assert_stats_close(plain, H.oracle_full(wl.grads, d, J, h))
