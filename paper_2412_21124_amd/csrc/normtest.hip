@@ -1413,6 +1413,13 @@ struct TileCfg {
 constexpr bool plain_stats(int esize, int J, int mode, bool gbar) {
   return (mode == MODE_STATS && !gbar) || (mode != MODE_ADAMW && J * esize <= 8);
 }
+// ... and how far, in coordinates of the call, the same holds for statistics with more bytes of rows (short vectors without
+// gbar among them, which run the kernels with it).  Without against with the test, us: 4 fp32 rows and gbar 24.1 / 26.8 at
+// d = 5e6, 69.1 / 71.0 at 2^24, 344 / 334 at 1e8; 8 bf16 rows 22.5 / 23.1 at 2^22, 105.4 / 106.3 at 3e7, 628 / 625 at 2e8;
+// 13 / 14 bf16 rows 12.3 / 12.8 and 12.6 / 13.0 at 2^20, 5 to 16 rows -0.3 .. -5 % up to 2^22, 14 rows +2 % at 5e6 .. 7e6.
+constexpr int64_t plain_coords(int esize, int J, int mode) {
+  return mode != MODE_STATS || J * esize < 16 ? 0 : J * esize == 16 ? 1ll << 25 : 1ll << 22;
+}
 constexpr int defer_row_bytes(int mode) { return mode == MODE_ADAMW ? NT_DEFER_ROW_BYTES_ADAMW : NT_DEFER_ROW_BYTES; }
 // Which launch class a call takes beside its row count, dtype and mode: CLS_LONG, the classes for long vectors
 // (large tiles, state update deferred, one generation of blocks per launch); CLS_SHORT_STATS, read-only statistics
@@ -1584,8 +1591,8 @@ hipError_t launch_step_shape(const StepParams& p, int cls, int64_t nfull, int64_
         break;                                                                                                  \
       }                                                                                                         \
     }                                                                                                           \
-    if constexpr (plain_stats(GT::ESIZE, JJ, MODE, GBAR)) {                                                     \
-      if (p.coord_thr < 0.f) {                                                                                  \
+    if constexpr (plain_stats(GT::ESIZE, JJ, MODE, GBAR) || plain_coords(GT::ESIZE, JJ, MODE) > 0) {            \
+      if (p.coord_thr < 0.f && (plain_stats(GT::ESIZE, JJ, MODE, GBAR) || p.d <= plain_coords(GT::ESIZE, JJ, MODE))) { \
         ended = launch_tiles_of<GT, JJ, MODE, BS, IS, TABLE, GBAR, GBAR, false, false>(NT_ARGS);                \
         break;                                                                                                  \
       }                                                                                                         \
