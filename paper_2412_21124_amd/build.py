@@ -10,8 +10,8 @@ SRC = os.path.join(_HERE, "csrc", "normtest.hip")
 LIB = os.path.join(_HERE, "libnormtest.so")
 INCLUDE = os.path.join(ROOT, "include")
 
-# contraction off: the error-free transformations of the finalize kernel and the bit-identical
-# fast/guarded paths rely on every fused multiply-add being an explicit one;
+# contraction off: the error-free transformations of the finalize kernel, and the bits that the copies of a tile's
+# code (whole and part tiles, every launch shape) have in common, rely on every fused multiply-add being an explicit one;
 # packed fp32 instructions are disabled for the device pass.
 HIPCC_FLAGS = [
     "-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-shared", "-ffp-contract=off",

@@ -586,10 +586,9 @@ __device__ inline float chunk_merge(bool first, int na, int nb, float K, double 
 }
 
 // ---------------------------------------------------------------------------------------------
-// Guarded tile: any J, any alignment, ragged end.  Same lane-to-coordinate map and the same
-// sequence of floating-point operations per coordinate as the fast tiles below (rows are re-read
-// instead of held in registers), so a tile's partial sums and outputs have the same bits on either
-// path.  Coordinates at or beyond d contribute exact zeros.
+// One coordinate by itself, any J and any alignment: what the per-layer table needs at a layer's ends, where a layer covers
+// a part of a tile (piece_sums).  The operations on a coordinate are those of the tiles below, in their order, and have to
+// stay so; only the sums over coordinates are formed in another order.  Rows are re-read instead of held in registers.
 // ---------------------------------------------------------------------------------------------
 template <class GT, bool TABLE>
 __device__ inline void coord_stats_generic(const StepParams& p, int64_t i, double& S, float& M2, float& a) {
@@ -659,7 +658,7 @@ __device__ inline void coord_stats(const StepParams& p, int64_t i, double& S, fl
 // below it; those (one group per call) are moved one by one, and what lies past d is zero rows on zero state, which add
 // exact zeros to every sum.  The arithmetic is the same for whole and part tiles, hence the same bits.  With at most 16
 // rows the part tile is a copy of its own (the branch in the only copy makes a wave wait for all its rows before the
-// first sum, -2 % on the fused step); beyond 16 rows that depends (whole_copy).  128 rows, d = 1,000,003, unpadded: 73 us
+// first sum, -2 % on the fused step); beyond 16 rows that depends (whole_copy).  128 rows, d = 1,000,003, unpadded: 58 us
 // against 386 us with the part tile and everything misaligned element by element.
 // ---------------------------------------------------------------------------------------------
 // coordinates i0 .. i0+3 that lie below d: 4 or fewer, 0 or negative where none does
@@ -1128,7 +1127,7 @@ __global__ __launch_bounds__(BLOCK) void k_step(StepParams p, int64_t nfull, int
 
 // A step that writes its result itself: AdamW only, which has no sums, or a single tile, whose partial is the total.  A
 // second kernel costs such a call 3.7 us on the host and some 4 on the GPU (steps back to back: 4 fp32 rows, d = 1000,
-// 9.9 -> 6.1 us; AdamW only, 8 bf16 rows, d = 1e6, 8.5 -> 6.7 us).  It is a kernel of its own because this tail in every
+// 9.5 -> 6.2 us; AdamW only, 8 bf16 rows, d = 1e6, 8.7 -> 6.8 us).  It is a kernel of its own because this tail in every
 // kernel slows the long steps by 0.3 to 1 %.  Steps of more tiles keep their reduction kernels: a handshake between blocks
 // needs a device-wide acquire in each, since the XCDs' L2s hand out stale partials otherwise, and that is dearer than a
 // launch (4 fp32 rows, d = 2^20: 17.6 us against 13.2).
@@ -1523,8 +1522,8 @@ constexpr auto step_kernel() {
     return k_step<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, DEFER_T>;
 }
 // ONE_TILE: the class that vectors of a single tile take.  Of those, matrices have a kernel that writes the result; pointer
-// tables of one tile keep the two kernels, as the 31 further kernels per dtype would serve only calls of at most 4096
-// coordinates whose rows are allocations of their own (not built, not measured).  Returns whether the launched kernel writes
+// tables of one tile keep the two kernels, as the 33 further kernels per dtype would serve only calls of at most 4096
+// coordinates whose rows are allocations of their own (not built, so not measured either).  Returns whether the launched kernel writes
 // the result when it is the step's last: the caller's only source for that, so that no step can end without a result.
 template <class GT, int J_T, int MODE, int BLOCK, int ITERS, bool TABLE, bool GBAR, bool ONE_TILE, bool DEFER_T = false,
           bool COORD = true>

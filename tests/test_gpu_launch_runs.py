@@ -1,8 +1,8 @@
 """A long vector is walked by several kernel launches, each over a run of consecutive tiles (2^27 coordinates for the
 fused step up to 16 rows, 2^25 for AdamW only and for AdamW from a stored mean, 2^23 beyond 16 rows).  These cases
-sit just past one or two such runs, with a ragged end and, in one variant each, with every buffer misaligned so that
-all tiles of all launches take the guarded path; each is compared with the oracle element by element, and the
-misaligned call with the aligned one bit for bit."""
+sit just past one or two such runs, with a ragged end and, in one variant each, with every buffer one element off a
+16-byte boundary, which the kernels' vector accesses have to take as they come; each is compared with the oracle element by
+element, and the misaligned call with the aligned one bit for bit."""
 import math
 
 import pytest
@@ -76,8 +76,8 @@ def test_adamw_only_over_several_launches_equals_the_fused_step():
 
 def test_fused_step_over_two_launches_aligned_and_misaligned():
     """The fused step just past one run of 2^27 coordinates: statistics, decision and every updated element against
-    the oracle; then the same data in misaligned buffers (every tile of both launches on the guarded path, the
-    ragged tile first) must give the same bits."""
+    the oracle; then the same data in buffers off every 16-byte boundary (the same kernels on other addresses, in both
+    launches and in the ragged tile) must give the same bits."""
     d = (1 << 27) + 2 * 4096 + 5
     wl = synth.flat_1p5b(d=d, seed=33, device=DEV)     # the headline's rows and state, 8 bf16 rows
     w0, m0, v0 = wl.w.clone(), wl.m.clone(), wl.v.clone()

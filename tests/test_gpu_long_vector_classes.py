@@ -64,7 +64,7 @@ CASES = [(14, torch.bfloat16), (15, torch.bfloat16), (16, torch.bfloat16),
 def test_fused_step_in_the_deferred_class(J, gdtype):
     """Statistics, decision, coordinate-wise count and every updated element against the oracle; the same bits in
     w, m, v as the interleaved class leaves (the arithmetic per coordinate is the same), the sums to rounding of a
-    differently ordered fp64 addition; and the same bits again from misaligned buffers (guarded tiles)."""
+    differently ordered fp64 addition; and the same bits again from buffers off every 16-byte boundary."""
     d = 5 * TILE + 3 * 512 + 77
     wl = synth.make("t", J, d, gdtype=gdtype, sigma=1e-2, seed=41 + J, device=DEV,
                     hyper=synth.Hyper(b_k=64, round_to=J, step=3))

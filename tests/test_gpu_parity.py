@@ -144,8 +144,8 @@ def test_two_runs_bit_identical():
 
 @pytest.mark.parametrize("J,gdtype", [(8, torch.bfloat16), (4, torch.float32), (40, torch.bfloat16)])
 def test_misaligned_and_padded_rows_same_bits(J, gdtype):
-    """Rows that start 1 element off a 16-byte boundary, or with a padded stride, take the guarded
-    kernel; the sums and the updated state must have the same bits as on the aligned fast path."""
+    """Rows and state that start 1 element off a 16-byte boundary, or rows with a padded or an odd stride: the same
+    kernels on other addresses; the sums and the updated state must have the same bits as of aligned ones."""
     d = 2 * B.normtest_tile_coords(J) + 1000
     wl = synth.make("t", J, d, gdtype=gdtype, sigma=1e-2, seed=1, device=DEV)
     state0 = (wl.w.clone(), wl.m.clone(), wl.v.clone())
@@ -461,7 +461,7 @@ def test_coordinatewise_count_degenerate_and_sharded():
     same[1, :100] = -1.0
     res = gpu_step(same, wl.w, wl.m, wl.v, wl.hyper, flags=B.NT_DO_STATS | B.NT_COORD_TEST)
     assert res["coord_fail"] == 100 and res["coord_max_ratio"] == math.inf
-    # shards: counts add up in normtest_combine, and the guarded (misaligned) path counts the same
+    # shards: counts add up in normtest_combine, and misaligned rows count the same
     whole = gpu_step(wl.grads, wl.w, wl.m, wl.v, wl.hyper, flags=B.NT_DO_STATS | B.NT_COORD_TEST)
     cuts = [0, 16384, 2 * 16384, d]
     parts = []
@@ -758,7 +758,7 @@ def test_canaries_around_every_buffer_survive(J, gdtype, flags):
     without alignment) the guards and everything past d are untouched."""
     d = 2 * 16384 + 3001
     guard = 64
-    for off in (0, 1):                                     # off = 1 breaks 16-byte alignment: guarded kernel path
+    for off in (0, 1):                                     # off = 1: no buffer on a 16-byte boundary
         wl = synth.make("t", J, d, gdtype=gdtype, seed=31, device=DEV)
         bufs = {}
         for name, src in (("w", wl.w), ("m", wl.m), ("v", wl.v), ("gbar", torch.zeros(d, device=DEV))):
@@ -1019,9 +1019,8 @@ def test_calib_streams_touches_only_its_streams():
 
 
 def test_long_row_table_with_one_misaligned_row_at_the_end():
-    """300 separately allocated rows: the alignment of all of them is checked once per call by a small kernel
-    (more rows than that kernel has threads); a single row off by one element, the last one, must send the whole
-    call down the guarded path, with the same bits as the aligned call and as the strided matrix."""
+    """300 separately allocated rows, the last one off a 16-byte boundary by one element: no row's alignment is looked
+    at, and a table that mixes them gives the same bits as the aligned call and as the strided matrix."""
     J, d = 300, 2 * 2048 + 100
     wl = synth.make("t", J, d, gdtype=torch.bfloat16, sigma=1e-2, seed=91, device=DEV, hyper=synth.Hyper(b_k=512, round_to=1))
     state0 = [t.clone() for t in (wl.w, wl.m, wl.v)]

@@ -1,7 +1,7 @@
 """Ragged ends and element-aligned buffers: the last tile of a vector holds whole groups of four coordinates, one group
 of one to three, and nothing behind it; rows and state may start at any element.  Sizes sit around the edges of a group,
-of a sweep and of a tile of every launch class; results are compared with the oracle, and the words in front of and
-behind every buffer must stay what they were."""
+of a sweep and of a tile: tables in the classes of short vectors, matrices in those of long ones too.  Results are compared
+with the oracle, and the words in front of and behind every buffer must stay what they were."""
 from __future__ import annotations
 
 import pytest
@@ -17,7 +17,7 @@ STATS, ADAMW = B.NT_DO_STATS, B.NT_DO_ADAMW
 
 # (J, dtype): fused and statistics classes up to 16 rows; one, two and more chunks of 16 rows beyond
 ROWS = [(2, torch.bfloat16), (5, torch.float32), (16, torch.bfloat16), (17, torch.float32), (40, torch.bfloat16)]
-# below and at one group, a sweep of 256 and 512 threads, tiles of 2048, 4096 and 16384 coordinates, each with 1..3 over
+# below and at one group, a sweep of 256 and 512 threads, tiles of 2048 and 4096 coordinates, several tiles, with 1..3 over
 SIZES = [1, 2, 3, 4, 1023, 1026, 2049, 4097, 6147, 16386, 20481]
 
 
