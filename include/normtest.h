@@ -227,7 +227,8 @@ int normtest_combine(const nt_result* partials, int32_t n, int64_t J, const nt_h
  * Arguments as in normtest_step; gbar_buf: device fp32[d], required; max_norm > 0 (<= 0: no clipping,
  * c = 1, and w, m, v come out bit-identical to normtest_step).  hyper->flags must contain NT_DO_STATS and
  * NT_DO_ADAMW and not NT_PARTIAL (a shard cannot know the global norm: see normtest_adamw_gbar).
- * The test statistic uses the unclipped gbar.  result_dev->clip_coef reports c.
+ * The test statistic uses the unclipped gbar.  result_dev->clip_coef reports c (1 where the norm is not finite, which
+ * the sums report as NaN).
  */
 int normtest_step_clipped(const void* grads, nt_dtype gdtype, int64_t J, int64_t d, int64_t ld,
                           float* w, float* m, float* v, float* gbar_buf, double max_norm,
