@@ -1086,12 +1086,13 @@ __device__ inline void run_tile(const StepParams& p, int64_t tile, double (*red)
 // 17 / 40 / 128 / 512 rows at d = 2^21 22.3 / 21.7, 40.3 / 38.5, 118.3 / 109.3, 404 / 392 us, 512 rows at 2^22 668 / 680;
 // fused step of 17 / 24 / 32 rows at d = 3e7 302 / 299, 371 / 365, 432 / 429 us, with gbar 17 rows 212 / 206).  It stays in
 // the tiles of the long class from 33 rows on, where it keeps the blocks of a full generation in step (512 rows, d = 2^24:
-// 2571 us with it, 2640 without; 64 rows 408 and 419), with AdamW only (32 rows, d = 3e7: 415 and 418 us) and with fp32 rows
-// (statistics of 17 rows, d = 2^24: 189 and 196 us).
-template <class GT, int MODE, int BLOCK, int ITERS>
+// 2571 us with it, 2640 without; 64 rows 408 and 419), with AdamW only (32 rows, d = 3e7: 415 and 418 us), with fp32 rows
+// (statistics of 17 rows, d = 2^24: 189 and 196 us) and with tables, whose row addresses leave a second copy no scalar
+// registers (85 of them spilled; fused step of 17 rows, d = 4000: 12.7 and 13.4 us, though 128 rows at 2^21 would gain 8 %).
+template <class GT, int MODE, int BLOCK, int ITERS, bool TABLE>
 __device__ inline bool whole_copy(int J) {
   constexpr bool LONG = BLOCK == NT_BLOCK_LARGE && ITERS == NT_ITERS_LARGE;
-  return GT::ESIZE == 2 && MODE != MODE_ADAMW && (!LONG || J <= 32);
+  return GT::ESIZE == 2 && MODE != MODE_ADAMW && !TABLE && (!LONG || J <= 32);
 }
 
 // GBAR = false compiles the gbar store out (statistics-only launch class, so that sweeps can overlap).
@@ -1112,7 +1113,7 @@ __device__ inline void walk_tiles(const StepParams& p, int64_t nfull, int64_t nt
     // rotate: the part tile (if any) first, then the whole tiles 0..nfull-1
     const bool part = t < npart;
     const int64_t tile = part ? nfull : t - npart;
-    if (!part && (J_T > 0 || whole_copy<GT, MODE, BLOCK, ITERS>(p.J)))
+    if (!part && (J_T > 0 || whole_copy<GT, MODE, BLOCK, ITERS, TABLE>(p.J)))
       run_tile<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, DEFER_T, COORD, false>(p, tile, red, buf, gbs);
     else
       run_tile<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, DEFER_T, COORD, true>(p, tile, red, buf, gbs);
