@@ -253,15 +253,82 @@ __device__ inline float lane_tree(const float* x) {
   return (x[0] + x[1]) + (x[2] + x[3]);
 }
 
-__device__ inline double wave_sum(double x) {
+// ---------------------------------------------------------------------------------------------
+// Sums over the 64 lanes of a wave, on the vector unit: lanes exchange values by swapping register halves (32 and 16 lanes
+// apart) and by row moves (8, 4, 2, 1 apart), not through LDS.  Four sums are formed together: a swap of two values' halves
+// leaves each value's lanes in one half of the wave, so the steps below it serve both, and from the third step on all four.
+// The additions are those of a butterfly 32, 16, 8, 4, 2, 1 of each value alone.  A tile's five values took 54
+// permutes through LDS in every wave of a block, a chain that nothing else covers in a step that lives for a few tiles, and
+// where a CU holds one block of 1024 threads: fused step of 4 fp32 rows 10.4 -> 8.5 us at d = 5000 and 13.1 -> 10.5 at 2^20, of
+// 8 bf16 rows 129 -> 122 us at 2^24 and 830 -> 820 at 124M, 4 rows with gbar 47.8 -> 41.1 us at 2^24, all launches of a step.
+// ---------------------------------------------------------------------------------------------
+template <class T>
+struct Words {   // a float or double as 32-bit registers
+  static constexpr int N = sizeof(T) / 4;
+  uint32_t w[N];
+};
+// lanes 32..63 of x change places with lanes 0..31 of y
+template <class T>
+__device__ inline void swap_halves(T& x, T& y) {
+  Words<T> a = __builtin_bit_cast(Words<T>, x), b = __builtin_bit_cast(Words<T>, y);
 #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) x += __shfl_xor(x, off, 64);
-  return x;
+  for (int k = 0; k < Words<T>::N; ++k) {
+    const auto r = __builtin_amdgcn_permlane32_swap(a.w[k], b.w[k], false, false);
+    a.w[k] = r[0];
+    b.w[k] = r[1];
+  }
+  x = __builtin_bit_cast(T, a);
+  y = __builtin_bit_cast(T, b);
 }
-__device__ inline float wave_max(float x) {
+// in each half of the wave, lanes 16..31 of x change places with lanes 0..15 of y
+template <class T>
+__device__ inline void swap_rows(T& x, T& y) {
+  Words<T> a = __builtin_bit_cast(Words<T>, x), b = __builtin_bit_cast(Words<T>, y);
 #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) x = __builtin_fmaxf(x, __shfl_xor(x, off, 64));
-  return x;
+  for (int k = 0; k < Words<T>::N; ++k) {
+    const auto r = __builtin_amdgcn_permlane16_swap(a.w[k], b.w[k], false, false);
+    a.w[k] = r[0];
+    b.w[k] = r[1];
+  }
+  x = __builtin_bit_cast(T, a);
+  y = __builtin_bit_cast(T, b);
+}
+// x of the lane OFF further on in the row of 16 lanes (zero past its end)
+template <int OFF, class T>
+__device__ inline T ahead(T x) {
+  Words<T> a = __builtin_bit_cast(Words<T>, x);
+#pragma unroll
+  for (int k = 0; k < Words<T>::N; ++k) a.w[k] = __builtin_amdgcn_mov_dpp(a.w[k], 0x100 + OFF, 0xf, 0xf, true);
+  return __builtin_bit_cast(T, a);
+}
+// Totals of a, b, c, n over the wave, in the first lane of the first, third, second and fourth row of 16 lanes (lane_value).
+// ADD(x, y): x from the lower lanes.
+template <class T, class ADD>
+__device__ inline T wave_sum4(T a, T b, T c, T n, ADD add) {
+  swap_halves(a, b);
+  swap_halves(c, n);
+  T x = add(a, b), y = add(c, n);   // a in the lower half of x, b in the upper; c and n in y
+  swap_rows(x, y);
+  x = add(x, y);
+  x = add(x, ahead<8>(x));
+  x = add(x, ahead<4>(x));
+  x = add(x, ahead<2>(x));
+  return add(x, ahead<1>(x));
+}
+// which of the four totals the first lane of a row holds
+__device__ inline int lane_value(int lane) { return (lane >> 5) | (lane >> 3 & 2); }
+// largest x of the wave (x >= 0), in lane 0
+template <class T>
+__device__ inline T wave_max(T x) {
+  T y = x;
+  swap_halves(x, y);
+  y = x = __builtin_elementwise_max(x, y);
+  swap_rows(x, y);
+  x = __builtin_elementwise_max(x, y);
+  x = __builtin_elementwise_max(x, ahead<8>(x));
+  x = __builtin_elementwise_max(x, ahead<4>(x));
+  x = __builtin_elementwise_max(x, ahead<2>(x));
+  return __builtin_elementwise_max(x, ahead<1>(x));
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -361,24 +428,6 @@ __host__ __device__ inline void decide(const DecideParams& q, nt_result* r) {
   }
 }
 
-__device__ inline dd dd_wave_sum(dd x) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    dd y;
-    y.hi = __shfl_xor(x.hi, off, 64);
-    y.lo = __shfl_xor(x.lo, off, 64);
-    // both partners must form the same sum: order the operands by lane
-    const bool low = (threadIdx.x & off) == 0;
-    x = low ? dd_add(x, y) : dd_add(y, x);
-  }
-  return x;
-}
-__device__ inline double wave_max(double x) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) x = __builtin_fmax(x, __shfl_xor(x, off, 64));
-  return x;
-}
-
 // Running totals of partial records: the NT_NSUM sums in double-double and the largest ratio.
 struct Totals {
   dd s[NT_NSUM];
@@ -391,65 +440,77 @@ __device__ inline void totals_clear(Totals& t) {
 }
 
 // Adds this thread's share (entries threadIdx.x, threadIdx.x + THREADS, ...) of n records into acc.
-// packed = false: tile partials {A, B, C, n_fail, r_max}; packed = true: group partials
-// {A, A_lo, B, B_lo, C, C_lo, n, n_lo, r_max, unused}.
-template <int THREADS>
-__device__ inline void totals_accumulate(const double* in, int64_t n, bool packed, Totals& acc) {
-  for (int64_t t = threadIdx.x; t < n; t += THREADS) {
-    const double* rec = in + (packed ? 2 * NT_NV : NT_NV) * t;
+// PACKED = false: tile partials {A, B, C, n_fail, r_max}; PACKED = true: group partials
+// {A, A_lo, B, B_lo, C, C_lo, n, n_lo, r_max, unused}.  Tile partials are loaded up to eight rounds
+// at a time: one round after the other, 2048 records in a block of 256 threads wait for memory eight times (k_reduce_groups
+// 7.2 -> 4.5 us).  Group partials are few (one per 8M coordinates), so theirs are not.  What lies past the end reads as the
+// last record and counts as zeros, which change nothing.
+template <int THREADS, bool PACKED>
+__device__ inline void totals_accumulate(const double* in, int64_t n, Totals& acc) {
+  constexpr int BATCH = PACKED ? 1 : THREADS <= 256 ? 8 : 4;
+  constexpr int LEN = PACKED ? 2 * NT_NV : NT_NV, USED = PACKED ? 2 * NT_NSUM + 1 : NT_NV;
+  for (int64_t t0 = 0; t0 < n; t0 += BATCH * THREADS) {
+    double rec[BATCH][USED];
 #pragma unroll
-    for (int k = 0; k < NT_NSUM; ++k) {
-      dd x;
-      if (!packed) {
-        x.hi = rec[k];
-        x.lo = 0.0;
-      } else {
-        x.hi = rec[2 * k];
-        x.lo = rec[2 * k + 1];
+    for (int b = 0; b < BATCH; ++b) {
+      const int64_t t = t0 + b * THREADS + threadIdx.x;
+      if (t0 + b * THREADS < n) {
+#pragma unroll
+        for (int k = 0; k < USED; ++k) rec[b][k] = in[LEN * (t < n ? t : n - 1) + k];
       }
-      acc.s[k] = dd_add(acc.s[k], x);
     }
-    acc.mx = __builtin_fmax(acc.mx, rec[packed ? 2 * NT_NSUM : NT_NSUM]);
+#pragma unroll
+    for (int b = 0; b < BATCH; ++b) {
+      if (t0 + b * THREADS < n) {
+        const bool there = t0 + b * THREADS + threadIdx.x < n;
+#pragma unroll
+        for (int k = 0; k < NT_NSUM; ++k) {
+          const dd x = PACKED ? dd{rec[b][2 * k], rec[b][(2 * k + 1) % USED]} : dd{rec[b][k], 0.0};
+          acc.s[k] = dd_add(acc.s[k], there ? x : dd{0.0, 0.0});
+        }
+        acc.mx = __builtin_fmax(acc.mx, rec[b][USED - 1]);
+      }
+    }
   }
 }
 
 // Block total of the threads' accumulators; all threads take part, thread 0 returns the totals.
 template <int THREADS>
 __device__ inline void block_totals_finish(Totals& acc, double (*sh)[2 * NT_NV], Totals& tot) {
-#pragma unroll
-  for (int k = 0; k < NT_NSUM; ++k) acc.s[k] = dd_wave_sum(acc.s[k]);
-  acc.mx = wave_max(acc.mx);
+  static_assert(NT_NSUM == 4, "wave_sum4");
+  const dd x = wave_sum4(acc.s[0], acc.s[1], acc.s[2], acc.s[3], [](dd p, dd q) { return dd_add(p, q); });
+  const double mx = wave_max(acc.mx);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  if (lane == 0) {
-#pragma unroll
-    for (int k = 0; k < NT_NSUM; ++k) {
-      sh[wave][2 * k] = acc.s[k].hi;
-      sh[wave][2 * k + 1] = acc.s[k].lo;
-    }
-    sh[wave][2 * NT_NSUM] = acc.mx;
+  if ((lane & 15) == 0) {
+    sh[wave][2 * lane_value(lane)] = x.hi;
+    sh[wave][2 * lane_value(lane) + 1] = x.lo;
+    if (lane == 0) sh[wave][2 * NT_NSUM] = mx;
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
+  if (wave == 0) {
+    // the sums of the waves in their order, one of the four per lane, then all to thread 0
+    const int k = lane < NT_NSUM ? lane : 0;
+    dd t = {sh[0][2 * k], sh[0][2 * k + 1]};
+    double m = sh[0][2 * NT_NSUM];
 #pragma unroll
-    for (int k = 0; k < NT_NSUM; ++k) {
-      tot.s[k].hi = sh[0][2 * k];
-      tot.s[k].lo = sh[0][2 * k + 1];
-      for (int wv = 1; wv < THREADS / 64; ++wv) {
-        dd x = {sh[wv][2 * k], sh[wv][2 * k + 1]};
-        tot.s[k] = dd_add(tot.s[k], x);
-      }
+    for (int wv = 1; wv < THREADS / 64; ++wv) {
+      t = dd_add(t, dd{sh[wv][2 * k], sh[wv][2 * k + 1]});
+      m = __builtin_fmax(m, sh[wv][2 * NT_NSUM]);
     }
-    tot.mx = sh[0][2 * NT_NSUM];
-    for (int wv = 1; wv < THREADS / 64; ++wv) tot.mx = __builtin_fmax(tot.mx, sh[wv][2 * NT_NSUM]);
+    tot.s[0] = t;
+    tot.s[1] = ahead<1>(t);
+    tot.s[2] = ahead<2>(t);
+    tot.s[3] = ahead<3>(t);
+    tot.mx = m;
   }
 }
 
 // Sum of n records (layouts as in totals_accumulate); thread 0 returns the totals.
-template <int THREADS>
-__device__ inline void block_totals(const double* in, int64_t n, bool packed, double (*sh)[2 * NT_NV], Totals& tot) {
+template <int THREADS, bool PACKED>
+__device__ inline void block_totals(const double* in, int64_t n, double (*sh)[2 * NT_NV], Totals& tot) {
   Totals acc;
   totals_clear(acc);
-  totals_accumulate<THREADS>(in, n, packed, acc);
+  totals_accumulate<THREADS, PACKED>(in, n, acc);
   block_totals_finish<THREADS>(acc, sh, tot);
 }
 
@@ -515,32 +576,23 @@ struct LaneAcc {
 template <int BLOCK>
 __device__ inline void tile_reduce(const LaneAcc& acc, double (*red)[BLOCK / 64][NT_NV], int buf, double* partials,
                                    int64_t tile) {
-  const double a = wave_sum(acc.A), b = wave_sum(acc.B), c = wave_sum(acc.C), n = wave_sum((double)acc.nfail);
+  const double x = wave_sum4(acc.A, acc.B, acc.C, (double)acc.nfail, [](double p, double q) { return p + q; });
   const float r = wave_max(acc.rmax);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  if (lane == 0) {
-    red[buf][wave][0] = a;
-    red[buf][wave][1] = b;
-    red[buf][wave][2] = c;
-    red[buf][wave][3] = n;
-    red[buf][wave][4] = (double)r;
+  if ((lane & 15) == 0) {
+    red[buf][wave][lane_value(lane)] = x;
+    if (lane == 0) red[buf][wave][NT_NSUM] = (double)r;
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    double sa = red[buf][0][0], sb = red[buf][0][1], sc = red[buf][0][2], sn = red[buf][0][3], sr = red[buf][0][4];
+  if (threadIdx.x < NT_NV) {
+    // the waves in their order, one of the five values per lane
+    double t = red[buf][0][threadIdx.x];
 #pragma unroll
     for (int wv = 1; wv < BLOCK / 64; ++wv) {
-      sa += red[buf][wv][0];
-      sb += red[buf][wv][1];
-      sc += red[buf][wv][2];
-      sn += red[buf][wv][3];
-      sr = __builtin_fmax(sr, red[buf][wv][4]);
+      const double y = red[buf][wv][threadIdx.x];
+      t = threadIdx.x < NT_NSUM ? t + y : __builtin_fmax(t, y);
     }
-    partials[NT_NV * tile + 0] = sa;
-    partials[NT_NV * tile + 1] = sb;
-    partials[NT_NV * tile + 2] = sc;
-    partials[NT_NV * tile + 3] = sn;
-    partials[NT_NV * tile + 4] = sr;
+    partials[NT_NV * tile + threadIdx.x] = t;
   }
 }
 
@@ -1139,10 +1191,13 @@ __global__ __launch_bounds__(BLOCK) void k_step_end(StepParams p, int64_t nfull,
   if (slot0 == 0 && blockIdx.x == 0 && threadIdx.x == 0) {
     Totals tot;
     totals_clear(tot);
-    // the only tile's partial, which this thread has stored, added to zero as in k_finalize: the addition leaves finite sums
+    // the only tile's partial, which this wave has stored, added to zero as in k_finalize: the addition leaves finite sums
     // as they are and turns an infinite one into NaN, so sums that overflow (and the clipping factor, which is 1 then) read
     // the same whatever the number of tiles
-    if constexpr (MODE != MODE_ADAMW) totals_accumulate<1>(p.partials, 1, false, tot);
+    if constexpr (MODE != MODE_ADAMW) {
+      __threadfence_block();
+      totals_accumulate<1, false>(p.partials, 1, tot);
+    }
     write_record(tot, fin.q, fin.out, fin.hdr, fin.hdr_out);
   }
 }
@@ -1161,7 +1216,7 @@ __global__ __launch_bounds__(NT_GROUP_THREADS) void k_reduce_groups(const double
   const int64_t t0 = (int64_t)blockIdx.x * NT_GROUP_TILES;
   const int64_t n = (ntiles - t0 < NT_GROUP_TILES) ? (ntiles - t0) : NT_GROUP_TILES;
   Totals tot;
-  block_totals<NT_GROUP_THREADS>(tiles + NT_NV * t0, n, false, sh, tot);
+  block_totals<NT_GROUP_THREADS, false>(tiles + NT_NV * t0, n, sh, tot);
   if (threadIdx.x == 0) {
     double* rec = groups + 2 * NT_NV * (int64_t)blockIdx.x;
 #pragma unroll
@@ -1176,14 +1231,14 @@ __global__ __launch_bounds__(NT_GROUP_THREADS) void k_reduce_groups(const double
 
 // One block: partials (tile or group) -> A, B, C in double-double, then the decision.  THREADS: 1024, or 256 for
 // up to NT_FIN_SMALL records (short vectors, where this kernel's latency is a large part of the step).
-template <int THREADS>
-__global__ __launch_bounds__(THREADS) void k_finalize(const double* in, int64_t n, bool packed, DecideParams q,
-                                                      nt_result* out, WsRecord hdr, WsRecord* hdr_out) {
+template <int THREADS, bool PACKED>
+__global__ __launch_bounds__(THREADS) void k_finalize(const double* in, int64_t n, DecideParams q, nt_result* out,
+                                                      WsRecord hdr, WsRecord* hdr_out) {
   __shared__ double sh[THREADS / 64][2 * NT_NV];
   const bool stats = (q.flags & NT_DO_STATS) != 0;
   Totals tot;
   totals_clear(tot);
-  if (stats) block_totals<THREADS>(in, n, packed, sh, tot);
+  if (stats) block_totals<THREADS, PACKED>(in, n, sh, tot);
   if (threadIdx.x != 0) return;
   write_record(tot, q, out, hdr, hdr_out);
 }
@@ -1273,11 +1328,11 @@ __global__ __launch_bounds__(NT_LAYER_THREADS) void k_layer_stats(StepParams p, 
   const double* groups = tiles + NT_NV * h.ntiles;
   const int64_t g0 = (first + NT_GROUP_TILES - 1) / NT_GROUP_TILES, g1 = last / NT_GROUP_TILES;
   if (h.ngroups > 0 && g0 < g1) {
-    totals_accumulate<NT_LAYER_THREADS>(tiles + NT_NV * first, g0 * NT_GROUP_TILES - first, false, acc);
-    totals_accumulate<NT_LAYER_THREADS>(groups + 2 * NT_NV * g0, g1 - g0, true, acc);
-    totals_accumulate<NT_LAYER_THREADS>(tiles + NT_NV * g1 * NT_GROUP_TILES, last - g1 * NT_GROUP_TILES, false, acc);
+    totals_accumulate<NT_LAYER_THREADS, false>(tiles + NT_NV * first, g0 * NT_GROUP_TILES - first, acc);
+    totals_accumulate<NT_LAYER_THREADS, true>(groups + 2 * NT_NV * g0, g1 - g0, acc);
+    totals_accumulate<NT_LAYER_THREADS, false>(tiles + NT_NV * g1 * NT_GROUP_TILES, last - g1 * NT_GROUP_TILES, acc);
   } else {
-    totals_accumulate<NT_LAYER_THREADS>(tiles + NT_NV * first, last - first, false, acc);
+    totals_accumulate<NT_LAYER_THREADS, false>(tiles + NT_NV * first, last - first, acc);
   }
   Totals tot;
   block_totals_finish<NT_LAYER_THREADS>(acc, sh, tot);
@@ -1653,13 +1708,13 @@ hipError_t launch_step_mode(int mode, const StepParams& p, int cls, int64_t nful
 
 inline bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 
-inline void launch_finalize(const double* in, int64_t n, bool packed, const DecideParams& q, nt_result* out,
-                            const WsRecord& hdr, WsRecord* hdr_out, hipStream_t st) {
+template <bool PACKED>
+inline void launch_finalize(const double* in, int64_t n, const DecideParams& q, nt_result* out, const WsRecord& hdr,
+                            WsRecord* hdr_out, hipStream_t st) {
   if (n <= NT_FIN_SMALL)
-    hipLaunchKernelGGL(k_finalize<256>, dim3(1), dim3(256), 0, st, in, n, packed, q, out, hdr, hdr_out);
+    hipLaunchKernelGGL((k_finalize<256, PACKED>), dim3(1), dim3(256), 0, st, in, n, q, out, hdr, hdr_out);
   else
-    hipLaunchKernelGGL(k_finalize<NT_FIN_THREADS>, dim3(1), dim3(NT_FIN_THREADS), 0, st, in, n, packed, q, out, hdr,
-                       hdr_out);
+    hipLaunchKernelGGL((k_finalize<NT_FIN_THREADS, PACKED>), dim3(1), dim3(NT_FIN_THREADS), 0, st, in, n, q, out, hdr, hdr_out);
 }
 
 }  // namespace
@@ -1814,9 +1869,9 @@ static int enqueue_step(const void* grads, bool table, nt_dtype gdtype, int64_t 
     hipLaunchKernelGGL(k_reduce_groups, dim3((unsigned)ngroups), dim3(NT_GROUP_THREADS), 0, st, partials, ntiles, groups);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_code(e);
-    launch_finalize(groups, ngroups, true, q, result_dev, record, hdr_out, st);
+    launch_finalize<true>(groups, ngroups, q, result_dev, record, hdr_out, st);
   } else {
-    launch_finalize(partials, ntiles, false, q, result_dev, record, hdr_out, st);
+    launch_finalize<false>(partials, ntiles, q, result_dev, record, hdr_out, st);
   }
   return hip_code(hipGetLastError());
 }
