@@ -19,7 +19,8 @@
  * fp32 state.  Between those limits results are scale-invariant to the stated tolerances.
  *
  * All pointers named "device" must be dereferenceable by the GPU (device memory; result may also be
- * pinned host memory).  The library allocates nothing, keeps no state between calls, never
+ * pinned host memory).  The library allocates nothing, keeps nothing of one call for the next
+ * (its launches count their blocks in counters of its own on the device, which every launch leaves at zero), never
  * synchronises the device and never touches host copies of the data: it validates, enqueues kernels
  * on the caller's stream and returns.  No C++ types or exceptions cross this boundary.
  */
@@ -160,7 +161,8 @@ size_t normtest_workspace_bytes_for(nt_dtype gdtype, int64_t J, int64_t d, uint3
  * has synchronised it.  A call enqueues kernel launches only (no memsets, copies or allocations): a long vector
  * is walked by several launches of the same kernel over consecutive runs of tiles (about one per 1.3e8
  * coordinates up to 16 rows, one per 8e6 beyond; the memory system serves blocks that start together faster),
- * followed by one or two small reduction kernels (none after AdamW only, or where a matrix's rows are one tile); results do not depend on how many launches there were.  Any element-aligned pointer and
+ * followed by one or two small reduction kernels (none after AdamW only, or with few tiles outside graph capture: up to
+ * 2^20 coordinates, 2^18 beyond 16 rows); results do not depend on how many launches there were.  Any element-aligned pointer and
  * any row stride is accepted: the kernels access rows, w, m, v and gbar_out with the same vector instructions whatever
  * the alignment, with bit-identical results.  d == 0 succeeds (sums are 0).
  * AdamW is fused into the same pass: it has been applied even if status reports NONFINITE.

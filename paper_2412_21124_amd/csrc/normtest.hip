@@ -3,7 +3,7 @@
 // One streaming kernel (k_step) reads the J gradient rows and w, m, v once, writes w, m, v once and
 // leaves five fp64 values per fixed-size tile of coordinates (the sums A, B, C, the count of coordinates
 // failing the coordinate-wise form of the test, and their largest ratio); k_reduce_groups / k_finalize then add
-// the tile partials in double-double arithmetic and take Alg. 1's decision on the device (steps of one tile, and AdamW only,
+// the tile partials in double-double arithmetic and take Alg. 1's decision on the device (steps of few tiles, and AdamW only,
 // need no second kernel: k_step_end).  The partials stay in the caller's workspace
 // behind a small record of the step, from which k_layer_stats can regroup them into a per-layer table.
 // k_adamw_gbar is the second phase of the gradient-clipped variant.  The
@@ -95,7 +95,16 @@
 #define NT_MCHUNK 16          // beyond that, rows are walked this many at a time (2 .. NT_JCHUNK + 1; 16 measured best)
 #define NT_ROUND_TO_MAX (1ll << 31)  // bound on nt_hyper.round_to that keeps the rounding chain inside int64
 #define NT_FIN_THREADS 1024
-#define NT_FIN_SMALL 4096       // up to this many records the finalize kernel runs with 256 threads
+#define NT_FIN_SMALL 4096       // up to this many records the finalize kernel runs with ...
+#define NT_FIN_SHORT 256        // ... this many threads
+// Up to this many tiles a step's own last block adds up the tile partials (k_step_end), in one launch instead of two (3.7 us of
+// host time).  Device time of the step, one launch against two: 4 fp32 rows 6.8 / 8.5 us at d = 5000 and 7.2 / 8.5 at 2^18,
+// read-only statistics of 8 bf16 rows 5.7 / 8.0 and 6.9 / 8.3; at 2^20 (256 tiles) 10.8 / 10.5 and 8.9 / 8.6, at 2^21 19.1 / 18.2:
+// the more blocks end together, the longer they queue at the counter, and the host is ahead of the device by then.  More than
+// 16 rows (twice the tiles, longer kernels): 64 rows 13.6 / 14.4 at d = 5000, 17.9 / 18.1 at 2^18 (128 tiles), statistics 12.9 /
+// 13.8 and 16.1 / 15.9, at 2^20 29.8 / 28.2.
+#define NT_TICKET_TILES 256
+#define NT_TICKET_TILES_MANY 128
 #define NT_NSUM 4              // summed values per tile partial: A, B, C and the count of failing coordinates
 #define NT_NV 5                // values per tile partial: the sums, then the largest coordinate-wise ratio
 #define NT_GROUP_THREADS 256   // first-stage reduction: threads per block
@@ -109,6 +118,12 @@
 // cannot hand over (or allocate) a workspace.  One copy per GPU, held until the process ends.
 #define NT_SCRATCH_BYTES (16u << 20)
 static __device__ __align__(256) unsigned char scratch[NT_SCRATCH_BYTES];
+
+// Counters with which the blocks of a launch find out which of them comes last (tile_reduce).  Zero when the library is loaded,
+// and every launch leaves the one it was given at zero.  A call takes the next one in turn, so two launches can only share one
+// if a whole round of calls lies between them while both run: more launches than a device's queues hold (32 of 16384 packets).
+#define NT_TICKETS (1u << 20)
+static __device__ uint32_t tickets[NT_TICKETS];
 
 namespace {
 
@@ -474,14 +489,15 @@ __device__ inline void totals_accumulate(const double* in, int64_t n, Totals& ac
   }
 }
 
-// Block total of the threads' accumulators; all threads take part, thread 0 returns the totals.
+// Total of the accumulators of the block's first THREADS threads (whole waves); all threads of the block take part, thread 0
+// returns the totals.
 template <int THREADS>
 __device__ inline void block_totals_finish(Totals& acc, double (*sh)[2 * NT_NV], Totals& tot) {
   static_assert(NT_NSUM == 4, "wave_sum4");
   const dd x = wave_sum4(acc.s[0], acc.s[1], acc.s[2], acc.s[3], [](dd p, dd q) { return dd_add(p, q); });
   const double mx = wave_max(acc.mx);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  if ((lane & 15) == 0) {
+  if (wave < THREADS / 64 && (lane & 15) == 0) {
     sh[wave][2 * lane_value(lane)] = x.hi;
     sh[wave][2 * lane_value(lane) + 1] = x.lo;
     if (lane == 0) sh[wave][2 * NT_NSUM] = mx;
@@ -505,12 +521,13 @@ __device__ inline void block_totals_finish(Totals& acc, double (*sh)[2 * NT_NV],
   }
 }
 
-// Sum of n records (layouts as in totals_accumulate); thread 0 returns the totals.
+// Sum of n records (layouts as in totals_accumulate) by the block's first THREADS threads, in an order that does not depend on
+// the block's size; thread 0 returns the totals.
 template <int THREADS, bool PACKED>
 __device__ inline void block_totals(const double* in, int64_t n, double (*sh)[2 * NT_NV], Totals& tot) {
   Totals acc;
   totals_clear(acc);
-  totals_accumulate<THREADS, PACKED>(in, n, acc);
+  if (threadIdx.x < THREADS) totals_accumulate<THREADS, PACKED>(in, n, acc);
   block_totals_finish<THREADS>(acc, sh, tot);
 }
 
@@ -552,12 +569,13 @@ __device__ inline void write_record(const Totals& tot, const DecideParams& q, nt
   *out = r;
 }
 
-// What a step takes along that needs no reduction kernel: AdamW only (no sums), or a vector of a single tile.
+// What a step takes along whose own kernel writes the result.
 struct Finish {
   DecideParams q;
   WsRecord hdr;
   WsRecord* hdr_out;
-  nt_result* out;   // null: k_finalize follows
+  nt_result* out;     // null: k_finalize follows
+  uint32_t* ticket;   // steps of more than one tile: where its blocks count themselves
 };
 
 // ---------------------------------------------------------------------------------------------
@@ -571,11 +589,22 @@ struct LaneAcc {
   float rmax = 0.f;
 };
 
+// What the first wave of a block keeps of its tile's end in a step that writes its own result: its lane's value of the tile
+// partial and, in lane 0, how many blocks had counted themselves before.
+struct TileEnd {
+  double value;
+  uint32_t before;
+};
+
 // Block partial of one tile -> partials[NT_NV*tile ..].  `buf` alternates between tiles so that one
 // barrier per tile is enough.
-template <int BLOCK>
-__device__ inline void tile_reduce(const LaneAcc& acc, double (*red)[BLOCK / 64][NT_NV], int buf, double* partials,
-                                   int64_t tile) {
+// END: the launch has a block per tile and its last one adds up the partials (k_step_end).  The partial then goes through this
+// XCD's L2 to memory, and once it is there the block counts itself.  Both accesses are relaxed on purpose: a release would
+// write back all of the L2, in every block.  Nobody waits for another block; the state, if any, is stored after the counting, so
+// that its way to memory is not waited for.
+template <int BLOCK, bool END>
+__device__ inline TileEnd tile_reduce(const LaneAcc& acc, double (*red)[BLOCK / 64][NT_NV], int buf, double* partials,
+                                      int64_t tile, uint32_t* ticket) {
   const double x = wave_sum4(acc.A, acc.B, acc.C, (double)acc.nfail, [](double p, double q) { return p + q; });
   const float r = wave_max(acc.rmax);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -584,6 +613,7 @@ __device__ inline void tile_reduce(const LaneAcc& acc, double (*red)[BLOCK / 64]
     if (lane == 0) red[buf][wave][NT_NSUM] = (double)r;
   }
   __syncthreads();
+  TileEnd end = {0.0, 0};
   if (threadIdx.x < NT_NV) {
     // the waves in their order, one of the five values per lane
     double t = red[buf][0][threadIdx.x];
@@ -592,8 +622,19 @@ __device__ inline void tile_reduce(const LaneAcc& acc, double (*red)[BLOCK / 64]
       const double y = red[buf][wv][threadIdx.x];
       t = threadIdx.x < NT_NSUM ? t + y : __builtin_fmax(t, y);
     }
-    partials[NT_NV * tile + threadIdx.x] = t;
+    double* const to = partials + NT_NV * tile + threadIdx.x;
+    if constexpr (END) {
+      end.value = t;
+      __hip_atomic_store(to, t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (ticket) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if (threadIdx.x == 0) end.before = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+    } else {
+      *to = t;
+    }
   }
+  return end;
 }
 
 // Coordinate-wise form of the test (Sec. 4, Prop. 1): with thr = eta^2 b_k (J - ddof), a coordinate with centred
@@ -903,11 +944,15 @@ __device__ inline void sweep_rows(const StepParams& p, const typename GT::raw_t*
 constexpr bool pin_loads(int esize, int J, bool coord) { return !coord && (J == 15 || (J == 11 && esize == 4)); }
 
 // State update interleaved with the rows: each sweep reads its rows and w, m, v, and writes the state back.
-template <class GT, int J, int MODE, int BLOCK, int ITERS, bool TABLE, bool GBAR, bool COORD, bool PART>
-__device__ inline void tile_rows(const StepParams& p, int64_t tile, double (*red)[BLOCK / 64][NT_NV], int buf) {
+template <class GT, int J, int MODE, int BLOCK, int ITERS, bool TABLE, bool GBAR, bool COORD, bool PART, bool END>
+__device__ inline TileEnd tile_rows(const StepParams& p, int64_t tile, double (*red)[BLOCK / 64][NT_NV], int buf,
+                                    uint32_t* ticket) {
   constexpr int VEC = GT::VEC;
   constexpr int TILE = BLOCK * VEC * ITERS;
+  constexpr bool EARLY = END && MODE == MODE_FULL;   // the sums are handed on before the state is stored
+  static_assert(!EARLY || ITERS == 1, "the sums are complete after the only sweep");
   LaneAcc acc;
+  TileEnd end = {0.0, 0};
   // a statistics-only sweep with few rows has little in flight per lane: overlap sweeps up to about 64 bytes (read-only,
   // 128 bytes are 35 % slower at 4 bf16 rows), and where gbar is stored two sweeps of 64 bytes (8 bf16 rows, d = 2e8: 656
   // -> 630 us; 4 fp32 rows 674 -> 650; two sweeps of 40 or 48 bytes are 10 and 4 % slower than one)
@@ -932,13 +977,15 @@ __device__ inline void tile_rows(const StepParams& p, int64_t tile, double (*red
     }
     float gb[VEC];
     sweep_rows<GT, J, MODE, COORD>(p, raw, gb, acc);
+    if constexpr (EARLY) end = tile_reduce<BLOCK, true>(acc, red, buf, p.partials, tile, ticket);
     if constexpr (MODE != MODE_STATS) adamw_store<PART>(p, pl, n, gb, state);
     if (GBAR && p.gbar) store4<PART>(p.gbar, pl, n, f32x4{gb[0], gb[1], gb[2], gb[3]});
   }
-  if constexpr (MODE != MODE_ADAMW) tile_reduce<BLOCK>(acc, red, buf, p.partials, tile);
+  if constexpr (MODE != MODE_ADAMW && !EARLY) end = tile_reduce<BLOCK, END>(acc, red, buf, p.partials, tile, ticket);
   // AdamW-only tiles end with a block barrier like the other modes: the waves of a block then finish together
   // and the next block's waves start together (measured +2 %)
   if constexpr (MODE == MODE_ADAMW) __syncthreads();
+  return end;
 }
 
 template <int MODE, int BLOCK, int ITERS, bool GBAR, bool PART>
@@ -965,14 +1012,15 @@ __device__ inline void deferred_sweeps(const StepParams& p, int64_t tile, const 
 // row has been read, then w, m, v of all sweeps are read and written in one go.  The memory system charges writes
 // sprinkled among reads several times their volume; gathered at the end of a block's life, and with all blocks
 // of a launch living at the same time (one generation per launch), they reach it as a dense burst.
-template <int MODE, int BLOCK, int ITERS, bool GBAR, bool PART>
-__device__ inline void deferred_update(const StepParams& p, int64_t tile, double (*red)[BLOCK / 64][NT_NV], int buf,
-                                       const LaneAcc& acc, const f32x4* gbs) {
+template <int MODE, int BLOCK, int ITERS, bool GBAR, bool PART, bool END>
+__device__ inline TileEnd deferred_update(const StepParams& p, int64_t tile, double (*red)[BLOCK / 64][NT_NV], int buf,
+                                          const LaneAcc& acc, const f32x4* gbs, uint32_t* ticket) {
   constexpr int VEC = 4;
   constexpr int TILE = BLOCK * VEC * ITERS;
   // the barrier inside keeps the waves of the block together on their way into the write phase
+  TileEnd end = {0.0, 0};
   if constexpr (MODE != MODE_ADAMW)
-    tile_reduce<BLOCK>(acc, red, buf, p.partials, tile);
+    end = tile_reduce<BLOCK, END>(acc, red, buf, p.partials, tile, ticket);
   else
     __syncthreads();
   if (MODE != MODE_STATS || p.gbar) {
@@ -982,6 +1030,7 @@ __device__ inline void deferred_update(const StepParams& p, int64_t tile, double
     else
       deferred_sweeps<MODE, BLOCK, ITERS, GBAR, true>(p, tile, gbs);
   }
+  return end;
 }
 
 // Deferred state update, rows in registers: the sweeps read rows only.
@@ -1002,7 +1051,7 @@ __device__ inline void tile_defer(const StepParams& p, int64_t tile, double (*re
     sweep_rows<GT, J, MODE, true>(p, raw, gb, acc);
     gbs[it * BLOCK + threadIdx.x] = f32x4{gb[0], gb[1], gb[2], gb[3]};
   }
-  deferred_update<MODE, BLOCK, ITERS, GBAR, PART>(p, tile, red, buf, acc, gbs);
+  deferred_update<MODE, BLOCK, ITERS, GBAR, PART, false>(p, tile, red, buf, acc, gbs, nullptr);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1049,9 +1098,9 @@ __device__ inline void accumulate_last(int nb, const typename GT::raw_t* raw, co
 
 // The state update (and the gbar store) of a tile is deferred (see deferred_update): with many rows the writes are
 // a few per cent of the traffic.
-template <class GT, int MODE, int BLOCK, int ITERS, bool TABLE, bool GBAR, bool PART>
-__device__ inline void tile_multi(const StepParams& p, int64_t tile, double (*red)[BLOCK / 64][NT_NV], int buf,
-                                       f32x4* gbs) {
+template <class GT, int MODE, int BLOCK, int ITERS, bool TABLE, bool GBAR, bool PART, bool END>
+__device__ inline TileEnd tile_multi(const StepParams& p, int64_t tile, double (*red)[BLOCK / 64][NT_NV], int buf, f32x4* gbs,
+                                     uint32_t* ticket) {
   constexpr int VEC = GT::VEC;
   static_assert(VEC == 4, "one 16-byte LDS slot per lane and sweep");
   constexpr int TILE = BLOCK * VEC * ITERS;
@@ -1112,9 +1161,9 @@ __device__ inline void tile_multi(const StepParams& p, int64_t tile, double (*re
     if constexpr (WRITES) gbs[it * BLOCK + threadIdx.x] = f32x4{gb[0], gb[1], gb[2], gb[3]};
   }
   if constexpr (WRITES)
-    deferred_update<MODE, BLOCK, ITERS, GBAR, PART>(p, tile, red, buf, acc, gbs);
+    return deferred_update<MODE, BLOCK, ITERS, GBAR, PART, END>(p, tile, red, buf, acc, gbs, ticket);
   else
-    tile_reduce<BLOCK>(acc, red, buf, p.partials, tile);
+    return tile_reduce<BLOCK, END>(acc, red, buf, p.partials, tile, ticket);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1123,14 +1172,18 @@ __device__ inline void tile_multi(const StepParams& p, int64_t tile, double (*re
 // ntiles - 1), that one has slot 0, so that its few element-sized accesses overlap with everything else.
 // J_T = 0 selects the J > 16 row-walking variant.
 // ---------------------------------------------------------------------------------------------
-template <class GT, int J_T, int MODE, int BLOCK, int ITERS, bool TABLE, bool GBAR, bool DEFER_T, bool COORD, bool PART>
-__device__ inline void run_tile(const StepParams& p, int64_t tile, double (*red)[BLOCK / 64][NT_NV], int buf, f32x4* gbs) {
-  if constexpr (J_T == 0)
-    tile_multi<GT, MODE, BLOCK, ITERS, TABLE, GBAR, PART>(p, tile, red, buf, gbs);
-  else if constexpr (DEFER_T)
+template <class GT, int J_T, int MODE, int BLOCK, int ITERS, bool TABLE, bool GBAR, bool DEFER_T, bool COORD, bool PART, bool END>
+__device__ inline TileEnd run_tile(const StepParams& p, int64_t tile, double (*red)[BLOCK / 64][NT_NV], int buf, f32x4* gbs,
+                                   uint32_t* ticket) {
+  if constexpr (J_T == 0) {
+    return tile_multi<GT, MODE, BLOCK, ITERS, TABLE, GBAR, PART, END>(p, tile, red, buf, gbs, ticket);
+  } else if constexpr (DEFER_T) {
+    static_assert(!END || MODE == MODE_ADAMW, "steps with sums that write their own result are not in this class");
     tile_defer<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, PART>(p, tile, red, buf, gbs);
-  else
-    tile_rows<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, COORD, PART>(p, tile, red, buf);
+    return {0.0, 0};
+  } else {
+    return tile_rows<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, COORD, PART, END>(p, tile, red, buf, ticket);
+  }
 }
 
 // More than 16 rows: which of a kernel's whole tiles run a copy of the walk without the part branch instead of the copy that
@@ -1150,8 +1203,9 @@ __device__ inline bool whole_copy(int J) {
 // GBAR = false compiles the gbar store out (statistics-only launch class, so that sweeps can overlap).
 // DEFER_T: up to 16 rows with the state update deferred to the end of the tile (always so beyond 16 rows).
 // COORD = false compiles the coordinate-wise test out (see plain_stats).
-template <class GT, int J_T, int MODE, int BLOCK, int ITERS, bool TABLE, bool GBAR, bool DEFER_T, bool COORD>
-__device__ inline void walk_tiles(const StepParams& p, int64_t nfull, int64_t ntiles, int64_t slot0, int64_t slot1) {
+template <class GT, int J_T, int MODE, int BLOCK, int ITERS, bool TABLE, bool GBAR, bool DEFER_T, bool COORD, bool END>
+__device__ inline TileEnd walk_tiles(const StepParams& p, int64_t nfull, int64_t ntiles, int64_t slot0, int64_t slot1,
+                                     uint32_t* ticket) {
   constexpr int TILE = BLOCK * GT::VEC * ITERS;
   static_assert(NT_TILE_MAX % TILE == 0, "tile sizes must divide NT_TILE_MAX");
   __shared__ double red[2][BLOCK / 64][NT_NV];
@@ -1160,46 +1214,70 @@ __device__ inline void walk_tiles(const StepParams& p, int64_t nfull, int64_t nt
   static_assert(!DEFER_T || DEFER, "a deferred update needs something to write");
   __shared__ f32x4 gbs[DEFER ? ITERS * BLOCK + NT_LDS_PAD_LARGE / 16 : 1];
   int buf = 0;
+  TileEnd end = {0.0, 0};
   const int64_t npart = ntiles - nfull;  // 0 or 1
   for (int64_t t = slot0 + blockIdx.x; t < slot1; t += gridDim.x) {
     // rotate: the part tile (if any) first, then the whole tiles 0..nfull-1
     const bool part = t < npart;
     const int64_t tile = part ? nfull : t - npart;
     if (!part && (J_T > 0 || whole_copy<GT, MODE, BLOCK, ITERS, TABLE>(p.J)))
-      run_tile<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, DEFER_T, COORD, false>(p, tile, red, buf, gbs);
+      end = run_tile<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, DEFER_T, COORD, false, END>(p, tile, red, buf, gbs, ticket);
     else
-      run_tile<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, DEFER_T, COORD, true>(p, tile, red, buf, gbs);
+      end = run_tile<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, DEFER_T, COORD, true, END>(p, tile, red, buf, gbs, ticket);
+    if (END && MODE != MODE_ADAMW) break;   // a block per tile
     buf ^= 1;
   }
+  return end;
 }
 
 template <class GT, int J_T, int MODE, int BLOCK, int ITERS, bool TABLE, bool GBAR, bool DEFER_T = false, bool COORD = true>
 __global__ __launch_bounds__(BLOCK) void k_step(StepParams p, int64_t nfull, int64_t ntiles, int64_t slot0, int64_t slot1) {
-  walk_tiles<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, DEFER_T, COORD>(p, nfull, ntiles, slot0, slot1);
+  walk_tiles<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, DEFER_T, COORD, false>(p, nfull, ntiles, slot0, slot1, nullptr);
 }
 
-// A step that writes its result itself: AdamW only, which has no sums, or a single tile, whose partial is the total.  A
-// second kernel costs such a call 3.7 us on the host and some 4 on the GPU (steps back to back: 4 fp32 rows, d = 1000,
-// 9.5 -> 6.2 us; AdamW only, 8 bf16 rows, d = 1e6, 8.7 -> 6.8 us).  It is a kernel of its own because this tail in every
-// kernel slows the long steps by 0.3 to 1 %.  Steps of more tiles keep their reduction kernels: a handshake between blocks
-// needs a device-wide acquire in each, since the XCDs' L2s hand out stale partials otherwise, and that is dearer than a
-// launch (4 fp32 rows, d = 2^20: 17.6 us against 13.2).
+// A step that writes its result itself: AdamW only, which has no sums; a single tile, whose partial is the total; or a few
+// tiles, a block each, of which the last to finish adds up the partials in k_finalize's order.  A second kernel costs such a
+// call 3.7 us on the host and some 2 on the GPU.  It is a kernel of its own because this tail in every kernel slows the long
+// steps by 0.3 to 1 %.  What makes the handshake between blocks cheap is that it neither releases nor waits: see tile_reduce.
+// (With marks beside the partials, which each block looks at after an agent-wide acquire of its own, the step of 256 tiles took
+// 17.6 us against 13.2 for two launches at the time.)
 template <class GT, int J_T, int MODE, int BLOCK, int ITERS, bool TABLE, bool GBAR, bool DEFER_T = false>
 __global__ __launch_bounds__(BLOCK) void k_step_end(StepParams p, int64_t nfull, int64_t ntiles, int64_t slot0,
                                                     int64_t slot1, Finish fin) {
-  walk_tiles<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, DEFER_T, true>(p, nfull, ntiles, slot0, slot1);
-  if (slot0 == 0 && blockIdx.x == 0 && threadIdx.x == 0) {
-    Totals tot;
-    totals_clear(tot);
-    // the only tile's partial, which this wave has stored, added to zero as in k_finalize: the addition leaves finite sums
-    // as they are and turns an infinite one into NaN, so sums that overflow (and the clipping factor, which is 1 then) read
-    // the same whatever the number of tiles
-    if constexpr (MODE != MODE_ADAMW) {
-      __threadfence_block();
-      totals_accumulate<1, false>(p.partials, 1, tot);
+  const TileEnd end = walk_tiles<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, DEFER_T, true, true>(p, nfull, ntiles, slot0, slot1,
+                                                                                               fin.ticket);
+  Totals tot;
+  totals_clear(tot);
+  if constexpr (MODE == MODE_ADAMW) {
+    if (slot0 != 0 || blockIdx.x != 0) return;
+  } else if (!fin.ticket) {
+    // the only tile's partial, added to zero as in k_finalize: the addition leaves finite sums as they are and turns an
+    // infinite one into NaN, so sums that overflow (and the clipping factor, which is 1 then) read the same whatever the
+    // number of tiles
+    const dd t = dd_add(dd{0.0, 0.0}, dd{end.value, 0.0});
+    tot.s[0] = t;
+    tot.s[1] = ahead<1>(t);
+    tot.s[2] = ahead<2>(t);
+    tot.s[3] = ahead<3>(t);
+    tot.mx = ahead<4>(end.value);
+  } else {
+    // The last block to count itself finds every partial in memory; it invalidates its caches, which may hold older ones, and
+    // leaves the counter as it was given.
+    __shared__ bool last;
+    __shared__ double sh[NT_FIN_SHORT / 64][2 * NT_NV];
+    if (threadIdx.x == 0) {
+      const bool me = end.before == (uint32_t)ntiles - 1;
+      if (me) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        __hip_atomic_store(fin.ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+      last = me;
     }
-    write_record(tot, fin.q, fin.out, fin.hdr, fin.hdr_out);
+    __syncthreads();
+    if (!last) return;
+    block_totals<NT_FIN_SHORT, false>(p.partials, ntiles, sh, tot);
   }
+  if (threadIdx.x == 0) write_record(tot, fin.q, fin.out, fin.hdr, fin.hdr_out);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1577,15 +1655,14 @@ constexpr auto step_kernel() {
   else
     return k_step<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, DEFER_T>;
 }
-// ONE_TILE: the class that vectors of a single tile take.  Of those, matrices have a kernel that writes the result; pointer
-// tables of one tile keep the two kernels, as the 33 further kernels per dtype would serve only calls of at most 4096
-// coordinates whose rows are allocations of their own (not built, so not measured either).  Returns whether the launched kernel writes
-// the result when it is the step's last: the caller's only source for that, so that no step can end without a result.
-template <class GT, int J_T, int MODE, int BLOCK, int ITERS, bool TABLE, bool GBAR, bool ONE_TILE, bool DEFER_T = false,
+// FEW_TILES: the class that vectors of one or a few tiles take; it has kernels that write the result (with the coordinate-wise
+// test, whether it is asked for or not: up to 2^20 coordinates it costs nothing measurable).  Returns whether the launched
+// kernel writes the result when it is the step's last: the caller's only source for that, so that no step can end without one.
+template <class GT, int J_T, int MODE, int BLOCK, int ITERS, bool TABLE, bool GBAR, bool FEW_TILES, bool DEFER_T = false,
           bool COORD = true>
 bool launch_tiles_of(const StepParams& p, int64_t nfull, int64_t ntiles, int64_t slot0, int64_t slot1, const Finish& fin,
                      unsigned grid, hipStream_t st) {
-  if constexpr (MODE == MODE_ADAMW || (ONE_TILE && !TABLE)) {
+  if constexpr (MODE == MODE_ADAMW || FEW_TILES) {
     if (fin.out) {
       hipLaunchKernelGGL((k_step_end<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, DEFER_T>), dim3(grid), dim3(BLOCK), 0, st, p,
                          nfull, ntiles, slot0, slot1, fin);
@@ -1712,7 +1789,7 @@ template <bool PACKED>
 inline void launch_finalize(const double* in, int64_t n, const DecideParams& q, nt_result* out, const WsRecord& hdr,
                             WsRecord* hdr_out, hipStream_t st) {
   if (n <= NT_FIN_SMALL)
-    hipLaunchKernelGGL((k_finalize<256, PACKED>), dim3(1), dim3(256), 0, st, in, n, q, out, hdr, hdr_out);
+    hipLaunchKernelGGL((k_finalize<NT_FIN_SHORT, PACKED>), dim3(1), dim3(NT_FIN_SHORT), 0, st, in, n, q, out, hdr, hdr_out);
   else
     hipLaunchKernelGGL((k_finalize<NT_FIN_THREADS, PACKED>), dim3(1), dim3(NT_FIN_THREADS), 0, st, in, n, q, out, hdr, hdr_out);
 }
@@ -1784,6 +1861,41 @@ static int check_step_args(const void* grads, nt_dtype gdtype, int64_t J, int64_
   return NT_OK;
 }
 
+// Address of this device's copy of `scratch` or `tickets`, looked up once per device (the array's name is only a host-side
+// handle of the symbol; kernels, copies and fills take this pointer).
+typedef void* PerDevice[64];
+static int device_address(const void* symbol, PerDevice& cached, void** out) {
+  int dev = 0;
+  const hipError_t e0 = hipGetDevice(&dev);
+  if (e0 != hipSuccess) return hip_code(e0);
+  if (dev < 0 || dev >= 64) return NT_ERR_UNSUPPORTED;
+  void* ptr = __atomic_load_n(&cached[dev], __ATOMIC_ACQUIRE);
+  if (!ptr) {
+    const hipError_t e = hipGetSymbolAddress(&ptr, symbol);
+    if (e != hipSuccess) return hip_code(e);
+    if (!ptr) return NT_ERR_UNSUPPORTED;
+    __atomic_store_n(&cached[dev], ptr, __ATOMIC_RELEASE);
+  }
+  *out = ptr;
+  return NT_OK;
+}
+
+// The next counter of this device, or false where there is none for this launch: a graph under capture would keep it and
+// replay beside a later call that is given the same one.
+static bool next_ticket(hipStream_t st, uint32_t** out) {
+  static PerDevice cached = {nullptr};
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  void* base = nullptr;
+  if (hipStreamIsCapturing(st, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone ||
+      device_address(HIP_SYMBOL(tickets), cached, &base) != NT_OK) {
+    (void)hipGetLastError();
+    return false;
+  }
+  static uint32_t turn = 0;
+  *out = (uint32_t*)base + __atomic_fetch_add(&turn, 1u, __ATOMIC_RELAXED) % NT_TICKETS;
+  return true;
+}
+
 // Enqueue the streaming kernel and the reduction/decision kernels.  Arguments are already validated.
 // `table`: grads is a device array of J row pointers instead of the first row of a strided matrix.
 // `d_whole`: length of the vector these d coordinates are a part of (d itself for a call that stands alone).
@@ -1843,7 +1955,8 @@ static int enqueue_step(const void* grads, bool table, nt_dtype gdtype, int64_t 
   if (ntiles > 0) {
     Finish fin;
     std::memset(&fin, 0, sizeof(fin));
-    if (mode == MODE_ADAMW || ntiles == 1) {   // no sums, or one partial that is the total: launch_tiles_of has the kernels
+    // no sums, one partial that is the total, or few enough for the last block: launch_tiles_of has the kernels
+    if (mode == MODE_ADAMW || ntiles == 1 || (ntiles <= (J <= NT_JCHUNK ? NT_TICKET_TILES : NT_TICKET_TILES_MANY) && next_ticket(st, &fin.ticket))) {
       fin.q = q;
       fin.hdr = record;
       fin.hdr_out = hdr_out;
@@ -1938,25 +2051,6 @@ int normtest_step_rows(const void* const* grad_rows_dev, nt_dtype gdtype, int64_
                              (hipStream_t)hip_stream);
 }
 
-// Address of this device's copy of `scratch`, looked up once per device (the array's name is only a host-side
-// handle of the symbol; kernels, copies and fills take this pointer).
-static int scratch_address(void** out) {
-  static void* cached[64] = {nullptr};
-  int dev = 0;
-  const hipError_t e0 = hipGetDevice(&dev);
-  if (e0 != hipSuccess) return hip_code(e0);
-  if (dev < 0 || dev >= 64) return NT_ERR_UNSUPPORTED;
-  void* ptr = __atomic_load_n(&cached[dev], __ATOMIC_ACQUIRE);
-  if (!ptr) {
-    const hipError_t e = hipGetSymbolAddress((void**)&ptr, HIP_SYMBOL(scratch));
-    if (e != hipSuccess) return hip_code(e);
-    if (!ptr) return NT_ERR_UNSUPPORTED;
-    __atomic_store_n(&cached[dev], ptr, __ATOMIC_RELEASE);
-  }
-  *out = ptr;
-  return NT_OK;
-}
-
 int64_t normtest_static_max_coords(int64_t J) {
   if (J < 2 || J > (1 << 20)) return 0;
   // largest d whose record, tile partials and group partials fit: partials_bytes is monotone in d
@@ -1978,8 +2072,9 @@ int normtest_step_static(const void* grads, nt_dtype gdtype, int64_t J, int64_t 
   const int rc = check_step_args(grads, gdtype, J, d, ld, w, m, v, gbar_out, hy.flags, &hy, shard, (const void*)256,
                                  (size_t)-1, result_dev);
   if (rc != NT_OK) return rc;
+  static PerDevice cached = {nullptr};
   void* ws = nullptr;
-  const int rs = scratch_address(&ws);
+  const int rs = device_address(HIP_SYMBOL(scratch), cached, &ws);
   if (rs != NT_OK) return rs;
   return enqueue_step_routed(grads, false, gdtype, J, d, shard, ld, w, m, v, gbar_out, &hy, ws, result_dev,
                              (hipStream_t)hip_stream);

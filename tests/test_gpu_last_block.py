@@ -1,0 +1,99 @@
+"""Steps of a few tiles, whose last block adds up the partials: the bits of the two launches that the same call takes under
+capture, with inputs that change from call to call, garbage in the workspace, and several streams at once."""
+from __future__ import annotations
+
+import ctypes
+
+import pytest
+import torch
+
+from paper_2412_21124_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+STATS, ADAMW, GBAR, COORD = B.NT_DO_STATS, B.NT_DO_ADAMW, B.NT_WRITE_GBAR, B.NT_COORD_TEST
+K = 4   # inputs, and streams
+
+
+def _hyper(flags):
+    # with lr, decay and (1 - beta) zero the state stays as it is, so that every call on the same inputs has the same outputs
+    return B.make_hyper(lr=0.0, weight_decay=0.0, beta1=0.0, beta2=0.0, step=10, b_k=64, b_max=8192, round_to=16, flags=flags)
+
+
+class _Calls:
+    """K inputs of one size, each with a state, a workspace full of garbage and a pointer table of its own."""
+    def __init__(self, J, gdtype, d, flags):
+        self.hy, self.d = _hyper(flags), d
+        self.grads = [(torch.randn(J, d, device=DEV) * 1e-2 * (k + 1)).to(gdtype) for k in range(K)]
+        self.rows = [[g[j] for j in range(J)] for g in self.grads]
+        self.tables = [B.make_row_table(r) for r in self.rows]
+        self.state = [[torch.rand(d, device=DEV) for _ in range(4)] for _ in range(K)]
+        self.ws = [torch.randint(0, 255, (B.normtest_workspace_bytes(J, d),), dtype=torch.uint8, device=DEV) for _ in range(K)]
+
+    def matrix(self, k, result, stream=None):
+        w, m, v, gbar = self.state[k]
+        B.normtest_step(self.grads[k], w, m, v, self.hy, gbar_out=gbar, workspace=self.ws[k], result=result, stream=stream)
+
+    def table(self, k, result, stream=None):
+        w, m, v, gbar = self.state[k]
+        B.normtest_step_rows(self.rows[k], w, m, v, self.hy, table=self.tables[k], gbar_out=gbar, workspace=self.ws[k],
+                             result=result, stream=stream)
+
+    def two_launches(self):
+        """Result and outputs for every input from a captured step, which has a reduction kernel of its own."""
+        out = []
+        for k in range(K):
+            r = torch.zeros(B.RESULT_BYTES, dtype=torch.uint8, device=DEV)
+            torch.cuda.synchronize()
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph):
+                self.matrix(k, r, torch.cuda.current_stream())
+            graph.replay()
+            torch.cuda.synchronize()
+            out.append((r.clone(), [t.clone() for t in self.state[k]]))
+        return out
+
+
+# the fewest tiles, a ragged last one, both sides of the last count that ends in one launch, for each class of short vectors
+@pytest.mark.parametrize("J,gdtype,flags,tile,most", [(2, torch.float32, STATS | ADAMW, 4096, 256), (16, torch.bfloat16, STATS, 4096, 256),
+                                                      (8, torch.bfloat16, STATS | GBAR | COORD, 4096, 256),
+                                                      (20, torch.float32, STATS | ADAMW | GBAR, 2048, 128), (40, torch.bfloat16, STATS, 2048, 128)])
+@pytest.mark.parametrize("past", [None, -1, 0, 1])
+def test_bits_of_two_launches(J, gdtype, flags, tile, most, past):
+    tiles = 2 if past is None else most + past
+    c = _Calls(J, gdtype, tiles * tile - 5, flags)
+    want = c.two_launches()
+    results = torch.zeros(2 * K * 20, B.RESULT_BYTES, dtype=torch.uint8, device=DEV)
+    for i in range(results.shape[0]):   # back to back, every input after another one
+        (c.matrix if i % (2 * K) < K else c.table)(i % K, results[i])
+    torch.cuda.synchronize()
+    assert all(torch.equal(results[i], want[i % K][0]) for i in range(results.shape[0]))
+    results.zero_()
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in range(K)]
+    for i in range(results.shape[0]):
+        c.matrix(i % K, results[i], streams[i % K])
+    torch.cuda.synchronize()
+    assert all(torch.equal(results[i], want[i % K][0]) for i in range(results.shape[0]))
+    for k in range(K):
+        assert all(torch.equal(a, b) for a, b in zip(c.state[k], want[k][1]))
+
+
+# more calls than there are counters (2^20): each is met again, and has been left at zero
+def test_counters_come_round():
+    c = _Calls(2, torch.float32, 4097, STATS)
+    want = c.two_launches()[0][0]
+    res = torch.zeros(B.RESULT_BYTES, dtype=torch.uint8, device=DEV)
+    fn = B.lib().normtest_step
+    args = (c.grads[0].data_ptr(), B.NT_F32, 2, c.d, c.d, None, None, None, None, ctypes.byref(c.hy), None, c.ws[0].data_ptr(),
+            c.ws[0].numel(), res.data_ptr(), torch.cuda.current_stream().cuda_stream)
+    for i in range((1 << 20) + 5):
+        if fn(*args) != 0:
+            raise AssertionError(i)
+        if i % (1 << 17) == 0:
+            print("call", i, flush=True)
+            torch.cuda.synchronize()
+            assert torch.equal(res, want)
+            res.zero_()
+    torch.cuda.synchronize()
+    assert torch.equal(res, want)
