@@ -74,18 +74,32 @@
 #define NT_ITERS_MANY_SHORT 2
 #define NT_BLOCK_LARGE_STATS 256 // J > 16, statistics only (nothing written per coordinate): short tiles, so that a
 #define NT_ITERS_LARGE_STATS 2   // vector of a few million coordinates still gives every CU several blocks
-#define NT_BLOCKS_PER_CU 4096    // grid = min(tiles, CUs * this); blocks stride over tiles beyond that
+#define NT_MAX_GRID (1ll << 21)  // blocks per launch at most: HIP's limit is on the threads, 2^32 - 1
+#define NT_COPY_BLOCKS_PER_CU 4096  // copy and yardstick: grid = min(blocks of work, CUs * this); blocks stride beyond that
 // A long vector is walked by several launches of the step kernel, each over a run of consecutive tiles.  Blocks
 // that start together move through their load and store phases together, so the memory system sees chip-wide
 // bursts of reads and of writes instead of an even mix, which it serves faster; inside one long launch that
 // lockstep drifts apart within some tens of block generations.  A kernel boundary restores it at the price of a
 // drained machine for a few microseconds.  Coordinates per launch, by class (measured; 0: one launch):
-#define NT_CHUNK_FULL (1ll << 27)        // J <= 16, fused step (+3 % at d = 1.5e9, +1 % at 16 rows)
+#define NT_CHUNK_FULL (1ll << 26)        // J <= 16, fused step (2^25 .. 2^27 within 0.5 %, 2^24 -2 %, 2^28 -1 %)
+#define NT_CHUNK_FULL_FEW (1ll << 25)    // ... of up to 8 bytes of rows, two blocks per CU (4 bf16 rows +1.2 .. 2 % against 2^27)
 #define NT_CHUNK_ADAMW (1ll << 25)       // J <= 16, AdamW only (+5 %)
+#define NT_CHUNK_ADAMW_LONG (1ll << 24)  // ... in vectors of at least NT_LONG_COORDS, two blocks per CU
+#define NT_LONG_COORDS (1ll << 28)
 #define NT_CHUNK_STATS_GBAR (1ll << 27)  // J <= 16, statistics + stored gbar (+2 % on the clipped step)
 #define NT_CHUNK_STATS 0                 // statistics only: nothing is written, nothing to gain
 #define NT_CHUNK_ADAMW_GBAR (1ll << 25)  // AdamW from a stored gbar (second phase of the clipped step)
 // J > 16, modes that write per coordinate: one generation of blocks per launch, see launch_step_shape
+
+// Two blocks of 1024 threads fit a CU where a kernel has at most 64 vector registers: the fused step of up to 4 bf16 or 3 fp32
+// rows (4 with the plain kernels) and AdamW only.  In short vectors that hides latency; where a vector fills the chip several
+// times over, one block at a time keeps the blocks in step and is served faster.  Asking for more than half of a CU's LDS sees to
+// it (one_block_lds).  One against two, us: fused step of 4 fp32 rows 34.8 / 32.5 at d = 2^22, 121.4 / 120.4 at 2^24, 819 / 857
+// at 124M, of 8 bf16 rows (where it keeps the next block from starting beside the last waves of a block) 35.5 / 34.7 at 2^22,
+// 9740 / 9830 at 1.5e9; AdamW only, 8 bf16 rows 29.4 / 27.4 at 2^22, 61.2 / 59.1 at 2^23, 112 / 116 at 2^24, 194 / 200 at 3e7,
+// 813 / 826 at 124M, 2013 / 1998 at 3e8; AdamW from a stored gbar +0.8 % from 6e7 on, -2 % at 1e7.  Up to 8 bytes of rows the
+// fused step prefers two at any length (4 bf16 rows 28.6 / 25.9 at 2^22, 1683 / 1661 at 304.6M), AdamW only is indifferent.
+#define NT_ONE_BLOCK_LDS 82000
 
 #define NT_VEC 4              // coordinates per lane and sweep: 16-byte fp32 accesses, 8-byte bf16 row loads
 #define NT_TILE_MAX 16384     // every tile size divides this: the alignment that keeps shard results bit-identical
@@ -151,20 +165,6 @@ __device__ inline T ld_nt(P p) {
   return __builtin_nontemporal_load((const T NT_GLOBAL*)p);
 }
 
-// A group of four bfloat16 coordinates of which only the first n = 0 .. 3 lie below d, without a branch between its loads:
-// which elements exist, as lane masks.  All three are loaded, the first in place of one that does not exist and the sweep's
-// first coordinate in place of a group that lies wholly past d.
-typedef uint32_t Part __attribute__((ext_vector_type(3)));
-struct Exists {
-  uint32_t first, second, third;   // all ones or zero
-  __device__ inline Exists(int n)
-      : first((int)(0u - (uint32_t)n) >> 31), second((int)(1u - (uint32_t)n) >> 31), third((int)(2u - (uint32_t)n) >> 31) {}
-};
-__device__ inline Part ld_part16(const char NT_GLOBAL* sweep, uint32_t lane, const Exists& x) {
-  const uint16_t NT_GLOBAL* q = (const uint16_t NT_GLOBAL*)(sweep + (lane & x.first));
-  return {q[0], q[x.second & 1u], q[x.third & 2u]};
-}
-
 struct F32 {
   static constexpr int VEC = 4;
   static constexpr int ESIZE = 4;
@@ -178,6 +178,11 @@ struct F32 {
     if (n > 1) r[1] = q[1];
     if (n > 2) r[2] = q[2];
     return r;
+  }
+  // coordinates sh, sh+1, ... of the four, zeros behind them
+  __device__ static inline raw_t moved(const raw_t& r, int sh) {
+    const raw_t x = sh & 1 ? raw_t{r[1], r[2], r[3], 0u} : r, y = sh & 2 ? raw_t{x[2], x[3], 0u, 0u} : x;
+    return sh < 4 ? y : raw_t{0u, 0u, 0u, 0u};
   }
   __device__ static inline float val(const raw_t& r, int e) { return __builtin_bit_cast(float, (uint32_t)r[e]); }
   __device__ static inline float ld(const void* base, int64_t i) { return ((const float*)base)[i]; }
@@ -196,8 +201,10 @@ struct BF16 {
     if (n > 2) r[1] = q[2];
     return r;
   }
-  __device__ static inline raw_t join(const Part& w, const Exists& x) {
-    return {(w[0] & x.first) | (w[1] << 16 & x.second), w[2] & x.third};
+  // coordinates sh, sh+1, ... of the four, zeros behind them
+  __device__ static inline raw_t moved(const raw_t& r, int sh) {
+    const uint64_t x = __builtin_bit_cast(uint64_t, r) >> (16 * sh & 63);
+    return __builtin_bit_cast(raw_t, sh < 4 ? x : 0);
   }
   // bfloat16 is the high half of a binary32: widening is a shift or a mask
   __device__ static inline float val(const raw_t& r, int e) {
@@ -596,30 +603,29 @@ struct TileEnd {
   uint32_t before;
 };
 
-// Block partial of one tile -> partials[NT_NV*tile ..].  `buf` alternates between tiles so that one
-// barrier per tile is enough.
+// Block partial of one tile -> partials[NT_NV*tile ..].
 // END: the launch has a block per tile and its last one adds up the partials (k_step_end).  The partial then goes through this
 // XCD's L2 to memory, and once it is there the block counts itself.  Both accesses are relaxed on purpose: a release would
 // write back all of the L2, in every block.  Nobody waits for another block; the state, if any, is stored after the counting, so
 // that its way to memory is not waited for.
 template <int BLOCK, bool END>
-__device__ inline TileEnd tile_reduce(const LaneAcc& acc, double (*red)[BLOCK / 64][NT_NV], int buf, double* partials,
+__device__ inline TileEnd tile_reduce(const LaneAcc& acc, double (*red)[NT_NV], double* partials,
                                       int64_t tile, uint32_t* ticket) {
   const double x = wave_sum4(acc.A, acc.B, acc.C, (double)acc.nfail, [](double p, double q) { return p + q; });
   const float r = wave_max(acc.rmax);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   if ((lane & 15) == 0) {
-    red[buf][wave][lane_value(lane)] = x;
-    if (lane == 0) red[buf][wave][NT_NSUM] = (double)r;
+    red[wave][lane_value(lane)] = x;
+    if (lane == 0) red[wave][NT_NSUM] = (double)r;
   }
   __syncthreads();
   TileEnd end = {0.0, 0};
   if (threadIdx.x < NT_NV) {
     // the waves in their order, one of the five values per lane
-    double t = red[buf][0][threadIdx.x];
+    double t = red[0][threadIdx.x];
 #pragma unroll
     for (int wv = 1; wv < BLOCK / 64; ++wv) {
-      const double y = red[buf][wv][threadIdx.x];
+      const double y = red[wv][threadIdx.x];
       t = threadIdx.x < NT_NSUM ? t + y : __builtin_fmax(t, y);
     }
     double* const to = partials + NT_NV * tile + threadIdx.x;
@@ -747,12 +753,15 @@ __device__ inline void coord_stats(const StepParams& p, int64_t i, double& S, fl
 }
 
 // ---------------------------------------------------------------------------------------------
-// Loads and stores of a lane's VEC coordinates i0 .. i0+3.  PART: the tile may reach past d and only n of the four lie
-// below it; those (one group per call) are moved one by one, and what lies past d is zero rows on zero state, which add
-// exact zeros to every sum.  The arithmetic is the same for whole and part tiles, hence the same bits.  With at most 16
-// rows the part tile is a copy of its own (the branch in the only copy makes a wave wait for all its rows before the
-// first sum, -2 % on the fused step); beyond 16 rows that depends (whole_copy).  128 rows, d = 1,000,003, unpadded: 58 us
-// against 386 us with the part tile and everything misaligned element by element.
+// Loads and stores of a lane's VEC coordinates i0 .. i0+3.  part: the tile may reach past d.  A group that does is loaded by the
+// same instruction as every other, as the vector's last four coordinates, and moved down to where it belongs (Reach, settle);
+// what lies past d is then zero rows on zero state, which add exact zeros to every sum.  Its 1 to 3 values are stored one by
+// one.  The arithmetic is the same for whole and part tiles, hence the same bits.  Element by element, in a branch of its own,
+// such a group's rows were a chain of loads that a short vector waits for (d = 100,003: fused step of 16 bf16 rows 11.1 -> 9.9
+// us, of 512 rows 126 -> 106, statistics of 64 / 256 rows in tables 29.6 -> 15.2 and 119 -> 56).
+// AdamW only of at most 16 rows has one copy of the code, in which part tiles differ by block-uniform branches; elsewhere whole
+// tiles and part tiles have a copy each (with one, the fused step of 4 fp32 rows takes 7.4 instead of 6.7 us at d = 5000, of 8
+// bf16 rows 9843 instead of 9745 at 1.5e9; sweeps of statistics could not overlap).
 // ---------------------------------------------------------------------------------------------
 // coordinates i0 .. i0+3 that lie below d: 4 or fewer, 0 or negative where none does
 __device__ inline int below(int64_t d, int64_t i0) { return (int)(d - i0 < 4 ? (d - i0 < 0 ? 0 : d - i0) : 4); }
@@ -776,6 +785,37 @@ __device__ inline T NT_GLOBAL* at(T* base, const Place& pl) {
   return scalar(base + pl.s0) + pl.u;
 }
 
+// Where a lane's vector loads start, at coordinate s0 + u (s0 uniform), and by how many coordinates sh what they return has to be
+// moved: in a part tile the group that reaches past d, and every group behind it, loads the vector's last four coordinates
+// instead.  What it reads of its neighbour's coordinates, which that lane may have updated by then, is moved out.  A vector of
+// fewer than four has no such place; its values are loaded one by one (load_sweep).
+struct Reach {
+  int64_t s0;
+  uint32_t u;
+  int sh;
+};
+__device__ inline Reach reach(bool part, const StepParams& p, const Place& pl) {
+  if (__builtin_expect(!part || p.d < 4, 1)) return {pl.s0, pl.u, 0};
+  // as far from s0 - 4 as from s0 - 1 on the last four coordinates begin, so that lanes' offsets stay positive
+  const int64_t s0 = pl.s0 < 4 ? 0 : pl.s0 - 4;
+  const int64_t last = p.d - 4 - s0;
+  const uint32_t want = (uint32_t)(pl.s0 - s0) + pl.u;
+  const uint32_t most = last < (1 << 20) ? (uint32_t)last : 1u << 20;
+  const uint32_t u = want < most ? want : most;
+  return {s0, u, (int)(want - u)};
+}
+// Rows or state as loaded -> as they belong
+template <class GT, int N>
+__device__ inline void settle(bool part, const Reach& r, typename GT::raw_t* raw) {
+  if (__builtin_expect(part, 0)) {
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      raw[j] = GT::moved(raw[j], r.sh);
+      asm volatile("" : "+v"(raw[j]));   // one row after the other: interleaved, 16 fp32 rows need registers there are not
+    }
+  }
+}
+
 // Rows j0, j0+1, ... at coordinate s0, one after the other: a matrix is walked by adding its row stride.
 template <class GT, bool TABLE>
 struct RowWalk {
@@ -793,23 +833,15 @@ struct RowWalk {
   }
 };
 
-// Rows j0 .. j0+N-1 of the lane's coordinates, and with STATE w, m, v too, all under one branch so that every load of a
-// sweep is in flight before the first wait.  The sweep's first coordinate lies below d.  In the branch for the part group
-// every row is used at once, so that none of its loads is pending behind it: the wait before each row's first use below would
-// have to allow for it and be a wait for all rows (24 rows, d = 3e7: 377 -> 454 us).  A bf16 matrix without the state has up
-// to eight rows in flight there: one by one they were the longest chain of loads in a short vector (128 unpadded rows of
-// 1,000,003 coordinates 76 us against 58, statistics of 16 rows over 100,003 coordinates 12.5 against 11.4).  Elsewhere they
-// do go one by one.  With the state the elements would wait in vector registers that take the fused kernels of 8 and 12 rows
-// past the next step in how many waves a CU holds (11 rows with 98 instead of 91: +3 %), with a table the pointers in scalar
-// registers that the kernels which also carry the result's record do not have (they would need scratch memory); and beyond 16
-// fp32 rows four blocks instead of three fit a CU then, which is slower by 2 to 4 % from 2^22 coordinates on and gains 0.3 %
-// on ragged vectors.
-template <class GT, bool TABLE, bool PART, int N, bool STATE>
-__device__ inline void load_sweep(const StepParams& p, int j0, const Place& pl, int n, typename GT::raw_t* raw,
-                                  u32x4* state) {
-  const uint32_t lane = pl.u * GT::ESIZE;
-  if (!PART || n >= GT::VEC) {
-    RowWalk<GT, TABLE> row(p, j0, pl.s0);
+// Rows j0 .. j0+N-1 of the lane's coordinates, and with STATE w, m, v too, as loaded (see settle).  The sweep's first coordinate
+// lies below d.  Every row of a vector of fewer than four coordinates is used at once, so that no load is pending behind that
+// branch: the wait before each row's first use would have to allow for it and be a wait for all rows.
+template <class GT, bool TABLE, int N, bool STATE>
+__device__ inline void load_sweep(bool part, const StepParams& p, int j0, const Reach& r, typename GT::raw_t* raw, u32x4* state) {
+  const uint32_t lane = r.u * GT::ESIZE;
+  const Place pl = {r.s0, r.u};
+  RowWalk<GT, TABLE> row(p, j0, r.s0);
+  if (__builtin_expect(!part || p.d >= 4, 1)) {
 #pragma unroll
     for (int j = 0; j < N; ++j) raw[j] = GT::ldraw(row.next() + lane);
     if constexpr (STATE) {
@@ -817,8 +849,8 @@ __device__ inline void load_sweep(const StepParams& p, int j0, const Place& pl, 
       state[1] = ld16(at(p.m, pl));
       state[2] = ld16(at(p.v, pl));
     }
-  } else if constexpr (STATE || TABLE || GT::ESIZE == 4) {
-    RowWalk<GT, TABLE> row(p, j0, pl.s0);
+  } else {
+    const int n = below(p.d, pl.i0());
 #pragma unroll
     for (int j = 0; j < N; ++j) {
       raw[j] = GT::ldraw_part(row.next() + lane, n);
@@ -829,47 +861,27 @@ __device__ inline void load_sweep(const StepParams& p, int j0, const Place& pl, 
       state[1] = F32::ldraw_part((const char NT_GLOBAL*)at(p.m, pl), n);
       state[2] = F32::ldraw_part((const char NT_GLOBAL*)at(p.v, pl), n);
     }
-  } else {
-    int few = n;   // opaque: the masks are not to be kept in registers throughout the loop over tiles
-    asm volatile("" : "+v"(few));
-    const Exists x(few);
-    RowWalk<GT, TABLE> row(p, j0, pl.s0);
-    constexpr int RUN = N < 8 ? N : 8;
-#pragma unroll
-    for (int j = 0; j < N; j += RUN) {
-      Part w[RUN];
-#pragma unroll
-      for (int k = 0; k < RUN; ++k)
-        if (j + k < N) w[k] = ld_part16(row.next(), lane, x);
-#pragma unroll
-      for (int k = 0; k < RUN; ++k)
-        if (j + k < N) {
-          raw[j + k] = GT::join(w[k], x);
-          asm volatile("" : "+v"(raw[j + k]));
-        }
-    }
   }
 }
-template <class GT, bool TABLE, bool PART, int N>
-__device__ inline void load_rows(const StepParams& p, int j0, const Place& pl, int n, typename GT::raw_t* raw) {
-  load_sweep<GT, TABLE, PART, N, false>(p, j0, pl, n, raw, nullptr);
+template <class GT, bool TABLE, int N>
+__device__ inline void load_rows(bool part, const StepParams& p, int j0, const Reach& r, typename GT::raw_t* raw) {
+  load_sweep<GT, TABLE, N, false>(part, p, j0, r, raw, nullptr);
 }
 
-template <bool PART>
-__device__ inline void store4(float* base, const Place& pl, int n, f32x4 x) {
-  if (!PART || n >= 4) {
+__device__ inline void store4(bool part, const StepParams& p, float* base, const Place& pl, f32x4 x) {
+  const int n = part ? below(p.d, pl.i0()) : 4;
+  if (__builtin_expect(n >= 4, 1)) {
     st16(at(base, pl), x);
   } else {
-    float NT_GLOBAL* p = at(base, pl);
+    float NT_GLOBAL* q = at(base, pl);
 #pragma unroll
     for (int e = 0; e < 3; ++e)
-      if (e < n) p[e] = x[e];
+      if (e < n) q[e] = x[e];
   }
 }
 
 // AdamW on VEC coordinates whose state was loaded as 16-byte vectors, then the stores.
-template <bool PART>
-__device__ inline void adamw_store(const StepParams& p, const Place& pl, int n, const float* gb,
+__device__ inline void adamw_store(bool part, const StepParams& p, const Place& pl, const float* gb,
                                    const u32x4* state) {
   f32x4 ow, om, ov;
 #pragma unroll
@@ -882,14 +894,14 @@ __device__ inline void adamw_store(const StepParams& p, const Place& pl, int n, 
     om[e] = m;
     ov[e] = v;
   }
-  if (!PART || n >= 4) {
-    store4<false>(p.w, pl, 4, ow);
-    store4<false>(p.m, pl, 4, om);
-    store4<false>(p.v, pl, 4, ov);
+  if (__builtin_expect(!part, 1)) {
+    st16(at(p.w, pl), ow);
+    st16(at(p.m, pl), om);
+    st16(at(p.v, pl), ov);
   } else {
-    store4<true>(p.w, pl, n, ow);
-    store4<true>(p.m, pl, n, om);
-    store4<true>(p.v, pl, n, ov);
+    store4(true, p, p.w, pl, ow);
+    store4(true, p, p.m, pl, om);
+    store4(true, p, p.v, pl, ov);
   }
 }
 
@@ -945,7 +957,7 @@ constexpr bool pin_loads(int esize, int J, bool coord) { return !coord && (J == 
 
 // State update interleaved with the rows: each sweep reads its rows and w, m, v, and writes the state back.
 template <class GT, int J, int MODE, int BLOCK, int ITERS, bool TABLE, bool GBAR, bool COORD, bool PART, bool END>
-__device__ inline TileEnd tile_rows(const StepParams& p, int64_t tile, double (*red)[BLOCK / 64][NT_NV], int buf,
+__device__ inline TileEnd tile_rows(bool part, const StepParams& p, int64_t tile, double (*red)[NT_NV],
                                     uint32_t* ticket) {
   constexpr int VEC = GT::VEC;
   constexpr int TILE = BLOCK * VEC * ITERS;
@@ -962,11 +974,11 @@ __device__ inline TileEnd tile_rows(const StepParams& p, int64_t tile, double (*
 #pragma unroll U
   for (int it = 0; it < ITERS; ++it) {
     const Place pl = {tile * TILE + (int64_t)it * BLOCK * VEC, threadIdx.x * VEC};
-    if (PART && pl.s0 >= p.d) break;
-    const int n = PART ? below(p.d, pl.i0()) : VEC;
+    if (PART && part && pl.s0 >= p.d) break;
     typename GT::raw_t raw[J];
     u32x4 state[3];
-    load_sweep<GT, TABLE, PART, J, MODE != MODE_STATS>(p, 0, pl, n, raw, state);
+    const Reach at = reach(PART && part, p, pl);
+    load_sweep<GT, TABLE, J, MODE != MODE_STATS>(PART && part, p, 0, at, raw, state);
     if constexpr (MODE == MODE_STATS && U == 1 && !PART && pin_loads(GT::ESIZE, J, COORD)) __builtin_amdgcn_sched_barrier(0);
     if constexpr (MODE != MODE_STATS) {
       // Every load of the sweep is issued before any arithmetic: the compiler must neither sink loads below
@@ -975,13 +987,17 @@ __device__ inline TileEnd tile_rows(const StepParams& p, int64_t tile, double (*
       // tiles are left free so that consecutive sweeps can overlap.
       __builtin_amdgcn_sched_barrier(0);
     }
+    settle<GT, J>(PART && part, at, raw);
     float gb[VEC];
     sweep_rows<GT, J, MODE, COORD>(p, raw, gb, acc);
-    if constexpr (EARLY) end = tile_reduce<BLOCK, true>(acc, red, buf, p.partials, tile, ticket);
-    if constexpr (MODE != MODE_STATS) adamw_store<PART>(p, pl, n, gb, state);
-    if (GBAR && p.gbar) store4<PART>(p.gbar, pl, n, f32x4{gb[0], gb[1], gb[2], gb[3]});
+    if constexpr (EARLY) end = tile_reduce<BLOCK, true>(acc, red, p.partials, tile, ticket);
+    if constexpr (MODE != MODE_STATS) {
+      settle<F32, 3>(PART && part, at, state);
+      adamw_store(PART && part, p, pl, gb, state);
+    }
+    if (GBAR && p.gbar) store4(PART && part, p, p.gbar, pl, f32x4{gb[0], gb[1], gb[2], gb[3]});
   }
-  if constexpr (MODE != MODE_ADAMW && !EARLY) end = tile_reduce<BLOCK, END>(acc, red, buf, p.partials, tile, ticket);
+  if constexpr (MODE != MODE_ADAMW && !EARLY) end = tile_reduce<BLOCK, END>(acc, red, p.partials, tile, ticket);
   // AdamW-only tiles end with a block barrier like the other modes: the waves of a block then finish together
   // and the next block's waves start together (measured +2 %)
   if constexpr (MODE == MODE_ADAMW) __syncthreads();
@@ -996,15 +1012,16 @@ __device__ inline void deferred_sweeps(const StepParams& p, int64_t tile, const 
   for (int it = 0; it < ITERS; ++it) {
     const Place pl = {tile * TILE + (int64_t)it * BLOCK * VEC, threadIdx.x * VEC};
     if (PART && pl.s0 >= p.d) break;
-    const int n = PART ? below(p.d, pl.i0()) : VEC;
     const f32x4 g4 = gbs[it * BLOCK + threadIdx.x];   // this lane's own values: no barrier needed for them
     const float gb[VEC] = {g4[0], g4[1], g4[2], g4[3]};
     if constexpr (MODE != MODE_STATS) {
       u32x4 state[3];
-      load_sweep<F32, false, PART, 0, true>(p, 0, pl, n, nullptr, state);
-      adamw_store<PART>(p, pl, n, gb, state);
+      const Reach at = reach(PART, p, pl);
+      load_sweep<F32, false, 0, true>(PART, p, 0, at, nullptr, state);
+      settle<F32, 3>(PART, at, state);
+      adamw_store(PART, p, pl, gb, state);
     }
-    if (GBAR && p.gbar) store4<PART>(p.gbar, pl, n, g4);
+    if (GBAR && p.gbar) store4(PART, p, p.gbar, pl, g4);
   }
 }
 
@@ -1013,14 +1030,14 @@ __device__ inline void deferred_sweeps(const StepParams& p, int64_t tile, const 
 // sprinkled among reads several times their volume; gathered at the end of a block's life, and with all blocks
 // of a launch living at the same time (one generation per launch), they reach it as a dense burst.
 template <int MODE, int BLOCK, int ITERS, bool GBAR, bool PART, bool END>
-__device__ inline TileEnd deferred_update(const StepParams& p, int64_t tile, double (*red)[BLOCK / 64][NT_NV], int buf,
+__device__ inline TileEnd deferred_update(const StepParams& p, int64_t tile, double (*red)[NT_NV],
                                           const LaneAcc& acc, const f32x4* gbs, uint32_t* ticket) {
   constexpr int VEC = 4;
   constexpr int TILE = BLOCK * VEC * ITERS;
   // the barrier inside keeps the waves of the block together on their way into the write phase
   TileEnd end = {0.0, 0};
   if constexpr (MODE != MODE_ADAMW)
-    end = tile_reduce<BLOCK, END>(acc, red, buf, p.partials, tile, ticket);
+    end = tile_reduce<BLOCK, END>(acc, red, p.partials, tile, ticket);
   else
     __syncthreads();
   if (MODE != MODE_STATS || p.gbar) {
@@ -1035,7 +1052,7 @@ __device__ inline TileEnd deferred_update(const StepParams& p, int64_t tile, dou
 
 // Deferred state update, rows in registers: the sweeps read rows only.
 template <class GT, int J, int MODE, int BLOCK, int ITERS, bool TABLE, bool GBAR, bool PART>
-__device__ inline void tile_defer(const StepParams& p, int64_t tile, double (*red)[BLOCK / 64][NT_NV], int buf,
+__device__ inline void tile_defer(const StepParams& p, int64_t tile, double (*red)[NT_NV],
                                        f32x4* gbs) {
   constexpr int VEC = GT::VEC;
   static_assert(VEC == 4, "one 16-byte LDS slot per lane and sweep");
@@ -1046,12 +1063,14 @@ __device__ inline void tile_defer(const StepParams& p, int64_t tile, double (*re
     const Place pl = {tile * TILE + (int64_t)it * BLOCK * VEC, threadIdx.x * VEC};
     if (PART && pl.s0 >= p.d) break;
     typename GT::raw_t raw[J];
-    load_rows<GT, TABLE, PART, J>(p, 0, pl, PART ? below(p.d, pl.i0()) : VEC, raw);
+    const Reach at = reach(PART, p, pl);
+    load_rows<GT, TABLE, J>(PART, p, 0, at, raw);
+    settle<GT, J>(PART, at, raw);
     float gb[VEC];
     sweep_rows<GT, J, MODE, true>(p, raw, gb, acc);
     gbs[it * BLOCK + threadIdx.x] = f32x4{gb[0], gb[1], gb[2], gb[3]};
   }
-  deferred_update<MODE, BLOCK, ITERS, GBAR, PART, false>(p, tile, red, buf, acc, gbs, nullptr);
+  deferred_update<MODE, BLOCK, ITERS, GBAR, PART, false>(p, tile, red, acc, gbs, nullptr);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1059,11 +1078,12 @@ __device__ inline void tile_defer(const StepParams& p, int64_t tile, double (*re
 // (fp64) and the sum of squares of the values shifted by K, the running mean of the rows before it, hence
 // its centred sum of squares without cancellation; see chunk_merge for the bookkeeping.
 // ---------------------------------------------------------------------------------------------
-template <class GT, int N>
-__device__ inline void chunk_accumulate(const typename GT::raw_t* raw, const float* K, double* sb, float* q) {
+template <class GT, bool PART, int N>
+__device__ inline void chunk_accumulate(typename GT::raw_t* raw, const Reach& at, const float* K, double* sb, float* q) {
   constexpr int VEC = GT::VEC;
 #pragma unroll
   for (int j = 0; j < N; ++j) {
+    if constexpr (PART) raw[j] = GT::moved(raw[j], at.sh);
 #pragma unroll
     for (int e = 0; e < VEC; ++e) {
       const float x = GT::val(raw[j], e);
@@ -1086,59 +1106,74 @@ __device__ inline void chunk_clear(double* sb, float* q) {
 // costs more than it saves).  The rows keep their order.
 static_assert(NT_MCHUNK <= 16, "the last chunk is walked in runs of 8, 4, 2 and 1 rows");
 template <class GT, bool TABLE, bool PART, int RUN>
-__device__ inline void load_last(const StepParams& p, int j0, int nb, const Place& pl, int n, typename GT::raw_t* raw) {
-  if (nb & RUN) load_rows<GT, TABLE, PART, RUN>(p, j0 + (nb & ~(2 * RUN - 1)), pl, n, raw);
-  if constexpr (RUN > 1) load_last<GT, TABLE, PART, RUN / 2>(p, j0, nb, pl, n, raw + RUN);
+__device__ inline void load_last(const StepParams& p, int j0, int nb, const Reach& at, typename GT::raw_t* raw) {
+  if (nb & RUN) load_rows<GT, TABLE, RUN>(PART, p, j0 + (nb & ~(2 * RUN - 1)), at, raw);
+  if constexpr (RUN > 1) load_last<GT, TABLE, PART, RUN / 2>(p, j0, nb, at, raw + RUN);
 }
-template <class GT, int RUN>
-__device__ inline void accumulate_last(int nb, const typename GT::raw_t* raw, const float* K, double* sb, float* q) {
-  if (nb & RUN) chunk_accumulate<GT, RUN>(raw, K, sb, q);
-  if constexpr (RUN > 1) accumulate_last<GT, RUN / 2>(nb, raw + RUN, K, sb, q);
+template <class GT, bool PART, int RUN>
+__device__ inline void accumulate_last(int nb, typename GT::raw_t* raw, const Reach& at, const float* K, double* sb, float* q) {
+  if (nb & RUN) chunk_accumulate<GT, PART, RUN>(raw, at, K, sb, q);
+  if constexpr (RUN > 1) accumulate_last<GT, PART, RUN / 2>(nb, raw + RUN, at, K, sb, q);
+}
+
+// Waits until all but four of a chunk's loads have arrived, before its first sum.  The walk of more than 32 bf16 rows in the class
+// for long vectors needs it to keep the blocks of a generation in step: without it, each sum starting as its row arrives, 64 /
+// 128 / 512 rows at d = 2^24 take 414 / 734 / 2622 us, with it 401 / 716 / 2571 (waiting for all of them 404 / 721 / 2570, for half
+// of them 401 / 721 / 2580).  With up to 32 rows it costs 0.5 %, in short vectors 1 to 5 %.
+__device__ inline void chunk_wait() {
+  __builtin_amdgcn_sched_barrier(0);
+  __builtin_amdgcn_s_waitcnt(0x0f70 | 4);   // vmcnt(4)
+  __builtin_amdgcn_sched_barrier(0);
 }
 
 // The state update (and the gbar store) of a tile is deferred (see deferred_update): with many rows the writes are
 // a few per cent of the traffic.
 template <class GT, int MODE, int BLOCK, int ITERS, bool TABLE, bool GBAR, bool PART, bool END>
-__device__ inline TileEnd tile_multi(const StepParams& p, int64_t tile, double (*red)[BLOCK / 64][NT_NV], int buf, f32x4* gbs,
+__device__ inline TileEnd tile_multi(const StepParams& p, int64_t tile, double (*red)[NT_NV], f32x4* gbs,
                                      uint32_t* ticket) {
   constexpr int VEC = GT::VEC;
   static_assert(VEC == 4, "one 16-byte LDS slot per lane and sweep");
   constexpr int TILE = BLOCK * VEC * ITERS;
   constexpr bool WRITES = (MODE != MODE_STATS) || GBAR;
+  constexpr bool WAITS = WRITES && MODE != MODE_ADAMW && GT::ESIZE == 2 && BLOCK * ITERS == NT_BLOCK_LARGE * NT_ITERS_LARGE;
   const int J = p.J;
   LaneAcc acc;
 #pragma unroll 1
   for (int it = 0; it < ITERS; ++it) {
     const Place pl = {tile * TILE + (int64_t)it * BLOCK * VEC, threadIdx.x * VEC};
     if (PART && pl.s0 >= p.d) break;
-    const int n = PART ? below(p.d, pl.i0()) : VEC;
     double S[VEC], sb[VEC];
     float M2[VEC], a[VEC], K[VEC], q[VEC];
 #pragma unroll
     for (int e = 0; e < VEC; ++e) a[e] = 0.f;
     typename GT::raw_t raw[NT_MCHUNK];
     // first chunk (J > NT_JCHUNK >= NT_MCHUNK - 1 here, so it is full), shifted by the first row
-    load_rows<GT, TABLE, PART, NT_MCHUNK>(p, 0, pl, n, raw);
+    const Reach at = reach(PART, p, pl);
+    load_rows<GT, TABLE, NT_MCHUNK>(PART, p, 0, at, raw);
+    if (WAITS && J > 32) chunk_wait();
+    if constexpr (PART) raw[0] = GT::moved(raw[0], at.sh);
 #pragma unroll
     for (int e = 0; e < VEC; ++e) K[e] = GT::val(raw[0], e);
     chunk_clear<VEC>(sb, q);
-    chunk_accumulate<GT, NT_MCHUNK>(raw, K, sb, q);
+    chunk_accumulate<GT, false, 1>(raw, at, K, sb, q);
+    chunk_accumulate<GT, PART, NT_MCHUNK - 1>(raw + 1, at, K, sb, q);
 #pragma unroll
     for (int e = 0; e < VEC; ++e) K[e] = chunk_merge(true, 0, NT_MCHUNK, K[e], sb[e], q[e], S[e], M2[e], a[e]);
     int j0 = NT_MCHUNK;
 #pragma unroll 1
     for (; j0 + NT_MCHUNK <= J; j0 += NT_MCHUNK) {
-      load_rows<GT, TABLE, PART, NT_MCHUNK>(p, j0, pl, n, raw);
+      load_rows<GT, TABLE, NT_MCHUNK>(PART, p, j0, at, raw);
+      if (WAITS && J > 32) chunk_wait();
       chunk_clear<VEC>(sb, q);
-      chunk_accumulate<GT, NT_MCHUNK>(raw, K, sb, q);
+      chunk_accumulate<GT, PART, NT_MCHUNK>(raw, at, K, sb, q);
 #pragma unroll
       for (int e = 0; e < VEC; ++e) K[e] = chunk_merge(false, j0, NT_MCHUNK, K[e], sb[e], q[e], S[e], M2[e], a[e]);
     }
     if (j0 < J) {
       const int nb = J - j0;
-      load_last<GT, TABLE, PART, 8>(p, j0, nb, pl, n, raw);
+      load_last<GT, TABLE, PART, 8>(p, j0, nb, at, raw);
       chunk_clear<VEC>(sb, q);
-      accumulate_last<GT, 8>(nb, raw, K, sb, q);
+      accumulate_last<GT, PART, 8>(nb, raw, at, K, sb, q);
 #pragma unroll
       for (int e = 0; e < VEC; ++e) K[e] = chunk_merge(false, j0, nb, K[e], sb[e], q[e], S[e], M2[e], a[e]);
     }
@@ -1161,78 +1196,71 @@ __device__ inline TileEnd tile_multi(const StepParams& p, int64_t tile, double (
     if constexpr (WRITES) gbs[it * BLOCK + threadIdx.x] = f32x4{gb[0], gb[1], gb[2], gb[3]};
   }
   if constexpr (WRITES)
-    return deferred_update<MODE, BLOCK, ITERS, GBAR, PART, END>(p, tile, red, buf, acc, gbs, ticket);
+    return deferred_update<MODE, BLOCK, ITERS, GBAR, PART, END>(p, tile, red, acc, gbs, ticket);
   else
-    return tile_reduce<BLOCK, END>(acc, red, buf, p.partials, tile, ticket);
+    return tile_reduce<BLOCK, END>(acc, red, p.partials, tile, ticket);
 }
 
 // ---------------------------------------------------------------------------------------------
-// Kernels.  A launch covers the slots slot0 .. slot1-1 of the ntiles tile slots; block b takes slots slot0 + b,
-// slot0 + b + gridDim.x, ...; tiles below nfull are whole, and when the vector ends in a part of a tile (nfull =
-// ntiles - 1), that one has slot 0, so that its few element-sized accesses overlap with everything else.
-// J_T = 0 selects the J > 16 row-walking variant.
+// Kernels.  A launch covers gridDim.x of the ntiles tile slots, from slot0 on, a block each; tiles below nfull are whole, and
+// when the vector ends in a part of a tile (nfull = ntiles - 1), that one has slot 0, so that it overlaps with everything else.
+// J_T = 0 selects the J > 16 row-walking variant.  (Walking tiles in a loop instead cost registers that every tile held: fused
+// step of 8 bf16 rows 82 vector and 89 scalar registers, 72 and 58 without; AdamW only 86 scalar ones, 66 without.)
 // ---------------------------------------------------------------------------------------------
 template <class GT, int J_T, int MODE, int BLOCK, int ITERS, bool TABLE, bool GBAR, bool DEFER_T, bool COORD, bool PART, bool END>
-__device__ inline TileEnd run_tile(const StepParams& p, int64_t tile, double (*red)[BLOCK / 64][NT_NV], int buf, f32x4* gbs,
+__device__ inline TileEnd run_tile(bool part, const StepParams& p, int64_t tile, double (*red)[NT_NV], f32x4* gbs,
                                    uint32_t* ticket) {
   if constexpr (J_T == 0) {
-    return tile_multi<GT, MODE, BLOCK, ITERS, TABLE, GBAR, PART, END>(p, tile, red, buf, gbs, ticket);
+    return tile_multi<GT, MODE, BLOCK, ITERS, TABLE, GBAR, PART, END>(p, tile, red, gbs, ticket);
   } else if constexpr (DEFER_T) {
     static_assert(!END || MODE == MODE_ADAMW, "steps with sums that write their own result are not in this class");
-    tile_defer<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, PART>(p, tile, red, buf, gbs);
+    tile_defer<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, PART>(p, tile, red, gbs);
     return {0.0, 0};
   } else {
-    return tile_rows<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, COORD, PART, END>(p, tile, red, buf, ticket);
+    return tile_rows<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, COORD, PART, END>(part, p, tile, red, ticket);
   }
 }
 
-// More than 16 rows: which of a kernel's whole tiles run a copy of the walk without the part branch instead of the copy that
-// the part tile needs anyway.  The branch costs a short walk and a short vector (bf16, with it against without: statistics of
-// 17 / 40 / 128 / 512 rows at d = 2^21 22.3 / 21.7, 40.3 / 38.5, 118.3 / 109.3, 404 / 392 us, 512 rows at 2^22 668 / 680;
-// fused step of 17 / 24 / 32 rows at d = 3e7 302 / 299, 371 / 365, 432 / 429 us, with gbar 17 rows 212 / 206).  It stays in
-// the tiles of the long class from 33 rows on, where it keeps the blocks of a full generation in step (512 rows, d = 2^24:
-// 2571 us with it, 2640 without; 64 rows 408 and 419), with AdamW only (32 rows, d = 3e7: 415 and 418 us), with fp32 rows
-// (statistics of 17 rows, d = 2^24: 189 and 196 us) and with tables, whose row addresses leave a second copy no scalar
-// registers (85 of them spilled; fused step of 17 rows, d = 4000: 12.7 and 13.4 us, though 128 rows at 2^21 would gain 8 %).
-template <class GT, int MODE, int BLOCK, int ITERS, bool TABLE>
+// More than 16 rows: whether whole tiles run a copy of the walk of their own.  In the copy for part tiles every row is moved to
+// its place (settle), which costs a short walk: statistics of 17 / 64 fp32 rows at d = 1e6 16.8 / 43.5 us in it, 15.5 / 42.1
+// beside it; 64 / 256 bf16 rows in tables 24.4 / 84.3 and 23.3 / 79.5, AdamW only, 20 bf16 rows 11.7 and 11.0.  It is the better
+// one where the delay keeps the blocks of a full generation in step: fused step of 32 / 64 fp32 rows at d = 3e7 731 / 1334 us in
+// it, 745 / 1350 beside it, and AdamW only from 33 bf16 rows on (64 rows, d = 2^24: 403 and 434 us).  (Statistics of 17 to 32
+// fp32 rows at 2^24 take 1 % more in either than when a part tile was loaded element by element.)  Short steps over tables that
+// write their own result have the one copy: the second would need scratch memory.
+template <class GT, int MODE, int BLOCK, int ITERS, bool TABLE, bool END>
 __device__ inline bool whole_copy(int J) {
-  constexpr bool LONG = BLOCK == NT_BLOCK_LARGE && ITERS == NT_ITERS_LARGE;
-  return GT::ESIZE == 2 && MODE != MODE_ADAMW && !TABLE && (!LONG || J <= 32);
+  constexpr bool LONG = BLOCK * ITERS == NT_BLOCK_LARGE * NT_ITERS_LARGE;
+  if (TABLE && END && !LONG) return false;
+  return GT::ESIZE == 4 ? !LONG || MODE == MODE_ADAMW || J <= NT_FEW_ROWS : MODE != MODE_ADAMW || J <= 32;
 }
 
 // GBAR = false compiles the gbar store out (statistics-only launch class, so that sweeps can overlap).
 // DEFER_T: up to 16 rows with the state update deferred to the end of the tile (always so beyond 16 rows).
 // COORD = false compiles the coordinate-wise test out (see plain_stats).
 template <class GT, int J_T, int MODE, int BLOCK, int ITERS, bool TABLE, bool GBAR, bool DEFER_T, bool COORD, bool END>
-__device__ inline TileEnd walk_tiles(const StepParams& p, int64_t nfull, int64_t ntiles, int64_t slot0, int64_t slot1,
-                                     uint32_t* ticket) {
+__device__ inline TileEnd block_tile(const StepParams& p, int64_t nfull, int64_t ntiles, int64_t slot0, uint32_t* ticket) {
   constexpr int TILE = BLOCK * GT::VEC * ITERS;
   static_assert(NT_TILE_MAX % TILE == 0, "tile sizes must divide NT_TILE_MAX");
-  __shared__ double red[2][BLOCK / 64][NT_NV];
+  __shared__ double red[BLOCK / 64][NT_NV];
   // the means of a tile's sweeps wait here for the deferred state update (see deferred_update)
   constexpr bool DEFER = (J_T == 0 || DEFER_T) && ((MODE != MODE_STATS) || GBAR);
   static_assert(!DEFER_T || DEFER, "a deferred update needs something to write");
   __shared__ f32x4 gbs[DEFER ? ITERS * BLOCK + NT_LDS_PAD_LARGE / 16 : 1];
-  int buf = 0;
-  TileEnd end = {0.0, 0};
   const int64_t npart = ntiles - nfull;  // 0 or 1
-  for (int64_t t = slot0 + blockIdx.x; t < slot1; t += gridDim.x) {
-    // rotate: the part tile (if any) first, then the whole tiles 0..nfull-1
-    const bool part = t < npart;
-    const int64_t tile = part ? nfull : t - npart;
-    if (!part && (J_T > 0 || whole_copy<GT, MODE, BLOCK, ITERS, TABLE>(p.J)))
-      end = run_tile<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, DEFER_T, COORD, false, END>(p, tile, red, buf, gbs, ticket);
-    else
-      end = run_tile<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, DEFER_T, COORD, true, END>(p, tile, red, buf, gbs, ticket);
-    if (END && MODE != MODE_ADAMW) break;   // a block per tile
-    buf ^= 1;
-  }
-  return end;
+  const int64_t t = slot0 + blockIdx.x;
+  // rotate: the part tile (if any) first, then the whole tiles 0..nfull-1
+  const bool part = t < npart;
+  const int64_t tile = part ? nfull : t - npart;
+  constexpr bool ONE_COPY = J_T > 0 && !DEFER_T && MODE == MODE_ADAMW;   // see load_sweep
+  if (!ONE_COPY && !part && (J_T > 0 || whole_copy<GT, MODE, BLOCK, ITERS, TABLE, END>(p.J)))
+    return run_tile<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, DEFER_T, COORD, false, END>(false, p, tile, red, gbs, ticket);
+  return run_tile<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, DEFER_T, COORD, true, END>(!ONE_COPY || part, p, tile, red, gbs, ticket);
 }
 
 template <class GT, int J_T, int MODE, int BLOCK, int ITERS, bool TABLE, bool GBAR, bool DEFER_T = false, bool COORD = true>
-__global__ __launch_bounds__(BLOCK) void k_step(StepParams p, int64_t nfull, int64_t ntiles, int64_t slot0, int64_t slot1) {
-  walk_tiles<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, DEFER_T, COORD, false>(p, nfull, ntiles, slot0, slot1, nullptr);
+__global__ __launch_bounds__(BLOCK) void k_step(StepParams p, int64_t nfull, int64_t ntiles, int64_t slot0) {
+  block_tile<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, DEFER_T, COORD, false>(p, nfull, ntiles, slot0, nullptr);
 }
 
 // A step that writes its result itself: AdamW only, which has no sums; a single tile, whose partial is the total; or a few
@@ -1243,9 +1271,8 @@ __global__ __launch_bounds__(BLOCK) void k_step(StepParams p, int64_t nfull, int
 // 17.6 us against 13.2 for two launches at the time.)
 template <class GT, int J_T, int MODE, int BLOCK, int ITERS, bool TABLE, bool GBAR, bool DEFER_T = false>
 __global__ __launch_bounds__(BLOCK) void k_step_end(StepParams p, int64_t nfull, int64_t ntiles, int64_t slot0,
-                                                    int64_t slot1, Finish fin) {
-  const TileEnd end = walk_tiles<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, DEFER_T, true, true>(p, nfull, ntiles, slot0, slot1,
-                                                                                               fin.ticket);
+                                                    Finish fin) {
+  const TileEnd end = block_tile<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, DEFER_T, true, true>(p, nfull, ntiles, slot0, fin.ticket);
   Totals tot;
   totals_clear(tot);
   if constexpr (MODE == MODE_ADAMW) {
@@ -1442,20 +1469,28 @@ __global__ __launch_bounds__(NT_LAYER_THREADS) void k_layer_stats(StepParams p, 
 
 // Phase 2 of the clipped variant: AdamW on scale * gbar, gbar read from memory.  One sweep per block, 4 coordinates
 // per lane.
+template <bool PART>
+__device__ inline void adamw_gbar_sweep(StepParams& p, const float* gbar, float scale, const Place& pl) {
+  u32x4 sg, state[3];
+  p.grads = gbar;   // as the only row
+  const Reach at = reach(PART, p, pl);
+  load_sweep<F32, false, 1, true>(PART, p, 0, at, &sg, state);
+  settle<F32, 1>(PART, at, &sg);
+  settle<F32, 3>(PART, at, state);
+  float gb[NT_VEC];
+#pragma unroll
+  for (int e = 0; e < NT_VEC; ++e) gb[e] = scale * __builtin_bit_cast(float, (uint32_t)sg[e]);
+  adamw_store(PART, p, pl, gb, state);
+}
 __global__ __launch_bounds__(NT_AUX_BLOCK) void k_adamw_gbar(StepParams p, const float* gbar, float grad_scale,
                                                          const nt_result* res, int64_t block0) {
   float scale = grad_scale;
   if (res) scale *= (float)res->clip_coef;
   const Place pl = {(block0 + blockIdx.x) * NT_AUX_BLOCK * NT_VEC, threadIdx.x * NT_VEC};
-  const int n = below(p.d, pl.i0());
-  if (n == 0) return;
-  u32x4 sg, state[3];
-  p.grads = gbar;   // as the only row
-  load_sweep<F32, false, true, 1, true>(p, 0, pl, n, &sg, state);
-  float gb[NT_VEC];
-#pragma unroll
-  for (int e = 0; e < NT_VEC; ++e) gb[e] = scale * __builtin_bit_cast(float, (uint32_t)sg[e]);
-  adamw_store<true>(p, pl, n, gb, state);
+  if (pl.s0 + NT_AUX_BLOCK * NT_VEC <= p.d)
+    adamw_gbar_sweep<false>(p, gbar, scale, pl);
+  else
+    adamw_gbar_sweep<true>(p, gbar, scale, pl);
 }
 
 __global__ __launch_bounds__(NT_AUX_BLOCK) void k_copy16(f32x4* dst, const u32x4* src, int64_t n16) {
@@ -1583,16 +1618,24 @@ static_assert(NT_BLOCK_DEFER * NT_ITERS_DEFER >= NT_BLOCK * NT_ITERS &&
                   NT_BLOCK_DEFER * NT_ITERS_DEFER >= NT_BLOCK_STATS_GBAR * NT_ITERS_STATS_GBAR,
               "the deferred class never has more tiles than the class it replaces: the workspace is sized by the latter");
 // tile slots per launch of the step kernel for the same classes (at least one, at most all)
-inline int64_t launch_tiles(int64_t J, int esize, int mode, bool gbar, int cls, int64_t ntiles) {
+inline int64_t launch_tiles(int64_t J, int esize, int mode, bool gbar, int cls, int64_t d, int64_t ntiles) {
   int64_t coords;
   if (J > NT_JCHUNK || cls != CLS_BASE)
     return ntiles;   // one launch, or generations of blocks: launch_step_shape knows the kernel's occupancy
   else if (mode == MODE_STATS)
     coords = gbar ? NT_CHUNK_STATS_GBAR : NT_CHUNK_STATS;
+  else if (mode == MODE_ADAMW)
+    coords = d < NT_LONG_COORDS ? NT_CHUNK_ADAMW : NT_CHUNK_ADAMW_LONG;
   else
-    coords = (mode == MODE_ADAMW) ? NT_CHUNK_ADAMW : NT_CHUNK_FULL;
+    coords = J * esize <= 8 ? NT_CHUNK_FULL_FEW : NT_CHUNK_FULL;
   const int64_t n = coords / tile_cfg(J, esize, mode, gbar, 0).coords();
   return (n < 1 || n > ntiles) ? ntiles : n;
+}
+// dynamic LDS of a kernel with blocks of 1024 threads, which decides how many of them a CU holds (see NT_ONE_BLOCK_LDS)
+inline unsigned one_block_lds(int64_t J, int esize, int mode, int64_t d) {
+  const bool one = mode == MODE_ADAMW ? J * esize >= 16 && d > (1ll << 23) && d < NT_LONG_COORDS
+                                      : J * esize >= (esize == 4 ? 12 : 16) && d >= (1ll << 25);
+  return one ? NT_ONE_BLOCK_LDS : 0;
 }
 // smallest tile any mode and gradient type uses for this J: sizes the workspace
 inline int64_t min_tile_coords(int64_t J) {
@@ -1660,28 +1703,29 @@ constexpr auto step_kernel() {
 // kernel writes the result when it is the step's last: the caller's only source for that, so that no step can end without one.
 template <class GT, int J_T, int MODE, int BLOCK, int ITERS, bool TABLE, bool GBAR, bool FEW_TILES, bool DEFER_T = false,
           bool COORD = true>
-bool launch_tiles_of(const StepParams& p, int64_t nfull, int64_t ntiles, int64_t slot0, int64_t slot1, const Finish& fin,
-                     unsigned grid, hipStream_t st) {
+bool launch_tiles_of(const StepParams& p, int64_t nfull, int64_t ntiles, int64_t slot0, unsigned grid, const Finish& fin,
+                     hipStream_t st) {
+  const unsigned lds = BLOCK == 1024 ? one_block_lds(p.J, GT::ESIZE, MODE, p.d) : 0;
   if constexpr (MODE == MODE_ADAMW || FEW_TILES) {
     if (fin.out) {
-      hipLaunchKernelGGL((k_step_end<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, DEFER_T>), dim3(grid), dim3(BLOCK), 0, st, p,
-                         nfull, ntiles, slot0, slot1, fin);
+      hipLaunchKernelGGL((k_step_end<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, DEFER_T>), dim3(grid), dim3(BLOCK), lds, st, p,
+                         nfull, ntiles, slot0, fin);
       return true;
     }
   }
   if constexpr (MODE != MODE_ADAMW)
-    hipLaunchKernelGGL((k_step<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, DEFER_T, COORD>), dim3(grid), dim3(BLOCK), 0, st, p,
-                       nfull, ntiles, slot0, slot1);
+    hipLaunchKernelGGL((k_step<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, DEFER_T, COORD>), dim3(grid), dim3(BLOCK), lds, st, p,
+                       nfull, ntiles, slot0);
   return false;
 }
 
 template <class GT, int MODE, bool TABLE, int BS, int IS, bool GBAR>
 hipError_t launch_step_shape(const StepParams& p, int cls, int64_t nfull, int64_t ntiles, const Finish& fin, bool& ended,
-                             int max_grid, hipStream_t st) {
+                             hipStream_t st) {
   const bool long_class = cls == CLS_LONG;
   constexpr bool WRITES = (MODE != MODE_STATS) || GBAR;
   const bool gbar = MODE == MODE_STATS && p.gbar != nullptr;
-  int64_t per_launch = launch_tiles(p.J, GT::ESIZE, MODE, gbar, cls, ntiles);
+  int64_t per_launch = launch_tiles(p.J, GT::ESIZE, MODE, gbar, cls, p.d, ntiles);
   if (WRITES && long_class) {
     // blocks that write per coordinate do so at the end of their lives: a launch holds whole generations of blocks
     // (as many as the chip runs at a time), so that all of them read together and write together
@@ -1709,12 +1753,12 @@ hipError_t launch_step_shape(const StepParams& p, int cls, int64_t nfull, int64_
   // AdamW only runs its launches from the last slots to the first: the launch with slot 0 writes the result (k_step_end), and
   // no result is to precede an update that has yet to be launched.  (Asking in the kernel for the last slot instead takes
   // scalar registers that the deferred kernels over pointer tables do not have: they would need scratch memory.)
+  if (per_launch > NT_MAX_GRID) per_launch = NT_MAX_GRID;
   const int64_t runs = (ntiles + per_launch - 1) / per_launch;
   for (int64_t run = 0; run < runs; ++run) {
     const int64_t slot0 = (MODE == MODE_ADAMW ? runs - 1 - run : run) * per_launch;
-    const int64_t slot1 = (ntiles - slot0 < per_launch) ? ntiles : slot0 + per_launch;
-    const unsigned grid = (unsigned)((slot1 - slot0 < max_grid) ? slot1 - slot0 : max_grid);
-#define NT_ARGS p, nfull, ntiles, slot0, slot1, fin, grid, st
+    const unsigned grid = (unsigned)(ntiles - slot0 < per_launch ? ntiles - slot0 : per_launch);
+#define NT_ARGS p, nfull, ntiles, slot0, grid, fin, st
 #define NT_CASE(JJ)                                                                                             \
   case JJ:                                                                                                      \
     if constexpr (WRITES && JJ * GT::ESIZE >= defer_row_bytes(MODE)) {                                          \
@@ -1757,29 +1801,27 @@ hipError_t launch_step_shape(const StepParams& p, int cls, int64_t nfull, int64_
 // picks the launch class (block size, sweeps per tile) that tile_cfg() describes
 template <class GT, int MODE, bool TABLE>
 hipError_t launch_step(const StepParams& p, int cls, int64_t nfull, int64_t ntiles, const Finish& fin, bool& ended,
-                       int grid, hipStream_t st) {
+                       hipStream_t st) {
   if constexpr (MODE == MODE_STATS) {
     // read-only statistics over a short vector borrow the kernels that can also store gbar (there is none to store)
     if (p.gbar || (cls == CLS_SHORT_STATS && p.J <= NT_JCHUNK))
       return launch_step_shape<GT, MODE, TABLE, NT_BLOCK_STATS_GBAR, NT_ITERS_STATS_GBAR, true>(p, cls, nfull, ntiles,
-                                                                                                 fin, ended, grid, st);
-    return launch_step_shape<GT, MODE, TABLE, NT_BLOCK_STATS, NT_ITERS_STATS, false>(p, cls, nfull, ntiles, fin, ended, grid,
-                                                                                      st);
+                                                                                                 fin, ended, st);
+    return launch_step_shape<GT, MODE, TABLE, NT_BLOCK_STATS, NT_ITERS_STATS, false>(p, cls, nfull, ntiles, fin, ended, st);
   } else if constexpr (MODE == MODE_ADAMW) {
-    return launch_step_shape<GT, MODE, TABLE, NT_BLOCK_ADAMW, NT_ITERS_ADAMW, true>(p, cls, nfull, ntiles, fin, ended, grid,
-                                                                                     st);
+    return launch_step_shape<GT, MODE, TABLE, NT_BLOCK_ADAMW, NT_ITERS_ADAMW, true>(p, cls, nfull, ntiles, fin, ended, st);
   } else {
-    return launch_step_shape<GT, MODE, TABLE, NT_BLOCK, NT_ITERS, true>(p, cls, nfull, ntiles, fin, ended, grid, st);
+    return launch_step_shape<GT, MODE, TABLE, NT_BLOCK, NT_ITERS, true>(p, cls, nfull, ntiles, fin, ended, st);
   }
 }
 
 template <class GT, bool TABLE>
 hipError_t launch_step_mode(int mode, const StepParams& p, int cls, int64_t nfull, int64_t ntiles, const Finish& fin,
-                            bool& ended, int grid, hipStream_t st) {
+                            bool& ended, hipStream_t st) {
   switch (mode) {
-    case MODE_FULL: return launch_step<GT, MODE_FULL, TABLE>(p, cls, nfull, ntiles, fin, ended, grid, st);
-    case MODE_STATS: return launch_step<GT, MODE_STATS, TABLE>(p, cls, nfull, ntiles, fin, ended, grid, st);
-    default: return launch_step<GT, MODE_ADAMW, TABLE>(p, cls, nfull, ntiles, fin, ended, grid, st);
+    case MODE_FULL: return launch_step<GT, MODE_FULL, TABLE>(p, cls, nfull, ntiles, fin, ended, st);
+    case MODE_STATS: return launch_step<GT, MODE_STATS, TABLE>(p, cls, nfull, ntiles, fin, ended, st);
+    default: return launch_step<GT, MODE_ADAMW, TABLE>(p, cls, nfull, ntiles, fin, ended, st);
   }
 }
 
@@ -1963,15 +2005,13 @@ static int enqueue_step(const void* grads, bool table, nt_dtype gdtype, int64_t 
       fin.out = result_dev;
     }
     const int64_t nfull = d / tc;
-    const int64_t max_grid = (int64_t)cu_count() * NT_BLOCKS_PER_CU;
-    const int grid = (int)(ntiles < max_grid ? ntiles : max_grid);
     hipError_t e;
     if (table)
-      e = (gdtype == NT_F32) ? launch_step_mode<F32, true>(mode, p, cls, nfull, ntiles, fin, ended, grid, st)
-                             : launch_step_mode<BF16, true>(mode, p, cls, nfull, ntiles, fin, ended, grid, st);
+      e = (gdtype == NT_F32) ? launch_step_mode<F32, true>(mode, p, cls, nfull, ntiles, fin, ended, st)
+                             : launch_step_mode<BF16, true>(mode, p, cls, nfull, ntiles, fin, ended, st);
     else
-      e = (gdtype == NT_F32) ? launch_step_mode<F32, false>(mode, p, cls, nfull, ntiles, fin, ended, grid, st)
-                             : launch_step_mode<BF16, false>(mode, p, cls, nfull, ntiles, fin, ended, grid, st);
+      e = (gdtype == NT_F32) ? launch_step_mode<F32, false>(mode, p, cls, nfull, ntiles, fin, ended, st)
+                             : launch_step_mode<BF16, false>(mode, p, cls, nfull, ntiles, fin, ended, st);
     if (e != hipSuccess) return hip_code(e);
   }
   if (ended) return NT_OK;
@@ -2006,8 +2046,8 @@ static int enqueue_adamw_gbar(const float* gbar, int64_t d, float* w, float* m, 
   const int64_t per_launch = NT_CHUNK_ADAMW_GBAR / per_block;
   for (int64_t b0 = 0; b0 < nblocks; b0 += per_launch) {
     const int64_t grid = (nblocks - b0 < per_launch) ? nblocks - b0 : per_launch;
-    hipLaunchKernelGGL(k_adamw_gbar, dim3((unsigned)grid), dim3(NT_AUX_BLOCK), 0, st, p, gbar, (float)grad_scale,
-                       result_dev, b0);
+    hipLaunchKernelGGL(k_adamw_gbar, dim3((unsigned)grid), dim3(NT_AUX_BLOCK), d >= (1ll << 25) ? NT_ONE_BLOCK_LDS : 0, st, p,
+                       gbar, (float)grad_scale, result_dev, b0);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_code(e);
   }
@@ -2230,7 +2270,7 @@ int normtest_calib_copy(void* dst, const void* src, size_t bytes, void* hip_stre
   if (bytes == 0) return NT_OK;
   const int64_t n16 = (int64_t)(bytes / 16);
   const int64_t want = (n16 + NT_AUX_BLOCK - 1) / NT_AUX_BLOCK;
-  const int64_t max_grid = (int64_t)cu_count() * NT_BLOCKS_PER_CU;
+  const int64_t max_grid = (int64_t)cu_count() * NT_COPY_BLOCKS_PER_CU;
   const int grid = (int)(want < max_grid ? want : max_grid);
   hipLaunchKernelGGL(k_copy16, dim3(grid), dim3(NT_AUX_BLOCK), 0, (hipStream_t)hip_stream, (f32x4*)dst,
                      (const u32x4*)src, n16);
@@ -2261,7 +2301,7 @@ int normtest_calib_streams(void* buf, size_t buf_bytes, int64_t coords, int row_
   const int64_t per_block = NT_AUX_BLOCK;
   int64_t per_launch = launch_coords > 0 ? launch_coords / 4 / per_block * per_block : ngroups;
   if (per_launch < per_block) per_launch = per_block;
-  const int64_t max_grid = (int64_t)cu_count() * NT_BLOCKS_PER_CU;
+  const int64_t max_grid = (int64_t)cu_count() * NT_COPY_BLOCKS_PER_CU;
   hipStream_t st = (hipStream_t)hip_stream;
   bool found = false;
 #define NT_CALIB(R8, R16, W, RMW)                                                                                  \
