@@ -72,7 +72,17 @@
 #define NT_MANY_LONG_COORDS_32 (1ll << 24)
 #define NT_BLOCK_MANY_SHORT 256
 #define NT_ITERS_MANY_SHORT 2
-#define NT_BLOCK_LARGE_STATS 256 // J > 16, statistics only (nothing written per coordinate): short tiles, so that a
+// J > 16, every mode, in the shortest vectors, whose tiles leave each CU at most a block or two: the same tile as one sweep of
+// 512 threads, so that a block walks the rows once.  Shape above -> this one, us: fused step of 17 / 64 / 512 bf16 rows at d =
+// 100,003 9.2 / 18.7 / 103 -> 7.6 / 13.7 / 66, at 3e5 10.1 / 18.0 / 89.7 -> 8.4 / 14.0 / 62.7, at 5e5 11.8 / 19.4 / 95.4 -> 9.8 / 15.3 /
+// 78.1, at 7e5 14.0 / 24.3 / 129 and 12.1 / 23.9 / 129, at 1e6 14.7 / 26.2 / 154 and 13.2 / 26.4 / 159, at 2e6 20 rows 23.7 and 25.5;
+// of 17 / 32 / 128 fp32 rows at 30,000 10.1 / 11.9 / 30.8 -> 8.5 / 9.6 / 24.0, at 1e6 18.6 / 27.1 and 20.6 / 27.7; AdamW only, 64 bf16
+// rows, 13.6 -> 10.0 at 3e5, 22.9 and 23.8 at 1e6.
+#define NT_BLOCK_MANY_TINY 512
+#define NT_ITERS_MANY_TINY 1
+#define NT_MANY_TINY_COORDS (1ll << 19)
+#define NT_MANY_TINY_COORDS_32 (1ll << 20)   // up to 32 bf16 rows, unless AdamW only
+#define NT_BLOCK_LARGE_STATS 256 // J > 16, statistics only otherwise (nothing written per coordinate): short tiles, so that a
 #define NT_ITERS_LARGE_STATS 2   // vector of a few million coordinates still gives every CU several blocks
 #define NT_MAX_GRID (1ll << 21)  // blocks per launch at most: HIP's limit is on the threads, 2^32 - 1
 #define NT_COPY_BLOCKS_PER_CU 4096  // copy and yardstick: grid = min(blocks of work, CUs * this); blocks stride beyond that
@@ -664,8 +674,9 @@ __device__ inline void coord_test(float thr, float c, float gb, LaneAcc& acc) {
 //   chunk sum of squares  a_b = q + K (2 sr + nb K)
 // and the chunk is merged into the running (S, M2) with  S += sb,  M2 += M2_b + delta^2 na nb/(na + nb),
 // delta = mean_b - mean_a.  Returns the shift for the next chunk.
-__device__ inline float chunk_merge(bool first, int na, int nb, float K, double sb, float q, double& S, float& M2,
-                                    float& a) {
+// inv_na, inv_n: 1/na and 1/(na + nb).
+__device__ inline float chunk_merge(bool first, int na, int nb, double inv_na, double inv_n, float K, double sb, float q,
+                                    double& S, float& M2, float& a) {
   const double sr = __builtin_fma(-(double)K, (double)nb, sb);
   const float srf = (float)sr;
   const float nbf = (float)nb;
@@ -677,11 +688,11 @@ __device__ inline float chunk_merge(bool first, int na, int nb, float K, double 
     M2 = M2b;
   } else {
     const float coef = ((float)na * nbf) / (float)(na + nb);
-    const float delta = (float)(((double)K - S * (1.0 / (double)na)) + sr * inv_nb);
+    const float delta = (float)(((double)K - S * inv_na) + sr * inv_nb);
     M2 = M2 + __builtin_fmaf(delta * delta, coef, M2b);
     S = S + sb;
   }
-  return (float)(S * (1.0 / (double)(na + nb)));
+  return (float)(S * inv_n);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -721,7 +732,7 @@ __device__ inline void coord_stats_generic(const StepParams& p, int64_t i, doubl
       sb += (double)x;
       q = __builtin_fmaf(r, r, q);
     }
-    K = chunk_merge(na == 0, na, nb, K, sb, q, S, M2, a);
+    K = chunk_merge(na == 0, na, nb, 1.0 / (double)na, 1.0 / (double)(na + nb), K, sb, q, S, M2, a);
     na += nb;
   }
 }
@@ -1141,7 +1152,8 @@ __device__ inline TileEnd tile_multi(const StepParams& p, int64_t tile, double (
 #pragma unroll 1
   for (int it = 0; it < ITERS; ++it) {
     const Place pl = {tile * TILE + (int64_t)it * BLOCK * VEC, threadIdx.x * VEC};
-    if (PART && pl.s0 >= p.d) break;
+    // a sweep or a wave that lies wholly past d adds nothing, and has no means to leave for the update
+    if (PART && pl.s0 + (int64_t)__builtin_amdgcn_readfirstlane(threadIdx.x) * VEC >= p.d) break;
     double S[VEC], sb[VEC];
     float M2[VEC], a[VEC], K[VEC], q[VEC];
 #pragma unroll
@@ -1158,7 +1170,8 @@ __device__ inline TileEnd tile_multi(const StepParams& p, int64_t tile, double (
     chunk_accumulate<GT, false, 1>(raw, at, K, sb, q);
     chunk_accumulate<GT, PART, NT_MCHUNK - 1>(raw + 1, at, K, sb, q);
 #pragma unroll
-    for (int e = 0; e < VEC; ++e) K[e] = chunk_merge(true, 0, NT_MCHUNK, K[e], sb[e], q[e], S[e], M2[e], a[e]);
+    for (int e = 0; e < VEC; ++e) K[e] = chunk_merge(true, 0, NT_MCHUNK, 0.0, 1.0 / NT_MCHUNK, K[e], sb[e], q[e], S[e], M2[e], a[e]);
+    double inv_j0 = 1.0 / NT_MCHUNK;
     int j0 = NT_MCHUNK;
 #pragma unroll 1
     for (; j0 + NT_MCHUNK <= J; j0 += NT_MCHUNK) {
@@ -1166,8 +1179,11 @@ __device__ inline TileEnd tile_multi(const StepParams& p, int64_t tile, double (
       if (WAITS && J > 32) chunk_wait();
       chunk_clear<VEC>(sb, q);
       chunk_accumulate<GT, PART, NT_MCHUNK>(raw, at, K, sb, q);
+      const double inv_n = 1.0 / (double)(j0 + NT_MCHUNK);
 #pragma unroll
-      for (int e = 0; e < VEC; ++e) K[e] = chunk_merge(false, j0, NT_MCHUNK, K[e], sb[e], q[e], S[e], M2[e], a[e]);
+      for (int e = 0; e < VEC; ++e)
+        K[e] = chunk_merge(false, j0, NT_MCHUNK, inv_j0, inv_n, K[e], sb[e], q[e], S[e], M2[e], a[e]);
+      inv_j0 = inv_n;
     }
     if (j0 < J) {
       const int nb = J - j0;
@@ -1175,7 +1191,8 @@ __device__ inline TileEnd tile_multi(const StepParams& p, int64_t tile, double (
       chunk_clear<VEC>(sb, q);
       accumulate_last<GT, PART, 8>(nb, raw, at, K, sb, q);
 #pragma unroll
-      for (int e = 0; e < VEC; ++e) K[e] = chunk_merge(false, j0, nb, K[e], sb[e], q[e], S[e], M2[e], a[e]);
+      for (int e = 0; e < VEC; ++e)
+        K[e] = chunk_merge(false, j0, nb, inv_j0, 0.0, K[e], sb[e], q[e], S[e], M2[e], a[e]);   // the last: K is not used again
     }
     float gb[VEC];
 #pragma unroll
@@ -1590,24 +1607,26 @@ constexpr int64_t plain_coords(int esize, int J, int mode) {
 }
 constexpr int defer_row_bytes(int mode) { return mode == MODE_ADAMW ? NT_DEFER_ROW_BYTES_ADAMW : NT_DEFER_ROW_BYTES; }
 // Which launch class a call takes beside its row count, dtype and mode: CLS_LONG, the classes for long vectors
-// (large tiles, state update deferred, one generation of blocks per launch); CLS_SHORT_STATS, read-only statistics
-// of up to 16 rows over a short vector; else CLS_BASE.  esize: bytes per gradient element; d_whole: length of the
+// (large tiles, state update deferred, one generation of blocks per launch); CLS_SHORT, read-only statistics of up to
+// 16 rows over a short vector, and anything of more rows over a shorter one; else CLS_BASE.  esize: bytes per gradient element; d_whole: length of the
 // vector the call is a part of (its own d unless the caller said otherwise), so that the parts of a vector and the
 // vector itself are cut into the same tiles.
-enum { CLS_BASE = 0, CLS_LONG = 1, CLS_SHORT_STATS = 2 };
+enum { CLS_BASE = 0, CLS_LONG = 1, CLS_SHORT = 2 };
 inline int launch_class(int64_t J, int esize, int mode, bool gbar, int64_t d_whole) {
-  if (mode == MODE_STATS && !gbar) return (J <= NT_JCHUNK && d_whole < NT_STATS_SHORT_COORDS) ? CLS_SHORT_STATS : CLS_BASE;
+  if (J > NT_JCHUNK && d_whole <= (J <= 32 && esize == 2 && mode != MODE_ADAMW ? NT_MANY_TINY_COORDS_32 : NT_MANY_TINY_COORDS)) return CLS_SHORT;
+  if (mode == MODE_STATS && !gbar) return (J <= NT_JCHUNK && d_whole < NT_STATS_SHORT_COORDS) ? CLS_SHORT : CLS_BASE;
   if (J > NT_JCHUNK) return d_whole >= (J <= 32 ? NT_MANY_LONG_COORDS_32 : NT_MANY_LONG_COORDS) ? CLS_LONG : CLS_BASE;
   return (J * esize >= defer_row_bytes(mode) && d_whole >= NT_DEFER_COORDS) ? CLS_LONG : CLS_BASE;
 }
 inline TileCfg tile_cfg(int64_t J, int esize, int mode, bool gbar, int64_t d_whole) {
   const int cls = launch_class(J, esize, mode, gbar, d_whole);
   if (J > NT_JCHUNK) {
+    if (cls == CLS_SHORT) return {NT_BLOCK_MANY_TINY, NT_ITERS_MANY_TINY};
     if (mode == MODE_STATS && !gbar) return {NT_BLOCK_LARGE_STATS, NT_ITERS_LARGE_STATS};
     return cls == CLS_LONG ? TileCfg{NT_BLOCK_LARGE, NT_ITERS_LARGE} : TileCfg{NT_BLOCK_MANY_SHORT, NT_ITERS_MANY_SHORT};
   }
   if (cls == CLS_LONG) return {NT_BLOCK_DEFER, NT_ITERS_DEFER};
-  if (mode == MODE_STATS && (gbar || cls == CLS_SHORT_STATS)) return {NT_BLOCK_STATS_GBAR, NT_ITERS_STATS_GBAR};
+  if (mode == MODE_STATS && (gbar || cls == CLS_SHORT)) return {NT_BLOCK_STATS_GBAR, NT_ITERS_STATS_GBAR};
   if (mode == MODE_STATS) return {NT_BLOCK_STATS, NT_ITERS_STATS};
   if (mode == MODE_ADAMW) return {NT_BLOCK_ADAMW, NT_ITERS_ADAMW};
   return {NT_BLOCK, NT_ITERS};
@@ -1779,11 +1798,13 @@ hipError_t launch_step_shape(const StepParams& p, int cls, int64_t nfull, int64_
       NT_CASE(2) NT_CASE(3) NT_CASE(4) NT_CASE(5) NT_CASE(6) NT_CASE(7) NT_CASE(8) NT_CASE(9)
       NT_CASE(10) NT_CASE(11) NT_CASE(12) NT_CASE(13) NT_CASE(14) NT_CASE(15) NT_CASE(16)
       default:
-        if constexpr (MODE == MODE_STATS && !GBAR) {
-          ended = launch_tiles_of<GT, 0, MODE, NT_BLOCK_LARGE_STATS, NT_ITERS_LARGE_STATS, TABLE, false, true>(NT_ARGS);
+        if (cls == CLS_SHORT) {
+          ended = launch_tiles_of<GT, 0, MODE, NT_BLOCK_MANY_TINY, NT_ITERS_MANY_TINY, TABLE, WRITES, true>(NT_ARGS);
+        } else if constexpr (MODE == MODE_STATS && !GBAR) {
+          ended = launch_tiles_of<GT, 0, MODE, NT_BLOCK_LARGE_STATS, NT_ITERS_LARGE_STATS, TABLE, false, false>(NT_ARGS);
         } else {
           if (!long_class)
-            ended = launch_tiles_of<GT, 0, MODE, NT_BLOCK_MANY_SHORT, NT_ITERS_MANY_SHORT, TABLE, true, true>(NT_ARGS);
+            ended = launch_tiles_of<GT, 0, MODE, NT_BLOCK_MANY_SHORT, NT_ITERS_MANY_SHORT, TABLE, true, false>(NT_ARGS);
           else if (p.J <= NT_FEW_ROWS)
             ended = launch_tiles_of<GT, 0, MODE, NT_BLOCK_FEW, NT_ITERS_FEW, TABLE, true, false>(NT_ARGS);
           else
@@ -1804,7 +1825,7 @@ hipError_t launch_step(const StepParams& p, int cls, int64_t nfull, int64_t ntil
                        hipStream_t st) {
   if constexpr (MODE == MODE_STATS) {
     // read-only statistics over a short vector borrow the kernels that can also store gbar (there is none to store)
-    if (p.gbar || (cls == CLS_SHORT_STATS && p.J <= NT_JCHUNK))
+    if (p.gbar || (cls == CLS_SHORT && p.J <= NT_JCHUNK))
       return launch_step_shape<GT, MODE, TABLE, NT_BLOCK_STATS_GBAR, NT_ITERS_STATS_GBAR, true>(p, cls, nfull, ntiles,
                                                                                                  fin, ended, st);
     return launch_step_shape<GT, MODE, TABLE, NT_BLOCK_STATS, NT_ITERS_STATS, false>(p, cls, nfull, ntiles, fin, ended, st);
