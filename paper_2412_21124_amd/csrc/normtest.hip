@@ -65,11 +65,10 @@
 #define NT_ITERS_DEFER 16
 #define NT_DEFER_UNROLL 1        // row sweeps in flight per lane in that class
 #define NT_GENS_DEFER 1          // generations of blocks per launch in that class (two: -7 .. -10 %)
-// J > 16, modes that write per coordinate: the shapes above from about one generation of blocks on (up to 32 rows,
-// where a generation is short-lived and a half-empty one costs more, from two); shorter vectors in one launch of
-// short tiles, else a few large blocks would have the chip to themselves (512 rows, d = 2^18: 607 -> 92 us).
-#define NT_MANY_LONG_COORDS (3ll << 21)
-#define NT_MANY_LONG_COORDS_32 (1ll << 24)
+// J > 16, modes that write per coordinate: the shapes above where a generation of blocks, NT_GENERATION coordinates on 256 CUs, or
+// several are nearly full (generations_pay); else one launch of short tiles, of which the chip takes any number (512 rows, d =
+// 2^18: 607 -> 92 us).
+#define NT_GENERATION (1ll << 23)
 #define NT_BLOCK_MANY_SHORT 256
 #define NT_ITERS_MANY_SHORT 2
 // J > 16, every mode, in the shortest vectors, whose tiles leave each CU at most a block or two: the same tile as one sweep of
@@ -1241,15 +1240,16 @@ __device__ inline TileEnd run_tile(bool part, const StepParams& p, int64_t tile,
 // More than 16 rows: whether whole tiles run a copy of the walk of their own.  In the copy for part tiles every row is moved to
 // its place (settle), which costs a short walk: statistics of 17 / 64 fp32 rows at d = 1e6 16.8 / 43.5 us in it, 15.5 / 42.1
 // beside it; 64 / 256 bf16 rows in tables 24.4 / 84.3 and 23.3 / 79.5, AdamW only, 20 bf16 rows 11.7 and 11.0.  It is the better
-// one where the delay keeps the blocks of a full generation in step: fused step of 32 / 64 fp32 rows at d = 3e7 731 / 1334 us in
-// it, 745 / 1350 beside it, and AdamW only from 33 bf16 rows on (64 rows, d = 2^24: 403 and 434 us).  (Statistics of 17 to 32
+// one with AdamW only from 33 bf16 rows on, where the delay keeps the blocks of a generation in step (64 rows, d = 2^24: 403 and
+// 434 us).  (With fp32 rows it gains 1 to 1.5 % in full generations, 64 rows at 3e7 1334 and 1350 us, but a part of a vector that
+// leaves most CUs idle loses more: 512 unpadded rows of 909,510 coordinates 854 us in it, 665 beside it.  Statistics of 17 to 32
 // fp32 rows at 2^24 take 1 % more in either than when a part tile was loaded element by element.)  Short steps over tables that
 // write their own result have the one copy: the second would need scratch memory.
 template <class GT, int MODE, int BLOCK, int ITERS, bool TABLE, bool END>
 __device__ inline bool whole_copy(int J) {
   constexpr bool LONG = BLOCK * ITERS == NT_BLOCK_LARGE * NT_ITERS_LARGE;
   if (TABLE && END && !LONG) return false;
-  return GT::ESIZE == 4 ? !LONG || MODE == MODE_ADAMW || J <= NT_FEW_ROWS : MODE != MODE_ADAMW || J <= 32;
+  return GT::ESIZE == 4 || MODE != MODE_ADAMW || J <= 32;
 }
 
 // GBAR = false compiles the gbar store out (statistics-only launch class, so that sweeps can overlap).
@@ -1612,10 +1612,21 @@ constexpr int defer_row_bytes(int mode) { return mode == MODE_ADAMW ? NT_DEFER_R
 // vector the call is a part of (its own d unless the caller said otherwise), so that the parts of a vector and the
 // vector itself are cut into the same tiles.
 enum { CLS_BASE = 0, CLS_LONG = 1, CLS_SHORT = 2 };
+// More than 16 rows: whether a vector of d coordinates is better walked in whole generations of blocks than in short tiles.  What
+// is left over after the last full generation runs by itself on a few CUs, with two waves a block.  Generations against short
+// tiles, us, fused step: 64 bf16 rows 179 / 178 at d = 6.4e6, 177 / 189 at 7e6, 291 / 226 at 8.4e6 (just past one), 298 / 274 at 1e7,
+// 319 / 310 at 1.15e7, 326 / 348 at 1.3e7, 478 / 448 at 1.68e7 (just past two), 486 / 482 at 1.75e7, 504 / 517 at 1.9e7, 604 / 681 at
+// 2.5e7; 256 rows 1021 / 744 at 8.4e6, 1116 / 1020 at 1.15e7, 1132 / 1142 at 1.3e7; 64 fp32 rows 481 / 449 at 9e6, 583 / 641 at 1.3e7;
+// 24 bf16 rows, whose generations are short-lived, 237 / 206 at 1.68e7, 251 / 236 at 1.9e7, 263 / 288 at 2.2e7.
+inline bool generations_pay(int64_t J, int esize, int64_t d) {
+  constexpr int64_t G = NT_GENERATION;
+  if (J <= 32) return d >= 2 * G && !(J > NT_FEW_ROWS && esize == 2 && d > 2 * G && d <= 2 * G + G / 4);
+  return d >= G * 13 / 16 && !(d > G && d <= G + (esize == 2 ? G * 3 / 8 : G / 4)) && !(esize == 2 && d > 2 * G && d <= 2 * G + G / 8);
+}
 inline int launch_class(int64_t J, int esize, int mode, bool gbar, int64_t d_whole) {
   if (J > NT_JCHUNK && d_whole <= (J <= 32 && esize == 2 && mode != MODE_ADAMW ? NT_MANY_TINY_COORDS_32 : NT_MANY_TINY_COORDS)) return CLS_SHORT;
   if (mode == MODE_STATS && !gbar) return (J <= NT_JCHUNK && d_whole < NT_STATS_SHORT_COORDS) ? CLS_SHORT : CLS_BASE;
-  if (J > NT_JCHUNK) return d_whole >= (J <= 32 ? NT_MANY_LONG_COORDS_32 : NT_MANY_LONG_COORDS) ? CLS_LONG : CLS_BASE;
+  if (J > NT_JCHUNK) return generations_pay(J, esize, d_whole) ? CLS_LONG : CLS_BASE;
   return (J * esize >= defer_row_bytes(mode) && d_whole >= NT_DEFER_COORDS) ? CLS_LONG : CLS_BASE;
 }
 inline TileCfg tile_cfg(int64_t J, int esize, int mode, bool gbar, int64_t d_whole) {
@@ -1653,7 +1664,7 @@ inline int64_t launch_tiles(int64_t J, int esize, int mode, bool gbar, int cls, 
 // dynamic LDS of a kernel with blocks of 1024 threads, which decides how many of them a CU holds (see NT_ONE_BLOCK_LDS)
 inline unsigned one_block_lds(int64_t J, int esize, int mode, int64_t d) {
   const bool one = mode == MODE_ADAMW ? J * esize >= 16 && d > (1ll << 23) && d < NT_LONG_COORDS
-                                      : J * esize >= (esize == 4 ? 12 : 16) && d >= (1ll << 25);
+                                      : J * esize >= (esize == 4 ? 12 : 16) && d > (esize == 4 ? 1ll << 24 : 1ll << 25);
   return one ? NT_ONE_BLOCK_LDS : 0;
 }
 // smallest tile any mode and gradient type uses for this J: sizes the workspace

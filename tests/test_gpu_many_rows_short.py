@@ -33,3 +33,29 @@ def test_same_outputs_on_both_sides_of_a_length(J, gdtype, edge, flags):
         outs.append(state)
     for a, b in zip(*outs):
         assert torch.equal(a[:edge], b[:edge])
+
+
+# just past a generation of blocks, and where the class for long vectors takes over again; one more coordinate, of zeros, on
+# the other side of the edge adds nothing
+@pytest.mark.parametrize("J,gdtype,edge", [(33, torch.bfloat16, (1 << 23) * 13 // 16 - 1), (33, torch.bfloat16, 1 << 23),
+                                           (40, torch.bfloat16, (1 << 23) * 11 // 8), (33, torch.float32, (1 << 23) * 5 // 4),
+                                           (21, torch.bfloat16, 1 << 24), (24, torch.bfloat16, (1 << 23) * 9 // 4),
+                                           (33, torch.bfloat16, (1 << 23) * 17 // 8), (20, torch.float32, (1 << 24) - 1)])
+@pytest.mark.parametrize("flags", [STATS | ADAMW, STATS | GBAR])
+def test_same_outputs_in_generations_and_in_short_tiles(J, gdtype, edge, flags):
+    g = torch.Generator(device=DEV).manual_seed(J)
+    rows = torch.empty((J, edge + 1), dtype=gdtype, device=DEV)
+    for r in rows:
+        r.copy_(torch.randn(edge + 1, generator=g, device=DEV) * 1e-2)
+    rows[:, edge] = 0
+    start = [torch.rand(edge + 1, generator=g, device=DEV) * 0.02 for _ in range(4)]
+    hy = B.make_hyper(lr=4e-4, step=10, b_k=256, b_max=8192, round_to=J, flags=flags)
+    outs, sums = [], []
+    for d in (edge, edge + 1):
+        state = [t.clone() for t in start]
+        sums.append(B.read_result(B.normtest_step(rows, *state[:3], hy, d=d, gbar_out=state[3])).as_dict())
+        outs.append(state)
+    for a, b in zip(*outs):
+        assert torch.equal(a[:edge], b[:edge])
+    for k in ("A", "B", "C"):   # fp32 terms of four coordinates, the same ones, added in fp64 in another order
+        assert sums[0][k] == pytest.approx(sums[1][k], rel=1e-13)
