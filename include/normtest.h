@@ -155,7 +155,8 @@ size_t normtest_workspace_bytes_for(nt_dtype gdtype, int64_t J, int64_t d, uint3
  * normtest_workspace_bytes_for(gdtype, J, d, hyper->flags) bytes, 8-byte aligned; contents irrelevant before; afterwards it holds the
  * call's per-tile partial sums in a private format, which only normtest_layer_stats reads.
  * result_dev: device or pinned-host nt_result, 8-byte aligned, written by the last kernel.
- * hip_stream: a hipStream_t (NULL = the default stream).
+ * hip_stream: a hipStream_t (NULL = the default stream).  It may belong to another device than the current one (a short step then
+ * ends in a second kernel, as under graph capture: the counters that save it are the current device's).
  *
  * Everything is enqueued on the stream; the result and the updated state are valid once the caller
  * has synchronised it.  A call enqueues kernel launches only (no memsets, copies or allocations): a long vector
@@ -194,7 +195,8 @@ int normtest_step_rows(const void* const* grad_rows_dev, nt_dtype gdtype, int64_
  * normtest_step, without `workspace`: the tile partial sums and the record of the step go to a 16 MiB array that
  * the library holds in each GPU's memory (a static __device__ array; no hipMalloc, hipFree or other allocating
  * call is made here, on any path).  Limits: d <= normtest_static_max_coords(J) (about 1.7e9 coordinates up to
- * 16 rows, 0.86e9 beyond), else NT_ERR_TOO_LARGE and nothing is enqueued.  The array keeps the last call's contents;
+ * 16 rows, 0.86e9 beyond), else NT_ERR_TOO_LARGE and nothing is enqueued.  The array is the current device's, so
+ * hip_stream has to be a stream of that device.  It keeps the last call's contents;
  * nothing in it has to be cleared between calls.  All calls on one GPU share it: two calls that overlap in time
  * on the same GPU (different streams, or graphs replayed concurrently) race and give wrong statistics; calls on
  * one stream, or ordered by events, are fine.  normtest_layer_stats cannot follow this call (it needs the

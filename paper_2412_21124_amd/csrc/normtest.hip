@@ -1954,13 +1954,23 @@ static int device_address(const void* symbol, PerDevice& cached, void** out) {
   return NT_OK;
 }
 
+// Whether a launch on st runs on the current device: the null stream and its two named forms do, other streams have a device of
+// their own.
+static bool on_current_device(hipStream_t st) {
+  if (st == nullptr || st == hipStreamLegacy || st == hipStreamPerThread) return true;
+  int current = 0;
+  hipDevice_t own = 0;
+  return hipGetDevice(&current) == hipSuccess && hipStreamGetDevice(st, &own) == hipSuccess && own == current;
+}
+
 // The next counter of this device, or false where there is none for this launch: a graph under capture would keep it and
-// replay beside a later call that is given the same one.
+// replay beside a later call that is given the same one, and the blocks of a launch on another device would count themselves in
+// memory that is not theirs.
 static bool next_ticket(hipStream_t st, uint32_t** out) {
   static PerDevice cached = {nullptr};
   hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
   void* base = nullptr;
-  if (hipStreamIsCapturing(st, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone ||
+  if (hipStreamIsCapturing(st, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone || !on_current_device(st) ||
       device_address(HIP_SYMBOL(tickets), cached, &base) != NT_OK) {
     (void)hipGetLastError();
     return false;

@@ -1,0 +1,81 @@
+"""What a call launches, seen without a GPU: the library runs on a runtime that only prints its launches (fake_hip.c), in a process
+of its own."""
+from __future__ import annotations
+
+import json
+import os
+import re
+import subprocess
+import sys
+
+import pytest
+
+from paper_2412_21124_amd import binding as B
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+STATS, ADAMW, GBAR, COORD = B.NT_DO_STATS, B.NT_DO_ADAMW, B.NT_WRITE_GBAR, B.NT_COORD_TEST
+FULL = STATS | ADAMW
+
+# calls from stdin, one JSON list per line; fabricated pointers, as nothing is ever dereferenced
+CLIENT = """
+import ctypes, json, struct, sys
+fake = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
+lib = ctypes.CDLL(sys.argv[2])
+vp, i64 = ctypes.c_void_p, ctypes.c_int64
+for line in sys.stdin:
+    c = json.loads(line)
+    fake.fake_set(c["device"], c["capture"])
+    hyper = struct.pack("6d4qiI", 1e-3, 0.9, 0.95, 1e-8, 0.1, 0.1, 1, 64, 0, 1, 1, c["flags"])
+    shard = struct.pack("2i2q", 0, 1, 0, c["whole"]) if c["whole"] else None
+    J, d, g = c["J"], c["d"], c["gdtype"]
+    tail = (vp(0x2000), vp(0x3000), vp(0x4000), vp(0x5000), hyper, shard, vp(0x6000), ctypes.c_size_t(1 << 40), vp(0x7000),
+            vp(c["stream"]))
+    if c["table"]:
+        rc = lib.normtest_step_rows(vp(0x1000), g, i64(J), i64(d), *tail)
+    else:
+        rc = lib.normtest_step(vp(0x1000), g, i64(J), i64(d), i64(d), *tail)
+    print("rc", rc, flush=True)
+"""
+
+
+def _call(J, gdtype, d, flags, whole=0, table=False, device=0, stream=0, capture=0):
+    return dict(J=J, gdtype=gdtype, d=d, flags=flags, whole=whole, table=table, device=device, stream=stream, capture=capture)
+
+
+@pytest.fixture(scope="module")
+def launches(tmp_path_factory):
+    """Function from a list of calls to the launches of each: (kernel, template arguments, blocks, threads, dynamic LDS)."""
+    fake = str(tmp_path_factory.mktemp("fake") / "libfakehip.so")
+    subprocess.run(["gcc", "-std=gnu99", "-Wall", "-Wextra", "-Werror", "-shared", "-fPIC", os.path.join(HERE, "fake_hip.c"), "-o", fake],
+                   check=True)
+
+    def run(calls):
+        out = subprocess.run([sys.executable, "-c", CLIENT, fake, B.lib()._name], check=True, capture_output=True, text=True,
+                             input="".join(json.dumps(c) + "\n" for c in calls)).stdout
+        got, now = [], []
+        for line in out.splitlines():
+            if line.startswith("rc "):
+                assert line == "rc 0"
+                got.append(now)
+                now = []
+            else:
+                name, grid, block, lds = line.split()
+                now.append((re.search(r"\d(k_[a-z_0-9]*[a-z])", name).group(1), re.findall(r"L[ib](\d+)E", name), int(grid), int(block),
+                            int(lds)))
+        assert len(got) == len(calls) and not now
+        return got
+
+    return run
+
+
+def _names(step):
+    return [k[0] for k in step]
+
+
+# A step of a few tiles counts its blocks in memory of the library, which is a device's own.  On a stream of another device than
+# the current one, and in a graph, it takes the reduction kernel instead.
+def test_counters_are_those_of_the_streams_device(launches):
+    call = dict(J=4, gdtype=B.NT_F32, d=100_000, flags=FULL)
+    got = launches([_call(**call), _call(**call, stream=1), _call(**call, stream=3 << 16, device=3), _call(**call, stream=1 << 16),
+                    _call(**call, stream=2 << 16, device=1), _call(**call, capture=1)])
+    assert [_names(s) for s in got] == [["k_step_end"]] * 3 + [["k_step", "k_finalize"]] * 3
