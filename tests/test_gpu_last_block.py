@@ -22,8 +22,9 @@ def _hyper(flags):
 
 class _Calls:
     """K inputs of one size, each with a state, a workspace full of garbage and a pointer table of its own."""
-    def __init__(self, J, gdtype, d, flags):
+    def __init__(self, J, gdtype, d, flags, whole=0):
         self.hy, self.d = _hyper(flags), d
+        self.shard = B.nt_shard_info(0, 1, 0, whole) if whole else None   # a part of a longer vector
         self.grads = [(torch.randn(J, d, device=DEV) * 1e-2 * (k + 1)).to(gdtype) for k in range(K)]
         self.rows = [[g[j] for j in range(J)] for g in self.grads]
         self.tables = [B.make_row_table(r) for r in self.rows]
@@ -32,12 +33,13 @@ class _Calls:
 
     def matrix(self, k, result, stream=None):
         w, m, v, gbar = self.state[k]
-        B.normtest_step(self.grads[k], w, m, v, self.hy, gbar_out=gbar, workspace=self.ws[k], result=result, stream=stream)
+        B.normtest_step(self.grads[k], w, m, v, self.hy, shard=self.shard, gbar_out=gbar, workspace=self.ws[k], result=result,
+                        stream=stream)
 
     def table(self, k, result, stream=None):
         w, m, v, gbar = self.state[k]
-        B.normtest_step_rows(self.rows[k], w, m, v, self.hy, table=self.tables[k], gbar_out=gbar, workspace=self.ws[k],
-                             result=result, stream=stream)
+        B.normtest_step_rows(self.rows[k], w, m, v, self.hy, table=self.tables[k], shard=self.shard, gbar_out=gbar,
+                             workspace=self.ws[k], result=result, stream=stream)
 
     def two_launches(self):
         """Result and outputs for every input from a captured step, which has a reduction kernel of its own."""
@@ -54,14 +56,17 @@ class _Calls:
         return out
 
 
-# the fewest tiles, a ragged last one, both sides of the last count that ends in one launch, for each class of short vectors
-@pytest.mark.parametrize("J,gdtype,flags,tile,most", [(2, torch.float32, STATS | ADAMW, 4096, 256), (16, torch.bfloat16, STATS, 4096, 256),
-                                                      (8, torch.bfloat16, STATS | GBAR | COORD, 4096, 256),
-                                                      (20, torch.float32, STATS | ADAMW | GBAR, 2048, 128), (40, torch.bfloat16, STATS, 2048, 128)])
+# the fewest tiles, a ragged last one, both sides of the last count that ends in one launch, for each class of short vectors and,
+# beyond 16 rows, of short tiles
+@pytest.mark.parametrize("J,gdtype,flags,tile,most,whole", [
+    (2, torch.float32, STATS | ADAMW, 4096, 256, 0), (16, torch.bfloat16, STATS, 4096, 256, 0),
+    (8, torch.bfloat16, STATS | GBAR | COORD, 4096, 256, 0), (20, torch.float32, STATS | ADAMW | GBAR, 2048, 128, 0),
+    (40, torch.bfloat16, STATS, 2048, 128, 0), (24, torch.bfloat16, STATS | ADAMW | GBAR, 2048, 128, 1 << 22),
+    (33, torch.float32, STATS | GBAR, 2048, 128, 1 << 22), (19, torch.float32, STATS, 2048, 128, 1 << 30)])
 @pytest.mark.parametrize("past", [None, -1, 0, 1])
-def test_bits_of_two_launches(J, gdtype, flags, tile, most, past):
+def test_bits_of_two_launches(J, gdtype, flags, tile, most, whole, past):
     tiles = 2 if past is None else most + past
-    c = _Calls(J, gdtype, tiles * tile - 5, flags)
+    c = _Calls(J, gdtype, tiles * tile - 5, flags, whole)
     want = c.two_launches()
     results = torch.zeros(2 * K * 20, B.RESULT_BYTES, dtype=torch.uint8, device=DEV)
     for i in range(results.shape[0]):   # back to back, every input after another one

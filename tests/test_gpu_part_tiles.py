@@ -25,7 +25,8 @@ def _step(rows, state, d, flags, shard, table):
     return B.read_result(res).as_dict(), (w, m, v, gbar)
 
 
-@pytest.mark.parametrize("whole", [None, 1 << 26])   # the classes of short vectors, and of a part of a long one
+# the classes of short vectors, of a part of a longer one, and of a part of a long one
+@pytest.mark.parametrize("whole", [None, 1 << 22, 1 << 26])
 @pytest.mark.parametrize("flags", [STATS | ADAMW | GBAR, STATS | COORD, STATS | GBAR, ADAMW])
 @pytest.mark.parametrize("J,gdtype,table", [(4, torch.bfloat16, False), (5, torch.float32, True), (16, torch.bfloat16, True),
                                             (16, torch.float32, False), (19, torch.float32, False), (24, torch.bfloat16, True),

@@ -79,3 +79,14 @@ def test_counters_are_those_of_the_streams_device(launches):
     got = launches([_call(**call), _call(**call, stream=1), _call(**call, stream=3 << 16, device=3), _call(**call, stream=1 << 16),
                     _call(**call, stream=2 << 16, device=1), _call(**call, capture=1)])
     assert [_names(s) for s in got] == [["k_step_end"]] * 3 + [["k_step", "k_finalize"]] * 3
+
+
+# One tile, up to 16 rows in the classes of short vectors and beyond 16 rows wherever short tiles are walked, also as a part of a longer vector
+@pytest.mark.parametrize("gdtype", [B.NT_BF16, B.NT_F32])
+@pytest.mark.parametrize("flags", [FULL, STATS, STATS | GBAR, FULL | COORD])
+def test_one_tile_is_one_launch(launches, gdtype, flags):
+    calls = [_call(J, gdtype, d, flags, whole) for J in (2, 8, 16) for d in (1, 4096) for whole in (0, 1 << 20)]
+    calls += [_call(J, gdtype, d, flags, whole) for J in (17, 24, 33, 512) for d in (1, 2048) for whole in (0, 1 << 20, 1 << 22)]
+    if flags == STATS:   # short tiles at any length
+        calls += [_call(J, gdtype, 2048, flags, 1 << 30) for J in (17, 33, 512)]
+    assert [_names(s) for s in launches(calls)] == [["k_step_end"]] * len(calls)
