@@ -764,14 +764,11 @@ __device__ inline void coord_stats(const StepParams& p, int64_t i, double& S, fl
 
 // ---------------------------------------------------------------------------------------------
 // Loads and stores of a lane's VEC coordinates i0 .. i0+3.  part: the tile may reach past d.  A group that does is loaded by the
-// same instruction as every other, as the vector's last four coordinates, and moved down to where it belongs (Reach, settle);
-// what lies past d is then zero rows on zero state, which add exact zeros to every sum.  Its 1 to 3 values are stored one by
-// one.  The arithmetic is the same for whole and part tiles, hence the same bits.  Element by element, in a branch of its own,
+// same instruction as every other, as the vector's last four coordinates, and where there are sums moved down to where it belongs
+// (Reach, settle); what lies past d is then zero rows on zero state, which add exact zeros to every sum.  Its 1 to 3 values are
+// stored one by one.  The arithmetic is the same for whole and part tiles, hence the same bits.  Element by element, in a branch of its own,
 // such a group's rows were a chain of loads that a short vector waits for (d = 100,003: fused step of 16 bf16 rows 11.1 -> 9.9
 // us, of 512 rows 126 -> 106, statistics of 64 / 256 rows in tables 29.6 -> 15.2 and 119 -> 56).
-// AdamW only of at most 16 rows has one copy of the code, in which part tiles differ by block-uniform branches; elsewhere whole
-// tiles and part tiles have a copy each (with one, the fused step of 4 fp32 rows takes 7.4 instead of 6.7 us at d = 5000, of 8
-// bf16 rows 9843 instead of 9745 at 1.5e9; sweeps of statistics could not overlap).
 // ---------------------------------------------------------------------------------------------
 // coordinates i0 .. i0+3 that lie below d: 4 or fewer, 0 or negative where none does
 __device__ inline int below(int64_t d, int64_t i0) { return (int)(d - i0 < 4 ? (d - i0 < 0 ? 0 : d - i0) : 4); }
@@ -814,9 +811,29 @@ __device__ inline Reach reach(bool part, const StepParams& p, const Place& pl) {
   const uint32_t u = want < most ? want : most;
   return {s0, u, (int)(want - u)};
 }
-// Rows or state as loaded -> as they belong
-template <class GT, int N>
-__device__ inline void settle(bool part, const Reach& r, typename GT::raw_t* raw) {
+// The copies of the code of a tile.  AdamW only of at most 16 rows has one, in which part tiles differ by branches that are the same
+// for the whole block, and so has the class for long vectors beyond 20 bf16 rows, whose generations stay in step better (32 rows,
+// d = 2^24: 245 us against 256).  Elsewhere whole tiles and part tiles have a copy each (with one, the fused step of 4 fp32 rows
+// takes 7.4 instead of 6.7 us at d = 5000, of 8 bf16 rows 9843 instead of 9745 at 1.5e9; sweeps of statistics could not overlap); see
+// also whole_copy.
+template <class GT, int J_T, int MODE, int BLOCK, int ITERS, bool DEFER_T>
+constexpr bool one_copy() {
+  return MODE == MODE_ADAMW && !DEFER_T &&
+         (J_T > 0 || (GT::ESIZE == 2 && BLOCK == NT_BLOCK_LARGE && ITERS == NT_ITERS_LARGE));
+}
+// Whether a part tile's rows and state are moved to the lane's own coordinates once they are loaded.  Sums need that: what lies past
+// d has to be zeros.  With AdamW only a lane updates the coordinates that it has loaded, and stores its own ones among them (store4):
+// moving the rows is a long way through cold code (16 / 8 fp32 rows, d = 1000: 6.1 / 4.6 us with it, 4.7 / 3.8 without).
+// In the classes for long vectors tables keep it, where two copies without it would be given scratch memory.
+template <class GT, int J_T, int MODE, int BLOCK, int ITERS, bool TABLE, bool DEFER_T>
+constexpr bool moves_rows() {
+  return MODE != MODE_ADAMW || (J_T == 0 && TABLE && BLOCK * ITERS == NT_BLOCK_LARGE * NT_ITERS_LARGE &&
+                                !one_copy<GT, J_T, MODE, BLOCK, ITERS, DEFER_T>());
+}
+// Rows or state as loaded -> as they belong, if they are moved, and where the lane then is.
+template <class GT, int N, bool MOVES>
+__device__ inline Reach settle(bool part, const Place& pl, const Reach& r, typename GT::raw_t* raw) {
+  if constexpr (!MOVES) return r;
   if (__builtin_expect(part, 0)) {
 #pragma unroll
     for (int j = 0; j < N; ++j) {
@@ -824,6 +841,7 @@ __device__ inline void settle(bool part, const Reach& r, typename GT::raw_t* raw
       asm volatile("" : "+v"(raw[j]));   // one row after the other: interleaved, 16 fp32 rows need registers there are not
     }
   }
+  return {pl.s0, pl.u, 0};
 }
 
 // Rows j0, j0+1, ... at coordinate s0, one after the other: a matrix is walked by adding its row stride.
@@ -878,20 +896,23 @@ __device__ inline void load_rows(bool part, const StepParams& p, int j0, const R
   load_sweep<GT, TABLE, N, false>(part, p, j0, r, raw, nullptr);
 }
 
-__device__ inline void store4(bool part, const StepParams& p, float* base, const Place& pl, f32x4 x) {
+// Values of the coordinates at r.  Of a group that was loaded from the vector's end and not moved (r.sh > 0), the lane's own ones
+// are those from sh on.
+__device__ inline void store4(bool part, const StepParams& p, float* base, const Reach& r, f32x4 x) {
+  const Place pl = {r.s0, r.u};
   const int n = part ? below(p.d, pl.i0()) : 4;
-  if (__builtin_expect(n >= 4, 1)) {
+  if (__builtin_expect(n >= 4 && r.sh == 0, 1)) {
     st16(at(base, pl), x);
   } else {
     float NT_GLOBAL* q = at(base, pl);
 #pragma unroll
-    for (int e = 0; e < 3; ++e)
-      if (e < n) q[e] = x[e];
+    for (int e = 0; e < 4; ++e)
+      if (e >= r.sh && e < n) q[e] = x[e];
   }
 }
 
 // AdamW on VEC coordinates whose state was loaded as 16-byte vectors, then the stores.
-__device__ inline void adamw_store(bool part, const StepParams& p, const Place& pl, const float* gb,
+__device__ inline void adamw_store(bool part, const StepParams& p, const Reach& r, const float* gb,
                                    const u32x4* state) {
   f32x4 ow, om, ov;
 #pragma unroll
@@ -905,13 +926,14 @@ __device__ inline void adamw_store(bool part, const StepParams& p, const Place& 
     ov[e] = v;
   }
   if (__builtin_expect(!part, 1)) {
+    const Place pl = {r.s0, r.u};
     st16(at(p.w, pl), ow);
     st16(at(p.m, pl), om);
     st16(at(p.v, pl), ov);
   } else {
-    store4(true, p, p.w, pl, ow);
-    store4(true, p, p.m, pl, om);
-    store4(true, p, p.v, pl, ov);
+    store4(true, p, p.w, r, ow);
+    store4(true, p, p.m, r, om);
+    store4(true, p, p.v, r, ov);
   }
 }
 
@@ -997,15 +1019,15 @@ __device__ inline TileEnd tile_rows(bool part, const StepParams& p, int64_t tile
       // tiles are left free so that consecutive sweeps can overlap.
       __builtin_amdgcn_sched_barrier(0);
     }
-    settle<GT, J>(PART && part, at, raw);
+    const Reach out = settle<GT, J, MODE != MODE_ADAMW>(PART && part, pl, at, raw);
     float gb[VEC];
     sweep_rows<GT, J, MODE, COORD>(p, raw, gb, acc);
     if constexpr (EARLY) end = tile_reduce<BLOCK, true>(acc, red, p.partials, tile, ticket);
     if constexpr (MODE != MODE_STATS) {
-      settle<F32, 3>(PART && part, at, state);
-      adamw_store(PART && part, p, pl, gb, state);
+      settle<F32, 3, MODE != MODE_ADAMW>(PART && part, pl, at, state);
+      adamw_store(PART && part, p, out, gb, state);
     }
-    if (GBAR && p.gbar) store4(PART && part, p, p.gbar, pl, f32x4{gb[0], gb[1], gb[2], gb[3]});
+    if (GBAR && p.gbar) store4(PART && part, p, p.gbar, out, f32x4{gb[0], gb[1], gb[2], gb[3]});
   }
   if constexpr (MODE != MODE_ADAMW && !EARLY) end = tile_reduce<BLOCK, END>(acc, red, p.partials, tile, ticket);
   // AdamW-only tiles end with a block barrier like the other modes: the waves of a block then finish together
@@ -1014,7 +1036,7 @@ __device__ inline TileEnd tile_rows(bool part, const StepParams& p, int64_t tile
   return end;
 }
 
-template <int MODE, int BLOCK, int ITERS, bool GBAR, bool PART>
+template <int MODE, int BLOCK, int ITERS, bool GBAR, bool PART, bool MOVES>
 __device__ inline void deferred_sweeps(const StepParams& p, int64_t tile, const f32x4* gbs) {
   constexpr int VEC = 4;
   constexpr int TILE = BLOCK * VEC * ITERS;
@@ -1024,14 +1046,15 @@ __device__ inline void deferred_sweeps(const StepParams& p, int64_t tile, const 
     if (PART && pl.s0 >= p.d) break;
     const f32x4 g4 = gbs[it * BLOCK + threadIdx.x];   // this lane's own values: no barrier needed for them
     const float gb[VEC] = {g4[0], g4[1], g4[2], g4[3]};
+    Reach out = {pl.s0, pl.u, 0};
     if constexpr (MODE != MODE_STATS) {
       u32x4 state[3];
       const Reach at = reach(PART, p, pl);
       load_sweep<F32, false, 0, true>(PART, p, 0, at, nullptr, state);
-      settle<F32, 3>(PART, at, state);
-      adamw_store(PART, p, pl, gb, state);
+      out = settle<F32, 3, MOVES>(PART, pl, at, state);
+      adamw_store(PART, p, out, gb, state);
     }
-    if (GBAR && p.gbar) store4(PART, p, p.gbar, pl, g4);
+    if (GBAR && p.gbar) store4(PART, p, p.gbar, out, g4);
   }
 }
 
@@ -1039,7 +1062,7 @@ __device__ inline void deferred_sweeps(const StepParams& p, int64_t tile, const 
 // row has been read, then w, m, v of all sweeps are read and written in one go.  The memory system charges writes
 // sprinkled among reads several times their volume; gathered at the end of a block's life, and with all blocks
 // of a launch living at the same time (one generation per launch), they reach it as a dense burst.
-template <int MODE, int BLOCK, int ITERS, bool GBAR, bool PART, bool END>
+template <int MODE, int BLOCK, int ITERS, bool GBAR, bool PART, bool END, bool MOVES>
 __device__ inline TileEnd deferred_update(const StepParams& p, int64_t tile, double (*red)[NT_NV],
                                           const LaneAcc& acc, const f32x4* gbs, uint32_t* ticket) {
   constexpr int VEC = 4;
@@ -1053,9 +1076,9 @@ __device__ inline TileEnd deferred_update(const StepParams& p, int64_t tile, dou
   if (MODE != MODE_STATS || p.gbar) {
     // a copy of the loop for whole tiles: its sweeps overlap
     if (!PART || tile * TILE + TILE <= p.d)
-      deferred_sweeps<MODE, BLOCK, ITERS, GBAR, false>(p, tile, gbs);
+      deferred_sweeps<MODE, BLOCK, ITERS, GBAR, false, false>(p, tile, gbs);
     else
-      deferred_sweeps<MODE, BLOCK, ITERS, GBAR, true>(p, tile, gbs);
+      deferred_sweeps<MODE, BLOCK, ITERS, GBAR, true, MOVES>(p, tile, gbs);
   }
   return end;
 }
@@ -1075,12 +1098,12 @@ __device__ inline void tile_defer(const StepParams& p, int64_t tile, double (*re
     typename GT::raw_t raw[J];
     const Reach at = reach(PART, p, pl);
     load_rows<GT, TABLE, J>(PART, p, 0, at, raw);
-    settle<GT, J>(PART, at, raw);
+    settle<GT, J, MODE != MODE_ADAMW>(PART, pl, at, raw);
     float gb[VEC];
     sweep_rows<GT, J, MODE, true>(p, raw, gb, acc);
     gbs[it * BLOCK + threadIdx.x] = f32x4{gb[0], gb[1], gb[2], gb[3]};
   }
-  deferred_update<MODE, BLOCK, ITERS, GBAR, PART, false>(p, tile, red, acc, gbs, nullptr);
+  deferred_update<MODE, BLOCK, ITERS, GBAR, PART, false, MODE != MODE_ADAMW>(p, tile, red, acc, gbs, nullptr);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1088,12 +1111,12 @@ __device__ inline void tile_defer(const StepParams& p, int64_t tile, double (*re
 // (fp64) and the sum of squares of the values shifted by K, the running mean of the rows before it, hence
 // its centred sum of squares without cancellation; see chunk_merge for the bookkeeping.
 // ---------------------------------------------------------------------------------------------
-template <class GT, bool PART, int N>
+template <class GT, bool MOVES, int N>
 __device__ inline void chunk_accumulate(typename GT::raw_t* raw, const Reach& at, const float* K, double* sb, float* q) {
   constexpr int VEC = GT::VEC;
 #pragma unroll
   for (int j = 0; j < N; ++j) {
-    if constexpr (PART) raw[j] = GT::moved(raw[j], at.sh);
+    if constexpr (MOVES) raw[j] = GT::moved(raw[j], at.sh);
 #pragma unroll
     for (int e = 0; e < VEC; ++e) {
       const float x = GT::val(raw[j], e);
@@ -1115,21 +1138,22 @@ __device__ inline void chunk_clear(double* sb, float* q) {
 // The last nb < 16 rows, in runs of 8, 4, 2 and 1 with a branch each, first all loads and then all sums (a branch per row
 // costs more than it saves).  The rows keep their order.
 static_assert(NT_MCHUNK <= 16, "the last chunk is walked in runs of 8, 4, 2 and 1 rows");
-template <class GT, bool TABLE, bool PART, int RUN>
-__device__ inline void load_last(const StepParams& p, int j0, int nb, const Reach& at, typename GT::raw_t* raw) {
-  if (nb & RUN) load_rows<GT, TABLE, RUN>(PART, p, j0 + (nb & ~(2 * RUN - 1)), at, raw);
-  if constexpr (RUN > 1) load_last<GT, TABLE, PART, RUN / 2>(p, j0, nb, at, raw + RUN);
+template <class GT, bool TABLE, int RUN>
+__device__ inline void load_last(bool part, const StepParams& p, int j0, int nb, const Reach& at, typename GT::raw_t* raw) {
+  if (nb & RUN) load_rows<GT, TABLE, RUN>(part, p, j0 + (nb & ~(2 * RUN - 1)), at, raw);
+  if constexpr (RUN > 1) load_last<GT, TABLE, RUN / 2>(part, p, j0, nb, at, raw + RUN);
 }
-template <class GT, bool PART, int RUN>
+template <class GT, bool MOVES, int RUN>
 __device__ inline void accumulate_last(int nb, typename GT::raw_t* raw, const Reach& at, const float* K, double* sb, float* q) {
-  if (nb & RUN) chunk_accumulate<GT, PART, RUN>(raw, at, K, sb, q);
-  if constexpr (RUN > 1) accumulate_last<GT, PART, RUN / 2>(nb, raw + RUN, at, K, sb, q);
+  if (nb & RUN) chunk_accumulate<GT, MOVES, RUN>(raw, at, K, sb, q);
+  if constexpr (RUN > 1) accumulate_last<GT, MOVES, RUN / 2>(nb, raw + RUN, at, K, sb, q);
 }
 
 // Waits until all but four of a chunk's loads have arrived, before its first sum.  The walk of more than 32 bf16 rows in the class
 // for long vectors needs it to keep the blocks of a generation in step: without it, each sum starting as its row arrives, 64 /
 // 128 / 512 rows at d = 2^24 take 414 / 734 / 2622 us, with it 401 / 716 / 2571 (waiting for all of them 404 / 721 / 2570, for half
-// of them 401 / 721 / 2580).  With up to 32 rows it costs 0.5 %, in short vectors 1 to 5 %.
+// of them 401 / 721 / 2580).  With up to 32 rows it costs 0.5 %, in short vectors 1 to 5 %.  AdamW only, 64 rows: 406 us with it, 410
+// without.
 __device__ inline void chunk_wait() {
   __builtin_amdgcn_sched_barrier(0);
   __builtin_amdgcn_s_waitcnt(0x0f70 | 4);   // vmcnt(4)
@@ -1139,45 +1163,46 @@ __device__ inline void chunk_wait() {
 // The state update (and the gbar store) of a tile is deferred (see deferred_update): with many rows the writes are
 // a few per cent of the traffic.
 template <class GT, int MODE, int BLOCK, int ITERS, bool TABLE, bool GBAR, bool PART, bool END>
-__device__ inline TileEnd tile_multi(const StepParams& p, int64_t tile, double (*red)[NT_NV], f32x4* gbs,
+__device__ inline TileEnd tile_multi(bool part, const StepParams& p, int64_t tile, double (*red)[NT_NV], f32x4* gbs,
                                      uint32_t* ticket) {
   constexpr int VEC = GT::VEC;
   static_assert(VEC == 4, "one 16-byte LDS slot per lane and sweep");
   constexpr int TILE = BLOCK * VEC * ITERS;
   constexpr bool WRITES = (MODE != MODE_STATS) || GBAR;
-  constexpr bool WAITS = WRITES && MODE != MODE_ADAMW && GT::ESIZE == 2 && BLOCK * ITERS == NT_BLOCK_LARGE * NT_ITERS_LARGE;
+  constexpr bool MOVES = PART && moves_rows<GT, 0, MODE, BLOCK, ITERS, TABLE, false>();
+  constexpr bool WAITS = WRITES && GT::ESIZE == 2 && BLOCK * ITERS == NT_BLOCK_LARGE * NT_ITERS_LARGE;
   const int J = p.J;
   LaneAcc acc;
 #pragma unroll 1
   for (int it = 0; it < ITERS; ++it) {
     const Place pl = {tile * TILE + (int64_t)it * BLOCK * VEC, threadIdx.x * VEC};
     // a sweep or a wave that lies wholly past d adds nothing, and has no means to leave for the update
-    if (PART && pl.s0 + (int64_t)__builtin_amdgcn_readfirstlane(threadIdx.x) * VEC >= p.d) break;
+    if (PART && part && pl.s0 + (int64_t)__builtin_amdgcn_readfirstlane(threadIdx.x) * VEC >= p.d) break;
     double S[VEC], sb[VEC];
     float M2[VEC], a[VEC], K[VEC], q[VEC];
 #pragma unroll
     for (int e = 0; e < VEC; ++e) a[e] = 0.f;
     typename GT::raw_t raw[NT_MCHUNK];
     // first chunk (J > NT_JCHUNK >= NT_MCHUNK - 1 here, so it is full), shifted by the first row
-    const Reach at = reach(PART, p, pl);
-    load_rows<GT, TABLE, NT_MCHUNK>(PART, p, 0, at, raw);
+    const Reach at = reach(PART && part, p, pl);
+    load_rows<GT, TABLE, NT_MCHUNK>(PART && part, p, 0, at, raw);
     if (WAITS && J > 32) chunk_wait();
-    if constexpr (PART) raw[0] = GT::moved(raw[0], at.sh);
+    if constexpr (MOVES) raw[0] = GT::moved(raw[0], at.sh);
 #pragma unroll
     for (int e = 0; e < VEC; ++e) K[e] = GT::val(raw[0], e);
     chunk_clear<VEC>(sb, q);
     chunk_accumulate<GT, false, 1>(raw, at, K, sb, q);
-    chunk_accumulate<GT, PART, NT_MCHUNK - 1>(raw + 1, at, K, sb, q);
+    chunk_accumulate<GT, MOVES, NT_MCHUNK - 1>(raw + 1, at, K, sb, q);
 #pragma unroll
     for (int e = 0; e < VEC; ++e) K[e] = chunk_merge(true, 0, NT_MCHUNK, 0.0, 1.0 / NT_MCHUNK, K[e], sb[e], q[e], S[e], M2[e], a[e]);
     double inv_j0 = 1.0 / NT_MCHUNK;
     int j0 = NT_MCHUNK;
 #pragma unroll 1
     for (; j0 + NT_MCHUNK <= J; j0 += NT_MCHUNK) {
-      load_rows<GT, TABLE, NT_MCHUNK>(PART, p, j0, at, raw);
+      load_rows<GT, TABLE, NT_MCHUNK>(PART && part, p, j0, at, raw);
       if (WAITS && J > 32) chunk_wait();
       chunk_clear<VEC>(sb, q);
-      chunk_accumulate<GT, PART, NT_MCHUNK>(raw, at, K, sb, q);
+      chunk_accumulate<GT, MOVES, NT_MCHUNK>(raw, at, K, sb, q);
       const double inv_n = 1.0 / (double)(j0 + NT_MCHUNK);
 #pragma unroll
       for (int e = 0; e < VEC; ++e)
@@ -1186,9 +1211,9 @@ __device__ inline TileEnd tile_multi(const StepParams& p, int64_t tile, double (
     }
     if (j0 < J) {
       const int nb = J - j0;
-      load_last<GT, TABLE, PART, 8>(p, j0, nb, at, raw);
+      load_last<GT, TABLE, 8>(PART && part, p, j0, nb, at, raw);
       chunk_clear<VEC>(sb, q);
-      accumulate_last<GT, PART, 8>(nb, raw, at, K, sb, q);
+      accumulate_last<GT, MOVES, 8>(nb, raw, at, K, sb, q);
 #pragma unroll
       for (int e = 0; e < VEC; ++e)
         K[e] = chunk_merge(false, j0, nb, inv_j0, 0.0, K[e], sb[e], q[e], S[e], M2[e], a[e]);   // the last: K is not used again
@@ -1212,7 +1237,7 @@ __device__ inline TileEnd tile_multi(const StepParams& p, int64_t tile, double (
     if constexpr (WRITES) gbs[it * BLOCK + threadIdx.x] = f32x4{gb[0], gb[1], gb[2], gb[3]};
   }
   if constexpr (WRITES)
-    return deferred_update<MODE, BLOCK, ITERS, GBAR, PART, END>(p, tile, red, acc, gbs, ticket);
+    return deferred_update<MODE, BLOCK, ITERS, GBAR, PART, END, MOVES>(p, tile, red, acc, gbs, ticket);
   else
     return tile_reduce<BLOCK, END>(acc, red, p.partials, tile, ticket);
 }
@@ -1227,7 +1252,7 @@ template <class GT, int J_T, int MODE, int BLOCK, int ITERS, bool TABLE, bool GB
 __device__ inline TileEnd run_tile(bool part, const StepParams& p, int64_t tile, double (*red)[NT_NV], f32x4* gbs,
                                    uint32_t* ticket) {
   if constexpr (J_T == 0) {
-    return tile_multi<GT, MODE, BLOCK, ITERS, TABLE, GBAR, PART, END>(p, tile, red, gbs, ticket);
+    return tile_multi<GT, MODE, BLOCK, ITERS, TABLE, GBAR, PART, END>(part, p, tile, red, gbs, ticket);
   } else if constexpr (DEFER_T) {
     static_assert(!END || MODE == MODE_ADAMW, "steps with sums that write their own result are not in this class");
     tile_defer<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, PART>(p, tile, red, gbs);
@@ -1237,19 +1262,14 @@ __device__ inline TileEnd run_tile(bool part, const StepParams& p, int64_t tile,
   }
 }
 
-// More than 16 rows: whether whole tiles run a copy of the walk of their own.  In the copy for part tiles every row is moved to
-// its place (settle), which costs a short walk: statistics of 17 / 64 fp32 rows at d = 1e6 16.8 / 43.5 us in it, 15.5 / 42.1
-// beside it; 64 / 256 bf16 rows in tables 24.4 / 84.3 and 23.3 / 79.5, AdamW only, 20 bf16 rows 11.7 and 11.0.  It is the better
-// one with AdamW only from 33 bf16 rows on, where the delay keeps the blocks of a generation in step (64 rows, d = 2^24: 403 and
-// 434 us).  (With fp32 rows it gains 1 to 1.5 % in full generations, 64 rows at 3e7 1334 and 1350 us, but a part of a vector that
-// leaves most CUs idle loses more: 512 unpadded rows of 909,510 coordinates 854 us in it, 665 beside it.  Statistics of 17 to 32
-// fp32 rows at 2^24 take 1 % more in either than when a part tile was loaded element by element.)  Short steps over tables that
-// write their own result have the one copy: the second would need scratch memory.
-template <class GT, int MODE, int BLOCK, int ITERS, bool TABLE, bool END>
-__device__ inline bool whole_copy(int J) {
-  constexpr bool LONG = BLOCK * ITERS == NT_BLOCK_LARGE * NT_ITERS_LARGE;
-  if (TABLE && END && !LONG) return false;
-  return GT::ESIZE == 4 || MODE != MODE_ADAMW || J <= 32;
+// Whether whole tiles run a copy of the walk of their own: more than 16 rows.  In the copy for part tiles every row is moved to its
+// place (settle), which costs a short walk (statistics of 17 / 64 fp32 rows at d = 1e6 16.8 / 43.5 us in it, 15.5 / 42.1 beside it), so
+// they do, but for short steps over tables that write their own result: there the second copy would need scratch memory.  With AdamW
+// only nothing is moved, and the second copy is still the better one (64 bf16 rows 58.7 and 64.4 us at 2^21; 20 rows in tables 10.7
+// and 11.6 at 1e6; 64 fp32 rows 510 and 527 at 1.2e7), but where one_copy says otherwise.
+template <int MODE, int BLOCK, int ITERS, bool TABLE, bool END>
+constexpr bool whole_copy() {
+  return MODE == MODE_ADAMW || !TABLE || !END || BLOCK * ITERS == NT_BLOCK_LARGE * NT_ITERS_LARGE;
 }
 
 // GBAR = false compiles the gbar store out (statistics-only launch class, so that sweeps can overlap).
@@ -1269,8 +1289,8 @@ __device__ inline TileEnd block_tile(const StepParams& p, int64_t nfull, int64_t
   // rotate: the part tile (if any) first, then the whole tiles 0..nfull-1
   const bool part = t < npart;
   const int64_t tile = part ? nfull : t - npart;
-  constexpr bool ONE_COPY = J_T > 0 && !DEFER_T && MODE == MODE_ADAMW;   // see load_sweep
-  if (!ONE_COPY && !part && (J_T > 0 || whole_copy<GT, MODE, BLOCK, ITERS, TABLE, END>(p.J)))
+  constexpr bool ONE_COPY = one_copy<GT, J_T, MODE, BLOCK, ITERS, DEFER_T>();
+  if (!ONE_COPY && !part && (J_T > 0 || whole_copy<MODE, BLOCK, ITERS, TABLE, END>()))
     return run_tile<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, DEFER_T, COORD, false, END>(false, p, tile, red, gbs, ticket);
   return run_tile<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, DEFER_T, COORD, true, END>(!ONE_COPY || part, p, tile, red, gbs, ticket);
 }
@@ -1492,12 +1512,10 @@ __device__ inline void adamw_gbar_sweep(StepParams& p, const float* gbar, float 
   p.grads = gbar;   // as the only row
   const Reach at = reach(PART, p, pl);
   load_sweep<F32, false, 1, true>(PART, p, 0, at, &sg, state);
-  settle<F32, 1>(PART, at, &sg);
-  settle<F32, 3>(PART, at, state);
   float gb[NT_VEC];
 #pragma unroll
   for (int e = 0; e < NT_VEC; ++e) gb[e] = scale * __builtin_bit_cast(float, (uint32_t)sg[e]);
-  adamw_store(PART, p, pl, gb, state);
+  adamw_store(PART, p, at, gb, state);
 }
 __global__ __launch_bounds__(NT_AUX_BLOCK) void k_adamw_gbar(StepParams p, const float* gbar, float grad_scale,
                                                          const nt_result* res, int64_t block0) {
