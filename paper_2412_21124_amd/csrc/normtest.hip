@@ -65,9 +65,9 @@
 #define NT_ITERS_DEFER 16
 #define NT_DEFER_UNROLL 1        // row sweeps in flight per lane in that class
 #define NT_GENS_DEFER 1          // generations of blocks per launch in that class (two: -7 .. -10 %)
-// J > 16, modes that write per coordinate: the shapes above where a generation of blocks, NT_GENERATION coordinates on 256 CUs, or
-// several are nearly full (generations_pay); else one launch of short tiles, of which the chip takes any number (512 rows, d =
-// 2^18: 607 -> 92 us).
+// J > 16, modes that write per coordinate: the shapes above where a generation of blocks (NT_GENERATION coordinates: four blocks on each
+// of 256 CUs) is nearly full, or enough of the one after the first or second (generations_pay); else one launch of short tiles, of
+// which the chip takes any number (512 rows, d = 2^18: 607 -> 92 us).
 #define NT_GENERATION (1ll << 23)
 #define NT_BLOCK_MANY_SHORT 256
 #define NT_ITERS_MANY_SHORT 2
@@ -1631,20 +1631,31 @@ constexpr int defer_row_bytes(int mode) { return mode == MODE_ADAMW ? NT_DEFER_R
 // vector itself are cut into the same tiles.
 enum { CLS_BASE = 0, CLS_LONG = 1, CLS_SHORT = 2 };
 // More than 16 rows: whether a vector of d coordinates is better walked in whole generations of blocks than in short tiles.  What
-// is left over after the last full generation runs by itself on a few CUs, with two waves a block.  Generations against short
-// tiles, us, fused step: 64 bf16 rows 179 / 178 at d = 6.4e6, 177 / 189 at 7e6, 291 / 226 at 8.4e6 (just past one), 298 / 274 at 1e7,
-// 319 / 310 at 1.15e7, 326 / 348 at 1.3e7, 478 / 448 at 1.68e7 (just past two), 486 / 482 at 1.75e7, 504 / 517 at 1.9e7, 604 / 681 at
-// 2.5e7; 256 rows 1021 / 744 at 8.4e6, 1116 / 1020 at 1.15e7, 1132 / 1142 at 1.3e7; 64 fp32 rows 481 / 449 at 9e6, 583 / 641 at 1.3e7;
-// 24 bf16 rows, whose generations are short-lived, 237 / 206 at 1.68e7, 251 / 236 at 1.9e7, 263 / 288 at 2.2e7.
-inline bool generations_pay(int64_t J, int esize, int64_t d) {
+// is left over after the last full generation runs by itself on a few CUs, with two waves a block, and takes about as long whether it
+// is little or much; short tiles take 5 to 10 % more per coordinate.  So what is left over decides: it has to be nothing or more than a
+// part of a generation that shrinks with the number of full ones, and shrinks the sooner the more bytes a tile moves.  Generations
+// against short tiles, us, fused step: 64 bf16 rows 158 / 173 at d = 6.3e6, 177 / 189 at 7e6, 291 / 226 at 8.4e6 (just past one),
+// 298 / 274 at 1e7, 319 / 310 at 1.15e7, 326 / 348 at 1.3e7, 478 / 448 at 1.68e7 (just past two), 486 / 482 at 1.75e7, 504 / 517 at 1.9e7,
+// 604 / 681 at 2.5e7; 40 rows 138 / 135 at 6.6e6; 256 rows 1021 / 744 at 8.4e6, 1116 / 1020 at 1.15e7, 1132 / 1142 at 1.3e7; 64 fp32 rows 306 /
+// 317 at 6.3e6, 481 / 449 at 9e6, 477 / 518 at 1.04e7; 24 bf16 rows, whose generations are short-lived, 237 / 206 at 1.68e7, 251 / 236 at
+// 1.9e7, 263 / 288 at 2.2e7.  Statistics with the mean, 128 bf16 rows 275 / 265 at 6.5e6, 64 fp32 rows 298 / 287; AdamW only, 64 fp32 rows
+// 298 / 316 at 6.3e6, 449 / 469 at 9.5e6, 457 / 508 at 1.04e7, 128 bf16 rows 524 / 545 at 1.15e7, 64 rows 459 / 467 at 1.78e7.  Just past
+// three generations and more, short tiles have not been measured.
+// The generation is a constant, not the device's: the parts of a vector are cut into the same tiles wherever they run.
+inline bool generations_pay(int64_t J, int esize, int mode, int64_t d) {
   constexpr int64_t G = NT_GENERATION;
-  if (J <= 32) return d >= 2 * G && !(J > NT_FEW_ROWS && esize == 2 && d > 2 * G && d <= 2 * G + G / 4);
-  return d >= G * 13 / 16 && !(d > G && d <= G + (esize == 2 ? G * 3 / 8 : G / 4)) && !(esize == 2 && d > 2 * G && d <= 2 * G + G / 8);
+  const int64_t full = d / G, left = d % G;
+  const bool bf16 = esize == 2, adamw = mode == MODE_ADAMW;
+  if (J <= 32) return full > 2 || (full == 2 && (J <= NT_FEW_ROWS || !bf16 || left == 0 || left > G / 4));
+  if (full == 0) return left >= ((mode == MODE_FULL && J * esize >= 96) || (adamw && !bf16) ? G * 3 / 4 : G * 13 / 16);
+  if (left == 0 || full > 2) return true;
+  if (full == 1) return left > (bf16 ? (adamw && J >= 64 ? G * 5 / 16 : G * 3 / 8) : adamw ? G / 16 : mode == MODE_FULL ? G / 8 : G / 4);
+  return !bf16 || left > (adamw && J >= 64 ? G / 16 : G / 8);
 }
 inline int launch_class(int64_t J, int esize, int mode, bool gbar, int64_t d_whole) {
   if (J > NT_JCHUNK && d_whole <= (J <= 32 && esize == 2 && mode != MODE_ADAMW ? NT_MANY_TINY_COORDS_32 : NT_MANY_TINY_COORDS)) return CLS_SHORT;
   if (mode == MODE_STATS && !gbar) return (J <= NT_JCHUNK && d_whole < NT_STATS_SHORT_COORDS) ? CLS_SHORT : CLS_BASE;
-  if (J > NT_JCHUNK) return generations_pay(J, esize, d_whole) ? CLS_LONG : CLS_BASE;
+  if (J > NT_JCHUNK) return generations_pay(J, esize, mode, d_whole) ? CLS_LONG : CLS_BASE;
   return (J * esize >= defer_row_bytes(mode) && d_whole >= NT_DEFER_COORDS) ? CLS_LONG : CLS_BASE;
 }
 inline TileCfg tile_cfg(int64_t J, int esize, int mode, bool gbar, int64_t d_whole) {

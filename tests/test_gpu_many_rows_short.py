@@ -40,8 +40,10 @@ def test_same_outputs_on_both_sides_of_a_length(J, gdtype, edge, flags):
 @pytest.mark.parametrize("J,gdtype,edge", [(33, torch.bfloat16, (1 << 23) * 13 // 16 - 1), (33, torch.bfloat16, 1 << 23),
                                            (40, torch.bfloat16, (1 << 23) * 11 // 8), (33, torch.float32, (1 << 23) * 5 // 4),
                                            (21, torch.bfloat16, 1 << 24), (24, torch.bfloat16, (1 << 23) * 9 // 4),
-                                           (33, torch.bfloat16, (1 << 23) * 17 // 8), (20, torch.float32, (1 << 24) - 1)])
-@pytest.mark.parametrize("flags", [STATS | ADAMW, STATS | GBAR])
+                                           (33, torch.bfloat16, (1 << 23) * 17 // 8), (20, torch.float32, (1 << 24) - 1),
+                                           (48, torch.bfloat16, (1 << 23) * 3 // 4 - 1), (33, torch.float32, (1 << 23) * 9 // 8),
+                                           (64, torch.bfloat16, (1 << 23) * 21 // 16), (33, torch.float32, (1 << 23) * 17 // 16)])
+@pytest.mark.parametrize("flags", [STATS | ADAMW, STATS | GBAR, ADAMW])
 def test_same_outputs_in_generations_and_in_short_tiles(J, gdtype, edge, flags):
     g = torch.Generator(device=DEV).manual_seed(J)
     rows = torch.empty((J, edge + 1), dtype=gdtype, device=DEV)
@@ -57,5 +59,5 @@ def test_same_outputs_in_generations_and_in_short_tiles(J, gdtype, edge, flags):
         outs.append(state)
     for a, b in zip(*outs):
         assert torch.equal(a[:edge], b[:edge])
-    for k in ("A", "B", "C"):   # fp32 terms of four coordinates, the same ones, added in fp64 in another order
+    for k in ("A", "B", "C") if flags & STATS else ():   # fp32 terms of four coordinates, the same ones, added in fp64 in another order
         assert sums[0][k] == pytest.approx(sums[1][k], rel=1e-13)

@@ -90,3 +90,32 @@ def test_one_tile_is_one_launch(launches, gdtype, flags):
     if flags == STATS:   # short tiles at any length
         calls += [_call(J, gdtype, 2048, flags, 1 << 30) for J in (17, 33, 512)]
     assert [_names(s) for s in launches(calls)] == [["k_step_end"]] * len(calls)
+
+
+# Beyond 16 rows steps that write per coordinate run in generations of blocks of 8192 coordinates, or in short tiles where too much of
+# the last generation would be empty: the last length on either side of every edge, in 32nds of a generation.
+G = 1 << 23
+EDGES = [(J, g, f, 64, 0) for J in (17, 20) for g in (B.NT_BF16, B.NT_F32) for f in (FULL, STATS | GBAR, ADAMW)]
+EDGES += [(J, B.NT_F32, f, 64, 0) for J in (21, 32) for f in (FULL, STATS | GBAR, ADAMW)]
+EDGES += [(J, B.NT_BF16, f, 64, 8) for J in (21, 32) for f in (FULL, STATS | GBAR, ADAMW)]
+EDGES += [(33, B.NT_BF16, FULL, 26, 12, 4), (47, B.NT_BF16, FULL, 26, 12, 4), (48, B.NT_BF16, FULL, 24, 12, 4), (33, B.NT_F32, FULL, 24, 4, 0),
+          (33, B.NT_BF16, STATS | GBAR, 26, 12, 4), (100, B.NT_BF16, STATS | GBAR, 26, 12, 4), (33, B.NT_F32, STATS | GBAR, 26, 8, 0),
+          (33, B.NT_BF16, ADAMW, 26, 12, 4), (63, B.NT_BF16, ADAMW, 26, 12, 4), (64, B.NT_BF16, ADAMW, 26, 10, 2), (33, B.NT_F32, ADAMW, 24, 2, 0)]
+
+
+@pytest.mark.parametrize("J,gdtype,flags,first,after", [(*e[:4], e[4:]) for e in EDGES])
+def test_generations_of_blocks(launches, J, gdtype, flags, first, after):
+    start = first * G // 32
+    full = -(-start // G)
+    lengths, want = [start - 1, start, full * G], [False, True, True]
+    for k, left in enumerate(after):
+        lengths += [(full + k) * G + 1, (full + k) * G + left * G // 32, (full + k) * G + left * G // 32 + 1, (full + k + 1) * G]
+        want += [left == 0, True if left == 0 else False, True, True]
+    lengths += [3 * G + 1, 4 * G + 1]
+    want += [True, True]
+    got = launches([_call(J, gdtype, d, flags) for d in lengths])
+    for d, long_class, step in zip(lengths, want, got):
+        shape = ("256", "8") if J <= 20 else ("128", "16")
+        assert all(tuple(k[1][2:4]) == (shape if long_class else ("256", "2")) for k in step if k[0].startswith("k_step")), d
+        if long_class:   # launches of whole generations: 256 CUs x 4 blocks
+            assert [k[2] for k in step if k[0].startswith("k_step")].count(1024) == d // G
