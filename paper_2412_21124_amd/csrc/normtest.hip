@@ -109,6 +109,14 @@
 // 813 / 826 at 124M, 2013 / 1998 at 3e8; AdamW from a stored gbar +0.8 % from 6e7 on, -2 % at 1e7.  Up to 8 bytes of rows the
 // fused step prefers two at any length (4 bf16 rows 28.6 / 25.9 at 2^22, 1683 / 1661 at 304.6M), AdamW only is indifferent.
 #define NT_ONE_BLOCK_LDS 82000
+// Statistics that store the mean, up to 16 rows: the same with blocks of 512 threads, beyond 2^25 coordinates.  Three instead of the four
+// per CU that the registers allow, two / three / four blocks, us: 5 bf16 rows 292 / 279 / 286 at d = 1.24e8, 149 / 140 / 141 at 6e7.  Two from 12
+// bytes of rows on: 9 bf16 rows 310 / - / 323 at 9e7 (of three), 69 / - / 70 at 2^24; 4 fp32 rows 293 / - / 302 at 9e7; 6 bf16 rows 159 / 161 /
+// 160 at 6e7, 341 / 347 / 354 at 1.3e8; 6 fp32 rows 425 / 434 / 436 at 9e7.  8 and 10 to 16 bf16 rows have the registers of two anyway, or
+// are indifferent.
+#define NT_TWO_BLOCK_LDS 56000
+#define NT_THREE_BLOCK_LDS 42000
+#define NT_HOLD_GBAR_COORDS (1ll << 25)
 
 #define NT_VEC 4              // coordinates per lane and sweep: 16-byte fp32 accesses, 8-byte bf16 row loads
 #define NT_TILE_MAX 16384     // every tile size divides this: the alignment that keeps shard results bit-identical
@@ -1696,6 +1704,11 @@ inline unsigned one_block_lds(int64_t J, int esize, int mode, int64_t d) {
                                       : J * esize >= (esize == 4 ? 12 : 16) && d > (esize == 4 ? 1ll << 24 : 1ll << 25);
   return one ? NT_ONE_BLOCK_LDS : 0;
 }
+// ... and of statistics that store the mean (see NT_TWO_BLOCK_LDS)
+inline unsigned stats_gbar_lds(int64_t J, int esize, int64_t d) {
+  if (d <= NT_HOLD_GBAR_COORDS || J * esize < 10) return 0;
+  return J * esize < 12 ? NT_THREE_BLOCK_LDS : NT_TWO_BLOCK_LDS;
+}
 // smallest tile any mode and gradient type uses for this J: sizes the workspace
 inline int64_t min_tile_coords(int64_t J) {
   int64_t best = tile_cfg(J, 2, MODE_FULL, false, 0).coords();
@@ -1766,7 +1779,9 @@ template <class GT, int J_T, int MODE, int BLOCK, int ITERS, bool TABLE, bool GB
           bool COORD = true>
 bool launch_tiles_of(const StepParams& p, int64_t nfull, int64_t ntiles, int64_t slot0, unsigned grid, const Finish& fin,
                      hipStream_t st) {
-  const unsigned lds = BLOCK == 1024 ? one_block_lds(p.J, GT::ESIZE, MODE, p.d) : 0;
+  unsigned lds = 0;
+  if (BLOCK == 1024) lds = one_block_lds(p.J, GT::ESIZE, MODE, p.d);
+  if (MODE == MODE_STATS && GBAR && J_T > 0 && !DEFER_T) lds = stats_gbar_lds(p.J, GT::ESIZE, p.d);
   if constexpr (MODE == MODE_ADAMW || FEW_TILES) {
     if (fin.out) {
       hipLaunchKernelGGL((k_step_end<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, DEFER_T>), dim3(grid), dim3(BLOCK), lds, st, p,

@@ -68,15 +68,16 @@ def test_adamw_from_a_mean_continued_with_zeros():
             assert torch.equal(x, y[:d]), d
 
 
-# one block or two per CU, and launches of another length: the first coordinates of a longer vector, on both sides of each edge
-@pytest.mark.parametrize("J,flags,edge", [(8, ADAMW, 1 << 23), (8, STATS | ADAMW, 1 << 25), (2, ADAMW, 1 << 28)])
+# how many blocks a CU holds, and launches of another length: the first coordinates of a longer vector, on both sides of each edge
+@pytest.mark.parametrize("J,flags,edge", [(8, ADAMW, 1 << 23), (8, STATS | ADAMW, 1 << 25), (2, ADAMW, 1 << 28),
+                                          (5, STATS | GBAR, 1 << 25), (9, STATS | GBAR, 1 << 25)])
 def test_state_does_not_depend_on_the_length(J, flags, edge):
     rows = (torch.randn(J, edge + 4099, device=DEV) * 1e-2).to(torch.bfloat16)
-    state = [torch.rand(edge + 4099, device=DEV) * 0.02 for _ in range(3)]
+    state = [torch.rand(edge + 4099, device=DEV) * 0.02 for _ in range(4 if flags & GBAR else 3)]
     outs = []
     for d in (edge - 4096 + 1, edge + 4099):
         st = [s[:d].clone() for s in state]
-        B.normtest_step(rows, *st, B.make_hyper(**HYPER, flags=flags), d=d)
+        B.normtest_step(rows, *st[:3], B.make_hyper(**HYPER, flags=flags), d=d, gbar_out=st[3] if flags & GBAR else None)
         outs.append(st)
     for x, y in zip(*outs):
         assert torch.equal(x, y[:x.numel()])

@@ -119,3 +119,17 @@ def test_generations_of_blocks(launches, J, gdtype, flags, first, after):
         assert all(tuple(k[1][2:4]) == (shape if long_class else ("256", "2")) for k in step if k[0].startswith("k_step")), d
         if long_class:   # launches of whole generations: 256 CUs x 4 blocks
             assert [k[2] for k in step if k[0].startswith("k_step")].count(1024) == d // G
+
+
+# Dynamic LDS that keeps one block of 1024 threads on a CU (160 KB), or two or three of 512 of the statistics that store the mean.
+def test_blocks_held_per_cu(launches):
+    cases = [((8, B.NT_BF16, 1 << 25, FULL), 0), ((8, B.NT_BF16, (1 << 25) + 1, FULL), 1), ((4, B.NT_BF16, 1 << 28, FULL), 0),
+             ((3, B.NT_F32, 1 << 24, FULL), 0), ((3, B.NT_F32, (1 << 24) + 1, FULL), 1), ((8, B.NT_BF16, 1 << 23, ADAMW), 0),
+             ((8, B.NT_BF16, (1 << 23) + 1, ADAMW), 1), ((8, B.NT_BF16, 1 << 28, ADAMW), 0), ((7, B.NT_BF16, 1 << 24, ADAMW), 0)]
+    cases += [((J, g, d, STATS | GBAR), held if d > 1 << 25 else 0) for d in (1 << 25, (1 << 25) + 1)
+              for J, g, held in ((4, B.NT_BF16, 0), (5, B.NT_BF16, 3), (6, B.NT_BF16, 2), (9, B.NT_BF16, 2), (2, B.NT_F32, 0), (3, B.NT_F32, 2))]
+    cases += [((9, B.NT_BF16, 1 << 26, STATS), 0), ((20, B.NT_BF16, 1 << 26, STATS | GBAR), 0)]
+    for (call, held), step in zip(cases, launches([_call(*c) for c, _ in cases])):
+        for k in step:
+            if k[0].startswith("k_step"):
+                assert (163840 // k[4] if k[4] else 0) == held, (call, k)
