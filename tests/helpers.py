@@ -18,6 +18,22 @@ ADAMW_RTOL = 1e-6   # w', m', v' relative to max(|x_ref|, rms(x_ref)); also max-
 ORACLE_CHUNK = 1 << 22
 
 
+def captured(enqueue) -> None:
+    """Run what enqueue() puts on the current stream from a graph, once: under capture a step of a few tiles has a reduction kernel
+    of its own.  enqueue must not allocate."""
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        enqueue()
+    graph.replay()
+    torch.cuda.synchronize()
+
+
+def tile_of(workspace: torch.Tensor) -> int:
+    """Coordinates per tile of the step whose record a workspace holds."""
+    return int(workspace[:16].view(torch.int64)[1])
+
+
 def n_threads() -> int:
     return max(1, min(16, os.cpu_count() or 1))
 

@@ -7,6 +7,7 @@ import ctypes
 import pytest
 import torch
 
+import helpers as H
 from paper_2412_21124_amd import binding as B
 
 pytestmark = pytest.mark.gpu
@@ -15,9 +16,10 @@ STATS, ADAMW, GBAR, COORD = B.NT_DO_STATS, B.NT_DO_ADAMW, B.NT_WRITE_GBAR, B.NT_
 K = 4   # inputs, and streams
 
 
-def _hyper(flags):
-    # with lr, decay and (1 - beta) zero the state stays as it is, so that every call on the same inputs has the same outputs
-    return B.make_hyper(lr=0.0, weight_decay=0.0, beta1=0.0, beta2=0.0, step=10, b_k=64, b_max=8192, round_to=16, flags=flags)
+def _hyper(flags, **kw):
+    # without lr, decay and betas every call on the same inputs leaves the same state: w as it is, m = g, v = g^2
+    kw = {"lr": 0.0, "weight_decay": 0.0, "beta1": 0.0, "beta2": 0.0, **kw}
+    return B.make_hyper(step=10, b_k=64, b_max=8192, round_to=16, flags=flags, **kw)
 
 
 class _Calls:
@@ -41,19 +43,28 @@ class _Calls:
         B.normtest_step_rows(self.rows[k], w, m, v, self.hy, table=self.tables[k], shard=self.shard, gbar_out=gbar,
                              workspace=self.ws[k], result=result, stream=stream)
 
+    def reset(self):
+        """Values that no call leaves behind, so that a store left out shows."""
+        for w, *rest in self.state:
+            w.copy_(torch.linspace(0.5, 1.5, self.d, device=DEV))
+            for t in rest:
+                t.fill_(7.0)
+        torch.cuda.synchronize()
+
     def two_launches(self):
         """Result and outputs for every input from a captured step, which has a reduction kernel of its own."""
+        self.reset()
         out = []
         for k in range(K):
             r = torch.zeros(B.RESULT_BYTES, dtype=torch.uint8, device=DEV)
-            torch.cuda.synchronize()
-            graph = torch.cuda.CUDAGraph()
-            with torch.cuda.graph(graph):
-                self.matrix(k, r, torch.cuda.current_stream())
-            graph.replay()
-            torch.cuda.synchronize()
-            out.append((r.clone(), [t.clone() for t in self.state[k]]))
+            H.captured(lambda: self.matrix(k, r))
+            out.append((r, [t.clone() for t in self.state[k]]))
         return out
+
+    def check(self, want):
+        torch.cuda.synchronize()
+        for k in range(K):
+            assert all(torch.equal(a, b) for a, b in zip(self.state[k], want[k][1])), k
 
 
 # the fewest tiles, a ragged last one, both sides of the last count that ends in one launch, for each class of short vectors and,
@@ -68,20 +79,49 @@ def test_bits_of_two_launches(J, gdtype, flags, tile, most, whole, past):
     tiles = 2 if past is None else most + past
     c = _Calls(J, gdtype, tiles * tile - 5, flags, whole)
     want = c.two_launches()
+    c.reset()
     results = torch.zeros(2 * K * 20, B.RESULT_BYTES, dtype=torch.uint8, device=DEV)
     for i in range(results.shape[0]):   # back to back, every input after another one
         (c.matrix if i % (2 * K) < K else c.table)(i % K, results[i])
-    torch.cuda.synchronize()
+    c.check(want)
     assert all(torch.equal(results[i], want[i % K][0]) for i in range(results.shape[0]))
+    c.reset()
     results.zero_()
     torch.cuda.synchronize()
     streams = [torch.cuda.Stream() for _ in range(K)]
     for i in range(results.shape[0]):
         c.matrix(i % K, results[i], streams[i % K])
-    torch.cuda.synchronize()
+    c.check(want)
     assert all(torch.equal(results[i], want[i % K][0]) for i in range(results.shape[0]))
-    for k in range(K):
-        assert all(torch.equal(a, b) for a, b in zip(c.state[k], want[k][1]))
+    # one step that moves every part of the state
+    c.hy = _hyper(flags, lr=3e-2, weight_decay=0.1, beta1=0.9, beta2=0.95)
+    want = c.two_launches()
+    for way in (c.matrix, c.table):
+        c.reset()
+        for k in range(K):
+            way(k, results[k])
+        c.check(want)
+
+
+# Sums that are not finite: the last block's totals against the reduction kernel's, an infinite row and squares that overflow
+@pytest.mark.parametrize("J,gdtype,tile", [(2, torch.float32, 4096), (16, torch.bfloat16, 4096), (33, torch.float32, 2048)])
+@pytest.mark.parametrize("value", [float("inf"), float("nan"), 1e20])
+def test_sums_that_are_not_finite(J, gdtype, tile, value):
+    for tiles in (2, 100):
+        c = _Calls(J, gdtype, tiles * tile - 3, STATS | ADAMW | GBAR | COORD)
+        for g in c.grads:
+            g[:1 if value != 1e20 else J, tile + 7] = value
+        want = c.two_launches()
+        got = torch.zeros(2 * K, B.RESULT_BYTES, dtype=torch.uint8, device=DEV)
+        c.reset()
+        for k in range(K):
+            c.matrix(k, got[k])
+        for k in range(K):
+            c.table(k, got[K + k])
+        torch.cuda.synchronize()
+        assert B.read_result(got[0]).status == B.NT_STATUS_NONFINITE
+        # every word of the record, NaN by its bits
+        assert all(torch.equal(got[k], want[k % K][0]) for k in range(2 * K))
 
 
 # more calls than there are counters (2^20): each is met again, and has been left at zero
