@@ -1,4 +1,4 @@
-"""Steps whose own kernel writes the result: vectors of one tile, and AdamW only at any length.  Result and workspace start
+"""Steps whose own kernel writes the result: vectors of one tile or a few, and AdamW only at any length.  Result and workspace start
 as garbage; the sums, the decision and the per-layer table read from the workspace afterwards must be the oracle's."""
 from __future__ import annotations
 
@@ -27,7 +27,7 @@ def _run(wl, flags, **kw):
     return B.read_result(res).as_dict(), ws
 
 
-# one tile is 4096 coordinates up to 16 rows and 2048 beyond; one more coordinate takes the two-kernel way
+# one tile is 4096 coordinates up to 16 rows and 2048 beyond; with one more coordinate the last block adds up the partials
 @pytest.mark.parametrize("J,gdtype,tile", [(2, torch.bfloat16, 4096), (16, torch.float32, 4096), (33, torch.bfloat16, 2048)])
 @pytest.mark.parametrize("flags", [STATS | ADAMW, STATS, STATS | GBAR, STATS | ADAMW | COORD, STATS | ADAMW | PARTIAL])
 def test_one_tile(J, gdtype, tile, flags):
@@ -65,7 +65,7 @@ def _same(a, b):
         assert a[k] == b[k] or (a[k] != a[k] and b[k] != b[k]), (k, a[k], b[k])
 
 
-# a tile, which the step's kernel ends by itself for a matrix and not for a table, and one coordinate more
+# a tile, whose partial is the total; one coordinate more, which ends at the counter, and under capture in the reduction kernel
 @pytest.mark.parametrize("J,gdtype,tile", [(2, torch.float32, 4096), (16, torch.bfloat16, 4096), (33, torch.float32, 2048)])
 @pytest.mark.parametrize("value", [math.inf, 1e20])   # in one row; in all rows, finite, where only the squares overflow
 def test_sums_that_are_not_finite_read_the_same_on_every_way(J, gdtype, tile, value):
@@ -75,11 +75,19 @@ def test_sums_that_are_not_finite_read_the_same_on_every_way(J, gdtype, tile, va
     hy = B.make_hyper(lr=h.lr, beta1=h.beta1, beta2=h.beta2, eps=h.eps, weight_decay=h.weight_decay, eta=h.eta,
                       step=h.step, b_k=h.b_k, b_max=h.b_max, round_to=h.round_to, ddof=h.ddof)
     gbar = torch.empty(tile + 1, dtype=torch.float32, device=DEV)
+    ws = torch.empty(B.normtest_workspace_bytes(J, tile + 1), dtype=torch.uint8, device=DEV)
+
+    def captured(d, s):
+        out = torch.empty(B.RESULT_BYTES, dtype=torch.uint8, device=DEV)
+        H.captured(lambda: B.normtest_step(wl.grads, *s, hy, d=d, workspace=ws, result=out))
+        return out
+
     ways = {"matrix": lambda d, s: B.normtest_step(wl.grads, *s, hy, d=d),
             "table": lambda d, s: B.normtest_step_rows(list(wl.grads), *s, hy, d=d),
             "static": lambda d, s: B.normtest_step_static(
                 wl.grads, *s, hy, torch.empty(B.RESULT_BYTES, dtype=torch.uint8, device=DEV), d=d),
-            "clipped": lambda d, s: B.normtest_step_clipped(wl.grads, *s, gbar, 1.0, hy, d=d)}
+            "clipped": lambda d, s: B.normtest_step_clipped(wl.grads, *s, gbar, 1.0, hy, d=d),
+            "captured": captured}
     got = {}
     for name, way in ways.items():
         for d in (tile, tile + 1):
@@ -124,8 +132,8 @@ def test_adamw_only_writes_its_result_in_the_last_launch(J, d):
 @pytest.mark.parametrize("flags", [STATS | ADAMW, STATS, STATS | GBAR, STATS | COORD, ADAMW])
 def test_every_class_leaves_a_result(gdtype, flags, whole):
     """Whether the step's own kernel writes the result or a second one does, it is written, and it is the one that the same
-    rows in a pointer table give, which (AdamW only apart) always take the second kernel."""
-    d = 700
+    rows give in a pointer table and, continued with zeros into a second tile and captured, by way of the reduction kernel."""
+    d, longer = 700, 16384 + 700
     for J in [*range(2, 22), 33]:
         wl = synth.make("t", J, d, gdtype=gdtype, sigma=1e-2, seed=J, device=DEV, hyper=synth.Hyper(b_k=64, round_to=J))
         kw = {} if whole is None else {"shard": B.nt_shard_info(0, 1, 0, whole)}
@@ -137,6 +145,13 @@ def test_every_class_leaves_a_result(gdtype, flags, whole):
         gbar = torch.empty(d, dtype=torch.float32, device=DEV)
         out = torch.full((B.RESULT_BYTES,), 0xA5, dtype=torch.uint8, device=DEV)
         _same(res, B.read_result(B.normtest_step_rows(list(wl.grads), w, m, v, hy, gbar_out=gbar, result=out, **kw)).as_dict())
+        grads = torch.zeros(J, longer, dtype=gdtype, device=DEV)
+        grads[:, :d] = wl.grads[:, :d]
+        state = [torch.zeros(longer, dtype=torch.float32, device=DEV) for _ in range(4)]
+        ws = torch.empty(B.normtest_workspace_bytes(J, longer), dtype=torch.uint8, device=DEV)
+        out.fill_(0xA5)
+        H.captured(lambda: B.normtest_step(grads, *state[:3], hy, gbar_out=state[3], workspace=ws, result=out, **kw))
+        _same(res, B.read_result(out).as_dict())
         assert (res["status"] == B.NT_STATUS_NO_STATS) == (not flags & STATS)
         for a, b in zip((w, m, v), (wl.w, wl.m, wl.v)):
             assert torch.equal(a, b)
