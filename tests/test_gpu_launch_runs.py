@@ -1,6 +1,6 @@
-"""A long vector is walked by several kernel launches, each over a run of consecutive tiles (2^27 coordinates for the
-fused step up to 16 rows, 2^25 for AdamW only and for AdamW from a stored mean, 2^23 beyond 16 rows).  These cases
-sit just past one or two such runs, with a ragged end and, in one variant each, with every buffer one element off a
+"""A long vector is walked by several kernel launches, each over a run of consecutive tiles (2^26 coordinates for the
+fused step up to 16 rows, 2^27 for statistics that store the mean, 2^25 for AdamW only and for AdamW from a stored mean, 2^23
+beyond 16 rows).  These cases sit just past one or two such runs, with a ragged end and, in one variant each, with every buffer one element off a
 16-byte boundary, which the kernels' vector accesses have to take as they come; each is compared with the oracle element by
 element, and the misaligned call with the aligned one bit for bit."""
 import math
@@ -24,8 +24,8 @@ def hyper_of(h: synth.Hyper, flags=FULL) -> B.nt_hyper:
                         step=h.step, b_k=h.b_k, b_max=h.b_max, round_to=h.round_to, ddof=h.ddof, flags=flags)
 
 
-def step(wl, flags=FULL, d=None):
-    res = B.normtest_step(wl.grads, wl.w, wl.m, wl.v, hyper_of(wl.hyper, flags), d=d)
+def step(wl, flags=FULL, d=None, workspace=None):
+    res = B.normtest_step(wl.grads, wl.w, wl.m, wl.v, hyper_of(wl.hyper, flags), d=d, workspace=workspace)
     torch.cuda.synchronize()
     return B.read_result(res).as_dict()
 
@@ -45,12 +45,14 @@ def shifted_copy(wl: synth.Workload):
 
 @pytest.mark.parametrize("J,gdtype", [(24, torch.bfloat16), (17, torch.float32)])
 def test_many_rows_in_one_pass_over_several_launches(J, gdtype):
-    """More than 16 rows, state updated in the same pass: launches of 2^23 coordinates; two whole runs, a third of
-    three tiles and a ragged tile."""
-    d = 2 * (1 << 23) + 3 * 2048 + 77
+    """More than 16 rows, state updated in the same pass: launches of 2^23 coordinates; two whole runs, a third of half as many
+    and three tiles and a ragged one."""
+    d = 2 * (1 << 23) + (1 << 22) + 3 * 8192 + 77
     wl = synth.make("t", J, d, gdtype=gdtype, sigma=1e-2, seed=31, device=DEV, hyper=synth.Hyper(b_k=64, round_to=J, step=3))
     w0, m0, v0 = wl.w.clone(), wl.m.clone(), wl.v.clone()
-    res = step(wl, FULL | B.NT_ONE_PASS)
+    ws = torch.empty(B.normtest_workspace_bytes(J, d), dtype=torch.uint8, device=DEV)
+    res = step(wl, FULL | B.NT_ONE_PASS, workspace=ws)
+    assert H.tile_of(ws) == 8192   # the class that is walked in generations
     ref = H.oracle_full(wl.grads, d, J, wl.hyper)
     H.assert_stats_close(res, ref)
     H.assert_decision_matches(res, ref, wl.hyper)
@@ -59,7 +61,7 @@ def test_many_rows_in_one_pass_over_several_launches(J, gdtype):
 
 def test_adamw_only_over_several_launches_equals_the_fused_step():
     """AdamW only (the test skipped): launches of 2^25 coordinates.  Same bits in w, m, v as the fused step, whose
-    launches are four times as long, and within the bound of the oracle's AdamW."""
+    launches are twice as long, and within the bound of the oracle's AdamW."""
     d = 2 * (1 << 25) + 5 * 4096 + 13
     wl = synth.make("t", 8, d, gdtype=torch.bfloat16, sigma=1e-2, seed=32, device=DEV)
     w0, m0, v0 = wl.w.clone(), wl.m.clone(), wl.v.clone()
@@ -74,9 +76,9 @@ def test_adamw_only_over_several_launches_equals_the_fused_step():
     assert H.oracle_adamw_check(wl.grads, d, w0, m0, v0, wl.w, wl.m, wl.v, wl.hyper) == d
 
 
-def test_fused_step_over_two_launches_aligned_and_misaligned():
-    """The fused step just past one run of 2^27 coordinates: statistics, decision and every updated element against
-    the oracle; then the same data in buffers off every 16-byte boundary (the same kernels on other addresses, in both
+def test_fused_step_over_several_launches_aligned_and_misaligned():
+    """The fused step just past two runs of 2^26 coordinates: statistics, decision and every updated element against
+    the oracle; then the same data in buffers off every 16-byte boundary (the same kernels on other addresses, in all
     launches and in the ragged tile) must give the same bits."""
     d = (1 << 27) + 2 * 4096 + 5
     wl = synth.flat_1p5b(d=d, seed=33, device=DEV)     # the headline's rows and state, 8 bf16 rows

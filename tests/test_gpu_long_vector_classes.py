@@ -1,8 +1,8 @@
 """Up to 16 rows with at least 28 bytes of gradient per coordinate (14 bf16 or 7 fp32 rows; AdamW only: 20 bytes),
 in a vector of at least 2^26 coordinates: steps that write per coordinate run in a second launch class (rows in
 registers, the state update deferred to the end of an 8192-coordinate tile, one generation of blocks per launch).
-More than 16 rows run that way from 2^24 coordinates on (more than 32 rows: 3 * 2^21) and in one launch of
-2048-coordinate tiles below.  The class is chosen by the length of the whole vector, which a call that covers a
+More than 16 rows run that way where the last generation of 2^23 coordinates is full enough (always beyond three of them), else
+in one launch of 2048-coordinate tiles.  The class is chosen by the length of the whole vector, which a call that covers a
 part of it states in its shard record; the small cases here use that to reach the classes for long vectors with
 vectors the oracle finishes in a moment, the last ones run them at their real size."""
 import math
@@ -33,10 +33,10 @@ def part_of_long_vector(d):
     return B.nt_shard_info(0, 1, 0, max(d, WHOLE))
 
 
-def run(wl, flags=FULL, shard=None, grads=None, state=None, d=None, gbar_out=None):
+def run(wl, flags=FULL, shard=None, grads=None, state=None, d=None, gbar_out=None, workspace=None):
     w, m, v = state if state is not None else (wl.w, wl.m, wl.v)
     res = B.normtest_step(wl.grads if grads is None else grads, w, m, v, hyper_of(wl.hyper, flags), d=d, shard=shard,
-                          gbar_out=gbar_out)
+                          gbar_out=gbar_out, workspace=workspace)
     torch.cuda.synchronize()
     return B.read_result(res).as_dict()
 
@@ -204,7 +204,7 @@ def test_row_table_and_clipped_step_in_the_deferred_class():
     assert H.oracle_adamw_check(wl.grads, d, *state0, wl.w, wl.m, wl.v, wl.hyper, gbar=gbar, grad_scale=coef) == d
 
 
-@pytest.mark.parametrize("J,whole", [(16, WHOLE), (24, 1 << 24)])
+@pytest.mark.parametrize("J,whole", [(16, WHOLE), (24, 5 << 22)])
 def test_parts_of_a_long_vector_add_up_bit_exactly(J, whole):
     """A vector long enough for the class, cut at multiples of normtest_tile_coords into parts that are far too short
     for it on their own: with the whole length in their shard records they are cut into the same tiles, so the
@@ -213,7 +213,9 @@ def test_parts_of_a_long_vector_add_up_bit_exactly(J, whole):
     d = whole + 3 * tc + 517
     wl = synth.make("t", J, d, gdtype=torch.bfloat16, sigma=1e-2, seed=49, device=DEV, hyper=synth.Hyper(b_k=64, round_to=J, step=2))
     state0 = (wl.w.clone(), wl.m.clone(), wl.v.clone())
-    full = run(wl, FULL)
+    ws = torch.empty(B.normtest_workspace_bytes(J, d), dtype=torch.uint8, device=DEV)
+    full = run(wl, FULL, workspace=ws)
+    assert H.tile_of(ws) == TILE
     whole_state = (wl.w.clone(), wl.m.clone(), wl.v.clone())
     for t, s in zip((wl.w, wl.m, wl.v), state0):
         t.copy_(s)
@@ -221,8 +223,10 @@ def test_parts_of_a_long_vector_add_up_bit_exactly(J, whole):
     parts = []
     for sid, (lo, hi) in enumerate(zip(cuts[:-1], cuts[1:])):
         res = B.normtest_step(wl.grads[:, lo:hi], wl.w[lo:hi], wl.m[lo:hi], wl.v[lo:hi],
-                              hyper_of(wl.hyper, FULL | B.NT_PARTIAL), shard=B.nt_shard_info(sid, len(cuts) - 1, lo, d))
+                              hyper_of(wl.hyper, FULL | B.NT_PARTIAL), shard=B.nt_shard_info(sid, len(cuts) - 1, lo, d),
+                              workspace=ws)
         torch.cuda.synchronize()
+        assert H.tile_of(ws) == TILE
         parts.append(B.read_result(res))
     comb = B.normtest_combine(parts, J, hyper_of(wl.hyper)).as_dict()
     for k in ("A", "B", "C", "gbar_sq", "var_l1", "T", "next_b", "pass", "status"):
