@@ -8,8 +8,8 @@
 // behind a small record of the step, from which k_layer_stats can regroup them into a per-layer table.
 // k_adamw_gbar is the second phase of the gradient-clipped variant.  The
 // path is bound by HBM bandwidth (about two lane-operations per byte), so there is no MFMA here: the work is
-// fully coalesced 8- and 16-byte accesses, fp32 per-coordinate arithmetic, fp64 accumulation and wave64
-// shuffle reductions.  Launch shapes (block size, sweeps per tile, coordinates per launch) differ per class of
+// fully coalesced 8- and 16-byte accesses, fp32 per-coordinate arithmetic, fp64 accumulation and sums across a
+// wave by register swaps and row moves.  Launch shapes (block size, sweeps per tile, coordinates per launch) differ per class of
 // call and were chosen by measurement; see tile_cfg() and the NT_CHUNK_* constants.  Two things about the memory
 // system shape the host side: blocks that start together stay in step for a while and are served faster than an
 // even mix of loads and stores, so a long vector is walked by several launches; and writes sprinkled among many
@@ -91,7 +91,8 @@
 // lockstep drifts apart within some tens of block generations.  A kernel boundary restores it at the price of a
 // drained machine for a few microseconds.  Coordinates per launch, by class (measured; 0: one launch):
 #define NT_CHUNK_FULL (1ll << 26)        // J <= 16, fused step (2^25 .. 2^27 within 0.5 %, 2^24 -2 %, 2^28 -1 %)
-#define NT_CHUNK_FULL_FEW (1ll << 25)    // ... of up to 8 bytes of rows, two blocks per CU (4 bf16 rows +1.2 .. 2 % against 2^27)
+#define NT_CHUNK_FULL_FEW (1ll << 25)    // ... of up to 8 bytes of rows, two blocks per CU (4 bf16 rows +1.2 .. 2 % against 2^27);
+                                         // 5 to 7 bf16 rows, which take 2^26: 2^25 is -1.0 .. +0.8 %
 #define NT_CHUNK_ADAMW (1ll << 25)       // J <= 16, AdamW only (+5 %)
 #define NT_CHUNK_ADAMW_LONG (1ll << 24)  // ... in vectors of at least NT_LONG_COORDS, two blocks per CU
 #define NT_LONG_COORDS (1ll << 28)
@@ -100,14 +101,16 @@
 #define NT_CHUNK_ADAMW_GBAR (1ll << 25)  // AdamW from a stored gbar (second phase of the clipped step)
 // J > 16, modes that write per coordinate: one generation of blocks per launch, see launch_step_shape
 
-// Two blocks of 1024 threads fit a CU where a kernel has at most 64 vector registers: the fused step of up to 4 bf16 or 3 fp32
-// rows (4 with the plain kernels) and AdamW only.  In short vectors that hides latency; where a vector fills the chip several
+// Two blocks of 1024 threads fit a CU where a kernel has at most 64 vector registers: the fused step of up to 5 rows of either type
+// and AdamW only of up to 16 bf16 or 10 fp32 rows.  In short vectors that hides latency; where a vector fills the chip several
 // times over, one block at a time keeps the blocks in step and is served faster.  Asking for more than half of a CU's LDS sees to
 // it (one_block_lds).  One against two, us: fused step of 4 fp32 rows 34.8 / 32.5 at d = 2^22, 121.4 / 120.4 at 2^24, 819 / 857
 // at 124M, of 8 bf16 rows (where it keeps the next block from starting beside the last waves of a block) 35.5 / 34.7 at 2^22,
 // 9740 / 9830 at 1.5e9; AdamW only, 8 bf16 rows 29.4 / 27.4 at 2^22, 61.2 / 59.1 at 2^23, 112 / 116 at 2^24, 194 / 200 at 3e7,
 // 813 / 826 at 124M, 2013 / 1998 at 3e8; AdamW from a stored gbar +0.8 % from 6e7 on, -2 % at 1e7.  Up to 8 bytes of rows the
-// fused step prefers two at any length (4 bf16 rows 28.6 / 25.9 at 2^22, 1683 / 1661 at 304.6M), AdamW only is indifferent.
+// fused step prefers two at any length (4 bf16 rows 28.6 / 25.9 at 2^22, 1683 / 1661 at 304.6M), AdamW only is indifferent.  5 bf16
+// rows (10 bytes, two at any length): one is -4 % at 2^24, -0.6 % at 6e7 and 124M, +0.2 % at 3e8; 6 and 7 have the registers of one, and
+// asking for the LDS too costs them 1 % up to 304.6M.
 #define NT_ONE_BLOCK_LDS 82000
 // Statistics that store the mean, up to 16 rows: the same with blocks of 512 threads, beyond 2^25 coordinates.  Three instead of the four
 // per CU that the registers allow, two / three / four blocks, us: 5 bf16 rows 292 / 279 / 286 at d = 1.24e8, 149 / 140 / 141 at 6e7.  Two from 12
@@ -603,7 +606,7 @@ struct Finish {
 };
 
 // ---------------------------------------------------------------------------------------------
-// The tile loop's parts.
+// The parts of a tile's work.
 // ---------------------------------------------------------------------------------------------
 // What a lane gathers over the sweeps of one tile: the three sums in fp64 (each fed with fp32 sums of four
 // coordinates), the number of coordinates failing the coordinate-wise test and their largest ratio.
@@ -623,8 +626,10 @@ struct TileEnd {
 // Block partial of one tile -> partials[NT_NV*tile ..].
 // END: the launch has a block per tile and its last one adds up the partials (k_step_end).  The partial then goes through this
 // XCD's L2 to memory, and once it is there the block counts itself.  Both accesses are relaxed on purpose: a release would
-// write back all of the L2, in every block.  Nobody waits for another block; the state, if any, is stored after the counting, so
-// that its way to memory is not waited for.
+// write back all of the L2, in every block.  What orders them is the machine, not the language: on gfx950 a store of agent scope is
+// written through (sc1), s_waitcnt vmcnt(0) returns once it has reached the memory that all XCDs share, and the count is issued by
+// the same wave behind it; the last block's acquire then drops what its own caches may hold of the partials.  Nobody waits for another
+// block; the state, if any, is stored after the counting, so that its way to memory is not waited for.
 template <int BLOCK, bool END>
 __device__ inline TileEnd tile_reduce(const LaneAcc& acc, double (*red)[NT_NV], double* partials,
                                       int64_t tile, uint32_t* ticket) {
@@ -1254,7 +1259,7 @@ __device__ inline TileEnd tile_multi(bool part, const StepParams& p, int64_t til
 // Kernels.  A launch covers gridDim.x of the ntiles tile slots, from slot0 on, a block each; tiles below nfull are whole, and
 // when the vector ends in a part of a tile (nfull = ntiles - 1), that one has slot 0, so that it overlaps with everything else.
 // J_T = 0 selects the J > 16 row-walking variant.  (Walking tiles in a loop instead cost registers that every tile held: fused
-// step of 8 bf16 rows 82 vector and 89 scalar registers, 72 and 58 without; AdamW only 86 scalar ones, 66 without.)
+// step of 8 bf16 rows 79 vector and 91 scalar registers, 76 and 50 without; AdamW only 86 scalar ones, 74 without.)
 // ---------------------------------------------------------------------------------------------
 template <class GT, int J_T, int MODE, int BLOCK, int ITERS, bool TABLE, bool GBAR, bool DEFER_T, bool COORD, bool PART, bool END>
 __device__ inline TileEnd run_tile(bool part, const StepParams& p, int64_t tile, double (*red)[NT_NV], f32x4* gbs,
@@ -1356,11 +1361,9 @@ __global__ __launch_bounds__(BLOCK) void k_step_end(StepParams p, int64_t nfull,
 // Reduction of the tile partials.
 // ---------------------------------------------------------------------------------------------
 // First stage for long vectors: block g adds tile partials [g*NT_GROUP_TILES, ...) into one double-double
-// group partial.  The two stages are separate launches on purpose: the eight XCDs of this GPU do not share an
-// L2, so a block that waits for the other blocks' partials inside one kernel (a ticket taken after a device-wide
-// release, then a device-wide acquire) pays a write-back and an invalidation of its L2 on every block; measured,
-// that made the single launch slower (26 us at 15 groups) than these two small kernels (8 + 5 us), whose
-// visibility comes with the kernel boundary.
+// group partial.  The second stage is a launch of its own (4.7 + 4.5 us at 4 groups, 6.3 + 5.4 at 15).  One launch in which every
+// block counts itself after a device-wide release took 26 us at 15 groups: the eight XCDs of this GPU do not share an L2, and each
+// block then writes its own back.  The counting without a release that ends short steps (tile_reduce) has not been tried here.
 __global__ __launch_bounds__(NT_GROUP_THREADS) void k_reduce_groups(const double* tiles, int64_t ntiles, double* groups) {
   __shared__ double sh[NT_GROUP_THREADS / 64][2 * NT_NV];
   const int64_t t0 = (int64_t)blockIdx.x * NT_GROUP_TILES;
