@@ -1,5 +1,5 @@
 """A vector that ends inside a tile against the same vector continued with zeros to the tile's end: its last group of four
-coordinates is loaded from another place and moved, and every output has to have the bits of the whole tile."""
+coordinates is loaded from another place (and moved, where there are sums), and every output has to have the bits of the whole tile."""
 from __future__ import annotations
 
 import pytest
@@ -27,9 +27,9 @@ def _step(rows, state, d, flags, shard, table):
 
 # the classes of short vectors, of a part of a longer one, and of a part of a long one
 @pytest.mark.parametrize("whole", [None, 1 << 22, 1 << 26])
-@pytest.mark.parametrize("flags", [STATS | ADAMW | GBAR, STATS | COORD, STATS | GBAR, ADAMW])
+@pytest.mark.parametrize("flags", [STATS | ADAMW | GBAR, STATS | COORD, STATS | GBAR, ADAMW, ADAMW | GBAR])
 @pytest.mark.parametrize("J,gdtype,table", [(4, torch.bfloat16, False), (5, torch.float32, True), (16, torch.bfloat16, True),
-                                            (16, torch.float32, False), (19, torch.float32, False), (24, torch.bfloat16, True),
+                                            (16, torch.float32, False), (19, torch.float32, False), (18, torch.bfloat16, True), (24, torch.bfloat16, True),
                                             (47, torch.bfloat16, False), (33, torch.float32, True)])
 def test_bits_of_the_vector_continued_with_zeros(J, gdtype, table, flags, whole):
     n = 32768
