@@ -132,13 +132,19 @@
 #define NT_FIN_SMALL 4096       // up to this many records the finalize kernel runs with ...
 #define NT_FIN_SHORT 256        // ... this many threads
 // Up to this many tiles a step's own last block adds up the tile partials (k_step_end), in one launch instead of two (3.7 us of
-// host time).  Device time of the step, one launch against two: 4 fp32 rows 6.8 / 8.5 us at d = 5000 and 7.2 / 8.5 at 2^18,
-// read-only statistics of 8 bf16 rows 5.7 / 8.0 and 6.9 / 8.3; at 2^20 (256 tiles) 10.8 / 10.5 and 8.9 / 8.6, at 2^21 19.1 / 18.2:
-// the more blocks end together, the longer they queue at the counter, and the host is ahead of the device by then.  More than
-// 16 rows (twice the tiles, longer kernels): 64 rows 13.6 / 14.4 at d = 5000, 17.9 / 18.1 at 2^18 (128 tiles), statistics 12.9 /
-// 13.8 and 16.1 / 15.9, at 2^20 29.8 / 28.2.
+// host time).  Device time of the step, one launch against two: 4 fp32 rows 6.8 / 8.5 us at d = 5000, 7.2 / 8.5 at 2^18 and 8.9 /
+// 10.5 at 2^20 (256 tiles); read-only statistics of 8 bf16 rows 5.7 / 8.0, 6.9 / 8.3 and 6.9 / 8.6; at 2^21 (512 tiles) the fused
+// step of 4 and 8 bf16 rows 15.4 / 14.6 and 18.5 / 18.2, with a stored mean 8.5 / 8.6 and 10.6 / 10.8, where it is the second launch
+// on the host that counts; at 2^22 14.1 / 13.4.  More than 16 rows (twice the tiles, longer kernels): statistics of 17 / 64 bf16
+// rows 7.9 / 8.2 and 14.5 / 15.0 at 2^19 (256 tiles), but the fused step of 128 rows 56.2 / 55.7 at 1e6 (489).
 #define NT_TICKET_TILES 256
-#define NT_TICKET_TILES_MANY 128
+#define NT_TICKET_TILES_STATS 512
+#define NT_TICKET_TILES_MANY 256
+// Beyond this many tiles the blocks count themselves in NT_LEAVES counters, whose last ones then count themselves in one more: a
+// counter takes some 10 ns per block, one after the other, and blocks that start together end together (256 tiles: fused step of 4
+// fp32 rows 10.5 -> 8.9 us, statistics 8.2 -> 6.3; 128 tiles 7.9 -> 7.4 and 6.7 -> 6.3; 74 tiles 0.1 us slower; 16 or 32 leaves are no faster).
+#define NT_LEAF_TILES 96
+#define NT_LEAVES 8
 #define NT_NSUM 4              // summed values per tile partial: A, B, C and the count of failing coordinates
 #define NT_NV 5                // values per tile partial: the sums, then the largest coordinate-wise ratio
 #define NT_GROUP_THREADS 256   // first-stage reduction: threads per block
@@ -153,11 +159,12 @@
 #define NT_SCRATCH_BYTES (16u << 20)
 static __device__ __align__(256) unsigned char scratch[NT_SCRATCH_BYTES];
 
-// Counters with which the blocks of a launch find out which of them comes last (tile_reduce).  Zero when the library is loaded,
-// and every launch leaves the one it was given at zero.  A call takes the next one in turn, so two launches can only share one
+// Counters with which the blocks of a launch find out which of them comes last (tile_reduce): one, and NT_LEAVES more, each in an
+// array of its own so that their counting does not meet.  Zero when the library is loaded, and every launch leaves the ones it was
+// given at zero.  A call takes the next ones in turn, so two launches can only share them
 // if a whole round of calls lies between them while both run: more launches than a device's queues hold (32 of 16384 packets).
 #define NT_TICKETS (1u << 20)
-static __device__ uint32_t tickets[NT_TICKETS];
+static __device__ uint32_t tickets[(1 + NT_LEAVES) * NT_TICKETS];
 
 namespace {
 
@@ -604,6 +611,27 @@ struct Finish {
   nt_result* out;     // null: k_finalize follows
   uint32_t* ticket;   // steps of more than one tile: where its blocks count themselves
 };
+// The counter of one block of such a step: its leaf (blocks of neighbouring numbers have different ones), or the only one.
+__device__ inline uint32_t* leaf_of(uint32_t* ticket, int64_t ntiles) {
+  return ticket && ntiles > NT_LEAF_TILES ? ticket + (1 + blockIdx.x % NT_LEAVES) * (size_t)NT_TICKETS : ticket;
+}
+__device__ inline uint32_t count_up(uint32_t* ticket) {
+  return __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// Whether the block that found `before` others at its counter is the last of the step's; the counters are then as they were given.
+__device__ inline bool last_block(uint32_t* ticket, uint32_t ntiles, uint32_t before) {
+  uint32_t all = ntiles;
+  if (ntiles > NT_LEAF_TILES) {
+    const uint32_t leaf = blockIdx.x % NT_LEAVES;
+    if (before != (ntiles - leaf + NT_LEAVES - 1) / NT_LEAVES - 1) return false;
+    __hip_atomic_store(leaf_of(ticket, ntiles), 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    before = count_up(ticket);
+    all = NT_LEAVES;
+  }
+  if (before != all - 1) return false;
+  __hip_atomic_store(ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return true;
+}
 
 // ---------------------------------------------------------------------------------------------
 // The parts of a tile's work.
@@ -656,7 +684,7 @@ __device__ inline TileEnd tile_reduce(const LaneAcc& acc, double (*red)[NT_NV], 
       __hip_atomic_store(to, t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       if (ticket) {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        if (threadIdx.x == 0) end.before = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (threadIdx.x == 0) end.before = count_up(ticket);
       }
     } else {
       *to = t;
@@ -1322,7 +1350,8 @@ __global__ __launch_bounds__(BLOCK) void k_step(StepParams p, int64_t nfull, int
 template <class GT, int J_T, int MODE, int BLOCK, int ITERS, bool TABLE, bool GBAR, bool DEFER_T = false>
 __global__ __launch_bounds__(BLOCK) void k_step_end(StepParams p, int64_t nfull, int64_t ntiles, int64_t slot0,
                                                     Finish fin) {
-  const TileEnd end = block_tile<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, DEFER_T, true, true>(p, nfull, ntiles, slot0, fin.ticket);
+  const TileEnd end = block_tile<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, DEFER_T, true, true>(p, nfull, ntiles, slot0,
+                                                                                                      leaf_of(fin.ticket, ntiles));
   Totals tot;
   totals_clear(tot);
   if constexpr (MODE == MODE_ADAMW) {
@@ -1338,17 +1367,12 @@ __global__ __launch_bounds__(BLOCK) void k_step_end(StepParams p, int64_t nfull,
     tot.s[3] = ahead<3>(t);
     tot.mx = ahead<4>(end.value);
   } else {
-    // The last block to count itself finds every partial in memory; it invalidates its caches, which may hold older ones, and
-    // leaves the counter as it was given.
+    // The last block to count itself finds every partial in memory; it invalidates its caches, which may hold older ones.
     __shared__ bool last;
     __shared__ double sh[NT_FIN_SHORT / 64][2 * NT_NV];
     if (threadIdx.x == 0) {
-      const bool me = end.before == (uint32_t)ntiles - 1;
-      if (me) {
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-        __hip_atomic_store(fin.ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      }
-      last = me;
+      last = last_block(fin.ticket, (uint32_t)ntiles, end.before);
+      if (last) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     }
     __syncthreads();
     if (!last) return;
@@ -2089,7 +2113,8 @@ static int enqueue_step(const void* grads, bool table, nt_dtype gdtype, int64_t 
     Finish fin;
     std::memset(&fin, 0, sizeof(fin));
     // no sums, one partial that is the total, or few enough for the last block: launch_tiles_of has the kernels
-    if (mode == MODE_ADAMW || ntiles == 1 || (ntiles <= (J <= NT_JCHUNK ? NT_TICKET_TILES : NT_TICKET_TILES_MANY) && next_ticket(st, &fin.ticket))) {
+    const int64_t most = J > NT_JCHUNK ? NT_TICKET_TILES_MANY : mode == MODE_STATS ? NT_TICKET_TILES_STATS : NT_TICKET_TILES;
+    if (mode == MODE_ADAMW || ntiles == 1 || (ntiles <= most && next_ticket(st, &fin.ticket))) {
       fin.q = q;
       fin.hdr = record;
       fin.hdr_out = hdr_out;

@@ -103,6 +103,24 @@ def test_bits_of_two_launches(J, gdtype, flags, tile, most, whole, past):
         c.check(want)
 
 
+# both sides of the count from which the blocks count themselves in several counters, one more than a round of those, and of the
+# last counts that end in one launch
+@pytest.mark.parametrize("J,gdtype,flags,tile,tiles", [
+    (3, torch.bfloat16, STATS | ADAMW, 4096, (96, 97, 104, 105, 256)), (6, torch.float32, STATS | GBAR | COORD, 4096, (97, 511, 512, 513)),
+    (9, torch.bfloat16, STATS, 4096, (103, 511)), (23, torch.float32, STATS | ADAMW, 2048, (96, 97, 256, 257)),
+    (50, torch.bfloat16, STATS | GBAR, 2048, (97, 256, 257))])
+def test_bits_of_two_launches_with_several_counters(J, gdtype, flags, tile, tiles):
+    for n in tiles:
+        c = _Calls(J, gdtype, n * tile - 5, flags)
+        want = c.two_launches()
+        c.reset()
+        results = torch.zeros(6 * K, B.RESULT_BYTES, dtype=torch.uint8, device=DEV)
+        for i in range(results.shape[0]):
+            c.matrix(i % K, results[i])
+        c.check(want)
+        assert all(torch.equal(results[i], want[i % K][0]) for i in range(results.shape[0])), n
+
+
 # Sums that are not finite: the last block's totals against the reduction kernel's, an infinite row and squares that overflow
 @pytest.mark.parametrize("J,gdtype,tile", [(2, torch.float32, 4096), (16, torch.bfloat16, 4096), (33, torch.float32, 2048)])
 @pytest.mark.parametrize("value", [float("inf"), float("nan"), 1e20])
