@@ -90,7 +90,7 @@ typedef struct {
  * coordinates, so a shard needs nothing from the others; the record is checked for consistency, and d_global
  * has one effect: long vectors are cut into larger tiles than short ones (steps that write per coordinate,
  * with 7 to 16 fp32 or 14 to 16 bf16 rows: from 2^26 coordinates; 17 to 32 rows: from 2^24; more rows: from
- * 3 * 2^21; a step with AdamW only, which forms no sums, also from 5 fp32 and 10 bf16 rows; read-only
+ * 3 * 2^21; every step of more than 16 rows: beyond 2^18; a step with AdamW only, which forms no sums, also from 5 fp32 and 10 bf16 rows; read-only
  * statistics of up to 16 rows: from 2^21), and a call with a shard record is cut the way a vector of d_global
  * coordinates is (a call without one: the way a vector of d is). */
 typedef struct {
@@ -139,7 +139,8 @@ typedef struct {
 int64_t normtest_tile_coords(int64_t J);
 
 /* Bytes of device workspace normtest_step needs for J rows of d coordinates (0 if J or d is invalid): a 256-byte
- * record of the step and a few doubles per tile of coordinates (about 0.01 byte per coordinate). */
+ * record of the step and a few doubles per tile of coordinates (about 0.01 byte per coordinate, more than 16 rows 0.02 and up to 2^18
+ * coordinates 0.04). */
 size_t normtest_workspace_bytes(int64_t J, int64_t d);
 
 /* The same for a known gradient dtype and nt_hyper.flags: what normtest_step (and the other step entry points)
@@ -163,10 +164,10 @@ size_t normtest_workspace_bytes_for(nt_dtype gdtype, int64_t J, int64_t d, uint3
  * is walked by several launches of the same kernel over consecutive runs of tiles (one per 2^24 to 2^27
  * coordinates up to 16 rows, one per 2^23 where 14 or more bf16 or 7 or more fp32 rows, with AdamW only 10 or 5, are 2^26 coordinates
  * or longer, and beyond 16 rows where such runs are full enough, else one; the memory system serves blocks that start together faster),
- * followed by one or two small reduction kernels.  There is none after AdamW only, after a call of a single tile (2048 coordinates
- * beyond 16 rows, else 4096) and, outside graph capture, after one of up to 2^20 coordinates, 2^19 beyond 16 rows (statistics of up to
- * 16 rows: 2^21, without a stored mean below that); a part of a
- * vector that is itself longer (d_global) has one if that vector is read in larger tiles, or if more than 16 rows come as a table.
+ * followed by one or two small reduction kernels.  There is none after AdamW only, after a call of a single tile (1024 coordinates
+ * beyond 16 rows, else 4096) and, outside graph capture, after one of up to 2^20 coordinates, 2^18 beyond 16 rows (statistics of up to
+ * 16 rows: 2^21, without a stored mean below that); a part of a vector that is itself longer (d_global) has one if that vector is read in
+ * larger tiles, or if more than 16 rows come as a table.
  * Results do not depend on how many launches there were.  Any element-aligned pointer and
  * any row stride is accepted: the kernels access rows, w, m, v and gbar_out with the same vector instructions whatever
  * the alignment, with bit-identical results.  d == 0 succeeds (sums are 0).

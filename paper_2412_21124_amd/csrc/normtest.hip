@@ -20,9 +20,10 @@
 // Numerics.  The centred sum C = sum_j (g_j - gbar)^2 is formed directly from the J values of a
 // coordinate held in registers, never as A - B/J (which cancels badly when the workers agree).  A
 // rounding error e in gbar only adds J e^2 to a coordinate's centred sum because the cross term
-// sums to zero.  For more than 16 rows the rows are taken 16 at a time, each chunk shifted by the
+// sums to zero.  More than 16 fp32 rows are taken 16 at a time, each chunk shifted by the
 // running mean so far, and the chunks' means and centred sums are merged with the pairwise update
-// M2 += M2_b + delta^2 n_a n_b / (n_a + n_b).  Row sums are carried in fp64, so the mean handed to
+// M2 += M2_b + delta^2 n_a n_b / (n_a + n_b).  More than 16 bf16 rows, whose squares have 16 bits, are summed with their squares in
+// fp64, where both are exact or nearly so, and C is the difference (centred).  Row sums are carried in fp64, so the mean handed to
 // AdamW is correctly rounded even when the rows cancel.
 // Per-lane sums leave fp32 after one group of 4 coordinates; everything above is fp64 in a fixed
 // order, so results do not depend on the grid size and are reproducible bit for bit.
@@ -69,9 +70,10 @@
 // of 256 CUs) is nearly full, or enough of the one after the first or second (generations_pay); else one launch of short tiles, of
 // which the chip takes any number (512 rows, d = 2^18: 607 -> 92 us).
 #define NT_GENERATION (1ll << 23)
+#define NT_PAUSE_ROWS 48         // bf16 rows from which the walk pauses between chunks (chunk_pause)
 #define NT_BLOCK_MANY_SHORT 256
 #define NT_ITERS_MANY_SHORT 2
-// J > 16, every mode, in the shortest vectors, whose tiles leave each CU at most a block or two: the same tile as one sweep of
+// J > 16, every mode, in short vectors, whose tiles leave each CU at most a block or two: the same tile as one sweep of
 // 512 threads, so that a block walks the rows once.  Shape above -> this one, us: fused step of 17 / 64 / 512 bf16 rows at d =
 // 100,003 9.2 / 18.7 / 103 -> 7.6 / 13.7 / 66, at 3e5 10.1 / 18.0 / 89.7 -> 8.4 / 14.0 / 62.7, at 5e5 11.8 / 19.4 / 95.4 -> 9.8 / 15.3 /
 // 78.1, at 7e5 14.0 / 24.3 / 129 and 12.1 / 23.9 / 129, at 1e6 14.7 / 26.2 / 154 and 13.2 / 26.4 / 159, at 2e6 20 rows 23.7 and 25.5;
@@ -81,6 +83,16 @@
 #define NT_ITERS_MANY_TINY 1
 #define NT_MANY_TINY_COORDS (1ll << 19)
 #define NT_MANY_TINY_COORDS_32 (1ll << 20)   // up to 32 bf16 rows, unless AdamW only
+// J > 16, every mode, in the shortest vectors: tiles of 1024 coordinates.  A CU reads some 45 GB/s at most, whatever it has in flight, so
+// what counts is how many of them have a tile.  bf16 rows: the waves of a block share the rows as well (tile_split), two of them up to
+// 32 rows and four beyond, as one wave alone walks 512 rows in 32 steps of 2 us, most of it arithmetic.  fp32 rows: blocks of 256 threads.
+// Shape above -> these, us: fused step of 17 / 64 / 128 / 512 bf16 rows at d = 20,001 7.8 / 13.7 / 21.4 / 66 -> 7.2 / 10.0 / 13.1 /
+// 32, at 2^18 9.0 / 13.9 / 20.7 / 61 -> 8.3 / 11.4 / 16.5 / 46; of 17 / 64 / 512 fp32 rows at d = 100,003 9.3 / 15.9 / 84 -> 8.0 /
+// 12.9 / 60; AdamW only, 64 bf16 rows 8.8 -> 6.1 at 100,003.  Beyond 2^18 coordinates some CUs have two tiles: 64 bf16 rows at 3e5 14.2
+// and 15.1.
+#define NT_SPLIT_TILE 1024
+#define NT_SPLIT_COORDS (1ll << 18)
+#define NT_SPLIT 1000            // J_T of the kernels whose waves share the rows is NT_SPLIT + how many of them
 #define NT_BLOCK_LARGE_STATS 256 // J > 16, statistics only otherwise (nothing written per coordinate): short tiles, so that a
 #define NT_ITERS_LARGE_STATS 2   // vector of a few million coordinates still gives every CU several blocks
 #define NT_MAX_GRID (1ll << 21)  // blocks per launch at most: HIP's limit is on the threads, 2^32 - 1
@@ -126,6 +138,7 @@
 #define NT_AUX_BLOCK 1024     // threads per block of the AdamW-from-gbar, copy and yardstick kernels
 
 #define NT_JCHUNK 16          // up to this many rows a coordinate's values are all held in registers
+#define NT_SEGMENTS 4
 #define NT_MCHUNK 16          // beyond that, rows are walked this many at a time (2 .. NT_JCHUNK + 1; 16 measured best)
 #define NT_ROUND_TO_MAX (1ll << 31)  // bound on nt_hyper.round_to that keeps the rounding chain inside int64
 #define NT_FIN_THREADS 1024
@@ -135,11 +148,12 @@
 // host time).  Device time of the step, one launch against two: 4 fp32 rows 6.8 / 8.5 us at d = 5000, 7.2 / 8.5 at 2^18 and 8.9 /
 // 10.5 at 2^20 (256 tiles); read-only statistics of 8 bf16 rows 5.7 / 8.0, 6.9 / 8.3 and 6.9 / 8.6; at 2^21 (512 tiles) the fused
 // step of 4 and 8 bf16 rows 15.4 / 14.6 and 18.5 / 18.2, with a stored mean 8.5 / 8.6 and 10.6 / 10.8, where it is the second launch
-// on the host that counts; at 2^22 14.1 / 13.4.  More than 16 rows (twice the tiles, longer kernels): statistics of 17 / 64 bf16
-// rows 7.9 / 8.2 and 14.5 / 15.0 at 2^19 (256 tiles), but the fused step of 128 rows 56.2 / 55.7 at 1e6 (489).
+// on the host that counts; at 2^22 14.1 / 13.4.  More than 16 rows: in the shortest vectors up to 256 tiles, 64 bf16 rows at 2^18 11.4 /
+// 13.6; in the longer ones' tiles of 2048 coordinates, in kernels that live longer, up to 128: 17 / 64 rows at 2^19 (256 tiles) are
+// equal, but 64 fp32 rows take 20.9 / 20.6 at 388,160 and 128 bf16 rows 56.2 / 55.7 at 1e6.
 #define NT_TICKET_TILES 256
 #define NT_TICKET_TILES_STATS 512
-#define NT_TICKET_TILES_MANY 256
+#define NT_TICKET_TILES_MANY 128
 // Beyond this many tiles the blocks count themselves in NT_LEAVES counters, whose last ones then count themselves in one more: a
 // counter takes some 10 ns per block, one after the other, and blocks that start together end together (256 tiles: fused step of 4
 // fp32 rows 10.5 -> 8.9 us, statistics 8.2 -> 6.3; 128 tiles 7.9 -> 7.4 and 6.7 -> 6.3; 74 tiles 0.1 us slower; 16 or 32 leaves are no faster).
@@ -735,6 +749,22 @@ __device__ inline float chunk_merge(bool first, int na, int nb, double inv_na, d
   return (float)(S * inv_n);
 }
 
+// More than 16 bf16 rows: sum x and sum x^2 of a coordinate in fp64, hence the centred sum without a shift.  x^2 has 16 bits, so both
+// sums are exact unless the rows' magnitudes lie a factor of 2^14 or more apart, where no centred sum is small.  Against 64 bits C is
+// 2.4e-10 off (128 rows, d = 1,000,003) and 2.2e-9 (24 rows, 100,003), where sums of fp32 squares with a shift were 3.4e-9 and 1.6e-8.
+// An element takes 17 cycles of a SIMD, with the
+// shift and the merges 27.  The rows are added up in up to four segments of whole chunks, one after the other within a segment, and
+// the segments in their order: the waves of a block can then take one each (tile_split) with the same bits.
+__host__ __device__ inline int segment_rows(int J) {
+  return ((J + NT_MCHUNK - 1) / NT_MCHUNK + NT_SEGMENTS - 1) / NT_SEGMENTS * NT_MCHUNK;
+}
+// sum x^2 - S^2 / J: the difference J Q - S^2 with the product's rounding error, so that equal rows give zero
+__device__ inline float centred(int J, double inv_J, double S, double Q) {
+  const double n = (double)J, t = n * Q;
+  const double c = __builtin_fma(-S, S, t) + __builtin_fma(n, Q, -t);
+  return (float)((c < 0.0 ? 0.0 : c) * inv_J);
+}
+
 // ---------------------------------------------------------------------------------------------
 // One coordinate by itself, any J and any alignment: what the per-layer table needs at a layer's ends, where a layer covers
 // a part of a tile (piece_sums).  The operations on a coordinate are those of the tiles below, in their order, and have to
@@ -758,6 +788,26 @@ __device__ inline void coord_stats_generic(const StepParams& p, int64_t i, doubl
     }
     S = sb;
     M2 = cb;
+    return;
+  }
+  if constexpr (GT::ESIZE == 2) {
+    const int segment = segment_rows(J);
+    double Q = 0.0;
+    S = 0.0;
+    for (int j0 = 0; j0 < J; j0 += segment) {
+      const int end = J - j0 < segment ? J : j0 + segment;
+      double s = 0.0, q = 0.0;
+#pragma unroll 8
+      for (int j = j0; j < end; ++j) {
+        const double x = (double)GT::ld(row_base<GT, TABLE>(p, j), i);
+        s += x;
+        q = __builtin_fma(x, x, q);
+      }
+      S += s;
+      Q += q;
+    }
+    a = (float)Q;
+    M2 = centred(J, p.inv_J, S, Q);
     return;
   }
   float K = GT::ld(row_base<GT, TABLE>(p, 0), i);
@@ -1176,6 +1226,28 @@ __device__ inline void chunk_clear(double* sb, float* q) {
   }
 }
 
+template <class GT, bool MOVES, int N>
+__device__ inline void chunk_moments(typename GT::raw_t* raw, const Reach& at, double* s, double* q) {
+#pragma unroll
+  for (int j = 0; j < N; ++j) {
+    if constexpr (MOVES) raw[j] = GT::moved(raw[j], at.sh);
+#pragma unroll
+    for (int e = 0; e < GT::VEC; ++e) {
+      const double x = (double)GT::val(raw[j], e);
+      s[e] += x;
+      q[e] = __builtin_fma(x, x, q[e]);
+    }
+  }
+}
+template <int VEC>
+__device__ inline void segment_end(double* S, double* Q, double* s, double* q) {
+#pragma unroll
+  for (int e = 0; e < VEC; ++e) {
+    S[e] += s[e];
+    Q[e] += q[e];
+    s[e] = q[e] = 0.0;
+  }
+}
 // The last nb < 16 rows, in runs of 8, 4, 2 and 1 with a branch each, first all loads and then all sums (a branch per row
 // costs more than it saves).  The rows keep their order.
 static_assert(NT_MCHUNK <= 16, "the last chunk is walked in runs of 8, 4, 2 and 1 rows");
@@ -1189,16 +1261,111 @@ __device__ inline void accumulate_last(int nb, typename GT::raw_t* raw, const Re
   if (nb & RUN) chunk_accumulate<GT, MOVES, RUN>(raw, at, K, sb, q);
   if constexpr (RUN > 1) accumulate_last<GT, MOVES, RUN / 2>(nb, raw + RUN, at, K, sb, q);
 }
+template <class GT, bool MOVES, int RUN>
+__device__ inline void moments_last(int nb, typename GT::raw_t* raw, const Reach& at, double* s, double* q) {
+  if (nb & RUN) chunk_moments<GT, MOVES, RUN>(raw, at, s, q);
+  if constexpr (RUN > 1) moments_last<GT, MOVES, RUN / 2>(nb, raw + RUN, at, s, q);
+}
 
-// Waits until all but four of a chunk's loads have arrived, before its first sum.  The walk of more than 32 bf16 rows in the class
-// for long vectors needs it to keep the blocks of a generation in step: without it, each sum starting as its row arrives, 64 /
-// 128 / 512 rows at d = 2^24 take 414 / 734 / 2622 us, with it 401 / 716 / 2571 (waiting for all of them 404 / 721 / 2570, for half
-// of them 401 / 721 / 2580).  With up to 32 rows it costs 0.5 %, in short vectors 1 to 5 %.  AdamW only, 64 rows: 406 us with it, 410
-// without.
-__device__ inline void chunk_wait() {
+// How the walk of more than 32 bf16 rows in the class for long vectors keeps the blocks of a generation in step.  A chunk's first sum
+// waits until its loads have arrived: without it, each sum starting as its row arrives, 64 / 128 / 512 rows at d = 2^24 took 414 / 734 /
+// 2622 us, with it 401 / 716 / 2571; in short vectors it costs 1 to 5 %, with up to 32 rows 0.5 %, and below 48 rows all but four loads
+// are the better count (40 rows with the mean 231 us, waiting for all of them 236).  And where a launch is a whole generation, so that
+// every CU has four blocks, a wave of 48 rows or more pauses after each chunk: the memory system serves fewer requests at a time
+// faster.  Without and with the pause, us: fused step of 128 / 256 / 512 rows at 2^24 726 / 1348 / 2587 and 712 / 1323 / 2518, AdamW
+// only of 256 rows at 2^23 692 and 662, 64 rows at 1e8 2302 and 2286; 40 rows 289 and 291.  In a launch with fewer blocks it costs 3 %.
+__device__ inline void chunk_wait(int J) {
   __builtin_amdgcn_sched_barrier(0);
-  __builtin_amdgcn_s_waitcnt(0x0f70 | 4);   // vmcnt(4)
+  if (J >= NT_PAUSE_ROWS)
+    __builtin_amdgcn_s_waitcnt(0x0f70);
+  else if (J > 32)
+    __builtin_amdgcn_s_waitcnt(0x0f70 | 4);   // vmcnt(4)
   __builtin_amdgcn_sched_barrier(0);
+}
+__device__ inline void chunk_pause(int J) {
+  if (J < NT_PAUSE_ROWS || gridDim.x < NT_GENERATION / (NT_BLOCK_LARGE * NT_ITERS_LARGE * NT_VEC)) return;
+  __builtin_amdgcn_sched_barrier(0);
+  if (J >= 2 * NT_PAUSE_ROWS)
+    __builtin_amdgcn_s_sleep(18);   // 64 cycles each
+  else
+    __builtin_amdgcn_s_sleep(12);
+}
+
+// All rows of the lane's coordinates: row sum, centred sum and sum of squares.  bf16 rows, by their moments (see centred).
+template <class GT, bool TABLE, bool MOVES, bool WAITS>
+__device__ inline void walk_moments(bool part, const StepParams& p, const Reach& at, double* S, float* M2, float* a) {
+  constexpr int VEC = GT::VEC;
+  const int J = p.J, segment = segment_rows(J);
+  double Q[VEC], s[VEC], q[VEC];
+#pragma unroll
+  for (int e = 0; e < VEC; ++e) S[e] = Q[e] = s[e] = q[e] = 0.0;
+  typename GT::raw_t raw[NT_MCHUNK];
+  int j0 = 0, end = segment;
+#pragma unroll 1
+  for (; j0 + NT_MCHUNK <= J; j0 += NT_MCHUNK) {
+    if (j0 == end) {
+      end += segment;
+      segment_end<VEC>(S, Q, s, q);
+    }
+    load_rows<GT, TABLE, NT_MCHUNK>(part, p, j0, at, raw);
+    if (WAITS) chunk_wait(J);
+    chunk_moments<GT, MOVES, NT_MCHUNK>(raw, at, s, q);
+    if (WAITS) chunk_pause(J);
+  }
+  if (j0 < J) {
+    if (j0 == end) segment_end<VEC>(S, Q, s, q);
+    load_last<GT, TABLE, 8>(part, p, j0, J - j0, at, raw);
+    moments_last<GT, MOVES, 8>(J - j0, raw, at, s, q);
+  }
+  segment_end<VEC>(S, Q, s, q);
+#pragma unroll
+  for (int e = 0; e < VEC; ++e) {
+    a[e] = (float)Q[e];
+    M2[e] = centred(J, p.inv_J, S[e], Q[e]);
+  }
+}
+// fp32 rows, whose squares need twice fp64's digits: every chunk shifted by the mean of the rows before it (see chunk_merge).
+template <class GT, bool TABLE, bool MOVES>
+__device__ inline void walk_shifted(bool part, const StepParams& p, const Reach& at, double* S, float* M2, float* a) {
+  constexpr int VEC = GT::VEC;
+  const int J = p.J;
+  double sb[VEC];
+  float K[VEC], q[VEC];
+#pragma unroll
+  for (int e = 0; e < VEC; ++e) a[e] = 0.f;
+  typename GT::raw_t raw[NT_MCHUNK];
+  // first chunk (J > NT_JCHUNK >= NT_MCHUNK - 1 here, so it is full), shifted by the first row
+  load_rows<GT, TABLE, NT_MCHUNK>(part, p, 0, at, raw);
+  if constexpr (MOVES) raw[0] = GT::moved(raw[0], at.sh);
+#pragma unroll
+  for (int e = 0; e < VEC; ++e) K[e] = GT::val(raw[0], e);
+  chunk_clear<VEC>(sb, q);
+  chunk_accumulate<GT, false, 1>(raw, at, K, sb, q);
+  chunk_accumulate<GT, MOVES, NT_MCHUNK - 1>(raw + 1, at, K, sb, q);
+#pragma unroll
+  for (int e = 0; e < VEC; ++e) K[e] = chunk_merge(true, 0, NT_MCHUNK, 0.0, 1.0 / NT_MCHUNK, K[e], sb[e], q[e], S[e], M2[e], a[e]);
+  double inv_j0 = 1.0 / NT_MCHUNK;
+  int j0 = NT_MCHUNK;
+#pragma unroll 1
+  for (; j0 + NT_MCHUNK <= J; j0 += NT_MCHUNK) {
+    load_rows<GT, TABLE, NT_MCHUNK>(part, p, j0, at, raw);
+    chunk_clear<VEC>(sb, q);
+    chunk_accumulate<GT, MOVES, NT_MCHUNK>(raw, at, K, sb, q);
+    const double inv_n = 1.0 / (double)(j0 + NT_MCHUNK);
+#pragma unroll
+    for (int e = 0; e < VEC; ++e)
+      K[e] = chunk_merge(false, j0, NT_MCHUNK, inv_j0, inv_n, K[e], sb[e], q[e], S[e], M2[e], a[e]);
+    inv_j0 = inv_n;
+  }
+  if (j0 < J) {
+    const int nb = J - j0;
+    load_last<GT, TABLE, 8>(part, p, j0, nb, at, raw);
+    chunk_clear<VEC>(sb, q);
+    accumulate_last<GT, MOVES, 8>(nb, raw, at, K, sb, q);
+#pragma unroll
+    for (int e = 0; e < VEC; ++e)
+      K[e] = chunk_merge(false, j0, nb, inv_j0, 0.0, K[e], sb[e], q[e], S[e], M2[e], a[e]);   // the last: K is not used again
+  }
 }
 
 // The state update (and the gbar store) of a tile is deferred (see deferred_update): with many rows the writes are
@@ -1212,53 +1379,19 @@ __device__ inline TileEnd tile_multi(bool part, const StepParams& p, int64_t til
   constexpr bool WRITES = (MODE != MODE_STATS) || GBAR;
   constexpr bool MOVES = PART && moves_rows<GT, 0, MODE, BLOCK, ITERS, TABLE, false>();
   constexpr bool WAITS = WRITES && GT::ESIZE == 2 && BLOCK * ITERS == NT_BLOCK_LARGE * NT_ITERS_LARGE;
-  const int J = p.J;
   LaneAcc acc;
 #pragma unroll 1
   for (int it = 0; it < ITERS; ++it) {
     const Place pl = {tile * TILE + (int64_t)it * BLOCK * VEC, threadIdx.x * VEC};
     // a sweep or a wave that lies wholly past d adds nothing, and has no means to leave for the update
     if (PART && part && pl.s0 + (int64_t)__builtin_amdgcn_readfirstlane(threadIdx.x) * VEC >= p.d) break;
-    double S[VEC], sb[VEC];
-    float M2[VEC], a[VEC], K[VEC], q[VEC];
-#pragma unroll
-    for (int e = 0; e < VEC; ++e) a[e] = 0.f;
-    typename GT::raw_t raw[NT_MCHUNK];
-    // first chunk (J > NT_JCHUNK >= NT_MCHUNK - 1 here, so it is full), shifted by the first row
+    double S[VEC];
+    float M2[VEC], a[VEC];
     const Reach at = reach(PART && part, p, pl);
-    load_rows<GT, TABLE, NT_MCHUNK>(PART && part, p, 0, at, raw);
-    if (WAITS && J > 32) chunk_wait();
-    if constexpr (MOVES) raw[0] = GT::moved(raw[0], at.sh);
-#pragma unroll
-    for (int e = 0; e < VEC; ++e) K[e] = GT::val(raw[0], e);
-    chunk_clear<VEC>(sb, q);
-    chunk_accumulate<GT, false, 1>(raw, at, K, sb, q);
-    chunk_accumulate<GT, MOVES, NT_MCHUNK - 1>(raw + 1, at, K, sb, q);
-#pragma unroll
-    for (int e = 0; e < VEC; ++e) K[e] = chunk_merge(true, 0, NT_MCHUNK, 0.0, 1.0 / NT_MCHUNK, K[e], sb[e], q[e], S[e], M2[e], a[e]);
-    double inv_j0 = 1.0 / NT_MCHUNK;
-    int j0 = NT_MCHUNK;
-#pragma unroll 1
-    for (; j0 + NT_MCHUNK <= J; j0 += NT_MCHUNK) {
-      load_rows<GT, TABLE, NT_MCHUNK>(PART && part, p, j0, at, raw);
-      if (WAITS && J > 32) chunk_wait();
-      chunk_clear<VEC>(sb, q);
-      chunk_accumulate<GT, MOVES, NT_MCHUNK>(raw, at, K, sb, q);
-      const double inv_n = 1.0 / (double)(j0 + NT_MCHUNK);
-#pragma unroll
-      for (int e = 0; e < VEC; ++e)
-        K[e] = chunk_merge(false, j0, NT_MCHUNK, inv_j0, inv_n, K[e], sb[e], q[e], S[e], M2[e], a[e]);
-      inv_j0 = inv_n;
-    }
-    if (j0 < J) {
-      const int nb = J - j0;
-      load_last<GT, TABLE, 8>(PART && part, p, j0, nb, at, raw);
-      chunk_clear<VEC>(sb, q);
-      accumulate_last<GT, MOVES, 8>(nb, raw, at, K, sb, q);
-#pragma unroll
-      for (int e = 0; e < VEC; ++e)
-        K[e] = chunk_merge(false, j0, nb, inv_j0, 0.0, K[e], sb[e], q[e], S[e], M2[e], a[e]);   // the last: K is not used again
-    }
+    if constexpr (GT::ESIZE == 2)
+      walk_moments<GT, TABLE, MOVES, WAITS>(PART && part, p, at, S, M2, a);
+    else
+      walk_shifted<GT, TABLE, MOVES>(PART && part, p, at, S, M2, a);
     float gb[VEC];
 #pragma unroll
     for (int e = 0; e < VEC; ++e) gb[e] = (float)(S[e] * p.inv_J);
@@ -1284,9 +1417,122 @@ __device__ inline TileEnd tile_multi(bool part, const StepParams& p, int64_t til
 }
 
 // ---------------------------------------------------------------------------------------------
+// Tile, more than 16 bf16 rows, in the shortest vectors (see NT_SPLIT_TILE): a block's waves share the rows too.  SPLIT waves walk one
+// segment of the rows each at the same 256 coordinates; their sums meet in LDS, where each thread adds up the segments of its
+// coordinate (or two coordinates, with two segments) in their order, with the bits of tile_multi.  Bound by what one CU reads, 45 GB/s:
+// a tile of 512 rows takes 32 us, a MB at 33 GB/s; with a chunk split in halves, one in flight while the other is added up, 2 % more.
+// ---------------------------------------------------------------------------------------------
+template <int SPLIT, bool STATS>
+struct SplitShared {
+  double s[SPLIT][NT_SPLIT_TILE];
+  double q[STATS ? SPLIT : 1][STATS ? NT_SPLIT_TILE : 1];
+};
+// x of the lane whose number differs in the last two bits as CTRL says (quad permutation)
+template <int CTRL>
+__device__ inline float quad(float x) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), CTRL, 0xf, 0xf, true));
+}
+// lane_tree of the values of four neighbouring lanes
+__device__ inline float quad_tree(float x) {
+  x += quad<0xb1>(x);          // lanes 1 0 3 2
+  return x + quad<0x4e>(x);    // lanes 2 3 0 1
+}
+
+template <class GT, int SPLIT, int MODE, bool TABLE, bool GBAR, bool END>
+__device__ inline TileEnd tile_split(bool part, const StepParams& p, int64_t tile, double (*red)[NT_NV],
+                                     SplitShared<SPLIT, MODE != MODE_ADAMW>& sh, uint32_t* ticket) {
+  constexpr int VEC = GT::VEC, T = NT_SPLIT_TILE, BLOCK = SPLIT * T / VEC;
+  constexpr int X = T / BLOCK;   // coordinates per thread
+  static_assert(X * BLOCK == T, "whole tiles");
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int mine = wave / (T / 256), col = wave % (T / 256);
+  const int J = p.J, segment = segment_rows(J);
+  const Place pl = {tile * T + col * 256, (uint32_t)lane * VEC};
+  // a wave that lies wholly past d loads the vector's first group and moves all of it out
+  const Reach at = pl.s0 < p.d ? reach(part, p, pl) : Reach{0, 0, 4};
+  int j0 = mine * segment;
+  const int end = j0 + segment < J ? j0 + segment : J;
+  typename GT::raw_t raw[NT_MCHUNK];
+  double s[VEC], q[VEC];
+#pragma unroll
+  for (int e = 0; e < VEC; ++e) s[e] = q[e] = 0.0;
+  // the state of the coordinates that this thread finishes, on its way meanwhile
+  bool own[X];
+  float w[X], m[X], v[X];
+#pragma unroll
+  for (int x = 0; x < X; ++x) {
+    const int i = threadIdx.x + x * BLOCK;
+    own[x] = !part || tile * T + i < p.d;
+    if constexpr (MODE != MODE_STATS) {
+      w[x] = m[x] = v[x] = 0.f;
+      if (own[x]) {
+        w[x] = ld_nt<float>(scalar(p.w + tile * T) + i);
+        m[x] = ld_nt<float>(scalar(p.m + tile * T) + i);
+        v[x] = ld_nt<float>(scalar(p.v + tile * T) + i);
+      }
+    }
+  }
+#pragma unroll 1
+  for (; j0 + NT_MCHUNK <= end; j0 += NT_MCHUNK) {
+    load_rows<GT, TABLE, NT_MCHUNK>(part, p, j0, at, raw);
+    settle<GT, NT_MCHUNK, true>(part, pl, at, raw);
+    chunk_moments<GT, false, NT_MCHUNK>(raw, at, s, q);
+  }
+  if (j0 < end) {
+    load_last<GT, TABLE, 8>(part, p, j0, end - j0, at, raw);
+    moments_last<GT, true, 8>(end - j0, raw, at, s, q);
+  }
+#pragma unroll
+  for (int e = 0; e < VEC; ++e) {
+    sh.s[mine][col * 256 + lane * VEC + e] = s[e];
+    if constexpr (MODE != MODE_ADAMW) sh.q[mine][col * 256 + lane * VEC + e] = q[e];
+  }
+  __syncthreads();
+  LaneAcc acc;
+  float gb[X];
+#pragma unroll
+  for (int x = 0; x < X; ++x) {
+    const int i = threadIdx.x + x * BLOCK;
+    double S = 0.0, Q = 0.0;
+#pragma unroll
+    for (int k = 0; k < SPLIT; ++k)
+      if (k * segment < J) {
+        S += sh.s[k][i];
+        if constexpr (MODE != MODE_ADAMW) Q += sh.q[k][i];
+      }
+    gb[x] = (float)(S * p.inv_J);
+    if constexpr (MODE != MODE_ADAMW) {
+      const float sf = (float)S, c = centred(J, p.inv_J, S, Q);
+      coord_test(p.coord_thr, c, gb[x], acc);
+      const float ta = quad_tree((float)Q), tb = quad_tree(sf * sf), tc = quad_tree(c);
+      if ((lane & 3) == 0) {
+        acc.A += (double)ta;
+        acc.B += (double)tb;
+        acc.C += (double)tc;
+      }
+    }
+  }
+  TileEnd te = {0.0, 0};
+  if constexpr (MODE != MODE_ADAMW) te = tile_reduce<BLOCK, END>(acc, red, p.partials, tile, ticket);
+#pragma unroll
+  for (int x = 0; x < X; ++x)
+    if (own[x]) {
+      const int i = threadIdx.x + x * BLOCK;
+      if constexpr (MODE != MODE_STATS) {
+        adamw_coord(p, gb[x], w[x], m[x], v[x]);
+        __builtin_nontemporal_store(w[x], scalar(p.w + tile * T) + i);
+        __builtin_nontemporal_store(m[x], scalar(p.m + tile * T) + i);
+        __builtin_nontemporal_store(v[x], scalar(p.v + tile * T) + i);
+      }
+      if (GBAR && p.gbar) __builtin_nontemporal_store(gb[x], scalar(p.gbar + tile * T) + i);
+    }
+  return te;
+}
+
+// ---------------------------------------------------------------------------------------------
 // Kernels.  A launch covers gridDim.x of the ntiles tile slots, from slot0 on, a block each; tiles below nfull are whole, and
 // when the vector ends in a part of a tile (nfull = ntiles - 1), that one has slot 0, so that it overlaps with everything else.
-// J_T = 0 selects the J > 16 row-walking variant.  (Walking tiles in a loop instead cost registers that every tile held: fused
+// J_T = 0 selects the J > 16 row-walking variant, NT_SPLIT + n the one whose rows are shared by n waves.  (Walking tiles in a loop instead cost registers that every tile held: fused
 // step of 8 bf16 rows 79 vector and 91 scalar registers, 76 and 50 without; AdamW only 86 scalar ones, 74 without.)
 // ---------------------------------------------------------------------------------------------
 template <class GT, int J_T, int MODE, int BLOCK, int ITERS, bool TABLE, bool GBAR, bool DEFER_T, bool COORD, bool PART, bool END>
@@ -1318,7 +1564,8 @@ constexpr bool whole_copy() {
 // COORD = false compiles the coordinate-wise test out (see plain_stats).
 template <class GT, int J_T, int MODE, int BLOCK, int ITERS, bool TABLE, bool GBAR, bool DEFER_T, bool COORD, bool END>
 __device__ inline TileEnd block_tile(const StepParams& p, int64_t nfull, int64_t ntiles, int64_t slot0, uint32_t* ticket) {
-  constexpr int TILE = BLOCK * GT::VEC * ITERS;
+  constexpr int SPLIT = J_T > NT_SPLIT ? J_T - NT_SPLIT : 0;
+  constexpr int TILE = SPLIT ? NT_SPLIT_TILE : BLOCK * GT::VEC * ITERS;
   static_assert(NT_TILE_MAX % TILE == 0, "tile sizes must divide NT_TILE_MAX");
   __shared__ double red[BLOCK / 64][NT_NV];
   // the means of a tile's sweeps wait here for the deferred state update (see deferred_update)
@@ -1330,10 +1577,15 @@ __device__ inline TileEnd block_tile(const StepParams& p, int64_t nfull, int64_t
   // rotate: the part tile (if any) first, then the whole tiles 0..nfull-1
   const bool part = t < npart;
   const int64_t tile = part ? nfull : t - npart;
-  constexpr bool ONE_COPY = one_copy<GT, J_T, MODE, BLOCK, ITERS, DEFER_T>();
-  if (!ONE_COPY && !part && (J_T > 0 || whole_copy<MODE, BLOCK, ITERS, TABLE, END>()))
-    return run_tile<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, DEFER_T, COORD, false, END>(false, p, tile, red, gbs, ticket);
-  return run_tile<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, DEFER_T, COORD, true, END>(!ONE_COPY || part, p, tile, red, gbs, ticket);
+  if constexpr (SPLIT > 0) {
+    __shared__ SplitShared<SPLIT, MODE != MODE_ADAMW> sh;
+    return tile_split<GT, SPLIT, MODE, TABLE, GBAR, END>(part, p, tile, red, sh, ticket);
+  } else {
+    constexpr bool ONE_COPY = one_copy<GT, J_T, MODE, BLOCK, ITERS, DEFER_T>();
+    if (!ONE_COPY && !part && (J_T > 0 || whole_copy<MODE, BLOCK, ITERS, TABLE, END>()))
+      return run_tile<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, DEFER_T, COORD, false, END>(false, p, tile, red, gbs, ticket);
+    return run_tile<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, DEFER_T, COORD, true, END>(!ONE_COPY || part, p, tile, red, gbs, ticket);
+  }
 }
 
 template <class GT, int J_T, int MODE, int BLOCK, int ITERS, bool TABLE, bool GBAR, bool DEFER_T = false, bool COORD = true>
@@ -1341,6 +1593,12 @@ __global__ __launch_bounds__(BLOCK) void k_step(StepParams p, int64_t nfull, int
   block_tile<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, DEFER_T, COORD, false>(p, nfull, ntiles, slot0, nullptr);
 }
 
+// Blocks of 256 threads with one sweep, which fp32 rows take in the shortest vectors, are held to the 128 vector registers that four
+// waves of a SIMD may have: with two more the compiler orders the walk worse (512 rows 1.13 times the time at d = 1000, 1.14 at 20,001).
+template <int BLOCK, int ITERS>
+constexpr int waves_per_simd() {
+  return BLOCK == 256 && ITERS == 1 ? 4 : 1;
+}
 // A step that writes its result itself: AdamW only, which has no sums; a single tile, whose partial is the total; or a few
 // tiles, a block each, of which the last to finish adds up the partials in k_finalize's order.  A second kernel costs such a
 // call 3.7 us on the host and some 2 on the GPU.  It is a kernel of its own because this tail in every kernel slows the long
@@ -1348,7 +1606,7 @@ __global__ __launch_bounds__(BLOCK) void k_step(StepParams p, int64_t nfull, int
 // (With marks beside the partials, which each block looks at after an agent-wide acquire of its own, the step of 256 tiles took
 // 17.6 us against 13.2 for two launches at the time.)
 template <class GT, int J_T, int MODE, int BLOCK, int ITERS, bool TABLE, bool GBAR, bool DEFER_T = false>
-__global__ __launch_bounds__(BLOCK) void k_step_end(StepParams p, int64_t nfull, int64_t ntiles, int64_t slot0,
+__global__ __launch_bounds__(BLOCK, (waves_per_simd<BLOCK, ITERS>())) void k_step_end(StepParams p, int64_t nfull, int64_t ntiles, int64_t slot0,
                                                     Finish fin) {
   const TileEnd end = block_tile<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, DEFER_T, true, true>(p, nfull, ntiles, slot0,
                                                                                                       leaf_of(fin.ticket, ntiles));
@@ -1664,7 +1922,7 @@ constexpr int defer_row_bytes(int mode) { return mode == MODE_ADAMW ? NT_DEFER_R
 // 16 rows over a short vector, and anything of more rows over a shorter one; else CLS_BASE.  esize: bytes per gradient element; d_whole: length of the
 // vector the call is a part of (its own d unless the caller said otherwise), so that the parts of a vector and the
 // vector itself are cut into the same tiles.
-enum { CLS_BASE = 0, CLS_LONG = 1, CLS_SHORT = 2 };
+enum { CLS_BASE = 0, CLS_LONG = 1, CLS_SHORT = 2, CLS_TINY = 3 };
 // More than 16 rows: whether a vector of d coordinates is better walked in whole generations of blocks than in short tiles.  What
 // is left over after the last full generation runs by itself on a few CUs, with two waves a block, and takes about as long whether it
 // is little or much; short tiles take 5 to 10 % more per coordinate.  So what is left over decides: it has to be nothing or more than a
@@ -1688,6 +1946,7 @@ inline bool generations_pay(int64_t J, int esize, int mode, int64_t d) {
   return !bf16 || left > (adamw && J >= 64 ? G / 16 : G / 8);
 }
 inline int launch_class(int64_t J, int esize, int mode, bool gbar, int64_t d_whole) {
+  if (J > NT_JCHUNK && d_whole <= NT_SPLIT_COORDS) return CLS_TINY;
   if (J > NT_JCHUNK && d_whole <= (J <= 32 && esize == 2 && mode != MODE_ADAMW ? NT_MANY_TINY_COORDS_32 : NT_MANY_TINY_COORDS)) return CLS_SHORT;
   if (mode == MODE_STATS && !gbar) return (J <= NT_JCHUNK && d_whole < NT_STATS_SHORT_COORDS) ? CLS_SHORT : CLS_BASE;
   if (J > NT_JCHUNK) return generations_pay(J, esize, mode, d_whole) ? CLS_LONG : CLS_BASE;
@@ -1696,6 +1955,7 @@ inline int launch_class(int64_t J, int esize, int mode, bool gbar, int64_t d_who
 inline TileCfg tile_cfg(int64_t J, int esize, int mode, bool gbar, int64_t d_whole) {
   const int cls = launch_class(J, esize, mode, gbar, d_whole);
   if (J > NT_JCHUNK) {
+    if (cls == CLS_TINY) return {NT_SPLIT_TILE / NT_VEC, 1};
     if (cls == CLS_SHORT) return {NT_BLOCK_MANY_TINY, NT_ITERS_MANY_TINY};
     if (mode == MODE_STATS && !gbar) return {NT_BLOCK_LARGE_STATS, NT_ITERS_LARGE_STATS};
     return cls == CLS_LONG ? TileCfg{NT_BLOCK_LARGE, NT_ITERS_LARGE} : TileCfg{NT_BLOCK_MANY_SHORT, NT_ITERS_MANY_SHORT};
@@ -1736,14 +1996,14 @@ inline unsigned stats_gbar_lds(int64_t J, int esize, int64_t d) {
   if (d <= NT_HOLD_GBAR_COORDS || J * esize < 10) return 0;
   return J * esize < 12 ? NT_THREE_BLOCK_LDS : NT_TWO_BLOCK_LDS;
 }
-// smallest tile any mode and gradient type uses for this J: sizes the workspace
+// smallest tile any mode and gradient type uses for this J, where the vector is longer than NT_SPLIT_COORDS if J > 16: sizes the workspace
 inline int64_t min_tile_coords(int64_t J) {
-  int64_t best = tile_cfg(J, 2, MODE_FULL, false, 0).coords();
+  int64_t best = NT_TILE_MAX;
   const int modes[3] = {MODE_FULL, MODE_STATS, MODE_ADAMW};
   for (int m : modes)
     for (int g = 0; g < 2; ++g)
       for (int esize = 2; esize <= 4; esize += 2) {
-        for (int64_t d_whole = 0; d_whole <= NT_DEFER_COORDS; d_whole += NT_DEFER_COORDS) {   // shortest and longest
+        for (int64_t d_whole : {J > NT_JCHUNK ? NT_SPLIT_COORDS + 1 : 0, NT_DEFER_COORDS}) {   // shortest and longest
           const int64_t c = tile_cfg(J, esize, m, g != 0, d_whole).coords();
           if (c < best) best = c;
         }
@@ -1884,6 +2144,13 @@ hipError_t launch_step_shape(const StepParams& p, int cls, int64_t nfull, int64_
       default:
         if (cls == CLS_SHORT) {
           ended = launch_tiles_of<GT, 0, MODE, NT_BLOCK_MANY_TINY, NT_ITERS_MANY_TINY, TABLE, WRITES, true>(NT_ARGS);
+        } else if (cls == CLS_TINY) {
+          if constexpr (GT::ESIZE == 4)
+            ended = launch_tiles_of<GT, 0, MODE, NT_SPLIT_TILE / NT_VEC, 1, TABLE, WRITES, true>(NT_ARGS);
+          else if (p.J <= 2 * NT_MCHUNK)
+            ended = launch_tiles_of<GT, NT_SPLIT + 2, MODE, 2 * NT_SPLIT_TILE / NT_VEC, 1, TABLE, WRITES, true>(NT_ARGS);
+          else
+            ended = launch_tiles_of<GT, NT_SPLIT + 4, MODE, 4 * NT_SPLIT_TILE / NT_VEC, 1, TABLE, WRITES, true>(NT_ARGS);
         } else if constexpr (MODE == MODE_STATS && !GBAR) {
           ended = launch_tiles_of<GT, 0, MODE, NT_BLOCK_LARGE_STATS, NT_ITERS_LARGE_STATS, TABLE, false, !TABLE>(NT_ARGS);
         } else {
@@ -1950,7 +2217,11 @@ int64_t normtest_tile_coords(int64_t J) { return J >= 2 ? NT_TILE_MAX : 0; }
 // Bytes of the record, the tile partials and the group partials: what every call needs.
 static size_t partials_bytes(int64_t J, int64_t d) {
   const int64_t tc = min_tile_coords(J);
-  const int64_t ntiles = (d + tc - 1) / tc;
+  int64_t ntiles = (d + tc - 1) / tc;
+  if (J > NT_JCHUNK) {   // never less than a shorter vector takes
+    const int64_t small = ((d < NT_SPLIT_COORDS ? d : NT_SPLIT_COORDS) + NT_SPLIT_TILE - 1) / NT_SPLIT_TILE;
+    if (small > ntiles) ntiles = small;
+  }
   const int64_t n = ntiles > 0 ? ntiles : 1;
   const int64_t ngroups = ntiles > NT_DIRECT_TILES ? (ntiles + NT_GROUP_TILES - 1) / NT_GROUP_TILES : 0;
   return (size_t)(NT_WS_HEADER + n * NT_NV + ngroups * 2 * NT_NV) * sizeof(double);
@@ -2113,7 +2384,8 @@ static int enqueue_step(const void* grads, bool table, nt_dtype gdtype, int64_t 
     Finish fin;
     std::memset(&fin, 0, sizeof(fin));
     // no sums, one partial that is the total, or few enough for the last block: launch_tiles_of has the kernels
-    const int64_t most = J > NT_JCHUNK ? NT_TICKET_TILES_MANY : mode == MODE_STATS ? NT_TICKET_TILES_STATS : NT_TICKET_TILES;
+    const int64_t most = J > NT_JCHUNK ? (cls == CLS_TINY ? NT_TICKET_TILES : NT_TICKET_TILES_MANY)
+                                       : mode == MODE_STATS ? NT_TICKET_TILES_STATS : NT_TICKET_TILES;
     if (mode == MODE_ADAMW || ntiles == 1 || (ntiles <= most && next_ticket(st, &fin.ticket))) {
       fin.q = q;
       fin.hdr = record;

@@ -107,8 +107,8 @@ def test_bits_of_two_launches(J, gdtype, flags, tile, most, whole, past):
 # last counts that end in one launch
 @pytest.mark.parametrize("J,gdtype,flags,tile,tiles", [
     (3, torch.bfloat16, STATS | ADAMW, 4096, (96, 97, 104, 105, 256)), (6, torch.float32, STATS | GBAR | COORD, 4096, (97, 511, 512, 513)),
-    (9, torch.bfloat16, STATS, 4096, (103, 511)), (23, torch.float32, STATS | ADAMW, 2048, (96, 97, 256, 257)),
-    (50, torch.bfloat16, STATS | GBAR, 2048, (97, 256, 257))])
+    (9, torch.bfloat16, STATS, 4096, (103, 511)), (23, torch.float32, STATS | ADAMW, 1024, (96, 97, 255, 256, 257)),
+    (50, torch.bfloat16, STATS | GBAR, 1024, (97, 256, 257))])
 def test_bits_of_two_launches_with_several_counters(J, gdtype, flags, tile, tiles):
     for n in tiles:
         c = _Calls(J, gdtype, n * tile - 5, flags)

@@ -1,0 +1,112 @@
+"""More than 16 rows in the shortest vectors, where bf16 rows are shared by the waves of a block and tiles are 1024 coordinates: the
+state, the mean and the sums of the classes for longer vectors, at the edges of segments of rows, waves and tiles."""
+from __future__ import annotations
+
+import pytest
+import torch
+
+import helpers as H
+from paper_2412_21124_amd import binding as B
+from paper_2412_21124_amd import synth
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+STATS, ADAMW, GBAR, COORD = B.NT_DO_STATS, B.NT_DO_ADAMW, B.NT_WRITE_GBAR, B.NT_COORD_TEST
+# one coordinate, one load, a wave, the tile, several tiles; with 1 to 3 over, and waves that lie past the end
+SIZES = [1, 3, 4, 6, 256, 257, 515, 1023, 1024, 1026, 5 * 1024 + 259]
+
+
+def _step(rows, state, d, flags, whole, table):
+    st = [s[:d].clone() for s in state]
+    hy = B.make_hyper(lr=3e-4, step=5, b_k=64, b_max=8192, round_to=8, flags=flags)
+    shard = B.nt_shard_info(0, 1, 0, whole) if whole else None
+    if table:
+        res = B.normtest_step_rows([r[:d].contiguous() for r in rows], *st[:3], hy, gbar_out=st[3], shard=shard)
+    else:
+        res = B.normtest_step(rows, *st[:3], hy, d=d, gbar_out=st[3], shard=shard)
+    return B.read_result(res).as_dict(), st
+
+
+# rows: one more than a chunk, whole and ragged chunks, two, three and four segments, segments of several chunks
+@pytest.mark.parametrize("J", [17, 31, 32, 33, 48, 50, 64, 65, 96, 130, 512])
+@pytest.mark.parametrize("gdtype,flags,table,odd", [
+    (torch.bfloat16, STATS | ADAMW | GBAR | COORD, False, 0), (torch.bfloat16, STATS, True, 0), (torch.bfloat16, ADAMW, False, 1),
+    (torch.bfloat16, STATS | GBAR, False, 3), (torch.float32, STATS | ADAMW | GBAR | COORD, False, 1), (torch.float32, ADAMW, True, 0)])
+def test_outputs_of_longer_vectors(J, gdtype, flags, table, odd):
+    g = torch.Generator(device=DEV).manual_seed(J)
+    n = SIZES[-1]
+    rows = (torch.randn(J, n + 8 + odd, generator=g, device=DEV) * 1e-2).to(gdtype)[:, odd:]   # rows and their distance off 16 bytes
+    state = [torch.rand(n, generator=g, device=DEV) * 0.02 for _ in range(4)]
+    for d in SIZES:
+        got, a = _step(rows, state, d, flags, 0, table)
+        for whole in (1 << 18) + 1, 1 << 22, 1 << 26:
+            want, b = _step(rows, state, d, flags, whole, table)
+            for x, y in zip(a, b):
+                assert torch.equal(x, y), (d, whole)
+            if flags & STATS:
+                for k in ("A", "B", "C"):   # fp32 terms of four coordinates, the same ones, added in fp64 in another order
+                    assert got[k] == pytest.approx(want[k], rel=1e-13), (d, whole, k)
+                assert all(got[k] == want[k] for k in ("coord_fail", "coord_max_ratio", "pass", "next_b", "status"))
+
+
+# rows that cancel and rows of very different magnitude: the order of the additions shows in the mean, and is the same everywhere
+@pytest.mark.parametrize("J", [18, 40, 100])
+def test_order_of_the_rows(J):
+    d = 1500
+    g = torch.Generator(device=DEV).manual_seed(J)
+    scale = 10.0 ** torch.randint(-18, 19, (J, d), generator=g, device=DEV)
+    rows = (torch.randn(J, d, generator=g, device=DEV) * scale).to(torch.bfloat16)
+    rows[J // 2:J // 2 * 2] = -rows[:J // 2]
+    state = [torch.rand(d, generator=g, device=DEV) * 0.02 for _ in range(4)]
+    outs = [_step(rows, state, d, STATS | ADAMW | GBAR, whole, False) for whole in (0, 1 << 22, 1 << 26)]
+    for res, st in outs[1:]:
+        assert all(torch.equal(x, y) for x, y in zip(st, outs[0][1]))
+        assert all(res[k] == pytest.approx(outs[0][0][k], rel=1e-13) for k in ("A", "B", "C"))
+
+
+# the centred sum of bf16 rows comes from sum x and sum x^2: rows that agree to a bit, and rows that agree
+@pytest.mark.parametrize("J", [17, 64, 513])
+@pytest.mark.parametrize("whole", [0, 1 << 22, 1 << 26])
+def test_rows_that_nearly_agree(J, whole):
+    d = 3000
+    g = torch.Generator(device=DEV).manual_seed(J)
+    base = torch.randn(d, generator=g, device=DEV).to(torch.bfloat16)
+    rows = base.repeat(J, 1)
+    state = [torch.rand(d, generator=g, device=DEV) * 0.02 for _ in range(4)]
+    res, _ = _step(rows, state, d, STATS | COORD, whole, False)
+    assert res["C"] == 0.0 and res["coord_fail"] == 0 and res["coord_max_ratio"] == 0.0
+    rows.view(torch.int16)[J // 2, ::3] += 1   # one row a unit in the last place off, at every third coordinate
+    res, _ = _step(rows, state, d, STATS, whole, False)
+    x = rows.double()
+    # fp32 terms per coordinate and group of four: three roundings of 2^-24
+    for k, ref in (("A", x.square().sum()), ("B", x.sum(0).square().sum()), ("C", (x - x.mean(0)).square().sum())):
+        assert abs(res[k] - float(ref)) <= 3 * 2.0 ** -24 * float(ref), k
+
+
+@pytest.mark.parametrize("value", [float("inf"), float("nan"), 1e20])
+@pytest.mark.parametrize("J,row", [(17, 16), (64, 20), (512, 511)])
+def test_sums_that_are_not_finite(J, row, value):
+    d = 2500
+    rows = (torch.randn(J, d, device=DEV) * 1e-2).to(torch.bfloat16)
+    state = [torch.rand(d, device=DEV) for _ in range(4)]
+    rows[row, 1100] = value   # 1e20 overflows as a square only
+    for whole in 0, 1 << 22, 1 << 26:
+        res, st = _step(rows, state, d, STATS | ADAMW | GBAR, whole, False)
+        assert res["status"] == B.NT_STATUS_NONFINITE and res["pass"] == 1 and res["next_b"] == 64
+        assert torch.isfinite(st[3][1100]).item() == (value == 1e20)
+
+
+@pytest.mark.parametrize("J,gdtype,d", [(24, torch.bfloat16, 30_001), (128, torch.bfloat16, 1 << 18), (300, torch.bfloat16, 70_003),
+                                        (40, torch.float32, (1 << 18) - 1)])
+def test_against_the_oracle(J, gdtype, d):
+    wl = synth.make("t", J, d, gdtype=gdtype, sigma=1e-2, seed=J, device=DEV, noise="student_t3", hyper=synth.Hyper(b_k=64, round_to=J))
+    state0 = [t.clone() for t in (wl.w, wl.m, wl.v)]
+    h = wl.hyper
+    hy = B.make_hyper(lr=h.lr, beta1=h.beta1, beta2=h.beta2, eps=h.eps, weight_decay=h.weight_decay, eta=h.eta, step=h.step,
+                      b_k=h.b_k, b_max=h.b_max, round_to=h.round_to, ddof=h.ddof, flags=STATS | ADAMW | COORD)
+    res = B.read_result(B.normtest_step(wl.grads, wl.w, wl.m, wl.v, hy, d=d)).as_dict()
+    ref = H.oracle_full(wl.grads, d, J, h)
+    H.assert_stats_close(res, ref)
+    H.assert_decision_matches(res, ref, h)
+    H.assert_coord_matches(res, H.oracle_coord_counts(wl.grads, d, h))
+    assert H.oracle_adamw_check(wl.grads, d, *state0, wl.w, wl.m, wl.v, h) == d

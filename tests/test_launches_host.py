@@ -121,6 +121,23 @@ def test_generations_of_blocks(launches, J, gdtype, flags, first, after):
             assert [k[2] for k in step if k[0].startswith("k_step")].count(1024) == d // G
 
 
+# Beyond 16 rows the shortest vectors run in tiles of 1024 coordinates: bf16 rows shared by two or four waves, fp32 rows in blocks of 256
+# threads; both sides of the length, which is the whole vector's.
+@pytest.mark.parametrize("flags", [FULL, STATS, STATS | GBAR, ADAMW])
+def test_tiles_of_the_shortest_vectors(launches, flags):
+    edge = 1 << 18
+    cases = [(17, B.NT_BF16, (1002, 512)), (32, B.NT_BF16, (1002, 512)), (33, B.NT_BF16, (1004, 1024)), (600, B.NT_BF16, (1004, 1024)),
+             (17, B.NT_F32, (0, 256)), (600, B.NT_F32, (0, 256))]
+    for J, g, (j_t, block) in cases:
+        short, ends, past, part = launches([_call(J, g, 1025, flags), _call(J, g, edge, flags), _call(J, g, edge + 1, flags),
+                                            _call(J, g, 1025, flags, edge + 1)])
+        for step, grid in ((short, 2), (ends, 256)):
+            assert [(k[0], int(k[1][0]), int(k[1][2]), k[2], k[3]) for k in step] == [("k_step_end", j_t, block, grid, block)]
+        assert [(k[0], k[1][2:4], k[2]) for k in part] == [("k_step_end", ["512", "1"], 1)]
+        assert _names(past) == (["k_step_end"] if flags == ADAMW else ["k_step", "k_finalize"])
+        assert (past[0][1][2:4], past[0][2]) == (["512", "1"], 129)
+
+
 # Dynamic LDS that keeps one block of 1024 threads on a CU (160 KB), or two or three of 512 of the statistics that store the mean.
 def test_blocks_held_per_cu(launches):
     cases = [((8, B.NT_BF16, 1 << 25, FULL), 0), ((8, B.NT_BF16, (1 << 25) + 1, FULL), 1), ((4, B.NT_BF16, 1 << 28, FULL), 0),
