@@ -164,7 +164,7 @@ size_t normtest_workspace_bytes_for(nt_dtype gdtype, int64_t J, int64_t d, uint3
  * is walked by several launches of the same kernel over consecutive runs of tiles (one per 2^24 to 2^27
  * coordinates up to 16 rows, one per 2^23 where 14 or more bf16 or 7 or more fp32 rows, with AdamW only 10 or 5, are 2^26 coordinates
  * or longer, and beyond 16 rows where such runs are full enough, else one; the memory system serves blocks that start together faster),
- * followed by one or two small reduction kernels.  There is none after AdamW only, after a call of a single tile (1024 coordinates
+ * followed by a small reduction kernel.  There is none after AdamW only, after a call of a single tile (1024 coordinates
  * beyond 16 rows, else 4096) and, outside graph capture, after one of up to 2^20 coordinates, 2^18 beyond 16 rows (statistics of up to
  * 16 rows: 2^21, without a stored mean below that); a part of a vector that is itself longer (d_global) has one if that vector is read in
  * larger tiles, or if more than 16 rows come as a table.

@@ -2,7 +2,7 @@
 //
 // One streaming kernel (k_step) reads the J gradient rows and w, m, v once, writes w, m, v once and
 // leaves five fp64 values per fixed-size tile of coordinates (the sums A, B, C, the count of coordinates
-// failing the coordinate-wise form of the test, and their largest ratio); k_reduce_groups / k_finalize then add
+// failing the coordinate-wise form of the test, and their largest ratio); k_finalize or k_reduce_end then add
 // the tile partials in double-double arithmetic and take Alg. 1's decision on the device (steps of few tiles, and AdamW only,
 // need no second kernel: k_step_end).  The partials stay in the caller's workspace
 // behind a small record of the step, from which k_layer_stats can regroup them into a per-layer table.
@@ -141,9 +141,7 @@
 #define NT_SEGMENTS 4
 #define NT_MCHUNK 16          // beyond that, rows are walked this many at a time (2 .. NT_JCHUNK + 1; 16 measured best)
 #define NT_ROUND_TO_MAX (1ll << 31)  // bound on nt_hyper.round_to that keeps the rounding chain inside int64
-#define NT_FIN_THREADS 1024
-#define NT_FIN_SMALL 4096       // up to this many records the finalize kernel runs with ...
-#define NT_FIN_SHORT 256        // ... this many threads
+#define NT_FIN_THREADS 256      // threads that add up tile or group partials
 // Up to this many tiles a step's own last block adds up the tile partials (k_step_end), in one launch instead of two (3.7 us of
 // host time).  Device time of the step, one launch against two: 4 fp32 rows 6.8 / 8.5 us at d = 5000, 7.2 / 8.5 at 2^18 and 8.9 /
 // 10.5 at 2^20 (256 tiles); read-only statistics of 8 bf16 rows 5.7 / 8.0, 6.9 / 8.3 and 6.9 / 8.6; at 2^21 (512 tiles) the fused
@@ -161,10 +159,16 @@
 #define NT_LEAVES 8
 #define NT_NSUM 4              // summed values per tile partial: A, B, C and the count of failing coordinates
 #define NT_NV 5                // values per tile partial: the sums, then the largest coordinate-wise ratio
-#define NT_GROUP_THREADS 256   // first-stage reduction: threads per block
-#define NT_GROUP_TILES 2048    // ... and tile partials per block
-#define NT_DIRECT_TILES 4096   // up to this many tiles one block reads the tile partials itself
+// Up to this many tiles one block adds up the tile partials (k_finalize); beyond, one block per group_tiles of them, of which the last
+// to finish adds up the groups (k_reduce_end).  The launch alone takes 1.3 us and the chain of one block 1.5; a block reads some 45 GB/s,
+// 40 bytes a tile, and the counting costs 1.9 us.  What a step takes beyond its streaming kernel, us, one block / groups: 512 tiles 3.3,
+// 1024 3.8 / 5.7, 2048 4.8 / 5.0, 4096 7.0 / 5.4; 7325 tiles 5.1, in groups of 2048 and a second kernel for the groups 7.1.
+#define NT_DIRECT_TILES 2560
+// Tiles per group: enough groups to read the partials side by side, and not so many that they queue at the counter.
+inline __host__ __device__ int64_t group_tiles(int64_t ntiles) { return ntiles <= (1 << 16) ? 512 : 2048; }
+#define NT_GROUP_TILES_MIN 512
 #define NT_WS_HEADER 32        // doubles in front of the tile partials: a record of the step that wrote them
+#define NT_WS_COUNTER 16       // ... and behind it, at this double, the counter of k_reduce_end
 #define NT_WS_MAGIC 0x4e54574f524b5350ll
 #define NT_LAYER_THREADS 1024  // per-layer kernel: one block per layer
 
@@ -430,7 +434,7 @@ struct WsHeader {
   double coord_thr;                      // threshold factor of the coordinate-wise count, negative if off
   DecideParams q;
 };
-static_assert(sizeof(WsHeader) <= NT_WS_HEADER * sizeof(double) && sizeof(WsHeader) % 8 == 0, "workspace header");
+static_assert(sizeof(WsHeader) <= NT_WS_COUNTER * sizeof(double) && sizeof(WsHeader) % 8 == 0, "workspace header");
 // The record as words, the form in which kernels take and store it: a struct copied whole goes through scratch memory,
 // which every wave of the launch then pays for (fused step -33 %).
 struct WsRecord {
@@ -505,8 +509,8 @@ __device__ inline void totals_clear(Totals& t) {
 // Adds this thread's share (entries threadIdx.x, threadIdx.x + THREADS, ...) of n records into acc.
 // PACKED = false: tile partials {A, B, C, n_fail, r_max}; PACKED = true: group partials
 // {A, A_lo, B, B_lo, C, C_lo, n, n_lo, r_max, unused}.  Tile partials are loaded up to eight rounds
-// at a time: one round after the other, 2048 records in a block of 256 threads wait for memory eight times (k_reduce_groups
-// 7.2 -> 4.5 us).  Group partials are few (one per 8M coordinates), so theirs are not.  What lies past the end reads as the
+// at a time: one round after the other, 2048 records in a block of 256 threads wait for memory eight times (groups of 2048
+// 7.2 -> 4.5 us).  Group partials are few (one per 2M coordinates or more), so theirs are not.  What lies past the end reads as the
 // last record and counts as zeros, which change nothing.
 template <int THREADS, bool PACKED>
 __device__ inline void totals_accumulate(const double* in, int64_t n, Totals& acc) {
@@ -702,6 +706,8 @@ __device__ inline TileEnd tile_reduce(const LaneAcc& acc, double (*red)[NT_NV], 
       }
     } else {
       *to = t;
+      // the counter of the reduction that may follow, which is a kernel of its own
+      if (tile == 0 && threadIdx.x == 0) *(uint32_t*)(partials - NT_WS_HEADER + NT_WS_COUNTER) = 0;
     }
   }
   return end;
@@ -1627,14 +1633,14 @@ __global__ __launch_bounds__(BLOCK, (waves_per_simd<BLOCK, ITERS>())) void k_ste
   } else {
     // The last block to count itself finds every partial in memory; it invalidates its caches, which may hold older ones.
     __shared__ bool last;
-    __shared__ double sh[NT_FIN_SHORT / 64][2 * NT_NV];
+    __shared__ double sh[NT_FIN_THREADS / 64][2 * NT_NV];
     if (threadIdx.x == 0) {
       last = last_block(fin.ticket, (uint32_t)ntiles, end.before);
       if (last) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     }
     __syncthreads();
     if (!last) return;
-    block_totals<NT_FIN_SHORT, false>(p.partials, ntiles, sh, tot);
+    block_totals<NT_FIN_THREADS, false>(p.partials, ntiles, sh, tot);
   }
   if (threadIdx.x == 0) write_record(tot, fin.q, fin.out, fin.hdr, fin.hdr_out);
 }
@@ -1642,38 +1648,46 @@ __global__ __launch_bounds__(BLOCK, (waves_per_simd<BLOCK, ITERS>())) void k_ste
 // ---------------------------------------------------------------------------------------------
 // Reduction of the tile partials.
 // ---------------------------------------------------------------------------------------------
-// First stage for long vectors: block g adds tile partials [g*NT_GROUP_TILES, ...) into one double-double
-// group partial.  The second stage is a launch of its own (4.7 + 4.5 us at 4 groups, 6.3 + 5.4 at 15).  One launch in which every
-// block counts itself after a device-wide release took 26 us at 15 groups: the eight XCDs of this GPU do not share an L2, and each
-// block then writes its own back.  The counting without a release that ends short steps (tile_reduce) has not been tried here.
-__global__ __launch_bounds__(NT_GROUP_THREADS) void k_reduce_groups(const double* tiles, int64_t ntiles, double* groups) {
-  __shared__ double sh[NT_GROUP_THREADS / 64][2 * NT_NV];
-  const int64_t t0 = (int64_t)blockIdx.x * NT_GROUP_TILES;
-  const int64_t n = (ntiles - t0 < NT_GROUP_TILES) ? (ntiles - t0) : NT_GROUP_TILES;
+// Long vectors: block g adds the partials of the g-th group of tiles into one double-double record, and the last block to finish adds
+// up the records and takes the decision.  Records are handed over like the partials of k_step_end (tile_reduce), at a counter
+// in the workspace that the step's own kernel has set to zero: a graph takes it along.  (With a device-wide release by every
+// block, which writes back all of an XCD's L2, one launch took 26 us at 15 groups; as two launches 4.6 + 4.5.)
+__global__ __launch_bounds__(NT_FIN_THREADS) void k_reduce_end(const double* tiles, int64_t ntiles, double* groups, DecideParams q,
+                                                               nt_result* out, WsRecord hdr, WsRecord* hdr_out) {
+  __shared__ double sh[NT_FIN_THREADS / 64][2 * NT_NV];
+  __shared__ bool last;
+  const int64_t per = group_tiles(ntiles), t0 = (int64_t)blockIdx.x * per;
   Totals tot;
-  block_totals<NT_GROUP_THREADS, false>(tiles + NT_NV * t0, n, sh, tot);
+  totals_clear(tot);
+  block_totals<NT_FIN_THREADS, false>(tiles + NT_NV * t0, ntiles - t0 < per ? ntiles - t0 : per, sh, tot);
   if (threadIdx.x == 0) {
     double* rec = groups + 2 * NT_NV * (int64_t)blockIdx.x;
+    auto hand_on = [](double* to, double x) { __hip_atomic_store(to, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
 #pragma unroll
     for (int k = 0; k < NT_NSUM; ++k) {
-      rec[2 * k] = tot.s[k].hi;
-      rec[2 * k + 1] = tot.s[k].lo;
+      hand_on(rec + 2 * k, tot.s[k].hi);
+      hand_on(rec + 2 * k + 1, tot.s[k].lo);
     }
-    rec[2 * NT_NSUM] = tot.mx;
-    rec[2 * NT_NSUM + 1] = 0.0;
+    hand_on(rec + 2 * NT_NSUM, tot.mx);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    last = count_up((uint32_t*)(tiles - NT_WS_HEADER + NT_WS_COUNTER)) == gridDim.x - 1;
+    if (last) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
   }
+  __syncthreads();
+  if (!last) return;
+  totals_clear(tot);
+  block_totals<NT_FIN_THREADS, true>(groups, gridDim.x, sh, tot);
+  if (threadIdx.x == 0) write_record(tot, q, out, hdr, hdr_out);
 }
 
-// One block: partials (tile or group) -> A, B, C in double-double, then the decision.  THREADS: 1024, or 256 for
-// up to NT_FIN_SMALL records (short vectors, where this kernel's latency is a large part of the step).
-template <int THREADS, bool PACKED>
-__global__ __launch_bounds__(THREADS) void k_finalize(const double* in, int64_t n, DecideParams q, nt_result* out,
-                                                      WsRecord hdr, WsRecord* hdr_out) {
-  __shared__ double sh[THREADS / 64][2 * NT_NV];
+// One block: tile partials -> A, B, C in double-double, then the decision.
+__global__ __launch_bounds__(NT_FIN_THREADS) void k_finalize(const double* in, int64_t n, DecideParams q, nt_result* out,
+                                                             WsRecord hdr, WsRecord* hdr_out) {
+  __shared__ double sh[NT_FIN_THREADS / 64][2 * NT_NV];
   const bool stats = (q.flags & NT_DO_STATS) != 0;
   Totals tot;
   totals_clear(tot);
-  if (stats) block_totals<THREADS, PACKED>(in, n, sh, tot);
+  if (stats) block_totals<NT_FIN_THREADS, false>(in, n, sh, tot);
   if (threadIdx.x != 0) return;
   write_record(tot, q, out, hdr, hdr_out);
 }
@@ -1761,11 +1775,11 @@ __global__ __launch_bounds__(NT_LAYER_THREADS) void k_layer_stats(StepParams p, 
   acc.mx = (double)piece.rmax;
   const double* tiles = ws + NT_WS_HEADER;
   const double* groups = tiles + NT_NV * h.ntiles;
-  const int64_t g0 = (first + NT_GROUP_TILES - 1) / NT_GROUP_TILES, g1 = last / NT_GROUP_TILES;
+  const int64_t per = group_tiles(h.ntiles), g0 = (first + per - 1) / per, g1 = last / per;
   if (h.ngroups > 0 && g0 < g1) {
-    totals_accumulate<NT_LAYER_THREADS, false>(tiles + NT_NV * first, g0 * NT_GROUP_TILES - first, acc);
+    totals_accumulate<NT_LAYER_THREADS, false>(tiles + NT_NV * first, g0 * per - first, acc);
     totals_accumulate<NT_LAYER_THREADS, true>(groups + 2 * NT_NV * g0, g1 - g0, acc);
-    totals_accumulate<NT_LAYER_THREADS, false>(tiles + NT_NV * g1 * NT_GROUP_TILES, last - g1 * NT_GROUP_TILES, acc);
+    totals_accumulate<NT_LAYER_THREADS, false>(tiles + NT_NV * g1 * per, last - g1 * per, acc);
   } else {
     totals_accumulate<NT_LAYER_THREADS, false>(tiles + NT_NV * first, last - first, acc);
   }
@@ -2199,15 +2213,6 @@ hipError_t launch_step_mode(int mode, const StepParams& p, int cls, int64_t nful
 
 inline bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 
-template <bool PACKED>
-inline void launch_finalize(const double* in, int64_t n, const DecideParams& q, nt_result* out, const WsRecord& hdr,
-                            WsRecord* hdr_out, hipStream_t st) {
-  if (n <= NT_FIN_SMALL)
-    hipLaunchKernelGGL((k_finalize<NT_FIN_SHORT, PACKED>), dim3(1), dim3(NT_FIN_SHORT), 0, st, in, n, q, out, hdr, hdr_out);
-  else
-    hipLaunchKernelGGL((k_finalize<NT_FIN_THREADS, PACKED>), dim3(1), dim3(NT_FIN_THREADS), 0, st, in, n, q, out, hdr, hdr_out);
-}
-
 }  // namespace
 
 extern "C" {
@@ -2223,7 +2228,7 @@ static size_t partials_bytes(int64_t J, int64_t d) {
     if (small > ntiles) ntiles = small;
   }
   const int64_t n = ntiles > 0 ? ntiles : 1;
-  const int64_t ngroups = ntiles > NT_DIRECT_TILES ? (ntiles + NT_GROUP_TILES - 1) / NT_GROUP_TILES : 0;
+  const int64_t ngroups = ntiles > NT_DIRECT_TILES ? (ntiles + NT_GROUP_TILES_MIN - 1) / NT_GROUP_TILES_MIN : 0;   // at most
   return (size_t)(NT_WS_HEADER + n * NT_NV + ngroups * 2 * NT_NV) * sizeof(double);
 }
 
@@ -2363,7 +2368,7 @@ static int enqueue_step(const void* grads, bool table, nt_dtype gdtype, int64_t 
   q.ddof = hyper->ddof;
   q.flags = flags;
   const bool two_level = (flags & NT_DO_STATS) && ntiles > NT_DIRECT_TILES;
-  const int64_t ngroups = two_level ? (ntiles + NT_GROUP_TILES - 1) / NT_GROUP_TILES : 0;
+  const int64_t ngroups = two_level ? (ntiles + group_tiles(ntiles) - 1) / group_tiles(ntiles) : 0;
   WsHeader hdr;
   std::memset(&hdr, 0, sizeof(hdr));
   hdr.magic = NT_WS_MAGIC;
@@ -2405,15 +2410,11 @@ static int enqueue_step(const void* grads, bool table, nt_dtype gdtype, int64_t 
   if (ended) return NT_OK;
 
   const double* partials = (const double*)workspace + NT_WS_HEADER;
-  if (two_level) {
-    double* groups = (double*)workspace + NT_WS_HEADER + NT_NV * ntiles;
-    hipLaunchKernelGGL(k_reduce_groups, dim3((unsigned)ngroups), dim3(NT_GROUP_THREADS), 0, st, partials, ntiles, groups);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return hip_code(e);
-    launch_finalize<true>(groups, ngroups, q, result_dev, record, hdr_out, st);
-  } else {
-    launch_finalize<false>(partials, ntiles, q, result_dev, record, hdr_out, st);
-  }
+  if (two_level)
+    hipLaunchKernelGGL(k_reduce_end, dim3((unsigned)ngroups), dim3(NT_FIN_THREADS), 0, st, partials, ntiles,
+                       (double*)workspace + NT_WS_HEADER + NT_NV * ntiles, q, result_dev, record, hdr_out);
+  else
+    hipLaunchKernelGGL(k_finalize, dim3(1), dim3(NT_FIN_THREADS), 0, st, partials, ntiles, q, result_dev, record, hdr_out);
   return hip_code(hipGetLastError());
 }
 

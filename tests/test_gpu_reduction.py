@@ -68,3 +68,52 @@ def test_layer_sums_are_exact():
     for got, lo, hi in zip(B.read_layers(table), edges[:-1], edges[1:]):
         A, Bs, C, fail, _ = _sums(x[:, lo:hi])
         assert (got.A, got.B, got.C, got.coord_fail) == (A, Bs, C, fail)
+
+
+# one block for all tiles and a block per group of them; groups of 512 tiles, the last one whole, short or a single tile, and of 2048
+@pytest.mark.parametrize("tiles", [2559, 2560, 2561, 3072, 3073, 9000, (1 << 16) - 1, 1 << 16, (1 << 16) + 1])
+def test_sums_are_exact_over_groups_of_tiles(tiles):
+    d = tiles * 4096 - (tiles % 3)
+    x = _rows(2, d, torch.bfloat16, tiles)
+    gbar = torch.empty(d, device=DEV)
+    ws = torch.randint(0, 255, (B.normtest_workspace_bytes(2, d),), dtype=torch.uint8, device=DEV)
+    A, Bs, C, fail, _ = _sums(x)
+    for _ in range(3):   # the counter in the workspace is as the call before left it
+        res = B.read_result(B.normtest_step(x, None, None, None, _hyper(2, B.NT_DO_STATS | B.NT_WRITE_GBAR), gbar_out=gbar, workspace=ws))
+        assert (res.A, res.B, res.C, res.coord_fail) == (A, Bs, C, fail)
+    cut = [0, 5, 512 * 4096, 512 * 4096 + 1, 2048 * 4096, 2400 * 4096 - 7, d]
+    layers = B.read_layers(B.normtest_layer_stats(x, torch.tensor(cut, dtype=torch.int64, device=DEV), ws))
+    for got, lo, hi in zip(layers, cut[:-1], cut[1:]):
+        want = _sums(x[:, lo:hi])
+        assert (got.A, got.B, got.C, got.coord_fail) == want[:4], (lo, hi)
+
+
+# the counter is in the workspace, so a graph takes the same kernels; replayed with other inputs and eager steps of other sizes between
+def test_groups_of_tiles_in_a_graph():
+    d = 2600 * 4096 - 1
+    x = _rows(2, d, torch.float32, 1)
+    state = [torch.ones(d, device=DEV) for _ in range(3)]
+    ws = torch.randint(0, 255, (B.normtest_workspace_bytes(2, d),), dtype=torch.uint8, device=DEV)
+    res = torch.zeros(B.RESULT_BYTES, dtype=torch.uint8, device=DEV)
+    hy = _hyper(2, B.NT_DO_STATS | B.NT_DO_ADAMW)
+
+    def step():
+        return B.normtest_step(x, *state, hy, workspace=ws, result=res)
+
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph):
+        step()
+    for k in range(4):
+        x.copy_(_rows(2, d, torch.float32, 10 + k))
+        graph.replay()
+        torch.cuda.synchronize()
+        got = res.clone()
+        res.zero_()
+        B.normtest_step(x, *state, hy, d=4096 * (k + 1), workspace=ws, result=res)
+        step()
+        torch.cuda.synchronize()
+        assert torch.equal(got, res)
+        A, Bs, C, fail, _ = _sums(x)
+        r = B.read_result(got)
+        assert (r.A, r.B, r.C, r.coord_fail) == (A, Bs, C, fail)
