@@ -1,4 +1,5 @@
-"""ctypes binding of ``libnormtest.so`` (``include/normtest.h``): argument marshalling only.
+"""Binding of ``libnormtest.so`` (``include/normtest.h``): argument marshalling only, by ctypes and, for the calls of a training
+loop, by ``csrc/callpath.cpp``.
 
 Every step of the path runs in the library's HIP kernels.  torch supplies device memory and the
 current stream, nothing else.  There is no CPU fallback: if the library cannot be loaded or a call
@@ -7,6 +8,7 @@ fails, an exception is raised.
 from __future__ import annotations
 
 import ctypes
+import importlib
 from dataclasses import dataclass
 from typing import Optional
 
@@ -84,6 +86,21 @@ class NormtestError(RuntimeError):
 
 
 _lib = None
+_fast = None   # the native call path (csrc/callpath.cpp), loaded with the library
+
+
+def _load_callpath():
+    global _fast
+    _build.ensure_callpath()
+    _fast = importlib.import_module("._callpath", __package__)
+    _fast.init(nt_hyper, nt_shard_info, torch.nn.Parameter, torch._C._cuda_getCurrentRawStream)
+
+
+def _done(rc: Optional[int], where: str) -> bool:
+    """Whether the native call path took the call; raises if the library refused it."""
+    if rc is not None and rc != NT_OK:
+        raise NormtestError(rc, where)
+    return rc is not None
 
 
 def lib(path: Optional[str] = None):
@@ -135,6 +152,10 @@ def lib(path: Optional[str] = None):
         L.normtest_calib_streams.restype = ctypes.c_int
         L.normtest_strerror.argtypes = [ctypes.c_int]
         L.normtest_strerror.restype = ctypes.c_char_p
+        for name in ("normtest_step", "normtest_step_rows", "normtest_step_clipped", "normtest_adamw_gbar"):
+            setattr(L, name + "_entry", ctypes.cast(getattr(L, name), ctypes.c_void_p).value)
+        if _fast is None:
+            _load_callpath()
         _lib = L
     return _lib
 
@@ -197,9 +218,9 @@ def _nbytes(t: torch.Tensor) -> int:
     return t.numel() * t.element_size()
 
 
-# A small step is bound by the host: of 14.5 us per call (two launches) the library takes 7.5.  The stream's handle and the
-# device are therefore asked for directly: torch.cuda.current_stream builds a Stream object (1.9 us against 0.1) and
-# torch.cuda.device is only entered when another device is current (1.3 us against 0.1).
+# What the native call path does not take (an own stream, tensors of another device, buffers to be made here) goes through the checks
+# below.  The stream's handle and the device are asked for directly: torch.cuda.current_stream builds a Stream object (1.9 us against
+# 0.1) and torch.cuda.device is only entered when another device is current (1.3 us against 0.1).
 def _stream_handle(stream: Optional[torch.cuda.Stream], dev: torch.device) -> int:
     return torch._C._cuda_getCurrentRawStream(dev.index) if stream is None else stream.cuda_stream
 
@@ -222,6 +243,10 @@ def normtest_step(grads: torch.Tensor, w: Optional[torch.Tensor], m: Optional[to
     grads: (J, ld) device tensor whose rows are the gradient vectors (last axis contiguous); the first
     d columns are used (default: all).  w, m, v: float32 device vectors of length >= d, updated in place.
     """
+    if stream is None and workspace is not None and result is not None:
+        L = lib()
+        if _fast and _done(_fast.step(L.normtest_step_entry, grads, w, m, v, hyper, d, shard, gbar_out, workspace, result), "normtest_step"):
+            return result
     J, d, ld, dev = _matrix_layout(grads, d, "normtest_step")
     _check_vectors(dev, d, w=w, m=m, v=v, gbar_out=gbar_out)
     gdtype = _gdtype(grads)
@@ -277,6 +302,11 @@ def normtest_step_rows(rows, w: Optional[torch.Tensor], m: Optional[torch.Tensor
                        workspace: Optional[torch.Tensor] = None, result: Optional[torch.Tensor] = None,
                        stream: Optional[torch.cuda.Stream] = None) -> torch.Tensor:
     """normtest_step for J separately allocated gradient rows (a sequence of 1-D device tensors of one dtype)."""
+    if stream is None and table is not None and workspace is not None and result is not None:
+        L = lib()
+        if _fast and _done(_fast.step_rows(L.normtest_step_rows_entry, rows, w, m, v, hyper, d, table, shard, gbar_out, workspace, result),
+                           "normtest_step_rows"):
+            return result
     J = len(rows)
     dev = rows[0].device
     if dev.type != "cuda":
@@ -313,6 +343,11 @@ def normtest_step_clipped(grads: torch.Tensor, w: torch.Tensor, m: torch.Tensor,
                           result: Optional[torch.Tensor] = None,
                           stream: Optional[torch.cuda.Stream] = None) -> torch.Tensor:
     """Two-phase gradient-clipped step (statistics + gbar, then AdamW on the clipped gbar); see normtest_step."""
+    if stream is None and workspace is not None and result is not None:
+        L = lib()
+        if _fast and _done(_fast.step_clipped(L.normtest_step_clipped_entry, grads, w, m, v, gbar_buf, max_norm, hyper, d, shard, workspace,
+                                              result), "normtest_step_clipped"):
+            return result
     J, d, ld, dev = _matrix_layout(grads, d, "normtest_step_clipped")
     _check_vectors(dev, d, required=True, w=w, m=m, v=v, gbar_buf=gbar_buf)
     own_workspace = workspace is None
@@ -335,6 +370,10 @@ def normtest_adamw_gbar(gbar: torch.Tensor, w: torch.Tensor, m: torch.Tensor, v:
                         grad_scale: float = 1.0, *, d: Optional[int] = None, result: Optional[torch.Tensor] = None,
                         stream: Optional[torch.cuda.Stream] = None) -> None:
     """AdamW on grad_scale (* result.clip_coef) * gbar for a mean gradient already in device memory."""
+    if stream is None:
+        L = lib()
+        if _fast and _done(_fast.adamw_gbar(L.normtest_adamw_gbar_entry, gbar, w, m, v, hyper, grad_scale, d, result), "normtest_adamw_gbar"):
+            return
     d = gbar.numel() if d is None else d
     dev = gbar.device
     if dev.type != "cuda":

@@ -1,14 +1,18 @@
-"""Build ``libnormtest.so`` from ``csrc/normtest.hip`` for gfx950 with hipcc (works without a GPU)."""
+"""Build ``libnormtest.so`` from ``csrc/normtest.hip`` for gfx950 with hipcc (works without a GPU), and the binding's
+``_callpath.so`` from ``csrc/callpath.cpp`` with g++."""
 from __future__ import annotations
 
 import os
 import subprocess
+import sysconfig
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(_HERE)
 SRC = os.path.join(_HERE, "csrc", "normtest.hip")
 LIB = os.path.join(_HERE, "libnormtest.so")
 INCLUDE = os.path.join(ROOT, "include")
+CALLPATH_SRC = os.path.join(_HERE, "csrc", "callpath.cpp")
+CALLPATH = os.path.join(_HERE, "_callpath.so")
 
 # contraction off: the error-free transformations of the finalize kernel, and the bits that the copies of a tile's
 # code (whole and part tiles, every launch shape) have in common, rely on every fused multiply-add being an explicit one;
@@ -33,13 +37,40 @@ def build_library(out: str = LIB, quiet: bool = True) -> str:
     return out
 
 
+def build_callpath(out: str = CALLPATH) -> str:
+    import torch
+    from torch.utils.cpp_extension import include_paths
+    tmp = out + ".tmp.%d" % os.getpid()
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, "-I", INCLUDE]
+    for path in [*include_paths(), sysconfig.get_paths()["include"]]:
+        cmd += ["-isystem", path]
+    cmd += ["-o", tmp, CALLPATH_SRC, "-L" + os.path.join(os.path.dirname(torch.__file__), "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("g++ failed:\n%s\n%s" % (" ".join(cmd), res.stderr))
+    os.replace(tmp, out)
+    return out
+
+
+def _stale(built: str, *sources: str) -> bool:
+    return not os.path.exists(built) or os.path.getmtime(built) < max(os.path.getmtime(s) for s in sources)
+
+
 def ensure_built() -> str:
     """Path of the built library; builds it if nothing is there or a source is newer than the build."""
     header = os.path.join(INCLUDE, "normtest.h")
-    if not os.path.exists(LIB) or os.path.getmtime(LIB) < max(os.path.getmtime(SRC), os.path.getmtime(header)):
+    if _stale(LIB, SRC, header):
         build_library()
     return LIB
 
 
+def ensure_callpath() -> str:
+    """The same for the binding's native part."""
+    if _stale(CALLPATH, CALLPATH_SRC, os.path.join(INCLUDE, "normtest.h")):
+        build_callpath()
+    return CALLPATH
+
+
 if __name__ == "__main__":
     print(build_library(quiet=False))
+    print(build_callpath())
