@@ -87,8 +87,8 @@
 // what counts is how many of them have a tile.  bf16 rows: the waves of a block share the rows as well (tile_split), two of them up to
 // 32 rows and four beyond, as one wave alone walks 512 rows in 32 steps of 2 us, most of it arithmetic.  fp32 rows: blocks of 256 threads.
 // Shape above -> these, us: fused step of 17 / 64 / 128 / 512 bf16 rows at d = 20,001 7.8 / 13.7 / 21.4 / 66 -> 7.2 / 10.0 / 13.1 /
-// 32, at 2^18 9.0 / 13.9 / 20.7 / 61 -> 8.3 / 11.4 / 16.5 / 46; of 17 / 64 / 512 fp32 rows at d = 100,003 9.3 / 15.9 / 84 -> 8.0 /
-// 12.9 / 60; AdamW only, 64 bf16 rows 8.8 -> 6.1 at 100,003.  Beyond 2^18 coordinates some CUs have two tiles: 64 bf16 rows at 3e5 14.2
+// 32, at 2^18 9.0 / 13.9 / 20.7 / 61 -> 8.3 / 11.4 / 16.5 / 46; of 17 / 64 / 512 fp32 rows at d = 100,003 9.0 / 15.8 / 84 -> 8.1 /
+// 13.2 / 54; AdamW only, 64 bf16 rows 8.8 -> 6.1 at 100,003.  Beyond 2^18 coordinates some CUs have two tiles: 64 bf16 rows at 3e5 14.2
 // and 15.1.
 #define NT_SPLIT_TILE 1024
 #define NT_SPLIT_COORDS (1ll << 18)
@@ -138,7 +138,7 @@
 #define NT_AUX_BLOCK 1024     // threads per block of the AdamW-from-gbar, copy and yardstick kernels
 
 #define NT_JCHUNK 16          // up to this many rows a coordinate's values are all held in registers
-#define NT_SEGMENTS 4
+#define NT_SEGMENTS 4         // more than 16 bf16 rows are added up in up to this many segments (segment_rows)
 #define NT_MCHUNK 16          // beyond that, rows are walked this many at a time (2 .. NT_JCHUNK + 1; 16 measured best)
 #define NT_ROUND_TO_MAX (1ll << 31)  // bound on nt_hyper.round_to that keeps the rounding chain inside int64
 #define NT_FIN_THREADS 256      // threads that add up tile or group partials
@@ -170,7 +170,6 @@ inline __host__ __device__ int64_t group_tiles(int64_t ntiles) { return ntiles <
 #define NT_WS_HEADER 32        // doubles in front of the tile partials: a record of the step that wrote them
 #define NT_WS_COUNTER 16       // ... and behind it, at this double, the counter of k_reduce_end
 #define NT_WS_MAGIC 0x4e54574f524b5350ll
-#define NT_LAYER_THREADS 1024  // per-layer kernel: one block per layer
 
 // Scratch of normtest_step_static: the per-tile partial sums and the record of the step, for callers that
 // cannot hand over (or allocate) a workspace.  One copy per GPU, held until the process ends.
@@ -772,90 +771,26 @@ __device__ inline float centred(int J, double inv_J, double S, double Q) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// One coordinate by itself, any J and any alignment: what the per-layer table needs at a layer's ends, where a layer covers
-// a part of a tile (piece_sums).  The operations on a coordinate are those of the tiles below, in their order, and have to
-// stay so; only the sums over coordinates are formed in another order.  Rows are re-read instead of held in registers.
+// One coordinate by itself, up to NT_JCHUNK rows and any alignment: what the per-layer table needs at a layer's ends, where a layer
+// covers a part of a tile (piece_sums).  The operations on a coordinate are those of the tiles below, in their order, and have to
+// stay so; only the sums over coordinates are formed in another order.  The J loads of a coordinate are issued together.
 // ---------------------------------------------------------------------------------------------
-template <class GT, bool TABLE>
-__device__ inline void coord_stats_generic(const StepParams& p, int64_t i, double& S, float& M2, float& a) {
-  const int J = p.J;
-  a = 0.f;
-  if (J <= NT_JCHUNK) {
-    // all rows at once: fp64 row sum, then squares centred on the mean, exactly as in the tiles
-    double sb = (double)GT::ld(row_base<GT, TABLE>(p, 0), i);
-    for (int j = 1; j < J; ++j) sb += (double)GT::ld(row_base<GT, TABLE>(p, j), i);
-    const float mb = (float)(sb * p.inv_J);
-    float cb = 0.f;
-    for (int j = 0; j < J; ++j) {
-      const float x = GT::ld(row_base<GT, TABLE>(p, j), i);
-      const float r = x - mb;
-      cb = __builtin_fmaf(r, r, cb);
-      a = __builtin_fmaf(x, x, a);
-    }
-    S = sb;
-    M2 = cb;
-    return;
-  }
-  if constexpr (GT::ESIZE == 2) {
-    const int segment = segment_rows(J);
-    double Q = 0.0;
-    S = 0.0;
-    for (int j0 = 0; j0 < J; j0 += segment) {
-      const int end = J - j0 < segment ? J : j0 + segment;
-      double s = 0.0, q = 0.0;
-#pragma unroll 8
-      for (int j = j0; j < end; ++j) {
-        const double x = (double)GT::ld(row_base<GT, TABLE>(p, j), i);
-        s += x;
-        q = __builtin_fma(x, x, q);
-      }
-      S += s;
-      Q += q;
-    }
-    a = (float)Q;
-    M2 = centred(J, p.inv_J, S, Q);
-    return;
-  }
-  float K = GT::ld(row_base<GT, TABLE>(p, 0), i);
-  int na = 0;
-  for (int j0 = 0; j0 < J; j0 += NT_MCHUNK) {
-    const int nb = (J - j0 < NT_MCHUNK) ? (J - j0) : NT_MCHUNK;
-    double sb = 0.0;
-    float q = 0.f;
-    for (int j = 0; j < nb; ++j) {
-      const float x = GT::ld(row_base<GT, TABLE>(p, j0 + j), i);
-      const float r = x - K;
-      sb += (double)x;
-      q = __builtin_fmaf(r, r, q);
-    }
-    K = chunk_merge(na == 0, na, nb, 1.0 / (double)na, 1.0 / (double)(na + nb), K, sb, q, S, M2, a);
-    na += nb;
-  }
-}
-
-// The same for a row count known at compile time (2 .. NT_JCHUNK): the J loads of a coordinate are issued
-// together and kept in registers; the arithmetic is coord_stats_generic's, operation for operation.
-// J_T = 0 forwards to the generic form.
 template <class GT, bool TABLE, int J_T>
 __device__ inline void coord_stats(const StepParams& p, int64_t i, double& S, float& M2, float& a) {
-  if constexpr (J_T > 0) {
-    float x[J_T];
+  float x[J_T];
 #pragma unroll
-    for (int j = 0; j < J_T; ++j) x[j] = GT::ld(row_base<GT, TABLE>(p, j), i);
-    S = (double)x[0];
+  for (int j = 0; j < J_T; ++j) x[j] = GT::ld(row_base<GT, TABLE>(p, j), i);
+  S = (double)x[0];
 #pragma unroll
-    for (int j = 1; j < J_T; ++j) S += (double)x[j];
-    const float mb = (float)(S * p.inv_J);
-    M2 = 0.f;
-    a = 0.f;
+  for (int j = 1; j < J_T; ++j) S += (double)x[j];
+  const float mb = (float)(S * p.inv_J);
+  M2 = 0.f;
+  a = 0.f;
 #pragma unroll
-    for (int j = 0; j < J_T; ++j) {
-      const float r = x[j] - mb;
-      M2 = __builtin_fmaf(r, r, M2);
-      a = __builtin_fmaf(x[j], x[j], a);
-    }
-  } else {
-    coord_stats_generic<GT, TABLE>(p, i, S, M2, a);
+  for (int j = 0; j < J_T; ++j) {
+    const float r = x[j] - mb;
+    M2 = __builtin_fmaf(r, r, M2);
+    a = __builtin_fmaf(x[j], x[j], a);
   }
 }
 
@@ -1601,9 +1536,10 @@ __global__ __launch_bounds__(BLOCK) void k_step(StepParams p, int64_t nfull, int
 
 // Blocks of 256 threads with one sweep, which fp32 rows take in the shortest vectors, are held to the 128 vector registers that four
 // waves of a SIMD may have: with two more the compiler orders the walk worse (512 rows 1.13 times the time at d = 1000, 1.14 at 20,001).
-template <int BLOCK, int ITERS>
+// Not so read-only statistics over tables, which would need scratch memory.
+template <int MODE, int BLOCK, int ITERS, bool TABLE, bool GBAR>
 constexpr int waves_per_simd() {
-  return BLOCK == 256 && ITERS == 1 ? 4 : 1;
+  return BLOCK == 256 && ITERS == 1 && !(TABLE && MODE == MODE_STATS && !GBAR) ? 4 : 1;
 }
 // A step that writes its result itself: AdamW only, which has no sums; a single tile, whose partial is the total; or a few
 // tiles, a block each, of which the last to finish adds up the partials in k_finalize's order.  A second kernel costs such a
@@ -1612,7 +1548,7 @@ constexpr int waves_per_simd() {
 // (With marks beside the partials, which each block looks at after an agent-wide acquire of its own, the step of 256 tiles took
 // 17.6 us against 13.2 for two launches at the time.)
 template <class GT, int J_T, int MODE, int BLOCK, int ITERS, bool TABLE, bool GBAR, bool DEFER_T = false>
-__global__ __launch_bounds__(BLOCK, (waves_per_simd<BLOCK, ITERS>())) void k_step_end(StepParams p, int64_t nfull, int64_t ntiles, int64_t slot0,
+__global__ __launch_bounds__(BLOCK, (waves_per_simd<MODE, BLOCK, ITERS, TABLE, GBAR>())) void k_step_end(StepParams p, int64_t nfull, int64_t ntiles, int64_t slot0,
                                                     Finish fin) {
   const TileEnd end = block_tile<GT, J_T, MODE, BLOCK, ITERS, TABLE, GBAR, DEFER_T, true, true>(p, nfull, ntiles, slot0,
                                                                                                       leaf_of(fin.ticket, ntiles));
@@ -1692,21 +1628,58 @@ __global__ __launch_bounds__(NT_FIN_THREADS) void k_finalize(const double* in, i
   write_record(tot, q, out, hdr, hdr_out);
 }
 
-// Sums over the coordinates [plo, phi) taken one by one, NT_LAYER_THREADS apart per thread.  J_T > 0: row
-// count known at compile time; J_T = 0: any J.
+// Threads of the per-layer kernel: 1024, but where more than 16 fp32 rows are walked, for which 128 vector registers are too few.
+template <class GT, bool MANY>
+constexpr int layer_threads() {
+  return MANY && GT::ESIZE == 4 ? 512 : 1024;
+}
+// What a coordinate adds to the sums of its piece.
+__device__ inline void piece_add(const StepParams& p, double S, float M2, float a, LaneAcc& acc) {
+  const float gb = (float)(S * p.inv_J), sf = (float)S;
+  acc.A += (double)a;
+  acc.B += (double)(sf * sf);
+  acc.C += (double)M2;
+  coord_test(p.coord_thr, M2, gb, acc);
+}
+// Sums over the coordinates [plo, phi), up to 16 rows: one coordinate per thread.
 template <class GT, bool TABLE, int J_T>
 __device__ inline void piece_sums(const StepParams& p, int64_t plo, int64_t phi, LaneAcc& acc) {
 #pragma unroll 2
-  for (int64_t i = plo + threadIdx.x; i < phi; i += NT_LAYER_THREADS) {
+  for (int64_t i = plo + threadIdx.x; i < phi; i += layer_threads<GT, false>()) {
     double S;
-    float M2, aa;
-    coord_stats<GT, TABLE, J_T>(p, i, S, M2, aa);
-    const float gb = (float)(S * p.inv_J);
-    const float sf = (float)S;
-    acc.A += (double)aa;
-    acc.B += (double)(sf * sf);
-    acc.C += (double)M2;
-    coord_test(p.coord_thr, M2, gb, acc);
+    float M2, a;
+    coord_stats<GT, TABLE, J_T>(p, i, S, M2, a);
+    piece_add(p, S, M2, a, acc);
+  }
+}
+// Sums over the coordinates of two pieces [lo, hi), more than 16 rows, by the tiles' own walks: a wave takes 256 coordinates, the first
+// piece's before the second's.  With a coordinate per thread, whose rows are loaded two or four bytes at a time, and one piece after the other,
+// the table of 148 layers, 128 bf16 rows, d = 1,000,003 took 172 us, so 39; 12 layers, 512 rows, 100,003 556 and 56; 300 layers, 64
+// fp32 rows, 300,007 108 and 29.  (Up to 16 rows this way is 0.9 to 1.2 times as fast as a coordinate per thread.)
+template <class GT, bool TABLE>
+__device__ inline void pieces_walk(const StepParams& p, const int64_t (&lo)[2], const int64_t (&hi)[2], LaneAcc& acc) {
+  constexpr int SPAN = 64 * NT_VEC;
+  int64_t from[2], spans[2];
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    from[k] = lo[k] & ~(int64_t)(NT_VEC - 1);
+    spans[k] = lo[k] < hi[k] ? (hi[k] - from[k] + SPAN - 1) / SPAN : 0;
+  }
+#pragma unroll 1
+  for (int64_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); w < spans[0] + spans[1]; w += layer_threads<GT, true>() / 64) {
+    const bool second = w >= spans[0];
+    const Place pl = {second ? from[1] + (w - spans[0]) * SPAN : from[0] + w * SPAN, (threadIdx.x & 63) * NT_VEC};
+    const int64_t first = second ? lo[1] : lo[0], end = second ? hi[1] : hi[0];
+    const Reach at = reach(true, p, pl);
+    double S[NT_VEC];
+    float M2[NT_VEC], a[NT_VEC];
+    if constexpr (GT::ESIZE == 2)
+      walk_moments<GT, TABLE, true, false>(true, p, at, S, M2, a);
+    else
+      walk_shifted<GT, TABLE, true>(true, p, at, S, M2, a);
+#pragma unroll
+    for (int e = 0; e < NT_VEC; ++e)
+      if (pl.i0() + e >= first && pl.i0() + e < end) piece_add(p, S[e], M2[e], a[e], acc);
   }
 }
 
@@ -1716,10 +1689,11 @@ __device__ inline void piece_sums(const StepParams& p, int64_t plo, int64_t phi,
 // ends that cover only part of a tile; then the layer's own statistic (Alg. 1's T on the layer's
 // coordinates) is formed.  Offsets are clamped into [0, d], so every access stays in bounds whatever
 // the table holds; a clamped or descending pair is reported in the layer's status.
-template <class GT, bool TABLE>
-__global__ __launch_bounds__(NT_LAYER_THREADS) void k_layer_stats(StepParams p, const int64_t* offsets,
-                                                                  const double* ws, nt_layer_stats* out) {
-  __shared__ double sh[NT_LAYER_THREADS / 64][2 * NT_NV];
+template <class GT, bool TABLE, bool MANY>
+__global__ __launch_bounds__((layer_threads<GT, MANY>())) void k_layer_stats(StepParams p, const int64_t* offsets, const double* ws,
+                                                                           nt_layer_stats* out) {
+  constexpr int THREADS = layer_threads<GT, MANY>();
+  __shared__ double sh[THREADS / 64][2 * NT_NV];
   const WsHeader h = *(const WsHeader*)ws;
   const int l = blockIdx.x;
   const double nan = __builtin_nan("");
@@ -1753,19 +1727,22 @@ __global__ __launch_bounds__(NT_LAYER_THREADS) void k_layer_stats(StepParams p, 
     tail_lo = last * tc;
   }
   LaneAcc piece;
-  for (int part = 0; part < 2; ++part) {
-    const int64_t plo = part ? tail_lo : lo, phi = part ? hi : head_end;
-    if (plo >= phi) continue;
+  const int64_t plo[2] = {lo, tail_lo}, phi[2] = {head_end, hi};
+  if constexpr (MANY) {
+    pieces_walk<GT, TABLE>(p, plo, phi, piece);
+  } else {
+    for (int part = 0; part < 2; ++part) {
+      if (plo[part] >= phi[part]) continue;
 #define NT_CASE(JJ) \
   case JJ:          \
-    piece_sums<GT, TABLE, JJ>(p, plo, phi, piece); \
+    piece_sums<GT, TABLE, JJ>(p, plo[part], phi[part], piece); \
     break;
-    switch (p.J) {
-      NT_CASE(2) NT_CASE(3) NT_CASE(4) NT_CASE(5) NT_CASE(6) NT_CASE(7) NT_CASE(8) NT_CASE(9)
-      NT_CASE(10) NT_CASE(11) NT_CASE(12) NT_CASE(13) NT_CASE(14) NT_CASE(15) NT_CASE(16)
-      default: piece_sums<GT, TABLE, 0>(p, plo, phi, piece);
-    }
+      switch (p.J) {
+        NT_CASE(2) NT_CASE(3) NT_CASE(4) NT_CASE(5) NT_CASE(6) NT_CASE(7) NT_CASE(8) NT_CASE(9)
+        NT_CASE(10) NT_CASE(11) NT_CASE(12) NT_CASE(13) NT_CASE(14) NT_CASE(15) NT_CASE(16)
+      }
 #undef NT_CASE
+    }
   }
   Totals acc;
   acc.s[0] = {piece.A, 0.0};
@@ -1777,14 +1754,14 @@ __global__ __launch_bounds__(NT_LAYER_THREADS) void k_layer_stats(StepParams p, 
   const double* groups = tiles + NT_NV * h.ntiles;
   const int64_t per = group_tiles(h.ntiles), g0 = (first + per - 1) / per, g1 = last / per;
   if (h.ngroups > 0 && g0 < g1) {
-    totals_accumulate<NT_LAYER_THREADS, false>(tiles + NT_NV * first, g0 * per - first, acc);
-    totals_accumulate<NT_LAYER_THREADS, true>(groups + 2 * NT_NV * g0, g1 - g0, acc);
-    totals_accumulate<NT_LAYER_THREADS, false>(tiles + NT_NV * g1 * per, last - g1 * per, acc);
+    totals_accumulate<THREADS, false>(tiles + NT_NV * first, g0 * per - first, acc);
+    totals_accumulate<THREADS, true>(groups + 2 * NT_NV * g0, g1 - g0, acc);
+    totals_accumulate<THREADS, false>(tiles + NT_NV * g1 * per, last - g1 * per, acc);
   } else {
-    totals_accumulate<NT_LAYER_THREADS, false>(tiles + NT_NV * first, last - first, acc);
+    totals_accumulate<THREADS, false>(tiles + NT_NV * first, last - first, acc);
   }
   Totals tot;
-  block_totals_finish<NT_LAYER_THREADS>(acc, sh, tot);
+  block_totals_finish<THREADS>(acc, sh, tot);
   if (threadIdx.x != 0) return;
   nt_result t;
   t.A = tot.s[0].hi;
@@ -2549,17 +2526,18 @@ int normtest_layer_stats(const void* grads, int rows_are_table, nt_dtype gdtype,
   p.coord_thr = -1.0f;  // the kernel takes the threshold of the recorded step
   hipStream_t st = (hipStream_t)hip_stream;
   const double* ws = (const double*)workspace;
-  if (rows_are_table) {
-    if (gdtype == NT_F32)
-      hipLaunchKernelGGL((k_layer_stats<F32, true>), dim3(L), dim3(NT_LAYER_THREADS), 0, st, p, layer_offsets_dev, ws, layers_dev);
-    else
-      hipLaunchKernelGGL((k_layer_stats<BF16, true>), dim3(L), dim3(NT_LAYER_THREADS), 0, st, p, layer_offsets_dev, ws, layers_dev);
+  auto launch = [&](auto kernel, int threads) {
+    hipLaunchKernelGGL(kernel, dim3(L), dim3(threads), 0, st, p, layer_offsets_dev, ws, layers_dev);
+  };
+  const bool table = rows_are_table != 0, many = J > NT_JCHUNK;
+#define NT_LAYERS(GT, TABLE, MANY) \
+  if (table == TABLE && many == MANY) launch(k_layer_stats<GT, TABLE, MANY>, layer_threads<GT, MANY>());
+  if (gdtype == NT_F32) {
+    NT_LAYERS(F32, false, false) NT_LAYERS(F32, false, true) NT_LAYERS(F32, true, false) NT_LAYERS(F32, true, true)
   } else {
-    if (gdtype == NT_F32)
-      hipLaunchKernelGGL((k_layer_stats<F32, false>), dim3(L), dim3(NT_LAYER_THREADS), 0, st, p, layer_offsets_dev, ws, layers_dev);
-    else
-      hipLaunchKernelGGL((k_layer_stats<BF16, false>), dim3(L), dim3(NT_LAYER_THREADS), 0, st, p, layer_offsets_dev, ws, layers_dev);
+    NT_LAYERS(BF16, false, false) NT_LAYERS(BF16, false, true) NT_LAYERS(BF16, true, false) NT_LAYERS(BF16, true, true)
   }
+#undef NT_LAYERS
   return hip_code(hipGetLastError());
 }
 

@@ -110,3 +110,37 @@ def test_against_the_oracle(J, gdtype, d):
     H.assert_decision_matches(res, ref, h)
     H.assert_coord_matches(res, H.oracle_coord_counts(wl.grads, d, h))
     assert H.oracle_adamw_check(wl.grads, d, *state0, wl.w, wl.m, wl.v, h) == d
+
+
+# the per-layer table beyond 16 rows: small whole numbers, whose sums are exact in any order, and layers that begin and end anywhere in
+# tiles of 1024, 2048 and 8192 coordinates, from a matrix off 16 bytes and from a table.  32 rows and 64 make every mean exact, but the shift
+# of the last 16 of 64 fp32 rows is a mean of 48, so their C is one of fp32 terms: three roundings a square and 16 squares to a sum
+@pytest.mark.parametrize("gdtype,table", [(torch.bfloat16, False), (torch.bfloat16, True), (torch.float32, False), (torch.float32, True)])
+@pytest.mark.parametrize("J,d,whole", [(32, 3, 0), (32, 1027, 0), (64, 20_005, 0), (32, 20_005, 1 << 22), (64, 40_001, 1 << 26)])
+def test_layer_sums_are_exact(J, d, whole, gdtype, table):
+    g = torch.Generator(device=DEV).manual_seed(d)
+    rows = torch.randint(1, 5, (J, d + 3), generator=g, device=DEV).to(gdtype)[:, 1:d + 1]
+    hy = B.make_hyper(lr=0.0, weight_decay=0.0, eta=1.0, step=1, b_k=1, round_to=1, ddof=1, flags=STATS | ADAMW | COORD)
+    shard = B.nt_shard_info(0, 1, 0, whole) if whole else None
+    w, m, v = (torch.ones(d, device=DEV) for _ in range(3))
+    ws = torch.empty(B.normtest_workspace_bytes(J, d), dtype=torch.uint8, device=DEV)
+    each = [r.contiguous() for r in rows]
+    if table:
+        B.normtest_step_rows(each, w, m, v, hy, shard=shard, workspace=ws)
+    else:
+        B.normtest_step(rows, w, m, v, hy, d=d, shard=shard, workspace=ws)
+    cut = sorted({min(c, d) for c in (0, 1, 2, 5, 1021, 1024, 1027, 2048, 4097, 8191, 8192, 8194, 16384, 17000, d - 1, d)})
+    offsets = torch.tensor(cut + [d], dtype=torch.int64, device=DEV)   # the last layer is empty
+    layers = B.read_layers(B.normtest_layer_stats(each if table else rows, offsets, ws, d=d))
+    x = rows.double()
+    mean = x.mean(0)
+    terms = torch.stack([x.square().sum(0), x.sum(0).square(), (x - mean).square().sum(0)])
+    ratio = terms[2] / ((J - 1) * mean.square())
+    tol = 0.0 if gdtype == torch.bfloat16 else (16 + 3) * 2.0 ** -24
+    for got, lo, hi in zip(layers, offsets.tolist()[:-1], offsets.tolist()[1:]):
+        assert got.n == hi - lo
+        A, b, C = terms[:, lo:hi].sum(1).tolist()
+        assert (got.A, got.B) == (A, b) and abs(got.C - C) <= tol * C, (lo, hi)
+        assert got.coord_fail == int((ratio[lo:hi] > 1).sum())
+        if hi > lo:
+            assert abs(got.coord_max_ratio - float(ratio[lo:hi].max())) <= (2.0 ** -22 + tol) * float(ratio[lo:hi].max())
