@@ -152,7 +152,8 @@ def lib(path: Optional[str] = None):
         L.normtest_calib_streams.restype = ctypes.c_int
         L.normtest_strerror.argtypes = [ctypes.c_int]
         L.normtest_strerror.restype = ctypes.c_char_p
-        for name in ("normtest_step", "normtest_step_rows", "normtest_step_clipped", "normtest_adamw_gbar"):
+        for name in ("normtest_step", "normtest_step_rows", "normtest_step_clipped", "normtest_adamw_gbar", "normtest_layer_stats",
+                     "normtest_workspace_bytes_for"):
             setattr(L, name + "_entry", ctypes.cast(getattr(L, name), ctypes.c_void_p).value)
         if _fast is None:
             _load_callpath()
@@ -392,6 +393,11 @@ def normtest_layer_stats(grads, layer_offsets: torch.Tensor, workspace: torch.Te
     tensor of that step, or the sequence of rows given to normtest_step_rows (then `table` may carry the
     address table already made).  layer_offsets: int64 device tensor of L+1 ascending offsets.  Returns the
     device tensor (uint8[L * sizeof(nt_layer_stats)]); read it with `read_layers` after a sync."""
+    if stream is None and table is None and layers is not None and isinstance(grads, torch.Tensor):
+        L = lib()
+        if _fast and _done(_fast.layer_stats(L.normtest_layer_stats_entry, grads, layer_offsets, workspace,
+                                             L.normtest_workspace_bytes_for_entry, d, layers), "normtest_layer_stats"):
+            return layers
     rows = None if isinstance(grads, torch.Tensor) else list(grads)
     first = grads if rows is None else rows[0]
     dev = first.device

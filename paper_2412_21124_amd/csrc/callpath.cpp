@@ -235,6 +235,27 @@ PyObject* adamw_gbar(PyObject*, PyObject* const* a, Py_ssize_t n) {
   });
 }
 
+// layer_stats(entry, grads, layer_offsets, workspace, need, d, layers); grads: the (J, ld) tensor; need(gdtype, J, d, flags): bytes of the
+// workspace the step needed, an entry of the library too
+PyObject* layer_stats(PyObject*, PyObject* const* a, Py_ssize_t n) {
+  return guarded(n, 7, [&] {
+    auto* f = entry<decltype(normtest_layer_stats)>(a[0]);
+    const Matrix g = matrix_of(a[1], a[5]);
+    const at::Tensor& offsets = tensor(a[2]);
+    if (offsets.scalar_type() != at::kLong || offsets.device() != g.at_.device || offsets.dim() != 1 || !offsets.is_contiguous() ||
+        offsets.numel() < 2 || offsets.numel() > (1 << 24))
+      throw Refused();
+    const int32_t L = (int32_t)offsets.numel() - 1;
+    if (tensor(a[3]).device() != g.at_.device) throw Refused();
+    const Bytes ws = bytes_of(a[3]), layers = bytes_of(a[6]);
+    if (ws.size < entry<decltype(normtest_workspace_bytes_for)>(a[4])((nt_dtype)g.dtype, g.J, g.at_.d, NT_DO_STATS)) throw Refused();
+    if (layers.size < (size_t)L * sizeof(nt_layer_stats)) throw Refused();
+    void* st = stream_of(g.at_.device);
+    const int64_t* off = (const int64_t*)offsets.data_ptr();
+    return enqueue([&] { return f(g.data, 0, (nt_dtype)g.dtype, g.J, g.at_.d, g.ld, off, L, ws.data, (nt_layer_stats*)layers.data, st); });
+  });
+}
+
 // init(nt_hyper, nt_shard_info, torch.nn.Parameter, torch._C._cuda_getCurrentRawStream)
 PyObject* init(PyObject*, PyObject* const* a, Py_ssize_t n) {
   return guarded(n, 4, [&]() -> PyObject* {
@@ -248,7 +269,8 @@ PyObject* init(PyObject*, PyObject* const* a, Py_ssize_t n) {
 }
 
 #define FAST(f) {#f, (PyCFunction)(void (*)(void))f, METH_FASTCALL, nullptr}
-PyMethodDef methods[] = {FAST(init), FAST(step), FAST(step_clipped), FAST(step_rows), FAST(adamw_gbar), {nullptr, nullptr, 0, nullptr}};
+PyMethodDef methods[] = {FAST(init),       FAST(step),        FAST(step_clipped), FAST(step_rows),
+                         FAST(adamw_gbar), FAST(layer_stats), {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_callpath", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 
 }  // namespace

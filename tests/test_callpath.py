@@ -93,6 +93,17 @@ def test_outputs_are_those_of_the_python_path(monkeypatch, gdtype):
     c.same(monkeypatch, lambda w, m, v: B.normtest_step_clipped(g, w, m, v, c.gbar, 0.5, B.make_hyper(flags=FULL), d=d, **c.kw), True)
     c.same(monkeypatch, lambda w, m, v: B.normtest_adamw_gbar(rows[0].float(), w, m, v, hy, 0.25), True)
     c.same(monkeypatch, lambda w, m, v: B.normtest_adamw_gbar(rows[0].float(), w, m, v, hy, d=12), True)
+    off = torch.tensor([0, 5, 1500, d], dtype=torch.int64, device="cuda")
+    for lay in torch.zeros(3 * B.LAYER_BYTES, dtype=torch.uint8, device="cuda"), torch.zeros(400, dtype=torch.float64, device="cuda"):
+        B.normtest_step(g, None, None, None, stats, d=d, **c.kw)
+        tables = []
+        for fast in B._fast, None:
+            with monkeypatch.context() as mp:
+                mp.setattr(B, "_fast", fast)
+                lay.zero_()
+                assert B.normtest_layer_stats(g, off, c.ws, d=d, layers=lay) is lay
+                tables.append(lay.clone())
+        assert torch.equal(*(t.view(torch.int64) for t in tables)) and tables[0].any()
     # on another stream, and with numbers that are no plain int or float
     side = torch.cuda.Stream()
     with torch.cuda.stream(side):
@@ -123,5 +134,11 @@ def test_what_is_refused_stays_refused(monkeypatch):
            lambda w, m, v: B.normtest_step_clipped(g, w, m, v, None, 1.0, hy, d=d, **c.kw),
            lambda w, m, v: B.normtest_step_clipped(g, w, m, v, c.gbar, float("nan"), hy, d=d, **c.kw),
            lambda w, m, v: B.normtest_adamw_gbar(c.gbar, w, m, v, hy, float("inf")), lambda w, m, v: B.normtest_adamw_gbar(c.gbar, w, None, v, hy)]
+    off = torch.tensor([0, 5, d], dtype=torch.int64, device="cuda")
+    lay = torch.zeros(2 * B.LAYER_BYTES, dtype=torch.uint8, device="cuda")
+    bad += [lambda w, m, v: B.normtest_layer_stats(g, off.int(), c.ws, d=d, layers=lay), lambda w, m, v: B.normtest_layer_stats(g, off[:1], c.ws, d=d, layers=lay),
+            lambda w, m, v: B.normtest_layer_stats(g, off, c.ws[:200], d=d, layers=lay), lambda w, m, v: B.normtest_layer_stats(g, off, c.ws, d=d, layers=lay[:-1]),
+            lambda w, m, v: B.normtest_layer_stats(g, off, c.ws.cpu(), d=d, layers=lay), lambda w, m, v: B.normtest_layer_stats(g, off[::2], c.ws, d=d, layers=lay),
+            lambda w, m, v: B.normtest_layer_stats(g[:1], off, c.ws, d=d, layers=lay), lambda w, m, v: B.normtest_layer_stats(g.half(), off, c.ws, d=d, layers=lay)]
     for call in bad:
         c.same(monkeypatch, call, False)
