@@ -1753,7 +1753,7 @@ __global__ __launch_bounds__((layer_threads<GT, MANY>())) void k_layer_stats(Ste
   const double* tiles = ws + NT_WS_HEADER;
   const double* groups = tiles + NT_NV * h.ntiles;
   const int64_t per = group_tiles(h.ntiles), g0 = (first + per - 1) / per, g1 = last / per;
-  if (h.ngroups > 0 && g0 < g1) {
+  if (h.ngroups == (h.ntiles + per - 1) / per && g0 < g1) {   // a workspace kept from a build with other groups is read tile by tile
     totals_accumulate<THREADS, false>(tiles + NT_NV * first, g0 * per - first, acc);
     totals_accumulate<THREADS, true>(groups + 2 * NT_NV * g0, g1 - g0, acc);
     totals_accumulate<THREADS, false>(tiles + NT_NV * g1 * per, last - g1 * per, acc);

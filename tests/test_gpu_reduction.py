@@ -88,6 +88,23 @@ def test_sums_are_exact_over_groups_of_tiles(tiles):
         assert (got.A, got.B, got.C, got.coord_fail) == want[:4], (lo, hi)
 
 
+# a workspace whose record names another number of groups, as one kept from a build with groups of 2048 tiles: the table reads its tiles
+def test_groups_of_another_size_are_not_read():
+    d = 9000 * 4096
+    x = _rows(2, d, torch.bfloat16, 3)
+    gbar = torch.empty(d, device=DEV)
+    ws = torch.zeros(B.normtest_workspace_bytes(2, d), dtype=torch.uint8, device=DEV)
+    off = torch.tensor([0, 7 * 2048, 2048 * 4096, 8999 * 4096 + 5, d], dtype=torch.int64, device=DEV)
+    B.normtest_step(x, None, None, None, _hyper(2, B.NT_DO_STATS | B.NT_WRITE_GBAR), gbar_out=gbar, workspace=ws)
+    want = B.normtest_layer_stats(x, off, ws).clone()
+    record = ws.view(torch.int64)
+    ntiles = int(record[2])
+    assert int(record[3]) == -(-ntiles // 512)
+    record[3] = -(-ntiles // 2048)
+    ws.view(torch.float64)[32 + 5 * ntiles:] = float("nan")
+    assert torch.equal(B.normtest_layer_stats(x, off, ws), want)
+
+
 # the counter is in the workspace, so a graph takes the same kernels; replayed with other inputs and eager steps of other sizes between
 def test_groups_of_tiles_in_a_graph():
     d = 2600 * 4096 - 1
