@@ -197,6 +197,8 @@ enum { MODE_FULL = 0, MODE_STATS = 1, MODE_ADAMW = 2 };
 // j*d elements in) therefore run like aligned ones: a wave touches one more line per access.  J = 8 bf16,
 // d = 30,000,001, unpadded: 224 us (5.4 TB/s) against 406 us (3.0) element by element, which is how such calls ran.
 typedef uint32_t u32x2_any __attribute__((ext_vector_type(2), aligned(2)));
+typedef uint32_t u32x3 __attribute__((ext_vector_type(3)));
+typedef uint32_t u32x3_words __attribute__((ext_vector_type(3), aligned(4)));
 typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(4)));
 typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
 
@@ -1232,8 +1234,41 @@ __device__ inline void chunk_pause(int J) {
     __builtin_amdgcn_s_sleep(12);
 }
 
+// bf16 rows of a matrix whose first row begins on 4 bytes and whose row stride is odd: every second row begins between two words, and
+// loads of 8 bytes from there cost more than 12 from the word before, shifted.  What those read past the lane's coordinates, two bytes on
+// either side, is in the matrix: the row is not the first, and the row goes on where the lanes end.  8 bytes -> 12, us: fused step of
+// 20 / 64 / 128 / 512 rows at d = 300,001 8.6 / 16.5 / 25.8 / 81 -> 8.3 / 14.3 / 21.9 / 67, at 1,000,003 15.3 / 31.9 / 54.3 / 190 -> 14.4 / 28.8 /
+// 50.4 / 179, statistics of 64 rows at 3e6 71.2 -> 68.8.  Where state or the mean is written, 8 bytes stay the better loads in long vectors: from
+// 48 rows on, 64 / 128 at 1.8e6 56.7 / 101.6 -> 55.2 / 99.6, at 2e6 58.7 / 105.7 -> 58.6 / 107.5; 20 / 40 rows at 4e6 49.3 / 81.2 -> 48.6 / 80.0, 48
+// rows 92.8 -> 93.8, 20 rows at 1e7 117 -> 119; and in the class for long vectors (64 rows at 1e7 304 -> 315, AdamW only, 128 rows 548 -> 575).
+#define NT_ODD_ROWS 48
+#define NT_ODD_COORDS (7ll << 18)
+#define NT_ODD_COORDS_FEW (1ll << 22)    // below NT_ODD_ROWS rows
+template <bool WRITES>
+__device__ inline bool odd_rows(const StepParams& p, int64_t end) {
+  if (WRITES && p.d >= (p.J >= NT_ODD_ROWS ? NT_ODD_COORDS : NT_ODD_COORDS_FEW)) return false;
+  return (p.ld & 1) != 0 && ((uintptr_t)p.grads & 3) == 0 && end < p.d;
+}
+template <int N>
+__device__ inline void load_odd(const StepParams& p, int j0, const Reach& r, BF16::raw_t* raw) {
+  static_assert(N % 2 == 0, "pairs of rows");
+  const uint32_t lane = r.u * BF16::ESIZE;
+  RowWalk<BF16, false> row(p, j0, r.s0);
+  u32x3 o[N / 2];
+#pragma unroll
+  for (int j = 0; j < N; j += 2) {
+    raw[j] = BF16::ldraw(row.next() + lane);
+    o[j / 2] = ld_nt<u32x3_words>(row.next() - 2 + lane);
+  }
+#pragma unroll
+  for (int j = 1; j < N; j += 2) {
+    const u32x3 x = o[j / 2];
+    raw[j] = BF16::raw_t{__builtin_amdgcn_alignbit(x[1], x[0], 16), __builtin_amdgcn_alignbit(x[2], x[1], 16)};
+  }
+}
+
 // All rows of the lane's coordinates: row sum, centred sum and sum of squares.  bf16 rows, by their moments (see centred).
-template <class GT, bool TABLE, bool MOVES, bool WAITS>
+template <class GT, bool TABLE, bool MOVES, bool WAITS, bool ODD = false>
 __device__ inline void walk_moments(bool part, const StepParams& p, const Reach& at, double* S, float* M2, float* a) {
   constexpr int VEC = GT::VEC;
   const int J = p.J, segment = segment_rows(J);
@@ -1248,7 +1283,10 @@ __device__ inline void walk_moments(bool part, const StepParams& p, const Reach&
       end += segment;
       segment_end<VEC>(S, Q, s, q);
     }
-    load_rows<GT, TABLE, NT_MCHUNK>(part, p, j0, at, raw);
+    if constexpr (ODD)
+      load_odd<NT_MCHUNK>(p, j0, at, raw);
+    else
+      load_rows<GT, TABLE, NT_MCHUNK>(part, p, j0, at, raw);
     if (WAITS) chunk_wait(J);
     chunk_moments<GT, MOVES, NT_MCHUNK>(raw, at, s, q);
     if (WAITS) chunk_pause(J);
@@ -1319,6 +1357,7 @@ __device__ inline TileEnd tile_multi(bool part, const StepParams& p, int64_t til
   constexpr int TILE = BLOCK * VEC * ITERS;
   constexpr bool WRITES = (MODE != MODE_STATS) || GBAR;
   constexpr bool MOVES = PART && moves_rows<GT, 0, MODE, BLOCK, ITERS, TABLE, false>();
+  constexpr bool ODDS = GT::ESIZE == 2 && !TABLE && !PART && (!WRITES || BLOCK * ITERS != NT_BLOCK_LARGE * NT_ITERS_LARGE);
   constexpr bool WAITS = WRITES && GT::ESIZE == 2 && BLOCK * ITERS == NT_BLOCK_LARGE * NT_ITERS_LARGE;
   LaneAcc acc;
 #pragma unroll 1
@@ -1329,7 +1368,12 @@ __device__ inline TileEnd tile_multi(bool part, const StepParams& p, int64_t til
     double S[VEC];
     float M2[VEC], a[VEC];
     const Reach at = reach(PART && part, p, pl);
-    if constexpr (GT::ESIZE == 2)
+    if constexpr (ODDS) {
+      if (odd_rows<WRITES>(p, pl.s0 + BLOCK * VEC))
+        walk_moments<GT, TABLE, MOVES, WAITS, true>(PART && part, p, at, S, M2, a);
+      else
+        walk_moments<GT, TABLE, MOVES, WAITS>(PART && part, p, at, S, M2, a);
+    } else if constexpr (GT::ESIZE == 2)
       walk_moments<GT, TABLE, MOVES, WAITS>(PART && part, p, at, S, M2, a);
     else
       walk_shifted<GT, TABLE, MOVES>(PART && part, p, at, S, M2, a);
@@ -1413,8 +1457,16 @@ __device__ inline TileEnd tile_split(bool part, const StepParams& p, int64_t til
       }
     }
   }
+  // 64 / 128 / 512 rows of odd stride, fused, 8 -> 12 bytes: at d = 20,001 9.9 / 13.7 / 37.8 -> 9.6 / 12.7 / 31.6 us, at 2e5 12.0 / 17.4 / 47.4 ->
+  // 11.3 / 15.7 / 44.1; with two waves, and with AdamW only, the second loop costs even strides up to 6 and 4 %
+  const bool odd = SPLIT == 4 && MODE != MODE_ADAMW && !TABLE && odd_rows<true>(p, pl.s0 + 256);
 #pragma unroll 1
   for (; j0 + NT_MCHUNK <= end; j0 += NT_MCHUNK) {
+    if (odd) {
+      load_odd<NT_MCHUNK>(p, j0, at, raw);
+      chunk_moments<GT, false, NT_MCHUNK>(raw, at, s, q);
+      continue;
+    }
     load_rows<GT, TABLE, NT_MCHUNK>(part, p, j0, at, raw);
     settle<GT, NT_MCHUNK, true>(part, pl, at, raw);
     chunk_moments<GT, false, NT_MCHUNK>(raw, at, s, q);
