@@ -8,7 +8,8 @@ fails, an exception is raised.
 from __future__ import annotations
 
 import ctypes
-import importlib
+import importlib.util
+import warnings
 from dataclasses import dataclass
 from typing import Optional
 
@@ -86,14 +87,20 @@ class NormtestError(RuntimeError):
 
 
 _lib = None
-_fast = None   # the native call path (csrc/callpath.cpp), loaded with the library
+_fast = None   # the native call path (csrc/callpath.cpp), loaded with the library; None: every call is marshalled in Python
 
 
 def _load_callpath():
-    global _fast
-    _build.ensure_callpath()
-    _fast = importlib.import_module("._callpath", __package__)
-    _fast.init(nt_hyper, nt_shard_info, torch.nn.Parameter, torch._C._cuda_getCurrentRawStream)
+    """The native call path, ready for calls, or None where it cannot be built or loaded: nothing but the time of a call depends on it."""
+    try:
+        spec = importlib.util.spec_from_file_location(__package__ + "._callpath", _build.ensure_callpath())
+        module = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(module)
+        module.init(nt_hyper, nt_shard_info, torch.nn.Parameter, torch._C._cuda_getCurrentRawStream)
+        return module
+    except Exception as e:   # no compiler, no headers, a file that is no module of this Python and torch
+        warnings.warn("normtest: calls are marshalled in Python, which a short step notices: %s: %s" % (type(e).__name__, e), RuntimeWarning)
+        return None
 
 
 def _done(rc: Optional[int], where: str) -> bool:
@@ -105,7 +112,7 @@ def _done(rc: Optional[int], where: str) -> bool:
 
 def lib(path: Optional[str] = None):
     """The loaded C-ABI library (built on first use if missing).  `path` loads another build of it."""
-    global _lib
+    global _lib, _fast
     if _lib is None or path is not None:
         L = ctypes.CDLL(path if path is not None else _build.ensure_built())
         vp, i64 = ctypes.c_void_p, ctypes.c_int64
@@ -155,8 +162,8 @@ def lib(path: Optional[str] = None):
         for name in ("normtest_step", "normtest_step_rows", "normtest_step_clipped", "normtest_adamw_gbar", "normtest_layer_stats",
                      "normtest_workspace_bytes_for"):
             setattr(L, name + "_entry", ctypes.cast(getattr(L, name), ctypes.c_void_p).value)
-        if _fast is None:
-            _load_callpath()
+        if _lib is None:
+            _fast = _load_callpath()
         _lib = L
     return _lib
 

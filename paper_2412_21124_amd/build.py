@@ -1,5 +1,5 @@
-"""Build ``libnormtest.so`` from ``csrc/normtest.hip`` for gfx950 with hipcc (works without a GPU), and the binding's
-``_callpath.so`` from ``csrc/callpath.cpp`` with g++."""
+"""Build ``libnormtest.so`` from ``csrc/normtest.hip`` for gfx950 with hipcc (works without a GPU), and the binding's native call
+path from ``csrc/callpath.cpp`` with g++."""
 from __future__ import annotations
 
 import os
@@ -12,7 +12,6 @@ SRC = os.path.join(_HERE, "csrc", "normtest.hip")
 LIB = os.path.join(_HERE, "libnormtest.so")
 INCLUDE = os.path.join(ROOT, "include")
 CALLPATH_SRC = os.path.join(_HERE, "csrc", "callpath.cpp")
-CALLPATH = os.path.join(_HERE, "_callpath.so")
 
 # contraction off: the error-free transformations of the finalize kernel, and the bits that the copies of a tile's
 # code (whole and part tiles, every launch shape) have in common, rely on every fused multiply-add being an explicit one;
@@ -37,9 +36,16 @@ def build_library(out: str = LIB, quiet: bool = True) -> str:
     return out
 
 
-def build_callpath(out: str = CALLPATH) -> str:
+def callpath_file() -> str:
+    """Where the native call path is built: it fits one Python and one torch, so the name says which."""
+    import torch
+    return os.path.join(_HERE, "_callpath.torch-%s%s" % (torch.__version__, sysconfig.get_config_var("EXT_SUFFIX")))
+
+
+def build_callpath() -> str:
     import torch
     from torch.utils.cpp_extension import include_paths
+    out = callpath_file()
     tmp = out + ".tmp.%d" % os.getpid()
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, "-I", INCLUDE]
     for path in [*include_paths(), sysconfig.get_paths()["include"]]:
@@ -66,9 +72,10 @@ def ensure_built() -> str:
 
 def ensure_callpath() -> str:
     """The same for the binding's native part."""
-    if _stale(CALLPATH, CALLPATH_SRC, os.path.join(INCLUDE, "normtest.h")):
+    built = callpath_file()
+    if _stale(built, CALLPATH_SRC, os.path.join(INCLUDE, "normtest.h")):
         build_callpath()
-    return CALLPATH
+    return built
 
 
 if __name__ == "__main__":
