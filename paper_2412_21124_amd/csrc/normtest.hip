@@ -166,7 +166,12 @@
 #define NT_DIRECT_TILES 2560
 // Tiles per group: enough groups to read the partials side by side, and not so many that they queue at the counter.
 inline __host__ __device__ int64_t group_tiles(int64_t ntiles) { return ntiles <= (1 << 16) ? 512 : 2048; }
-#define NT_GROUP_TILES_MIN 512
+// ... and the most groups that any number of tiles up to ntiles has
+inline int64_t most_groups(int64_t ntiles) {
+  if (ntiles <= NT_DIRECT_TILES) return 0;
+  const int64_t n = (ntiles + group_tiles(ntiles) - 1) / group_tiles(ntiles), small = (1 << 16) / 512;
+  return ntiles > (1 << 16) && n < small ? small : n;
+}
 #define NT_WS_HEADER 32        // doubles in front of the tile partials: a record of the step that wrote them
 #define NT_WS_COUNTER 16       // ... and behind it, at this double, the counter of k_reduce_end
 #define NT_WS_MAGIC 0x4e54574f524b5350ll
@@ -2257,8 +2262,7 @@ static size_t partials_bytes(int64_t J, int64_t d) {
     if (small > ntiles) ntiles = small;
   }
   const int64_t n = ntiles > 0 ? ntiles : 1;
-  const int64_t ngroups = ntiles > NT_DIRECT_TILES ? (ntiles + NT_GROUP_TILES_MIN - 1) / NT_GROUP_TILES_MIN : 0;   // at most
-  return (size_t)(NT_WS_HEADER + n * NT_NV + ngroups * 2 * NT_NV) * sizeof(double);
+  return (size_t)(NT_WS_HEADER + n * NT_NV + most_groups(ntiles) * 2 * NT_NV) * sizeof(double);
 }
 
 size_t normtest_workspace_bytes(int64_t J, int64_t d) {

@@ -150,3 +150,23 @@ def test_blocks_held_per_cu(launches):
         for k in step:
             if k[0].startswith("k_step"):
                 assert (163840 // k[4] if k[4] else 0) == held, (call, k)
+
+
+# The record, the partials of all tiles and those of all groups fit in the bytes that a step of these rows asks for, at both sides of
+# every number of tiles where the groups change; and the built-in scratch holds as much as it did when groups had one size.
+def test_partials_fit_in_the_workspace(launches):
+    calls = [_call(J, g, n * tile + more, flags) for J, tile, flags in ((8, 4096, FULL), (4, 4096, STATS | GBAR), (2, 8192, STATS),
+                                                                       (24, 2048, FULL), (40, 2048, STATS), (40, 8192, STATS | GBAR))
+             for g in (B.NT_BF16, B.NT_F32) for n in (2560, 4096, 1 << 16, (1 << 17) - 1, 1 << 17, 1 << 18) for more in (0, 1)]
+    groups = set()
+    for c, step in zip(calls, launches(calls)):
+        tiles = sum(k[2] for k in step if k[0].startswith("k_step"))
+        n = sum(k[2] for k in step if k[0] == "k_reduce_end")
+        assert 256 + 40 * tiles + 80 * n <= B.normtest_workspace_bytes(c["J"], c["d"]), c
+        groups.add(n)
+    assert {0, 6, 32, 33, 64, 65, 128} <= groups
+    for J in (2, 16, 17, 512):
+        assert B.normtest_static_max_coords(J) == (1_716_281_344 if J <= 16 else 858_140_672)
+        d = [k * (1 << 26) // 3 for k in range(1, 100)]
+        sizes = [B.normtest_workspace_bytes(J, x) for x in sorted(d + [(1 << 16) * 2048, (1 << 16) * 2048 + 1, (1 << 16) * 4096, (1 << 16) * 4096 + 1])]
+        assert sizes == sorted(sizes)
