@@ -2,6 +2,8 @@
 refused or accepted as without it."""
 from __future__ import annotations
 
+import threading
+
 import pytest
 import torch
 
@@ -44,6 +46,18 @@ def test_host_tensors_are_refused(monkeypatch):
         B._fast.step(L.normtest_step_entry, g)
 
 
+class _Recorded:
+    """The native call path, and what it has returned: None for a call that it left to Python."""
+    def __init__(self, fast):
+        self.fast, self.back = fast, []
+
+    def __getattr__(self, name):
+        def call(*args):
+            self.back.append(getattr(self.fast, name)(*args))
+            return self.back[-1]
+        return call
+
+
 class _Gpu:
     def __init__(self, gdtype=torch.bfloat16, J=5, d=3001, ld=3008):
         g = torch.Generator(device="cuda").manual_seed(3)
@@ -64,15 +78,20 @@ class _Gpu:
         torch.cuda.synchronize()
         return ("result" if back is self.res else back), [t.clone() for t in (*s, self.gbar, self.res)]
 
-    def same(self, monkeypatch, call, taken=None):
+    def same(self, monkeypatch, call, taken, accepted=True):
+        """The call ends as it does in Python.  taken: the native call path has made it, and nobody else."""
         B.lib()
-        a = self.run(call)
         with monkeypatch.context() as m:
+            seen = _Recorded(B._fast)
+            m.setattr(B, "_fast", seen)
+            a = self.run(call)
             m.setattr(B, "_fast", None)
             b = self.run(call)
         assert a[0] == b[0]
         assert all(torch.equal(x, y) for x, y in zip(a[1], b[1]))
-        assert taken is None or (a[0] in ("result", None)) == taken, a[0]
+        assert (a[0] in ("result", None)) == accepted, a[0]
+        if accepted:
+            assert (seen.back == [B.NT_OK]) if taken else (seen.back in ([], [None])), seen.back
 
 
 @pytest.mark.gpu
@@ -96,21 +115,71 @@ def test_outputs_are_those_of_the_python_path(monkeypatch, gdtype):
     off = torch.tensor([0, 5, 1500, d], dtype=torch.int64, device="cuda")
     for lay in torch.zeros(3 * B.LAYER_BYTES, dtype=torch.uint8, device="cuda"), torch.zeros(400, dtype=torch.float64, device="cuda"):
         B.normtest_step(g, None, None, None, stats, d=d, **c.kw)
-        tables = []
-        for fast in B._fast, None:
+        tables, seen = [], _Recorded(B._fast)
+        for fast in seen, None:
             with monkeypatch.context() as mp:
                 mp.setattr(B, "_fast", fast)
                 lay.zero_()
                 assert B.normtest_layer_stats(g, off, c.ws, d=d, layers=lay) is lay
                 tables.append(lay.clone())
+        assert seen.back == [B.NT_OK]
         assert torch.equal(*(t.view(torch.int64) for t in tables)) and tables[0].any()
-    # on another stream, and with numbers that are no plain int or float
+    # on another stream; what is left to Python: a stream of its own, numbers that are no plain int or float, subclasses of tensors
     side = torch.cuda.Stream()
     with torch.cuda.stream(side):
         c.same(monkeypatch, lambda w, m, v: B.normtest_step(g, w, m, v, hy, d=d, gbar_out=c.gbar, **c.kw), True)
-    c.same(monkeypatch, lambda w, m, v: B.normtest_step(g, w, m, v, hy, d=d, gbar_out=c.gbar, stream=side, **c.kw), True)
-    c.same(monkeypatch, lambda w, m, v: B.normtest_step_clipped(g, w, m, v, c.gbar, 1, B.make_hyper(flags=FULL), d=d, **c.kw), True)
-    c.same(monkeypatch, lambda w, m, v: B.normtest_adamw_gbar(rows[0].float(), w, m, v, hy, 1), True)
+    c.same(monkeypatch, lambda w, m, v: B.normtest_step(g, w, m, v, hy, d=d, gbar_out=c.gbar, stream=side, **c.kw), False)
+    c.same(monkeypatch, lambda w, m, v: B.normtest_step_clipped(g, w, m, v, c.gbar, 1, B.make_hyper(flags=FULL), d=d, **c.kw), False)
+    c.same(monkeypatch, lambda w, m, v: B.normtest_adamw_gbar(rows[0].float(), w, m, v, hy, 1), False)
+    c.same(monkeypatch, lambda w, m, v: B.normtest_step(g.as_subclass(_Subclass), w, m, v, hy, d=d, gbar_out=c.gbar, **c.kw), False)
+    c.same(monkeypatch, lambda w, m, v: B.normtest_step_rows(rows, w, m.as_subclass(_Subclass), v, hy, table=table, gbar_out=c.gbar, **c.kw), False)
+
+
+class _Subclass(torch.Tensor):
+    pass
+
+
+# a graph of calls that the native call path has made, replayed between eager steps, and calls from several threads at once
+@pytest.mark.gpu
+def test_capture_and_threads(monkeypatch):
+    B.lib()
+    seen = _Recorded(B._fast)
+    monkeypatch.setattr(B, "_fast", seen)
+    hy = B.make_hyper(step=4, flags=FULL)
+    c = _Gpu()
+    state = [t.clone() for t in c.state]
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph):
+        B.normtest_step(c.grads, *state, hy, d=c.d, **c.kw)
+    assert seen.back == [B.NT_OK]
+    want = [t.clone() for t in c.state]
+    res, ws = torch.zeros_like(c.res), torch.empty_like(c.ws)
+    for _ in range(4):
+        B.normtest_step(c.grads, *want, hy, d=c.d, workspace=ws, result=res)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip((*state, c.res), (*want, res)))
+
+    def steps(k, out):
+        own = [t.clone() for t in c.state]
+        r, w = torch.zeros_like(c.res), torch.empty_like(c.ws)
+        stream = torch.cuda.Stream()
+        stream.wait_stream(torch.cuda.default_stream())
+        with torch.cuda.stream(stream):
+            back = [B._fast.fast.step(B.lib().normtest_step_entry, c.grads, *own, hy, c.d, None, None, w, r) for _ in range(40)]
+        stream.synchronize()
+        out[k] = (back == [B.NT_OK] * 40, own + [r])
+
+    alone, outs = {}, {}
+    steps(0, alone)
+    threads = [threading.Thread(target=steps, args=(k, outs)) for k in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert len(outs) == 4 and alone[0][0] and all(ok for ok, _ in outs.values())
+    assert all(torch.equal(a, b) for k in range(4) for a, b in zip(alone[0][1], outs[k][1]))
 
 
 @pytest.mark.gpu
@@ -141,4 +210,4 @@ def test_what_is_refused_stays_refused(monkeypatch):
             lambda w, m, v: B.normtest_layer_stats(g, off, c.ws.cpu(), d=d, layers=lay), lambda w, m, v: B.normtest_layer_stats(g, off[::2], c.ws, d=d, layers=lay),
             lambda w, m, v: B.normtest_layer_stats(g[:1], off, c.ws, d=d, layers=lay), lambda w, m, v: B.normtest_layer_stats(g.half(), off, c.ws, d=d, layers=lay)]
     for call in bad:
-        c.same(monkeypatch, call, False)
+        c.same(monkeypatch, call, None, accepted=False)
