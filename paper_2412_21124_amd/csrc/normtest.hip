@@ -92,6 +92,14 @@
 // and 15.1.
 #define NT_SPLIT_TILE 1024
 #define NT_SPLIT_COORDS (1ll << 18)
+// Not so where one tile of NT_BLOCK_MANY_TINY threads holds the vector and there are few rows: a step with sums is then a kernel of one
+// block, which counts nothing.  Tiles of 1024 -> one tile, us: fused step of 17 / 32 / 48 / 56 / 64 bf16 rows at d = 1025 6.8 / 7.2 / 8.8 / 9.0 /
+// 9.4 -> 5.7 / 6.7 / 8.1 / 8.9 / 9.5, at 2048 6.7 / 7.3 / 8.6 / 8.6 / 9.0 -> 5.1 / 6.0 / 7.2 / 7.9 / 8.4; of 17 / 40 / 56 fp32 rows 6.8 / 8.4 / 9.7 -> 6.0 /
+// 8.1 / 9.7 and 6.2 / 7.4 / 8.3 -> 5.0 / 6.8 / 8.1, statistics of 48 7.4 -> 7.9 and 7.4 -> 6.9.  Up to 1024 coordinates, one block either way: 17 / 24 /
+// 32 bf16 rows 5.2 / 5.3 / 5.6 -> 4.9 / 5.1 / 5.7, statistics of 24 4.7 -> 4.4; fp32 rows are equal.
+#define NT_ONE_TILE_ROWS 56
+#define NT_ONE_TILE_ROWS_32 40   // fp32 rows
+#define NT_ONE_TILE_ROWS_HALF 24 // bf16 rows, up to NT_SPLIT_TILE coordinates
 #define NT_SPLIT 1000            // J_T of the kernels whose waves share the rows is NT_SPLIT + how many of them
 #define NT_BLOCK_LARGE_STATS 256 // J > 16, statistics only otherwise (nothing written per coordinate): short tiles, so that a
 #define NT_ITERS_LARGE_STATS 2   // vector of a few million coordinates still gives every CU several blocks
@@ -1996,8 +2004,13 @@ inline bool generations_pay(int64_t J, int esize, int mode, int64_t d) {
   if (full == 1) return left > (bf16 ? (adamw && J >= 64 ? G * 5 / 16 : G * 3 / 8) : adamw ? G / 16 : mode == MODE_FULL ? G / 8 : G / 4);
   return !bf16 || left > (adamw && J >= 64 ? G / 16 : G / 8);
 }
+inline bool one_tile(int64_t J, int esize, int mode, int64_t d_whole) {
+  if (mode == MODE_ADAMW || d_whole > NT_BLOCK_MANY_TINY * NT_ITERS_MANY_TINY * NT_VEC) return false;
+  if (d_whole <= NT_SPLIT_TILE) return esize == 2 && J <= NT_ONE_TILE_ROWS_HALF;
+  return J <= (esize == 2 ? NT_ONE_TILE_ROWS : NT_ONE_TILE_ROWS_32);
+}
 inline int launch_class(int64_t J, int esize, int mode, bool gbar, int64_t d_whole) {
-  if (J > NT_JCHUNK && d_whole <= NT_SPLIT_COORDS) return CLS_TINY;
+  if (J > NT_JCHUNK && d_whole <= NT_SPLIT_COORDS) return one_tile(J, esize, mode, d_whole) ? CLS_SHORT : CLS_TINY;
   if (J > NT_JCHUNK && d_whole <= (J <= 32 && esize == 2 && mode != MODE_ADAMW ? NT_MANY_TINY_COORDS_32 : NT_MANY_TINY_COORDS)) return CLS_SHORT;
   if (mode == MODE_STATS && !gbar) return (J <= NT_JCHUNK && d_whole < NT_STATS_SHORT_COORDS) ? CLS_SHORT : CLS_BASE;
   if (J > NT_JCHUNK) return generations_pay(J, esize, mode, d_whole) ? CLS_LONG : CLS_BASE;

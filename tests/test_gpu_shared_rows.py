@@ -12,8 +12,8 @@ from paper_2412_21124_amd import synth
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 STATS, ADAMW, GBAR, COORD = B.NT_DO_STATS, B.NT_DO_ADAMW, B.NT_WRITE_GBAR, B.NT_COORD_TEST
-# one coordinate, one load, a wave, the tile, several tiles; with 1 to 3 over, and waves that lie past the end
-SIZES = [1, 3, 4, 6, 256, 257, 515, 1023, 1024, 1026, 5 * 1024 + 259]
+# one coordinate, one load, a wave, the tile, two tiles, several tiles; with 1 to 3 over, and waves that lie past the end
+SIZES = [1, 3, 4, 6, 256, 257, 515, 1023, 1024, 1026, 2047, 2048, 2049, 5 * 1024 + 259]
 
 
 def _step(rows, state, d, flags, whole, table):
@@ -37,9 +37,9 @@ def test_outputs_of_longer_vectors(J, gdtype, flags, table, odd):
     n = SIZES[-1]
     rows = (torch.randn(J, n + 8 + odd, generator=g, device=DEV) * 1e-2).to(gdtype)[:, odd:]   # rows and their distance off 16 bytes
     state = [torch.rand(n, generator=g, device=DEV) * 0.02 for _ in range(4)]
-    for d in SIZES:
-        got, a = _step(rows, state, d, flags, 0, table)
-        for whole in (1 << 18) + 1, 1 << 22, 1 << 26:
+    for d in SIZES:   # the parts of a vector of 2^18 coordinates run in tiles of 1024 whatever their length
+        got, a = _step(rows, state, d, flags, 1 << 18, table)
+        for whole in 0, (1 << 18) + 1, 1 << 22, 1 << 26:
             want, b = _step(rows, state, d, flags, whole, table)
             for x, y in zip(a, b):
                 assert torch.equal(x, y), (d, whole)
@@ -58,7 +58,7 @@ def test_order_of_the_rows(J):
     rows = (torch.randn(J, d, generator=g, device=DEV) * scale).to(torch.bfloat16)
     rows[J // 2:J // 2 * 2] = -rows[:J // 2]
     state = [torch.rand(d, generator=g, device=DEV) * 0.02 for _ in range(4)]
-    outs = [_step(rows, state, d, STATS | ADAMW | GBAR, whole, False) for whole in (0, 1 << 22, 1 << 26)]
+    outs = [_step(rows, state, d, STATS | ADAMW | GBAR, whole, False) for whole in (0, 1 << 18, 1 << 22, 1 << 26)]
     for res, st in outs[1:]:
         assert all(torch.equal(x, y) for x, y in zip(st, outs[0][1]))
         assert all(res[k] == pytest.approx(outs[0][0][k], rel=1e-13) for k in ("A", "B", "C"))
@@ -66,7 +66,7 @@ def test_order_of_the_rows(J):
 
 # the centred sum of bf16 rows comes from sum x and sum x^2: rows that agree to a bit, and rows that agree
 @pytest.mark.parametrize("J", [17, 64, 513])
-@pytest.mark.parametrize("whole", [0, 1 << 22, 1 << 26])
+@pytest.mark.parametrize("whole", [0, 1 << 18, 1 << 22, 1 << 26])
 def test_rows_that_nearly_agree(J, whole):
     d = 3000
     g = torch.Generator(device=DEV).manual_seed(J)
@@ -90,7 +90,7 @@ def test_sums_that_are_not_finite(J, row, value):
     rows = (torch.randn(J, d, device=DEV) * 1e-2).to(torch.bfloat16)
     state = [torch.rand(d, device=DEV) for _ in range(4)]
     rows[row, 1100] = value   # 1e20 overflows as a square only
-    for whole in 0, 1 << 22, 1 << 26:
+    for whole in 0, 1 << 18, 1 << 22, 1 << 26:
         res, st = _step(rows, state, d, STATS | ADAMW | GBAR, whole, False)
         assert res["status"] == B.NT_STATUS_NONFINITE and res["pass"] == 1 and res["next_b"] == 64
         assert torch.isfinite(st[3][1100]).item() == (value == 1e20)

@@ -129,13 +129,27 @@ def test_tiles_of_the_shortest_vectors(launches, flags):
     cases = [(17, B.NT_BF16, (1002, 512)), (32, B.NT_BF16, (1002, 512)), (33, B.NT_BF16, (1004, 1024)), (600, B.NT_BF16, (1004, 1024)),
              (17, B.NT_F32, (0, 256)), (600, B.NT_F32, (0, 256))]
     for J, g, (j_t, block) in cases:
-        short, ends, past, part = launches([_call(J, g, 1025, flags), _call(J, g, edge, flags), _call(J, g, edge + 1, flags),
+        short, ends, past, part = launches([_call(J, g, 2049, flags), _call(J, g, edge, flags), _call(J, g, edge + 1, flags),
                                             _call(J, g, 1025, flags, edge + 1)])
-        for step, grid in ((short, 2), (ends, 256)):
+        for step, grid in ((short, 3), (ends, 256)):
             assert [(k[0], int(k[1][0]), int(k[1][2]), k[2], k[3]) for k in step] == [("k_step_end", j_t, block, grid, block)]
         assert [(k[0], k[1][2:4], k[2]) for k in part] == [("k_step_end", ["512", "1"], 1)]
         assert _names(past) == (["k_step_end"] if flags == ADAMW else ["k_step", "k_finalize"])
         assert (past[0][1][2:4], past[0][2]) == (["512", "1"], 129)
+
+
+# ... but few rows of a vector that fits one tile of 2048 coordinates, where there are sums: both sides of each count of rows and length
+@pytest.mark.parametrize("flags", [FULL, STATS, STATS | GBAR, ADAMW])
+def test_one_tile_of_the_shortest_vectors(launches, flags):
+    calls = [_call(J, g, d, flags) for g, few, half in ((B.NT_BF16, 56, 24), (B.NT_F32, 40, 16)) for J in (17, half, half + 1, few, few + 1)
+             if J > 16 for d in (1, 1024, 1025, 2048, 2049)]
+    calls.append(_call(17, B.NT_BF16, 2000, flags, 2049))
+    for c, step in zip(calls, launches(calls)):
+        few, half = (56, 24) if c["gdtype"] == B.NT_BF16 else (40, 0)
+        one = flags != ADAMW and c["d"] <= 2048 and not c["whole"] and c["J"] <= (few if c["d"] > 1024 else half)
+        (name, args, grid, _, _), = step
+        assert name == "k_step_end" and grid == (1 if one else -(-c["d"] // 1024)), c
+        assert (args[0] == "0" and args[2:4] == ["512", "1"]) == one, c
 
 
 # Dynamic LDS that keeps one block of 1024 threads on a CU (160 KB), or two or three of 512 of the statistics that store the mean.
