@@ -20,7 +20,8 @@
  *
  * All pointers named "device" must be dereferenceable by the GPU (device memory; result may also be
  * pinned host memory).  The library allocates nothing, keeps nothing of one call for the next
- * (its launches count their blocks in counters of its own on the device, which every launch leaves at zero), never
+ * (its launches count their blocks in counters of its own on the device, which every launch leaves at zero; up to 4096 streams
+ * are given some of their own, found by the stream's handle, and a short step on any further stream ends in a second kernel), never
  * synchronises the device and never touches host copies of the data: it validates, enqueues kernels
  * on the caller's stream and returns.  No C++ types or exceptions cross this boundary.
  */

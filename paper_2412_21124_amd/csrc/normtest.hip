@@ -191,10 +191,10 @@ static __device__ __align__(256) unsigned char scratch[NT_SCRATCH_BYTES];
 
 // Counters with which the blocks of a launch find out which of them comes last (tile_reduce): one, and NT_LEAVES more, each in an
 // array of its own so that their counting does not meet.  Zero when the library is loaded, and every launch leaves the ones it was
-// given at zero.  A call takes the next ones in turn, so two launches can only share them
-// if a whole round of calls lies between them while both run: more launches than a device's queues hold (32 of 16384 packets).
-#define NT_TICKETS (1u << 20)
-static __device__ uint32_t tickets[(1 + NT_LEAVES) * NT_TICKETS];
+// given at zero.  A stream has its own (stream_slot), as launches on one stream never run at the same time; taken in turn by all
+// streams, a launch that waited on one of them while the others went once round could meet a later call at its counters.
+#define NT_STREAMS 4096
+static __device__ uint32_t tickets[(1 + NT_LEAVES) * NT_STREAMS];
 
 namespace {
 
@@ -645,7 +645,7 @@ struct Finish {
 };
 // The counter of one block of such a step: its leaf (blocks of neighbouring numbers have different ones), or the only one.
 __device__ inline uint32_t* leaf_of(uint32_t* ticket, int64_t ntiles) {
-  return ticket && ntiles > NT_LEAF_TILES ? ticket + (1 + blockIdx.x % NT_LEAVES) * (size_t)NT_TICKETS : ticket;
+  return ticket && ntiles > NT_LEAF_TILES ? ticket + (1 + blockIdx.x % NT_LEAVES) * NT_STREAMS : ticket;
 }
 __device__ inline uint32_t count_up(uint32_t* ticket) {
   return __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -2336,7 +2336,7 @@ static int check_step_args(const void* grads, nt_dtype gdtype, int64_t J, int64_
 // Address of this device's copy of `scratch` or `tickets`, looked up once per device (the array's name is only a host-side
 // handle of the symbol; kernels, copies and fills take this pointer).
 typedef void* PerDevice[64];
-static int device_address(const void* symbol, PerDevice& cached, void** out) {
+static int device_address(const void* symbol, PerDevice& cached, void** out, int* device = nullptr) {
   int dev = 0;
   const hipError_t e0 = hipGetDevice(&dev);
   if (e0 != hipSuccess) return hip_code(e0);
@@ -2349,6 +2349,7 @@ static int device_address(const void* symbol, PerDevice& cached, void** out) {
     __atomic_store_n(&cached[dev], ptr, __ATOMIC_RELEASE);
   }
   *out = ptr;
+  if (device) *device = dev;
   return NT_OK;
 }
 
@@ -2361,20 +2362,40 @@ static bool on_current_device(hipStream_t st) {
   return hipGetDevice(&current) == hipSuccess && hipStreamGetDevice(st, &own) == hipSuccess && own == current;
 }
 
-// The next counter of this device, or false where there is none for this launch: a graph under capture would keep it and
-// replay beside a later call that is given the same one, and the blocks of a launch on another device would count themselves in
+// A stream's place among the counters, or -1 where there is none left near its hash: the step then takes a reduction kernel.  A place
+// is kept until the process ends.  It passes to a stream that is made with the handle of one that was destroyed, whose work has ended
+// then: HIP lets nobody count on work that a stream was destroyed with.  hipStreamPerThread is another stream in every thread.
+static int stream_slot(int dev, hipStream_t st) {
+  static uint64_t taken[NT_STREAMS];
+  static thread_local char own;
+  const uint64_t handle = (uint64_t)(uintptr_t)(st == hipStreamPerThread ? (const void*)&own : (const void*)st);
+  const uint64_t key = (handle << 7) + 2 * (uint64_t)dev + 1;   // dev < 64
+  const uint64_t at = key * 0x9e3779b97f4a7c15ull >> 32;
+  for (uint64_t k = 0; k < 16; ++k) {
+    uint64_t* place = &taken[(at + k) % NT_STREAMS];
+    uint64_t who = __atomic_load_n(place, __ATOMIC_RELAXED);
+    if (who == 0) __atomic_compare_exchange_n(place, &who, key, false, __ATOMIC_RELAXED, __ATOMIC_RELAXED);   // who: 0, or who was faster
+    if (who == 0 || who == key) return (int)(place - taken);
+  }
+  return -1;
+}
+
+// The counter of this stream, or false where there is none for this launch: a graph under capture would keep it and
+// replay beside a later call on the stream, and the blocks of a launch on another device would count themselves in
 // memory that is not theirs.
-static bool next_ticket(hipStream_t st, uint32_t** out) {
+static bool stream_ticket(hipStream_t st, uint32_t** out) {
   static PerDevice cached = {nullptr};
   hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
   void* base = nullptr;
+  int dev = 0;
   if (hipStreamIsCapturing(st, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone || !on_current_device(st) ||
-      device_address(HIP_SYMBOL(tickets), cached, &base) != NT_OK) {
+      device_address(HIP_SYMBOL(tickets), cached, &base, &dev) != NT_OK) {
     (void)hipGetLastError();
     return false;
   }
-  static uint32_t turn = 0;
-  *out = (uint32_t*)base + __atomic_fetch_add(&turn, 1u, __ATOMIC_RELAXED) % NT_TICKETS;
+  const int slot = stream_slot(dev, st);
+  if (slot < 0) return false;
+  *out = (uint32_t*)base + slot;
   return true;
 }
 
@@ -2440,7 +2461,7 @@ static int enqueue_step(const void* grads, bool table, nt_dtype gdtype, int64_t 
     // no sums, one partial that is the total, or few enough for the last block: launch_tiles_of has the kernels
     const int64_t most = J > NT_JCHUNK ? (cls == CLS_TINY ? NT_TICKET_TILES : NT_TICKET_TILES_MANY)
                                        : mode == MODE_STATS ? NT_TICKET_TILES_STATS : NT_TICKET_TILES;
-    if (mode == MODE_ADAMW || ntiles == 1 || (ntiles <= most && next_ticket(st, &fin.ticket))) {
+    if (mode == MODE_ADAMW || ntiles == 1 || (ntiles <= most && stream_ticket(st, &fin.ticket))) {
       fin.q = q;
       fin.hdr = record;
       fin.hdr_out = hdr_out;

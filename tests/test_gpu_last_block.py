@@ -3,6 +3,7 @@ capture, with inputs that change from call to call, garbage in the workspace, an
 from __future__ import annotations
 
 import ctypes
+import threading
 
 import pytest
 import torch
@@ -142,7 +143,32 @@ def test_sums_that_are_not_finite(J, gdtype, tile, value):
         assert all(torch.equal(got[k], want[k % K][0]) for k in range(2 * K))
 
 
-# more calls than there are counters (2^20): each is met again, and has been left at zero
+# the default stream that every thread has of its own goes by one handle (2) in all of them
+def test_threads_own_streams():
+    c = _Calls(4, torch.float32, 200 * 4096 - 5, STATS | ADAMW | GBAR)
+    want = c.two_launches()
+    c.reset()
+    results = torch.zeros(K, 50, B.RESULT_BYTES, dtype=torch.uint8, device=DEV)
+    torch.cuda.synchronize()
+    fn, codes = B.lib().normtest_step, {}
+
+    def calls(k):
+        w, m, v, gbar = (t.data_ptr() for t in c.state[k])
+        codes[k] = [fn(c.grads[k].data_ptr(), B.NT_F32, 4, c.d, c.d, w, m, v, gbar, ctypes.byref(c.hy), None, c.ws[k].data_ptr(),
+                       c.ws[k].numel(), results[k, i].data_ptr(), 2) for i in range(50)]
+        torch.cuda.synchronize()
+
+    threads = [threading.Thread(target=calls, args=(k,)) for k in range(K)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert codes == {k: [0] * 50 for k in range(K)}
+    c.check(want)
+    assert all(torch.equal(results[k, i], want[k][0]) for k in range(K) for i in range(50))
+
+
+# more calls than the counters of all streams: the stream's own is met by each and left at zero
 def test_counters_come_round():
     c = _Calls(2, torch.float32, 4097, STATS)
     want = c.two_launches()[0][0]

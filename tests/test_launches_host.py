@@ -44,7 +44,8 @@ def _call(J, gdtype, d, flags, whole=0, table=False, device=0, stream=0, capture
 
 @pytest.fixture(scope="module")
 def launches(tmp_path_factory):
-    """Function from a list of calls to the launches of each: (kernel, template arguments, blocks, threads, dynamic LDS)."""
+    """Function from a list of calls to the launches of each: (kernel, template arguments, blocks, threads, dynamic LDS);
+    `counters` then holds for each call where the blocks of its k_step_end count themselves, None without one."""
     fake = str(tmp_path_factory.mktemp("fake") / "libfakehip.so")
     subprocess.run(["gcc", "-std=gnu99", "-Wall", "-Wextra", "-Werror", "-shared", "-fPIC", os.path.join(HERE, "fake_hip.c"), "-o", fake],
                    check=True)
@@ -52,14 +53,15 @@ def launches(tmp_path_factory):
     def run(calls):
         out = subprocess.run([sys.executable, "-c", CLIENT, fake, B.lib()._name], check=True, capture_output=True, text=True,
                              input="".join(json.dumps(c) + "\n" for c in calls)).stdout
-        got, now = [], []
+        got, now, run.counters, counter = [], [], [], []
         for line in out.splitlines():
             if line.startswith("rc "):
                 assert line == "rc 0"
                 got.append(now)
+                run.counters.append(int(counter[0], 16) if counter else None)
                 now = []
             else:
-                name, grid, block, lds = line.split()
+                name, grid, block, lds, *counter = line.split()
                 now.append((re.search(r"\d(k_[a-z_0-9]*[a-z])", name).group(1), re.findall(r"L[ib](\d+)E", name), int(grid), int(block),
                             int(lds)))
         assert len(got) == len(calls) and not now
@@ -150,6 +152,23 @@ def test_one_tile_of_the_shortest_vectors(launches, flags):
         (name, args, grid, _, _), = step
         assert name == "k_step_end" and grid == (1 if one else -(-c["d"] // 1024)), c
         assert (args[0] == "0" and args[2:4] == ["512", "1"]) == one, c
+
+
+# The blocks of a step that ends in one launch count themselves in words that no other stream has, as a launch may wait on its stream
+# for as long as it likes.  A stream that finds no place among them takes the reduction kernel.
+def test_counters_are_a_streams_own(launches):
+    base, places = 0x10000000, 4096   # see fake_hip.c; streams that have words
+    few = [(s << 16, s) for s in (0, 3, 0, 3)] + [(s, 0) for s in (1, 2, 5, 0, 6, 5, 2, 1, 6)]   # (stream, device)
+    many = [(s, 0) for s in range(17, 6017)]
+    asked = few + many + many[:50]
+    steps = launches([_call(4, B.NT_F32, 100_000, FULL, stream=s, device=dev) for s, dev in asked])
+    words = dict(zip(asked, launches.counters))
+    for who, word, step in zip(asked, launches.counters, steps):
+        assert word == words[who] and _names(step) == (["k_step_end"] if word else ["k_step", "k_finalize"])
+        assert word or who in many
+    own = [w for w in words.values() if w]
+    assert len(own) == len(set(own)) > places // 2
+    assert all(base <= w < base + 4 * places and w % 4 == 0 for w in own)
 
 
 # Dynamic LDS that keeps one block of 1024 threads on a CU (160 KB), or two or three of 512 of the statistics that store the mean.
