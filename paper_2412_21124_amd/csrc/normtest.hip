@@ -1234,8 +1234,10 @@ __device__ inline void moments_last(int nb, typename GT::raw_t* raw, const Reach
 // 2622 us, with it 401 / 716 / 2571; in short vectors it costs 1 to 5 %, with up to 32 rows 0.5 %, and below 48 rows all but four loads
 // are the better count (40 rows with the mean 231 us, waiting for all of them 236).  And where a launch is a whole generation, so that
 // every CU has four blocks, a wave of 48 rows or more pauses after each chunk: the memory system serves fewer requests at a time
-// faster.  Without and with the pause, us: fused step of 128 / 256 / 512 rows at 2^24 726 / 1348 / 2587 and 712 / 1323 / 2518, AdamW
-// only of 256 rows at 2^23 692 and 662, 64 rows at 1e8 2302 and 2286; 40 rows 289 and 291.  In a launch with fewer blocks it costs 3 %.
+// faster.  Without the pause / with 18 / with 30 times 64 cycles, us: fused step of 128 rows at 2^24 722 / 707 / 707, of 256 1339 / 1314 / 1316, of
+// 512 2573 / 2522 / 2524, of 64 407 / 405 / 412 and at 1e8 2304 / 2288 / 2347, of 96 565 / 566 / 570; AdamW only of 256 rows at 2^23 690 / 661 / 656,
+// of 48 175.0 / 173.3 / 172.8; 40 rows without and with it 289 and 291.  12 against 18: 128 rows at 2^24 710 / 706, 512 at 2^23 1293 / 1283, AdamW
+// only of 256 663 / 660, 64 rows equal.  In a launch with fewer blocks the pause costs 3 %.
 __device__ inline void chunk_wait(int J) {
   __builtin_amdgcn_sched_barrier(0);
   if (J >= NT_PAUSE_ROWS)
@@ -1247,10 +1249,7 @@ __device__ inline void chunk_wait(int J) {
 __device__ inline void chunk_pause(int J) {
   if (J < NT_PAUSE_ROWS || gridDim.x < NT_GENERATION / (NT_BLOCK_LARGE * NT_ITERS_LARGE * NT_VEC)) return;
   __builtin_amdgcn_sched_barrier(0);
-  if (J >= 2 * NT_PAUSE_ROWS)
-    __builtin_amdgcn_s_sleep(18);   // 64 cycles each
-  else
-    __builtin_amdgcn_s_sleep(12);
+  __builtin_amdgcn_s_sleep(18);
 }
 
 // bf16 rows of a matrix whose first row begins on 4 bytes and whose row stride is odd: every second row begins between two words, and
