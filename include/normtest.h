@@ -89,11 +89,14 @@ typedef struct {
 
 /* Where this call's coordinates sit in the full parameter vector (Sec. 3.3).  The sums are additive over
  * coordinates, so a shard needs nothing from the others; the record is checked for consistency, and d_global
- * has one effect: long vectors are cut into larger tiles than short ones (steps that write per coordinate,
- * with 7 to 16 fp32 or 14 to 16 bf16 rows: from 2^26 coordinates; 17 to 32 rows: from 2^24; more rows: from
- * 3 * 2^21; every step of more than 16 rows: beyond 2^18; a step with AdamW only, which forms no sums, also from 5 fp32 and 10 bf16 rows; read-only
- * statistics of up to 16 rows: from 2^21), and a call with a shard record is cut the way a vector of d_global
- * coordinates is (a call without one: the way a vector of d is). */
+ * has one effect: a call with a shard record is cut into tiles the way a vector of d_global coordinates is (a call
+ * without one: the way a vector of d is).  The size of the tiles changes with the vector's length,
+ *   up to 16 rows, read-only statistics: from 2^21 coordinates on;
+ *   up to 16 rows, steps that write per coordinate: from 2^26 on, with 7 to 16 fp32 or 14 to 16 bf16 rows (a step
+ *     with AdamW only, which forms no sums, also with 5 and 6 fp32 or 10 to 13 bf16 rows);
+ *   more than 16 rows: beyond 1024, beyond 2048 and beyond 2^18;
+ *   more than 16 rows, steps that write per coordinate: also, several times, between 2^24 (more than 32 rows:
+ *     3 * 2^21) and 3 * 2^23. */
 typedef struct {
   int32_t shard_id, num_shards;
   int64_t shard_offset, d_global;
@@ -134,7 +137,7 @@ typedef struct {
 /* Alignment, in coordinates, of the partial-sum tiles for J rows (every tile size divides it).  Results are
  * bit-identical for any split of a vector into calls whose boundaries are multiples of this, for the
  * same J, dtype and flags, when each call names the vector's full length in shard->d_global (without shard
- * records: when the parts and the whole are all on one side of the length named at nt_shard_info for that
+ * records: when the parts and the whole are all on one side of every length named at nt_shard_info for that
  * row count, or the row count has none).  The updated w, m, v and a stored gbar never depend on how a vector
  * is cut. */
 int64_t normtest_tile_coords(int64_t J);
@@ -166,9 +169,10 @@ size_t normtest_workspace_bytes_for(nt_dtype gdtype, int64_t J, int64_t d, uint3
  * coordinates up to 16 rows, one per 2^23 where 14 or more bf16 or 7 or more fp32 rows, with AdamW only 10 or 5, are 2^26 coordinates
  * or longer, and beyond 16 rows where such runs are full enough, else one; the memory system serves blocks that start together faster),
  * followed by a small reduction kernel.  There is none after AdamW only, after a call of a single tile (1024 coordinates
- * beyond 16 rows, else 4096) and, outside graph capture, after one of up to 2^20 coordinates, 2^18 beyond 16 rows (statistics of up to
- * 16 rows: 2^21, without a stored mean below that); a part of a vector that is itself longer (d_global) has one if that vector is read in
- * larger tiles, or if more than 16 rows come as a table.
+ * beyond 16 rows, up to 56 bf16 or 40 fp32 of them 2048, else 4096) and, outside graph capture, after one of up to
+ * 2^20 coordinates, 2^18 beyond 16 rows (statistics of up to 16 rows: 2^21, without a stored mean below that); a part
+ * of a vector that is itself longer (d_global) has one if that vector is read in larger tiles, or if more than 16 rows
+ * come as a table.
  * Results do not depend on how many launches there were.  Any element-aligned pointer and
  * any row stride is accepted: the kernels access rows, w, m, v and gbar_out with the same vector instructions whatever
  * the alignment, with bit-identical results.  d == 0 succeeds (sums are 0).

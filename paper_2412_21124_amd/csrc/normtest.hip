@@ -524,7 +524,8 @@ __device__ inline void totals_clear(Totals& t) {
 // PACKED = false: tile partials {A, B, C, n_fail, r_max}; PACKED = true: group partials
 // {A, A_lo, B, B_lo, C, C_lo, n, n_lo, r_max, unused}.  Tile partials are loaded up to eight rounds
 // at a time: one round after the other, 2048 records in a block of 256 threads wait for memory eight times (groups of 2048
-// 7.2 -> 4.5 us).  Group partials are few (one per 2M coordinates or more), so theirs are not.  What lies past the end reads as the
+// 7.2 -> 4.5 us).  Group partials are few (one per 1M coordinates or more, up to 2^19 tiles at most 256, one round), so theirs are
+// not.  What lies past the end reads as the
 // last record and counts as zeros, which change nothing.
 template <int THREADS, bool PACKED>
 __device__ inline void totals_accumulate(const double* in, int64_t n, Totals& acc) {
@@ -745,9 +746,8 @@ __device__ inline void coord_test(float thr, float c, float gb, LaneAcc& acc) {
   }
 }
 
-// Per-chunk bookkeeping of the J > 16 walk, shared by the tiles and the per-coordinate form below so that both
-// perform the same operations.  For one coordinate and a chunk of nb rows with shift K (the running
-// mean before the chunk, or the first row for the first chunk) two sums have been accumulated:
+// Per-chunk bookkeeping of the walk of more than 16 fp32 rows (walk_shifted).  For one coordinate and a chunk of nb rows with shift
+// K (the running mean before the chunk, or the first row for the first chunk) two sums have been accumulated:
 // sb = sum x in fp64 (exact for all practical purposes, so the mean handed to AdamW is correctly rounded
 // even when the rows cancel) and q = sum (x - K)^2 in fp32.  With sr = sb - nb K, the sum of the shifted values,
 //   chunk centred sum   M2_b = q - sr^2/nb
@@ -778,8 +778,10 @@ __device__ inline float chunk_merge(bool first, int na, int nb, double inv_na, d
 // More than 16 bf16 rows: sum x and sum x^2 of a coordinate in fp64, hence the centred sum without a shift.  x^2 has 16 bits, so both
 // sums are exact unless the rows' magnitudes lie a factor of 2^14 or more apart, where no centred sum is small.  Against 64 bits C is
 // 2.4e-10 off (128 rows, d = 1,000,003) and 2.2e-9 (24 rows, 100,003), where sums of fp32 squares with a shift were 3.4e-9 and 1.6e-8.
-// An element takes 17 cycles of a SIMD, with the
-// shift and the merges 27.  The rows are added up in up to four segments of whole chunks, one after the other within a segment, and
+// An element takes 17 cycles of a SIMD, with the shift and the merges 27.  Less arithmetic also sends a block's loads in denser bursts, which
+// at some lengths makes the short tiles of 2048 coordinates slower.  Shifted -> by moments in those tiles, us: fused step of 20 / 48 rows at
+// d = 2^21 25.8 / 50.2 -> 26.8 / 52.2, of 40 at 5e6 92.6 -> 95.1, but of 20 at 2.5e6 33.9 -> 30.7; statistics of 20 / 100 rows at 1e7
+// 66.7 / 306 -> 64.5 / 300.  The rows are added up in up to four segments of whole chunks, one after the other within a segment, and
 // the segments in their order: the waves of a block can then take one each (tile_split) with the same bits.
 __host__ __device__ inline int segment_rows(int J) {
   return ((J + NT_MCHUNK - 1) / NT_MCHUNK + NT_SEGMENTS - 1) / NT_SEGMENTS * NT_MCHUNK;
@@ -1160,9 +1162,9 @@ __device__ inline void tile_defer(const StepParams& p, int64_t tile, double (*re
 }
 
 // ---------------------------------------------------------------------------------------------
-// Tile, J > 16: rows are walked NT_MCHUNK at a time.  One pass over a chunk gives its plain sum
-// (fp64) and the sum of squares of the values shifted by K, the running mean of the rows before it, hence
-// its centred sum of squares without cancellation; see chunk_merge for the bookkeeping.
+// Tile, J > 16: rows are walked NT_MCHUNK at a time.  bf16 rows: one pass over a chunk adds its values and their squares, both in
+// fp64 (walk_moments, centred).  fp32 rows: it gives the chunk's plain sum (fp64) and the sum of squares of the values shifted by
+// K, the running mean of the rows before it, hence its centred sum of squares without cancellation (walk_shifted, chunk_merge).
 // ---------------------------------------------------------------------------------------------
 template <class GT, bool MOVES, int N>
 __device__ inline void chunk_accumulate(typename GT::raw_t* raw, const Reach& at, const float* K, double* sb, float* q) {
