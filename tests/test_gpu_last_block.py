@@ -71,8 +71,8 @@ class _Calls:
 # the fewest tiles, a ragged last one, both sides of the last count that ends in one launch, for each class of short vectors and,
 # beyond 16 rows, of short tiles
 @pytest.mark.parametrize("J,gdtype,flags,tile,most,whole", [
-    (2, torch.float32, STATS | ADAMW, 4096, 256, 0), (16, torch.bfloat16, STATS, 4096, 256, 0),
-    (8, torch.bfloat16, STATS | GBAR | COORD, 4096, 256, 0), (20, torch.float32, STATS | ADAMW | GBAR, 2048, 128, 0),
+    (2, torch.float32, STATS | ADAMW, 4096, 256, 0), (16, torch.bfloat16, STATS, 4096, 512, 0),
+    (8, torch.bfloat16, STATS | GBAR | COORD, 4096, 512, 0), (20, torch.float32, STATS | ADAMW | GBAR, 2048, 128, 0),
     (40, torch.bfloat16, STATS, 2048, 128, 0), (24, torch.bfloat16, STATS | ADAMW | GBAR, 2048, 128, 1 << 22),
     (33, torch.float32, STATS | GBAR, 2048, 128, 1 << 22), (19, torch.float32, STATS, 2048, 128, 1 << 30)])
 @pytest.mark.parametrize("past", [None, -1, 0, 1])
